@@ -75,7 +75,7 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
         for (int s = 0; s < sh->n_seq; ++s)
             if (sh->cu_seqlens[s + 1] - sh->cu_seqlens[s] < sh->n_q) return JQ_ERR_SHAPE;
     }
-    p.scale = sh->scale > 0.0f ? sh->scale : (float)(1.0 / std::sqrt((double)sh->d));
+    p.scale = sh->scale > 0.0f ? (double)sh->scale : 1.0 / std::sqrt((double)sh->d);
     const int64_t rows = (int64_t)p.n_q * p.group;
     if (rows > (1 << 20)) return JQ_ERR_UNSUPPORTED;
     p.rows = (int32_t)rows;
@@ -108,7 +108,8 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
     // its SIMD busy and the window of K in flight stays small.  The second pass finds part of K in the
     // Infinity Cache and has more arithmetic per tile; it does better with two waves per SIMD.  The cap makes
     // big calls run in several rounds.
-    const int64_t keys = (int64_t)p.n_layers * p.h_kv * p.T;
+    // (groups of 128 query rows beyond the first are further workgroups of the first pass's one launch)
+    const int64_t keys = (int64_t)p.n_layers * p.h_kv * p.T * p.row_groups;
     auto plan_waves = [&](int64_t target_waves, int32_t knob, int32_t* cu_chunk, int32_t* cu_cgrp, int32_t* chunk_keys,
                           int32_t* n_chunks) {
         int64_t chunk = (keys + target_waves - 1) / target_waves;
@@ -132,7 +133,15 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
         return ng;
     };
     const int64_t ng = plan_waves(1024, knobs().chunk_keys, p.tab.cu_chunk, p.tab.cu_cgrp, &p.chunk_keys, &p.n_chunks);
-    const int64_t ng2 = plan_waves(2048, knobs().chunk_keys2, p.cu_chunk2, p.cu_cgrp2, &p.chunk_keys2, &p.n_chunks2);
+    int64_t ng2 = plan_waves(2048, knobs().chunk_keys2, p.cu_chunk2, p.cu_cgrp2, &p.chunk_keys2, &p.n_chunks2);
+    if (p.row_groups > 1) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
+        ng2 = 0;
+        for (int s = 0; s < sh->n_seq; ++s) {
+            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
+            ng2 += (L + kMaxRowTiles * kKeyTile - 1) / (kMaxRowTiles * kKeyTile);
+            p.cu_cgrp2[s + 1] = (int32_t)ng2;
+        }
+    }
     if ((int64_t)p.n_layers * (ng > ng2 ? ng : ng2) * p.h_kv >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
     if ((int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
 
@@ -698,7 +707,7 @@ int jq_map_mse_fused(const jq_shape* shape, const void* Q_a, const void* Q_b, in
     hipStream_t st = (hipStream_t)stream;
     char* w = (char*)ws;
     float* map_a = (float*)(w + pa.off_scores);
-    float* map_b = (float*)(w + off_b + pb.off_scores);  // holds the sums of the response's earlier row groups, if any
+    float* map_b = (float*)(w + off_b + pb.off_scores);  // (addresses only: the comparing launch stores no scores)
     hipError_t e = launch_score(pa, Q_a, K, map_a, w, st);
     MseFuse fuse;
     fuse.ref = map_a;

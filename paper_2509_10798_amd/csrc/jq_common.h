@@ -44,13 +44,13 @@ struct Plan {
     const int32_t* layer_budgets;   // DEVICE [n_layers][n_seq] or null: per-layer budgets (tab.cu_bud then holds the largest)
     int32_t rows;         // n_q * group: query rows that share one KV head
     int32_t row_tiles;    // ceil(rows / 32)
-    int32_t row_groups;   // ceil(row_tiles / 4): passes of the score kernels over K
+    int32_t row_groups;   // ceil(row_tiles / 4): 1, or the groups of rows that the first pass handles side by side
     int32_t chunk_keys;   // a sequence of L keys gets ceil(L / chunk_keys) score waves per head (multiple of 32)
     int32_t n_chunks;     // such waves per layer and head, over all sequences (tab.cu_chunk counts them)
     // the same for the second K pass when a first one has run (tab holds the first pass's tables)
     int32_t chunk_keys2, n_chunks2;
     int32_t cu_chunk2[JQ_MAX_SEQ + 1], cu_cgrp2[JQ_MAX_SEQ + 1];
-    float scale;          // logit scale actually used
+    double scale;         // logit scale actually used
     // paged cache (block_table null: dense K, V): page = 1 << page_shift tokens, n_pages per layer's pool
     const int32_t* block_table;  // DEVICE [n_seq][max_pages]
     int32_t page_shift, n_pages, max_pages;

@@ -42,12 +42,12 @@ struct ScoreArgs {
     const uint16_t* K;
     const uint16_t* K_tail;  // [n_layers][n_seq][n_q][h_kv][d] keys of the soft tokens themselves, or null
     const float* lse;        // [n_layers][n_seq][n_q][h_q] caller-supplied natural-log normalisers, or null
-    float inv_scale;         // 1 / scale
+    double inv_scale, inv_c;        // 1 / scale, 1 / c
     int32_t one_L, one_waves;  // single-sequence calls: the sequence's length and its number of waves per head (0
                                // otherwise), next to the pointers, so that a wave's first kernel-argument reads
                                // do not chain through the per-sequence tables further down
     float2* stats;    // [n_layers][n_cgrp of pass 1][h_kv][RP]: (m, Z) per pass-1 workgroup
-    uint2* aug;       // [n_layers][n_seq][h_kv][RP]: bf16 triple of -beta/c
+    uint2* aug;       // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
     float* scores;    // [n_layers][h_kv][T]
     int32_t n_layers, n_seq, n_q, h_q, h_kv, group, rows, RP, chunk_keys, n_chunks;
     int32_t n_cgrp;       // workgroups per layer and head: sum over sequences of ceil(waves / 4)
@@ -57,8 +57,8 @@ struct ScoreArgs {
     int32_t group_shift;  // log2(group) when group is a power of two, else -1
     int32_t window;       // 1: the queries are the sequence's own last n_q tokens; query i sees keys 0 .. L - n_q + i
     int32_t depth;        // key tiles a wave keeps in flight: 1 (the default) or 2
-    int32_t row_tile0;   // first query-row tile of this launch
-    int32_t accumulate;  // pass 2: add to `scores` instead of overwriting
+    int32_t n_rg, rg0;    // first pass: groups of NQT query-row tiles in this launch (1 unless a head has more than
+                          // kMaxRowTiles), and the first of them
     float c;             // scale * log2(e)
     int64_t T;
     uint32_t* zero;      // combine: words to clear for the later selection stage (nullable)
@@ -111,6 +111,7 @@ __device__ __forceinline__ void wait_frags_read() {
 // surplus waves without tiles (they only help with the query rows).
 struct WaveItem {
     int layer, seq, g;
+    int rg;                           // group of query-row tiles (0 unless the launch has several)
     int wave, n_waves;                // w and W
     int L;                            // keys in the sequence
     int n_tiles;                      // tiles this wave owns (0: surplus wave)
@@ -118,12 +119,19 @@ struct WaveItem {
 };
 
 __device__ __forceinline__ void wave_item(const ScoreArgs& a, bool reverse, WaveItem& w) {
-    uint32_t b = blockIdx.x;  // the grid is exactly n_layers * n_cgrp * h_kv workgroups (below 2^31: 32-bit arithmetic)
+    uint32_t b = blockIdx.x;  // the grid is exactly n_layers * n_cgrp * n_rg * h_kv workgroups (below 2^31: 32-bit arithmetic)
     if (reverse) b = gridDim.x - 1 - b;
     // readfirstlane makes the wave index (and everything derived from it) a scalar for the compiler
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     w.g = (int)(b % (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row
-    const uint32_t rest = b / (uint32_t)a.h_kv;
+    uint32_t rest = b / (uint32_t)a.h_kv;
+    w.rg = 0;
+    if (a.n_rg > 1) {  // row groups next: the workgroups that read the same keys run side by side (with eight heads on one XCD)
+        w.rg = a.rg0 + (int)(rest % (uint32_t)a.n_rg);
+        rest /= (uint32_t)a.n_rg;
+    } else {
+        w.rg = a.rg0;
+    }
     const int cg = (int)(rest % (uint32_t)a.n_cgrp);
     w.layer = (int)(rest / (uint32_t)a.n_cgrp);
     if (a.one_L) {  // one sequence: nothing to look up
@@ -269,7 +277,7 @@ __device__ __forceinline__ void q_rows_where(const ScoreArgs& a, const WaveItem&
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + (lane >> 4);
-        const int row = (a.row_tile0 + wv) * kRowTile + r;
+        const int row = (w.rg * NQT + wv) * kRowTile + r;
         const bool valid = row < a.rows;
         const int rowc = valid ? row : 0;
         int it, hh;
@@ -500,7 +508,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
     // soft token of this lane's query row in each query tile (row r = i * group + hh): it sees soft tokens 0..i
     int soft_i[NQT];
 #pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) soft_i[qt] = ((a.row_tile0 + qt) * kRowTile + (lane & 31)) / a.group;
+    for (int qt = 0; qt < NQT; ++qt) soft_i[qt] = ((w.rg * NQT + qt) * kRowTile + (lane & 31)) / a.group;
     // The kernel holds TWO copies of the tile body, not one per case: the hot one (unmasked tile, offsets fixed
     // after the wave's first tile) and a general one whose masking and offset rule are run-time flags, used by the
     // few masked tiles (partial last tile, window, soft tokens' own keys) and by the rare repeat of a sweep.
@@ -574,7 +582,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
         if (half == 0) mine[qt * kRowTile + lane] = make_float2(mm, zz);
     }
     __syncthreads();
-    if (threadIdx.x < NQT * kRowTile) {
+    const int row = w.rg * NQT * kRowTile + (int)threadIdx.x;  // the last group may reach past the head's row tiles
+    if (threadIdx.x < NQT * kRowTile && row < a.RP) {
         float M = -1.0e30f, Z = 0.f;
 #pragma unroll
         for (int wv = 0; wv < kScoreWaves; ++wv) {
@@ -584,7 +593,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
             M = mm;
         }
         const int cg = (a.one_L ? 0 : a.tab.cu_cgrp[w.seq]) + w.wave / kScoreWaves;  // this workgroup among the layer's, per head
-        a.stats[(((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g) * a.RP + a.row_tile0 * kRowTile + threadIdx.x] = make_float2(M, Z);
+        a.stats[(((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g) * a.RP + row] = make_float2(M, Z);
     }
 }
 
@@ -592,7 +601,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
 // to the other kernels of a step in the library's code (see jq_lib.hip).
 template __global__ void jq_stats_kernel<4, false>(ScoreArgs);
 
-// -beta/c as the three truncated bf16 terms that enter the second pass through its extra MFMA step.
+// -beta/c as the three bf16 terms (all 24 bits of an fp32 number) that enter the second pass through its extra MFMA step.
+// (A fourth term, bits 25..32, is truncated away inside the MFMA's addition: a common factor 1 + 3e-7.)
 __device__ __forceinline__ uint2 split_bf16x3(float x) {
     const uint32_t hi = __float_as_uint(x) & 0xFFFF0000u;
     const float r1 = x - __uint_as_float(hi);
@@ -601,6 +611,15 @@ __device__ __forceinline__ uint2 split_bf16x3(float x) {
     const uint32_t lo = __float_as_uint(r2) & 0xFFFF0000u;
     return make_uint2((hi >> 16) | mid, lo >> 16);
 }
+// ... of a query row with statistics (m, Z): beta = m + log2 Z.  Every error here is a common factor in all scores of the
+// row, so it is formed in fp64 and rounded once.  v_log_f32 rounds towards zero -- at Z in 2^10..2^16 its results are
+// 4.7e-7 too small on average, a factor 1 + 3.2e-7 in every score -- so it only sees the mantissa (mean error 1e-8).
+// Scores are now 1e-7 from the 64-bit result (2-norm; 3.6e-7 before).
+__device__ __forceinline__ uint2 neg_beta_terms(float m, float z, double inv_c) {
+    const double beta = (double)m + (double)__builtin_amdgcn_frexp_expf(z) + (double)__builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(z));
+    return split_bf16x3((float)(-beta * inv_c));
+}
+constexpr float kPadTerm = -1.0e30f;  // for padded rows: 2^(c * x) = 0
 
 constexpr int kCombineLanes = 32;  // partial-lanes per query row
 __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(ScoreArgs a) {
@@ -608,50 +627,52 @@ __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(Sc
     __shared__ float2 part[kCombineLanes][kRowTile];
     const int r = threadIdx.x & (kRowTile - 1), kl = threadIdx.x / kRowTile;
     const int tiles = a.RP / kRowTile;
-    const int rt = blockIdx.x % tiles;
-    int rest = blockIdx.x / tiles;
-    const int g = rest % a.h_kv;
-    rest /= a.h_kv;
-    const int s = rest % a.n_seq;
-    const int layer = rest / a.n_seq;
-    const int row = rt * kRowTile + r;
-
     if (a.zero) {  // clear the selection histograms and counters while we are here
         const uint64_t per = (a.zero_words + gridDim.x - 1) / gridDim.x;
         const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
         for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
     }
 
-    const int c0 = a.tab.cu_cgrp[s], c1 = a.tab.cu_cgrp[s + 1];
-    const float2* p = a.stats + (((int64_t)layer * a.n_cgrp + c0) * a.h_kv + g) * a.RP + row;
-    const int64_t step = (int64_t)a.h_kv * a.RP;
-    float M = -1.0e30f, Z = 0.f;
-    for (int k0 = kl; k0 < c1 - c0; k0 += 8 * kCombineLanes) {  // 8 independent loads in flight per thread
-        float2 mz[8];
+    const int64_t n_items = (int64_t)a.n_layers * a.n_seq * a.h_kv * tiles;  // every workgroup of a normal call has one
+    for (int64_t item = blockIdx.x; item < n_items; item += gridDim.x) {
+        const int rt = (int)(item % tiles);
+        int64_t rest = item / tiles;
+        const int g = (int)(rest % a.h_kv);
+        rest /= a.h_kv;
+        const int s = (int)(rest % a.n_seq);
+        const int layer = (int)(rest / a.n_seq);
+        const int row = rt * kRowTile + r;
+        if (item != blockIdx.x) __syncthreads();  // `part` is still being read
+        const int c0 = a.tab.cu_cgrp[s], c1 = a.tab.cu_cgrp[s + 1];
+        const float2* p = a.stats + (((int64_t)layer * a.n_cgrp + c0) * a.h_kv + g) * a.RP + row;
+        const int64_t step = (int64_t)a.h_kv * a.RP;
+        float M = -1.0e30f, Z = 0.f;
+        for (int k0 = kl; k0 < c1 - c0; k0 += 8 * kCombineLanes) {  // 8 independent loads in flight per thread
+            float2 mz[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int k = k0 + u * kCombineLanes;
-            mz[u] = k < c1 - c0 ? p[k * step] : make_float2(-1.0e30f, 0.f);
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u * kCombineLanes;
+                mz[u] = k < c1 - c0 ? p[k * step] : make_float2(-1.0e30f, 0.f);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float mm = fmaxf(M, mz[u].x);
+                Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz[u].y * __builtin_amdgcn_exp2f(mz[u].x - mm);
+                M = mm;
+            }
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float mm = fmaxf(M, mz[u].x);
-            Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz[u].y * __builtin_amdgcn_exp2f(mz[u].x - mm);
-            M = mm;
+        part[kl][r] = make_float2(M, Z);
+        __syncthreads();
+        if (kl == 0) {
+            for (int k = 1; k < kCombineLanes; ++k) {  // fixed order: deterministic
+                const float2 mz = part[k][r];
+                const float mm = fmaxf(M, mz.x);
+                Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz.y * __builtin_amdgcn_exp2f(mz.x - mm);
+                M = mm;
+            }
+            a.aug[((int64_t)(layer * a.n_seq + s) * a.h_kv + g) * a.RP + row] = row < a.rows ? neg_beta_terms(M, Z, a.inv_c) : split_bf16x3(kPadTerm);
         }
     }
-    part[kl][r] = make_float2(M, Z);
-    __syncthreads();
-    if (kl != 0) return;
-    for (int k = 1; k < kCombineLanes; ++k) {  // fixed order: deterministic
-        const float2 mz = part[k][r];
-        const float mm = fmaxf(M, mz.x);
-        Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz.y * __builtin_amdgcn_exp2f(mz.x - mm);
-        M = mm;
-    }
-    // padded rows (row >= rows) get 2^(c*x) = 0
-    const float x = row < a.rows ? -(M + __log2f(Z)) / a.c : -1.0e30f;
-    a.aug[((int64_t)(layer * a.n_seq + s) * a.h_kv + g) * a.RP + row] = split_bf16x3(x);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -666,8 +687,7 @@ __device__ __forceinline__ f32x16 score_chain(const bf16x8 (&q)[8], bf16x8 qaug,
 }
 
 // FROM_LSE: the caller supplied the normalisers and no statistics pass has run: lse becomes the -beta/c terms
-// on the fly (beta = lse * log2 e, c = scale * log2 e, so -beta/c = -lse / scale), and the launch also clears
-// the words the selection stage needs cleared.
+// on the fly (beta = lse * log2 e, c = scale * log2 e, so -beta/c = -lse / scale), and the launch also clears the words the selection stage needs cleared.
 // DIFF: the scores are not stored; (ref / rows_ref - score / rows_own)^2 is summed instead (Eq. 5 of the paper on
 // the maps of Eq. 3 and Eq. 4), in fp64 per lane, then in a fixed order over lanes and waves.
 template <int NQT, bool FROM_LSE, bool PAGED, bool DIFF = false>
@@ -712,7 +732,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
     const int mrow = min((int)(threadIdx.x >> 1), NQT * kRowTile - 1);
     const int c0 = (a.one_L || !fused) ? 0 : a.cu_part[w.seq];
     const int n_p = !fused ? 1 : a.one_L ? a.n_part : a.cu_part[w.seq + 1] - c0;
-    const float2* pp = a.stats + (((int64_t)w.layer * a.n_part + c0) * a.h_kv + w.g) * a.RP + a.row_tile0 * kRowTile + mrow;
+    const float2* pp = a.stats + (((int64_t)w.layer * a.n_part + c0) * a.h_kv + w.g) * a.RP + mrow;
     const int64_t pstep = (int64_t)a.h_kv * a.RP;
     const u32x4* qsrc[8];
     uint32_t qpad;
@@ -720,12 +740,12 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
     const float* nsrc[NQT];  // FROM_LSE: the lane's rows' normalisers; otherwise the merged -beta/c terms of a combine launch
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
-        const int row = min((a.row_tile0 + qt) * kRowTile + (lane & 31), a.rows - 1);
+        const int row = min(qt * kRowTile + (lane & 31), a.rows - 1);
         if (FROM_LSE) {
             const int i = row / a.group, h = w.g * a.group + row % a.group;
             nsrc[qt] = a.lse + ((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q + i) * a.h_q + h;
         } else {
-            nsrc[qt] = (const float*)(a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + (a.row_tile0 + qt) * kRowTile + (lane & 31));
+            nsrc[qt] = (const float*)(a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + qt * kRowTile + (lane & 31));
         }
     }
     const int t_first = w.n_tiles > 0 ? tile_of(0) : 0;  // a surplus wave requests the sequence's first tile and drops it
@@ -756,9 +776,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
     if (FROM_LSE) {
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
-            const int row = (a.row_tile0 + qt) * kRowTile + (lane & 31);
-            // padded rows get 2^(c*x) = 0
-            aug_direct[qt] = split_bf16x3(row < a.rows ? -__uint_as_float(aug_direct[qt].x) * a.inv_scale : -1.0e30f);
+            const int row = qt * kRowTile + (lane & 31);
+            aug_direct[qt] = split_bf16x3(row < a.rows ? (float)(-(double)__uint_as_float(aug_direct[qt].x) * a.inv_scale) : kPadTerm);
         }
     }
     q_rows_stage<NQT>(lane, &lds[0][0][0], qraw, qpad, qf);
@@ -788,10 +807,10 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
         const float oM = __shfl_xor(cM, 1), oZ = __shfl_xor(cZ, 1);  // the odd neighbour's half; even threads finish the row
         const float mm = fmaxf(cM, oM);
         const float zz = cZ * __builtin_amdgcn_exp2f(cM - mm) + oZ * __builtin_amdgcn_exp2f(oM - mm);
-        const int crow = a.row_tile0 * kRowTile + (int)(threadIdx.x >> 1);
+        const int crow = (int)(threadIdx.x >> 1);
         const uint32_t aug_s = lds_addr(&lds[0][1][0]);  // the query rows have left this slot (second barrier of q_rows_stage)
         if (!(threadIdx.x & 1) && (threadIdx.x >> 1) < NQT * kRowTile) {
-            lds_put8(aug_s + 8u * (threadIdx.x >> 1), split_bf16x3(crow < a.rows ? -(mm + __log2f(zz)) / a.c : -1.0e30f));
+            lds_put8(aug_s + 8u * (threadIdx.x >> 1), crow < a.rows ? neg_beta_terms(mm, zz, a.inv_c) : split_bf16x3(kPadTerm));
             lds_wait_all();
         }
         bare_barrier();
@@ -829,11 +848,10 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
             float* o = out + t * kKeyTile + lane;
             if (t * kKeyTile + lane >= n_scored) v = 0.f;
             if (DIFF) {
-                const float own = a.accumulate ? *o + v : v;
-                const double d = (double)a.diff_ref[o - a.scores] * (double)a.diff_inv_ref - (double)own * (double)a.diff_inv_own;
+                const double d = (double)a.diff_ref[o - a.scores] * (double)a.diff_inv_ref - (double)v * (double)a.diff_inv_own;
                 dacc += d * d;
             } else {
-                *o = a.accumulate ? *o + v : v;
+                *o = v;
             }
         }
     };
@@ -899,6 +917,172 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
 template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  // placement: see jq_lib.hip
 
 // ------------------------------------------------------------------------------------------------
+// many query rows (more than kMaxRowTiles tiles per KV head): keys stationary, query rows streamed
+// ------------------------------------------------------------------------------------------------
+// With n_q * group > 128 (response tokens as queries: the upper bound of Eq. 4, the training objective) a head's rows
+// no longer fit a wave's registers.  The first pass then only gets a further grid dimension over groups of row tiles.
+// Here the roles swap: a workgroup holds 128 keys (four tiles, every wave all of them, 128 VGPRs) and its four waves
+// sweep the head's row tiles, each its own quarter, streaming them through their private LDS slots exactly as the other
+// kernels stream key tiles; a key's sum over all rows then forms in registers, is merged over the four waves in wave
+// order and stored once.  Before, every 128 rows took a launch of each pass that read K and added to the scores in
+// memory: launches of 64..256 keys per wave that were mostly start-up.  The work is a contraction that K does not
+// bound (every key is used by all rows): 9 MFMA per 32 x 32 logits against 16 exp2/mul/add per lane.  Measured at 16384
+// keys x 8 heads x 1024 rows: eight launches of 12.4 us and eight first passes of 10.9 us before, 46 + 45 us + 5 us for
+// the combine launch now.
+// -beta/c comes from `aug`, which a combine launch (or jq_lse_aug_kernel) has filled.
+template <bool PAGED, bool DIFF>
+__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(ScoreArgs a) {
+    __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
+    __shared__ double diff_s[DIFF ? 2 : 1];
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char* slots = &lds[wv][0][0];
+    // one workgroup per (layer, group of 128 keys, head), heads fastest: with eight heads an XCD's L2 holds one head's rows
+    WaveItem w;
+    w.g = (int)(blockIdx.x % (uint32_t)a.h_kv);
+    const uint32_t rest = blockIdx.x / (uint32_t)a.h_kv;
+    const int cg = (int)(rest % (uint32_t)a.n_cgrp);
+    w.layer = (int)(rest / (uint32_t)a.n_cgrp);
+    w.seq = a.one_L ? 0 : find_seq(a.tab.cu_cgrp, a.tab.n_seq, cg);
+    w.tok0 = a.tab.cu_seq[w.seq];
+    w.L = a.tab.cu_seq[w.seq + 1] - a.tab.cu_seq[w.seq];
+    const int tile0 = (cg - a.tab.cu_cgrp[w.seq]) * kMaxRowTiles;  // first key tile of the group
+
+    // ---- query-row tiles: global -> LDS, laid out as key tiles are (see fetch_tile) ----
+    const char* qbase = (const char*)a.Q + (((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q) * a.h_q + (int64_t)w.g * a.group) * kHeadDim * 2;
+    const int n_rt = (a.rows + kRowTile - 1) / kRowTile;
+    const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...
+    const uint2* aug = a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + (lane & 31);
+    const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
+    auto fetch_rows = [&](int k) __attribute__((always_inline)) {
+        const int r0 = (wv + k * kScoreWaves) * kRowTile;
+        char* slot = slots + (k & 1) * kSlotBytes;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = 4 * i + (lane >> 4);
+            const int row = min(r0 + r, a.rows - 1);  // rows past the end re-read the last one: their aug makes every term 0
+            int it, hh;
+            if (a.group_shift >= 0) { it = row >> a.group_shift; hh = row & (a.group - 1); }
+            else { it = row / a.group; hh = row % a.group; }
+            const char* src = qbase + it * tok_bytes + (int64_t)hh * (kHeadDim * 2) + (((lane & 15) ^ (r & 15)) << 4);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(slot + 1024 * i), 16, 0, 0);
+        }
+    };
+
+    // ---- start-up: wave wv fetches key tile wv into its second slot, its first row tile into its first ----
+    const KeyStream ks = key_stream<PAGED>(a, w);
+    const int last_tile = (w.L - 1) / kKeyTile;
+    {
+        const int t = min(tile0 + wv, last_tile);  // tiles past the sequence's end repeat its last one and are not stored
+        const uint32_t off = tile_offset<PAGED>(ks, t, tile_page<PAGED>(ks, t));
+        fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, w.L - t * kKeyTile), lane);
+    }
+    uint2 aug_next = make_uint2(0u, 0u);
+    if (n_mine > 0) {  // uniform; at least wave 0 has tiles
+        fetch_rows(0);
+        aug_next = aug[wv * kRowTile];
+    }
+    wait_tile_landed(false);
+    bare_barrier();
+    bf16x8 kf[kMaxRowTiles][8];
+#pragma unroll
+    for (int kt = 0; kt < kMaxRowTiles; ++kt) lds_get_frags_waited(lds_addr(&lds[kt][1][0]), kf[kt], lane);
+    bare_barrier();
+
+    u32x4 ones_bits = {0u, 0u, 0u, 0u};
+    if (half == 0) { ones_bits[0] = 0x3F803F80u; ones_bits[1] = 0x00003F80u; }  // 1.0 at elements 0..2
+    const bf16x8 ones = as_bf16x8(ones_bits);
+    const float c = a.c;
+    float sum[kMaxRowTiles];
+#pragma unroll
+    for (int kt = 0; kt < kMaxRowTiles; ++kt) sum[kt] = 0.f;
+    for (int k = 0; k < n_mine; ++k) {
+        wait_tile_landed(false);
+        bf16x8 qf[8];
+        lds_get_frags(slots + (k & 1) * kSlotBytes, qf, lane);
+        u32x4 av = {0u, 0u, 0u, 0u};
+        if (half == 0) { av[0] = aug_next.x; av[1] = aug_next.y; }
+        const bf16x8 qaug = as_bf16x8(av);
+        if (k + 1 < n_mine) {
+            wait_frags_read();
+            fetch_rows(k + 1);
+            aug_next = aug[(wv + (k + 1) * kScoreWaves) * kRowTile];
+        }
+        // as in jq_score_kernel: the MFMA chain of the next key tile runs between the exp2/add work of this one
+        f32x16 acc = score_chain(qf, qaug, kf[0], ones);
+#pragma unroll
+        for (int kt = 0; kt < kMaxRowTiles; ++kt) {
+            f32x16 nxt = acc;
+            if (kt + 1 < kMaxRowTiles) nxt = score_chain(qf, qaug, kf[kt + 1], ones);
+            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) {
+                s0 += __builtin_amdgcn_exp2f(acc[v + 0] * c);
+                s1 += __builtin_amdgcn_exp2f(acc[v + 1] * c);
+                s2 += __builtin_amdgcn_exp2f(acc[v + 2] * c);
+                s3 += __builtin_amdgcn_exp2f(acc[v + 3] * c);
+            }
+            sum[kt] += (s0 + s1) + (s2 + s3);
+            if (kt + 1 < kMaxRowTiles) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // then a few VALU
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            acc = nxt;
+        }
+    }
+#pragma unroll
+    for (int kt = 0; kt < kMaxRowTiles; ++kt) {
+        sum[kt] += __shfl_xor(sum[kt], 32);  // the two lane halves hold complementary query rows of the same key
+        if (half == 0) ((float*)slots)[kt * kKeyTile + lane] = sum[kt];  // the wave's slots are idle by now
+    }
+    __syncthreads();
+    const int key = tile0 * kKeyTile + (int)threadIdx.x;  // threads 0..127: one key each
+    double dacc = 0.0;
+    if (threadIdx.x < kMaxRowTiles * kKeyTile && key < w.L) {
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < kScoreWaves; ++i) v += ((const float*)&lds[i][0][0])[threadIdx.x];
+        if (a.window && key >= w.L - a.n_q) v = 0.f;  // the window's own positions report 0
+        const int64_t o = ((int64_t)w.layer * a.h_kv + w.g) * a.T + w.tok0 + key;
+        if (DIFF) {
+            const double d = (double)a.diff_ref[o] * (double)a.diff_inv_ref - (double)v * (double)a.diff_inv_own;
+            dacc = d * d;
+        } else {
+            a.scores[o] = v;
+        }
+    }
+    if (DIFF) {  // butterfly within waves 0 and 1, then their two sums: a fixed order
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) dacc += __shfl_xor(dacc, off);
+        if (lane == 0 && wv < 2) diff_s[wv] = dacc;
+        __syncthreads();
+        if (threadIdx.x == 0) a.diff_part[((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g] = diff_s[0] + diff_s[1];
+    }
+}
+
+// Supplied normalisers with many query rows: lse -> the bf16 terms of -beta/c (as jq_score_kernel<FROM_LSE>
+// does it per wave), one thread per row, and the words that the selection needs cleared.
+__global__ __launch_bounds__(256) void jq_lse_aug_kernel(ScoreArgs a, int64_t n) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+        const int row = (int)(i % a.RP);
+        const int64_t rest = i / a.RP;
+        const int g = (int)(rest % a.h_kv);
+        const int64_t ls = rest / a.h_kv;  // layer * n_seq + sequence
+        const int rowc = min(row, a.rows - 1);
+        const float x = a.lse[(ls * a.n_q + rowc / a.group) * a.h_q + (int64_t)g * a.group + rowc % a.group];
+        a.aug[i] = split_bf16x3(row < a.rows ? (float)(-(double)x * a.inv_scale) : kPadTerm);
+    }
+    if (a.zero)
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.zero_words; i += (uint64_t)stride) a.zero[i] = 0u;
+}
+
+// ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
 template <bool PAGED>
@@ -955,8 +1139,10 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.group_shift = -1;
     for (int sh = 0; sh < 16; ++sh)
         if (p.group == (1 << sh)) a.group_shift = sh;
-    a.row_tile0 = 0; a.accumulate = 0;
-    a.c = p.scale * 1.4426950408889634f;
+    a.n_rg = 1; a.rg0 = 0;
+    a.c = (float)(p.scale * 1.4426950408889634074);
+    a.inv_scale = 1.0 / p.scale;
+    a.inv_c = 1.0 / (double)a.c;
     a.T = p.T;
     a.zero = zero; a.zero_words = zero_words;
     a.tab = p.tab;
@@ -972,25 +1158,30 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     dim3 grid((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
     hipError_t e;
     a.lse = lse;
-    a.inv_scale = 1.0f / p.scale;
     a.n_part = 0; a.fuse_combine = 0;
     for (int s = 0; s <= p.n_seq; ++s) a.cu_part[s] = 0;
+    const bool many_rows = p.row_groups > 1;  // more query rows per KV head than a wave holds: jq_score_rows_kernel
     if (!lse) {
-        for (int rg = 0; rg < p.row_groups; ++rg) {
-            a.row_tile0 = rg * kMaxRowTiles;
-            const int nqt = min(kMaxRowTiles, p.row_tiles - a.row_tile0);
-            e = paged ? launch_stats_n<true>(nqt, a, grid, st, marks) : launch_stats_n<false>(nqt, a, grid, st, marks);
+        const int nqt = many_rows ? kMaxRowTiles : p.row_tiles;
+        // all row groups in one launch (in several where the grid would get too large for one)
+        const int64_t wgs = grid.x;
+        const int per_launch = (int)max((int64_t)1, min((int64_t)p.row_groups, ((int64_t)1 << 23) / wgs));
+        for (a.rg0 = 0; a.rg0 < p.row_groups; a.rg0 += per_launch) {
+            a.n_rg = min(per_launch, p.row_groups - a.rg0);
+            const dim3 g1((unsigned)(wgs * a.n_rg));
+            e = paged ? launch_stats_n<true>(nqt, a, g1, st, marks) : launch_stats_n<false>(nqt, a, g1, st, marks);
             if (e != hipSuccess) return e;
         }
+        a.n_rg = 1; a.rg0 = 0;
         // Pass 1 leaves one partial per workgroup.  With few of them per sequence every pass-2 workgroup merges
         // its head's partials itself; a very long sequence has hundreds, and then one small launch merges them
         // once (and clears the selection's words on the way).
         int max_parts = 0;
         for (int s = 0; s < p.n_seq; ++s) max_parts = max(max_parts, p.tab.cu_cgrp[s + 1] - p.tab.cu_cgrp[s]);
-        a.fuse_combine = max_parts <= 64;
+        a.fuse_combine = max_parts <= 64 && !many_rows;
         if (!a.fuse_combine) {
             const int64_t n_row_tiles = (int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles;
-            e = launch_kernel(jq_combine_kernel, dim3((unsigned)n_row_tiles), dim3(kRowTile * kCombineLanes), 0, st, nullptr, -1, a);
+            e = launch_kernel(jq_combine_kernel, dim3((unsigned)min(n_row_tiles, (int64_t)1 << 20)), dim3(kRowTile * kCombineLanes), 0, st, nullptr, -1, a);
             if (e != hipSuccess) return e;
             a.zero = nullptr;  // done by the combine launch
         }
@@ -1004,23 +1195,31 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
         a.depth = depth_second;
     }
-    for (int rg = 0; rg < p.row_groups; ++rg) {
-        a.row_tile0 = rg * kMaxRowTiles;
-        a.accumulate = rg > 0;
-        if (rg > 0) a.zero = nullptr;  // cleared once, by the first launch (normalisers supplied: no combine step does it)
-        const int nqt = min(kMaxRowTiles, p.row_tiles - a.row_tile0);
-        if (fuse && rg == p.row_groups - 1) {  // the last row group completes the scores: compare instead of storing
+    if (many_rows) {
+        if (lse) {  // the second pass's own tables and the -beta/c terms, which a combine launch provides otherwise
+            const int64_t n = (int64_t)p.n_layers * p.n_seq * p.h_kv * a.RP;
+            e = launch_kernel(jq_lse_aug_kernel, dim3((unsigned)min((n + 255) / 256, (int64_t)2048)), dim3(256), 0, st, nullptr, -1, a, n);
+            if (e != hipSuccess) return e;
+            for (int s = 0; s <= p.n_seq; ++s) a.tab.cu_cgrp[s] = p.cu_cgrp2[s];
+            a.n_cgrp = p.cu_cgrp2[p.n_seq];
+            grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
+        }
+        const dim3 block(kScoreWaves * 64);
+        if (fuse) {
             a.diff_ref = fuse->ref; a.diff_part = fuse->part;
             a.diff_inv_ref = fuse->inv_rows_ref; a.diff_inv_own = fuse->inv_rows_own;
-            e = launch_score_diff_n(nqt, a, grid, st);
-            if (e != hipSuccess) return e;
-            continue;
+            return launch_kernel(jq_score_rows_kernel<false, true>, grid, block, 0, st, nullptr, -1, a);
         }
-        if (paged) e = lse ? launch_score_n<true, true>(nqt, a, grid, st, marks) : launch_score_n<false, true>(nqt, a, grid, st, marks);
-        else e = lse ? launch_score_n<true, false>(nqt, a, grid, st, marks) : launch_score_n<false, false>(nqt, a, grid, st, marks);
-        if (e != hipSuccess) return e;
+        if (paged) return launch_kernel(jq_score_rows_kernel<true, false>, grid, block, 0, st, marks, kTrScore, a);
+        return launch_kernel(jq_score_rows_kernel<false, false>, grid, block, 0, st, marks, kTrScore, a);
     }
-    return hipSuccess;
+    if (fuse) {  // compare the scores instead of storing them
+        a.diff_ref = fuse->ref; a.diff_part = fuse->part;
+        a.diff_inv_ref = fuse->inv_rows_ref; a.diff_inv_own = fuse->inv_rows_own;
+        return launch_score_diff_n(p.row_tiles, a, grid, st);
+    }
+    if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);
+    return lse ? launch_score_n<true, false>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, false>(p.row_tiles, a, grid, st, marks);
 }
 
 }  // namespace jq
