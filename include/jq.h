@@ -368,10 +368,9 @@ int jq_copy_probe(const void* src, void* dst, size_t bytes, void* stream);
 
 /* Ablation and diagnosis knobs.  The library reads a few environment variables ONCE per process, at its first
  * call (never on the path of a later call): JQ_CHUNK_KEYS / JQ_CHUNK_KEYS_2 (keys per wave in the first / second
- * pass over K, multiples of 32 up to 8192), JQ_DEPTH_1 / JQ_DEPTH_2 (key tiles a wave keeps in flight, 1 or 2),
- * JQ_LOG (print the HIP error string when a launch is refused).  Results do not depend on them beyond rounding
- * order.  jq_reload_knobs reads the environment again; it must not run concurrently with other calls (tests use
- * it to force rarely taken code paths at small sizes).  Always returns JQ_OK. */
+ * pass over K, multiples of 32 up to 8192), JQ_LOG (print the HIP error string when a launch is refused).  Results do
+ * not depend on them beyond rounding order.  jq_reload_knobs reads the environment again; it must not run
+ * concurrently with other calls (tests use it to force rarely taken code paths at small sizes).  Always returns JQ_OK. */
 int jq_reload_knobs(void);
 
 /* Static, never-NULL description of a status code. */

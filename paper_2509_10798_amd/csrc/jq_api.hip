@@ -16,15 +16,9 @@ static Knobs read_knobs() {
         const long v = env ? std::atol(env) : 0;
         return (int32_t)((v >= kKeyTile && v <= 8192 && v % kKeyTile == 0) ? v : 0);
     };
-    auto depth = [](const char* name) {
-        const char* env = std::getenv(name);
-        return (int32_t)(env && (env[0] == '1' || env[0] == '2') && env[1] == 0 ? env[0] - '0' : 1);
-    };
     k.chunk_keys = chunk("JQ_CHUNK_KEYS");
     k.chunk_keys2 = chunk("JQ_CHUNK_KEYS_2");
     if (!std::getenv("JQ_CHUNK_KEYS_2")) k.chunk_keys2 = k.chunk_keys;
-    k.depth1 = depth("JQ_DEPTH_1");
-    k.depth2 = depth("JQ_DEPTH_2");
     k.log = std::getenv("JQ_LOG") != nullptr;
     return k;
 }

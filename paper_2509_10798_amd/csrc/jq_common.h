@@ -136,7 +136,6 @@ __device__ inline uint32_t select_key(float x, int j, int L, int keep_first, int
 struct Knobs {
     int32_t chunk_keys;   // JQ_CHUNK_KEYS: keys per wave in the pass that reads K cold (0: planned from the call's size)
     int32_t chunk_keys2;  // JQ_CHUNK_KEYS_2: the same for the second pass (0: JQ_CHUNK_KEYS if set, else planned)
-    int32_t depth1, depth2;  // JQ_DEPTH_1 / JQ_DEPTH_2: key tiles a wave keeps in flight (1 or 2)
     int32_t log;          // JQ_LOG: print the HIP error string when a launch is refused
 };
 const Knobs& knobs();

@@ -56,7 +56,6 @@ struct ScoreArgs {
     int32_t n_part, fuse_combine;
     int32_t group_shift;  // log2(group) when group is a power of two, else -1
     int32_t window;       // 1: the queries are the sequence's own last n_q tokens; query i sees keys 0 .. L - n_q + i
-    int32_t depth;        // key tiles a wave keeps in flight: 1 (the default) or 2
     int32_t n_rg, rg0;    // first pass: groups of NQT query-row tiles in this launch (1 unless a head has more than
                           // kMaxRowTiles), and the first of them
     float c;             // scale * log2(e)
@@ -83,12 +82,10 @@ constexpr int kSlotBytes = kKeyTile * kHeadDim * 2;  // 8 KiB
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // Key tiles arrive through loads that write LDS directly; the compiler does not track them, so the
-// waits are explicit.  Loads complete in issue order, and every tile is exactly 8 loads, hence
-// "at most 8 outstanding" means: everything older than the newest tile has landed.
+// waits are explicit.
 // (s_waitcnt immediates: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8; unused fields = no wait.)
-__device__ __forceinline__ void wait_tile_landed(bool newer_tile_in_flight) {
-    if (newer_tile_in_flight) __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0)
+__device__ __forceinline__ void wait_tile_landed() {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
 }
@@ -156,18 +153,12 @@ __device__ __forceinline__ void wave_item(const ScoreArgs& a, bool reverse, Wave
 // of row r = 4i + (l >> 4), and the hardware stores them at slot + 1024 i + 16 l, i.e. at row r,
 // physical 16-byte chunk (l & 15).  To realise the swizzle "logical chunk c lives at physical chunk
 // c ^ (r & 15)" the lane therefore fetches logical chunk (l & 15) ^ (r & 15) from global memory.
-// With (r & 15) = 4 (i & 3) + (l >> 4) the lane's byte offset takes four values over the 8 loads;
-// the rest of the address is wave-uniform (buffer resource + scalar offset).
-struct TileLanes {
-    uint32_t voff[4];  // (l >> 4) * row_bytes + 16 * (((l & 15) ^ (l >> 4)) ^ 4 j),  j = i & 3
-};
-
-__device__ __forceinline__ TileLanes tile_lanes(int lane, uint32_t row_bytes) {
-    TileLanes tl;
-    const uint32_t a = lane >> 4, x = (lane & 15) ^ a;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tl.voff[j] = a * row_bytes + ((x ^ (4u * j)) << 4);
-    return tl;
+// With (r & 15) = 4 (i & 3) + (l >> 4) the lane's byte offset takes four values over the 8 loads, which differ by an
+// exclusive or of 64 (i & 3) (row_bytes is a multiple of 256): one register; the rest of the address is wave-uniform
+// (buffer resource + scalar offset).
+__device__ __forceinline__ uint32_t tile_lane(int lane, uint32_t row_bytes) {  // the offset at i = 0
+    const uint32_t a = (uint32_t)lane >> 4;
+    return a * row_bytes + ((((uint32_t)lane & 15u) ^ a) << 4);
 }
 
 __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, char* dst, uint32_t voff, uint32_t soff) {
@@ -177,10 +168,10 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, char* dst
 
 // `tile_off` = byte offset of the tile's first key row inside the buffer resource (uniform).
 __device__ __forceinline__ void fetch_tile(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off,
-                                           uint32_t row_bytes, int valid, const TileLanes& tl, int lane) {
+                                           uint32_t row_bytes, int valid, uint32_t tl, int lane) {
     if (valid >= kKeyTile) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl.voff[i & 3], tile_off + 4 * i * row_bytes);
+        for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl ^ (64u * (i & 3)), tile_off + 4 * i * row_bytes);
     } else {  // last, partial tile of a sequence: rows past the end re-read the last valid key (masked later)
         asm volatile("" : "+v"(lane));  // keep this rarely taken path's address arithmetic out of the caller's loop
 #pragma unroll
@@ -206,13 +197,19 @@ __device__ __forceinline__ void fetch_tile_any(__amdgpu_buffer_rsrc_t rsrc, char
 
 // MFMA operand fragments of the tile in `slot`: lane l takes key row (l & 31), logical chunks
 // 2 ks + (l >> 5), ks = 0..7.  The 16 lanes of a quarter wave hit 16 distinct physical chunks.
+// `at` = frag_addr(): the address of ks = 0; the others differ from it by an exclusive or (the swizzle of chunk 2 ks + h is
+// (h ^ r) ^ 2 ks, and a row's 256 bytes are aligned), so that one register serves all eight.
+__device__ __forceinline__ uint32_t frag_addr(const char* slot, int lane) {
+    const uint32_t r = (uint32_t)lane & 31u;
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)slot + r * 256u + ((((uint32_t)lane >> 5) ^ (r & 15u)) << 4);
+}
+__device__ __forceinline__ bf16x8 lds_get_frag(uint32_t at, int ks) {
+    return as_bf16x8(*(const u32x4 __attribute__((address_space(3)))*)(uintptr_t)(at ^ ((uint32_t)ks << 5)));
+}
 __device__ __forceinline__ void lds_get_frags(const char* slot, bf16x8 (&kf)[8], int lane) {
-    const int r = lane & 31;
+    const uint32_t at = frag_addr(slot, lane);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        const int chunk = 2 * ks + (lane >> 5);
-        kf[ks] = as_bf16x8(*(const u32x4*)(slot + r * 256 + ((chunk ^ (r & 15)) << 4)));
-    }
+    for (int ks = 0; ks < 8; ++ks) kf[ks] = lds_get_frag(at, ks);
 }
 
 // ---- start-up: the query rows as MFMA operands of every wave, with the first key tile in flight ---------
@@ -350,14 +347,63 @@ __device__ __forceinline__ int tile_page(const KeyStream& ks, int t) {
     return PAGED ? ((const_i32_ptr)ks.pages)[((uint32_t)t * kKeyTile) >> ks.page_shift] : 0;
 }
 
+// One stage of the sweeps' software pipeline: `step(i)`, i = 0 .. NM - 1, issues the i-th matrix instruction of the NEXT
+// 32 x 32 block (and whatever goes with it, one LDS read), and the sum of 2^arg(v) over the lane's 16 logits of the
+// CURRENT one is formed in between.  A wave issues in order and the matrix core takes 32 cycles per instruction, during
+// which about six VALU instructions (two of them v_exp_f32, 8 cycles) fit; spread evenly, 8 MFMA + 48 VALU take 340
+// cycles, against 435 with the MFMAs in pairs, 520 with them in front, and 260 + 270 where either half stands alone.
+// The order is therefore written out, packet by packet, every value a packet or more ahead of its use, and each value is
+// pinned to its place (an empty volatile asm that names it; sched_barrier alone does not hold pure arithmetic).
+template <class T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+template <int NM, class Step, class Arg>
+__device__ __forceinline__ float exp2_sum_stage(Step step, Arg arg) {
+    static_assert(NM == 8 || NM == 9, "packets are laid out for 8 or 9 MFMAs");
+    float x[16], s[4];
+    auto f = [&](int v) __attribute__((always_inline)) { x[v] = arg(v); pin(x[v]); };
+    auto e = [&](int v) __attribute__((always_inline)) {
+        x[v] = __builtin_amdgcn_exp2f(x[v]);
+        pin(x[v]);
+        if (v < 4) s[v] = x[v];
+    };
+    auto a = [&](int v) __attribute__((always_inline)) { s[v & 3] += x[v]; pin(s[v & 3]); };
+    auto packet = [&](int i) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        step(i);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    packet(0); f(0); f(1); f(2); f(3); e(0); e(1);
+    packet(1); f(4); f(5); f(6); f(7); e(2); e(3);
+    packet(2); f(8); f(9); f(10); f(11); e(4); e(5);
+    packet(3); f(12); f(13); f(14); f(15); e(6); e(7);
+    packet(4); e(8); e(9); a(4); a(5); a(6); a(7);
+    if (NM == 8) {
+        packet(5); e(10); e(11); e(12); a(8); a(9);
+        packet(6); e(13); e(14); a(10); a(11); a(12);
+        packet(7); e(15); a(13); a(14);
+    } else {
+        packet(5); e(10); e(11); a(8); a(9);
+        packet(6); e(12); e(13); a(10); a(11);
+        packet(7); e(14); e(15); a(12); a(13);
+        packet(8); a(14);
+    }
+    a(15);
+    float sum = (s[0] + s[1]) + (s[2] + s[3]);
+    pin(sum);
+    __builtin_amdgcn_sched_barrier(0);
+    return sum;
+}
+
 // ------------------------------------------------------------------------------------------------
 // pass 1: softmax statistics
 // ------------------------------------------------------------------------------------------------
 // One 32-key tile against the wave's query rows: rows of the MFMA result are keys, columns are
 // query rows, so each lane updates the running (m, Z) of its own query column from its 16 keys.
-// MASKED: key (row of the tile) number >= valid[qt] does not exist for query tile qt's column of this lane --
-// used for the last, partial tile of a sequence (one uniform bound) and for the tiles of the soft tokens'
-// own keys, where the bound is causal and differs per lane.
+// Key (row of the tile) number >= valid[qt] does not exist for query tile qt's column of this lane -- the last, partial
+// tile of a sequence (one uniform bound) and the tiles of the soft tokens' own keys, where the bound is causal and
+// differs per lane.
+__device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 acc) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0); }
+__device__ __forceinline__ f32x16 zero_acc() { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; }
 __device__ __forceinline__ f32x16 stats_chain(const bf16x8 (&kf)[8], const bf16x8 (&q)[8]) {
     f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -365,61 +411,31 @@ __device__ __forceinline__ f32x16 stats_chain(const bf16x8 (&kf)[8], const bf16x
     return acc;
 }
 
-// Two instances exist.  <false, true>, the hot one: unmasked tile, offsets m kept as they are, only
-// Z += sum 2^(t - m).  Any offset gives the same (m, Z) pair up to rounding as long as no term overflows; terms
-// that underflow are negligible next to the contribution of the offset's own key.  `flag` there marks the wave's
-// first tile, which sets each lane's offset -- to the largest of four of the lane's 16 logits, so that the first
-// tile runs through the very code of all later ones.  <true, false>, the general one: masked, and `flag` says
-// whether the offsets are kept (then m stays and the update below reduces to Z += sum) or follow the running
-// maximum.
-template <int NQT, bool MASKED, bool FIXED>
+// The general tile: masked, and `keep` says whether the offsets stay as they are (any offset gives the same (m, Z) pair
+// up to rounding as long as no term overflows; terms that underflow are negligible next to the contribution of the
+// offset's own key) or follow the running maximum.
+template <int NQT>
 __device__ __forceinline__ void stats_tile(const bf16x8 (&kf)[8], const bf16x8 (&qf)[NQT][8], float (&m)[NQT],
-                                           float (&z)[NQT], float c, const int (&valid)[NQT], int half, bool flag) {
-    // software pipeline: the MFMA chain of query tile qt+1 is interleaved with the max/exp2/add work of tile qt
+                                           float (&z)[NQT], float c, const int (&valid)[NQT], int half, bool keep) {
     f32x16 acc = stats_chain(kf, qf[0]);
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
-        f32x16 nxt = acc;
-        if (qt + 1 < NQT) nxt = stats_chain(kf, qf[qt + 1]);
-        if (MASKED) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (8 * (v >> 2) + 4 * half + (v & 3) >= valid[qt]) acc[v] = -INFINITY;
-        }
-        float mnew = m[qt];
-        if (FIXED) mnew = flag ? fmaxf(fmaxf(acc[0], acc[5]), fmaxf(acc[10], acc[15])) * c : mnew;
-        if (!FIXED) {
-            float tmax = fmaxf(acc[0], acc[1]);
+        for (int v = 0; v < 16; ++v)
+            if (8 * (v >> 2) + 4 * half + (v & 3) >= valid[qt]) acc[v] = -INFINITY;
+        float tmax = fmaxf(acc[0], acc[1]);
 #pragma unroll
-            for (int v = 2; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
-            mnew = flag ? mnew : fmaxf(m[qt], tmax * c);  // a fully masked column keeps m: 2^(-inf - m) = 0 either way
-        }
-        float s0 = __builtin_amdgcn_exp2f(fmaf(acc[0], c, -mnew));
-        float s1 = __builtin_amdgcn_exp2f(fmaf(acc[1], c, -mnew));
-        float s2 = __builtin_amdgcn_exp2f(fmaf(acc[2], c, -mnew));
-        float s3 = __builtin_amdgcn_exp2f(fmaf(acc[3], c, -mnew));
-#pragma unroll
-        for (int v = 4; v < 16; v += 4) {
-            s0 += __builtin_amdgcn_exp2f(fmaf(acc[v + 0], c, -mnew));
-            s1 += __builtin_amdgcn_exp2f(fmaf(acc[v + 1], c, -mnew));
-            s2 += __builtin_amdgcn_exp2f(fmaf(acc[v + 2], c, -mnew));
-            s3 += __builtin_amdgcn_exp2f(fmaf(acc[v + 3], c, -mnew));
-        }
-        if (FIXED) {
-            z[qt] += (s0 + s1) + (s2 + s3);
-            m[qt] = mnew;
-        } else {
-            z[qt] = z[qt] * __builtin_amdgcn_exp2f(m[qt] - mnew) + ((s0 + s1) + (s2 + s3));
-            m[qt] = mnew;
-        }
-        if (qt + 1 < NQT) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);  // then a few VALU
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int v = 2; v < 16; ++v) tmax = fmaxf(tmax, acc[v]);
+        // a fully masked column keeps m: 2^(-inf - m) = 0 either way
+        const float mnew = keep ? m[qt] : fmaxf(m[qt], tmax * c);
+        z[qt] *= __builtin_amdgcn_exp2f(m[qt] - mnew);
+        m[qt] = mnew;
+        f32x16 nxt = zero_acc();
+        z[qt] += exp2_sum_stage<8>(
+            [&](int i) __attribute__((always_inline)) {
+                if (qt + 1 < NQT) { nxt = mfma_bf16(kf[i], qf[(qt + 1) % NQT][i], nxt); pin(nxt); }
+            },
+            [&](int v) __attribute__((always_inline)) { return fmaf(acc[v], c, -mnew); });
         acc = nxt;
     }
 }
@@ -434,7 +450,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
     char* slots = &lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))][0][0];
 
     const KeyStream ks = key_stream<PAGED>(a, w);
-    const TileLanes tl = tile_lanes(lane, ks.row_bytes);
+    const uint32_t tl = tile_lane(lane, ks.row_bytes);
     // With the soft tokens' own keys in the softmax, the sequence's first wave takes them as further tiles
     // after its prompt tiles (same row stride, n_q rows), masked causally per query row.
     const int n_tail = (a.K_tail && w.wave == 0) ? (a.n_q + kKeyTile - 1) / kKeyTile : 0;  // wave 0 always has tiles
@@ -465,8 +481,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
     };
     // The first key tile goes to slot 0 at once; the second slots first serve as the staging area that turns
     // the workgroup's query rows into operand order.  From then on the wave's tiles alternate between its two
-    // slots, and the next tile is requested as soon as the current one's fragments are in registers (with
-    // a.depth == 2 the tile after that one is in flight as well).
+    // slots, and the next tile is requested as soon as the current one's fragments are in registers.
     // As in the second pass the query rows are requested first, into registers, the key tile after them, and the
     // rows pass through LDS while the tile is in flight (explicit LDS instructions, every request unconditional in
     // one basic block: see lds_addr()).  A wave without tiles requests the sequence's first tile and drops it.
@@ -494,8 +509,6 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) { m[qt] = -1.0e30f; z[qt] = 0.0f; }
     if (n_all > 0) {  // not a surplus wave of the sequence's last workgroup
-    const int D = a.depth;  // uniform
-    if (D == 2 && n_all > 1) fetch(1);
 
     // Every load older than the second tile's eight (first tile, query rows) is covered
     // by the first wait of the sweep.  Tiles that lie entirely inside the keys every query row sees (all L
@@ -505,45 +518,78 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
     const int n_common = a.window ? w.L - a.n_q : w.L;
     const int common_tiles = n_common / kKeyTile;  // sequence tiles 0 .. common_tiles - 1 are unmasked
     const int n_full = common_tiles > w.wave ? min(w.n_tiles, (common_tiles - 1 - w.wave) / w.n_waves + 1) : 0;
-    // soft token of this lane's query row in each query tile (row r = i * group + hh): it sees soft tokens 0..i
-    int soft_i[NQT];
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) soft_i[qt] = ((w.rg * NQT + qt) * kRowTile + (lane & 31)) / a.group;
-    // The kernel holds TWO copies of the tile body, not one per case: the hot one (unmasked tile, offsets fixed
-    // after the wave's first tile) and a general one whose masking and offset rule are run-time flags, used by the
-    // few masked tiles (partial last tile, window, soft tokens' own keys) and by the rare repeat of a sweep.
-    // (A copy per case made the kernel 45 KB of code instead of 23 KB, for no gain in time.)
+    // Besides the hot sweep's body the kernel holds ONE general one, for the few masked tiles (partial last tile, window,
+    // soft tokens' own keys) and the rare repeat of a sweep.  (A copy per case made the kernel 45 KB of code, for no
+    // gain in time.)
     auto tile_prologue = [&](int k, bf16x8 (&kf)[8]) __attribute__((always_inline)) {
-        wait_tile_landed(D == 2 && k + 1 < n_all);
-        lds_get_frags(slots + (k & 1) * kSlotBytes, kf, lane);
-        if (k + D < n_all) {
+        int l = lane;
+        asm volatile("" : "+v"(l));  // as in valid_rows
+        wait_tile_landed();
+        lds_get_frags(slots + (k & 1) * kSlotBytes, kf, l);
+        if (k + 1 < n_all) {
             wait_frags_read();
-            fetch(k + D);
+            fetch(k + 1);
         }
     };
     // rows of tile k that exist for this lane's query row of each query tile (32 or more: all of them)
     auto valid_rows = [&](int k, int (&valid)[NQT]) __attribute__((always_inline)) {
-        if (k < w.n_tiles) {
-            const int t0 = (w.wave + k * w.n_waves) * kKeyTile;
+        int l = lane & 31;
+        asm volatile("" : "+v"(l));  // rarely taken: keeps what follows out of the hot sweep's registers
 #pragma unroll
-            for (int qt = 0; qt < NQT; ++qt) valid[qt] = (a.window ? n_common + soft_i[qt] + 1 : w.L) - t0;
-        } else {  // soft token t * 32 + j is visible to the row of soft token i iff it is <= i
-            const int t = k - w.n_tiles;
-#pragma unroll
-            for (int qt = 0; qt < NQT; ++qt) valid[qt] = soft_i[qt] + 1 - t * kKeyTile;
+        for (int qt = 0; qt < NQT; ++qt) {
+            // soft token of the lane's row (row r = i * group + hh): it sees soft tokens 0..i
+            const int soft_i = a.window || k >= w.n_tiles ? ((w.rg * NQT + qt) * kRowTile + l) / a.group : 0;
+            if (k < w.n_tiles) {
+                const int t0 = (w.wave + k * w.n_waves) * kKeyTile;
+                valid[qt] = (a.window ? n_common + soft_i + 1 : w.L) - t0;
+            } else {  // soft token t * 32 + j is visible to the row of soft token i iff it is <= i
+                valid[qt] = soft_i + 1 - (k - w.n_tiles) * kKeyTile;
+            }
         }
     };
-    // First sweep: the wave's first tile sets each lane's offset m from its logits there, later tiles keep it --
-    // no maximum to track.  A logit more than 2^7 (base 2) above that offset overflows 2^(t - m) to infinity, which
-    // cannot be repaired afterwards, so such a wave (wave-uniform decision) sweeps again with the running maximum.
+    // First sweep: the wave's first tile sets each lane's offset m (to the largest of four of its 16 logits), later tiles
+    // keep it -- no maximum to track.  A logit more than 2^7 (base 2) above that offset overflows 2^(t - m) to infinity,
+    // which cannot be repaired afterwards, so such a wave (wave-uniform decision) sweeps again with the running maximum.
     int k = 0;
-    for (; k < n_full; ++k) {
+    if (n_full > 0) {
+        // The hot sweep, tiles 0 .. n_full - 1, software-pipelined across tiles: while query tile qt's logits are
+        // exponentiated the MFMA chain of the next one runs, and behind the last one the chain of the NEXT tile's first,
+        // whose fragments were read during the stage before.  At every iteration's end tile k + 1 sits in registers and
+        // tile k + 2 is in flight.  The last iteration's look-ahead reads whatever its slot holds and drops it (a masked
+        // tile that follows is read again by its own prologue).
         bf16x8 kf[8];
-        tile_prologue(k, kf);
-        int valid[NQT];
+        wait_tile_landed();
+        lds_get_frags(slots, kf, lane);
+        wait_frags_read();
+        if (n_all > 1) fetch(1);
+        f32x16 acc = stats_chain(kf, qf[0]);
+        auto hot_tile = [&](bool first) __attribute__((always_inline)) {  // `first` is a constant in either copy
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) valid[qt] = kKeyTile;
-        stats_tile<NQT, false, true>(kf, qf, m, z, c, valid, half, k == 0);
+            for (int qt = 0; qt < NQT; ++qt) {
+                const bool reads = qt == (NQT > 1 ? NQT - 2 : 0);
+                const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
+                const uint32_t next_at = frag_addr(next_slot, lane);
+                if (reads) wait_tile_landed();
+                if (NQT == 1) lds_get_frags(next_slot, kf, lane);
+                if (first) m[qt] = fmaxf(fmaxf(acc[0], acc[5]), fmaxf(acc[10], acc[15])) * c;
+                f32x16 nxt = zero_acc();
+                z[qt] += exp2_sum_stage<8>(
+                    [&](int i) __attribute__((always_inline)) {
+                        nxt = mfma_bf16(kf[i], qf[(qt + 1) % NQT][i], nxt);
+                        pin(nxt);
+                        if (reads && NQT > 1) kf[i] = lds_get_frag(next_at, i);  // its last use was this MFMA
+                    },
+                    [&](int v) __attribute__((always_inline)) { return fmaf(acc[v], c, -m[qt]); });
+                if (reads) {
+                    wait_frags_read();
+                    if (k + 2 < n_all && k + 2 <= n_full) fetch(k + 2);
+                }
+                acc = nxt;
+            }
+            ++k;
+        };
+        hot_tile(true);
+        while (k < n_full) hot_tile(false);
     }
     bool repeat = false;  // uniform
     for (;;) {
@@ -552,7 +598,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
             tile_prologue(k, kf);
             int valid[NQT];
             valid_rows(k, valid);
-            stats_tile<NQT, true, false>(kf, qf, m, z, c, valid, half, !repeat && k > 0);
+            stats_tile<NQT>(kf, qf, m, z, c, valid, half, !repeat && k > 0);
         }
         bool overflow = false;
 #pragma unroll
@@ -564,7 +610,6 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
         wait_frags_read();
         first_page();
         fetch(0);
-        if (D == 2 && n_all > 1) fetch(1);
         k = 0;
     }
 
@@ -702,7 +747,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
     char* slots = &lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))][0][0];
 
     const KeyStream ks = key_stream<PAGED>(a, w);
-    const TileLanes tl = tile_lanes(lane, ks.row_bytes);
+    const uint32_t tl = tile_lane(lane, ks.row_bytes);
     // The wave walks its tiles from the last to the first (pass 1 swept the keys front to back, so the end
     // of the sequence is what the caches still hold): its k-th tile here is sequence tile tile_of(k).
     auto tile_of = [&](int k) { return w.wave + (w.n_tiles - 1 - k) * w.n_waves; };
@@ -830,8 +875,6 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
         if (DIFF) __syncthreads();  // the workgroup's final merge
         return;
     }
-    const int D = a.depth;  // uniform
-    if (D == 2 && w.n_tiles > 1) fetch(1);
     u32x4 ones_bits = {0u, 0u, 0u, 0u};
     if (half == 0) { ones_bits[0] = 0x3F803F80u; ones_bits[1] = 0x00003F80u; }  // 1.0 at elements 0..2
     const bf16x8 ones = as_bf16x8(ones_bits);
@@ -856,46 +899,42 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
         }
     };
 
-    // everything older than the second tile's eight loads (first tile, Q, the -beta/c terms) is in after this
-    wait_tile_landed(D == 2 && w.n_tiles > 1);
+    // Software pipeline over the query-row tiles and across key tiles, as in the first pass: while one tile's logits are
+    // exponentiated the MFMA chain of the next runs, and behind the last one that of the next key tile's first, whose
+    // fragments were read a stage earlier.  At an iteration's end tile k + 1 sits in registers and tile k + 2 is in
+    // flight; the last iteration's look-ahead reads whatever its slot holds and drops it.
+    wait_tile_landed();
+    bf16x8 kf[8];
+    lds_get_frags(slots, kf, lane);
+    wait_frags_read();
+    if (w.n_tiles > 1) fetch(1);
+    f32x16 acc = score_chain(qf[0], qaug[0], kf, ones);
     for (int k = 0; k < w.n_tiles; ++k) {
-        if (k > 0) wait_tile_landed(D == 2 && k + 1 < w.n_tiles);
-        bf16x8 kf[8];
-        lds_get_frags(slots + (k & 1) * kSlotBytes, kf, lane);
-        if (k > 0) store_tile(k - 1, pending);
-        if (k + D < w.n_tiles) {  // issued after the store: only these 8 loads are newer than tile k+1
-            wait_frags_read();
-            fetch(k + D);
-        }
-        // Software pipeline over the query-row tiles: the MFMA chain of tile qt+1 is issued between the
-        // exp2/add instructions of tile qt (a wave issues in order, so without interleaving its VALU work
-        // would sit behind the whole dependent MFMA chain).
-        float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-        f32x16 acc = score_chain(qf[0], qaug[0], kf, ones);
+        float sum = 0.f;
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
-            f32x16 nxt = acc;
-            if (qt + 1 < NQT) nxt = score_chain(qf[qt + 1], qaug[qt + 1], kf, ones);
-#pragma unroll
-            for (int v = 0; v < 16; v += 4) {
-                s0 += __builtin_amdgcn_exp2f(acc[v + 0] * c);
-                s1 += __builtin_amdgcn_exp2f(acc[v + 1] * c);
-                s2 += __builtin_amdgcn_exp2f(acc[v + 2] * c);
-                s3 += __builtin_amdgcn_exp2f(acc[v + 3] * c);
+            const bool reads = qt == (NQT > 1 ? NQT - 2 : 0);
+            const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
+            if (reads) wait_tile_landed();
+            const uint32_t next_at = frag_addr(next_slot, lane);
+            if (NQT == 1) lds_get_frags(next_slot, kf, lane);
+            f32x16 nxt = zero_acc();
+            sum += exp2_sum_stage<9>(
+                [&](int i) __attribute__((always_inline)) {
+                    nxt = i < 8 ? mfma_bf16(qf[(qt + 1) % NQT][i & 7], kf[i & 7], nxt) : mfma_bf16(qaug[(qt + 1) % NQT], ones, nxt);
+                    pin(nxt);
+                    if (reads && NQT > 1 && i < 8) kf[i & 7] = lds_get_frag(next_at, i);  // its last use was this MFMA
+                },
+                [&](int v) __attribute__((always_inline)) { return acc[v] * c; });
+            if (reads) {
+                wait_frags_read();
+                if (k > 0) store_tile(k - 1, pending);
+                if (k + 2 < w.n_tiles) fetch(k + 2);
             }
-            if (qt + 1 < NQT) {
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // then a few VALU
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
             acc = nxt;
         }
-        float s = (s0 + s1) + (s2 + s3);
-        s += __shfl_xor(s, 32);  // the two lane halves hold complementary query rows of the same key
-        pending = s;
+        sum += __shfl_xor(sum, 32);  // the two lane halves hold complementary query rows of the same key
+        pending = sum;
     }
     store_tile(w.n_tiles - 1, pending);
     if (DIFF) {  // lanes 0..31 hold the sums: butterfly within the half wave, then the four waves in wave order
@@ -983,7 +1022,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         fetch_rows(0);
         aug_next = aug[wv * kRowTile];
     }
-    wait_tile_landed(false);
+    wait_tile_landed();
     bare_barrier();
     bf16x8 kf[kMaxRowTiles][8];
 #pragma unroll
@@ -997,42 +1036,48 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     float sum[kMaxRowTiles];
 #pragma unroll
     for (int kt = 0; kt < kMaxRowTiles; ++kt) sum[kt] = 0.f;
-    for (int k = 0; k < n_mine; ++k) {
-        wait_tile_landed(false);
-        bf16x8 qf[8];
-        lds_get_frags(slots + (k & 1) * kSlotBytes, qf, lane);
+    // as in the other sweeps: the next key tile's MFMA chain runs between the exp2 work of this one, and behind the last
+    // one the first chain of the next row tile, read a stage earlier
+    auto aug_of = [&](uint2 t) __attribute__((always_inline)) {
         u32x4 av = {0u, 0u, 0u, 0u};
-        if (half == 0) { av[0] = aug_next.x; av[1] = aug_next.y; }
-        const bf16x8 qaug = as_bf16x8(av);
-        if (k + 1 < n_mine) {
-            wait_frags_read();
-            fetch_rows(k + 1);
-            aug_next = aug[(wv + (k + 1) * kScoreWaves) * kRowTile];
+        if (half == 0) { av[0] = t.x; av[1] = t.y; }
+        return as_bf16x8(av);
+    };
+    if (n_mine > 0) {
+        bf16x8 qf[8];
+        lds_get_frags(slots, qf, lane);
+        bf16x8 qaug = aug_of(aug_next);
+        wait_frags_read();
+        if (n_mine > 1) {
+            fetch_rows(1);
+            aug_next = aug[(wv + kScoreWaves) * kRowTile];
         }
-        // as in jq_score_kernel: the MFMA chain of the next key tile runs between the exp2/add work of this one
         f32x16 acc = score_chain(qf, qaug, kf[0], ones);
+        for (int k = 0; k < n_mine; ++k) {
 #pragma unroll
-        for (int kt = 0; kt < kMaxRowTiles; ++kt) {
-            f32x16 nxt = acc;
-            if (kt + 1 < kMaxRowTiles) nxt = score_chain(qf, qaug, kf[kt + 1], ones);
-            float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; v += 4) {
-                s0 += __builtin_amdgcn_exp2f(acc[v + 0] * c);
-                s1 += __builtin_amdgcn_exp2f(acc[v + 1] * c);
-                s2 += __builtin_amdgcn_exp2f(acc[v + 2] * c);
-                s3 += __builtin_amdgcn_exp2f(acc[v + 3] * c);
-            }
-            sum[kt] += (s0 + s1) + (s2 + s3);
-            if (kt + 1 < kMaxRowTiles) {
-#pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);  // then a few VALU
+            for (int kt = 0; kt < kMaxRowTiles; ++kt) {
+                const bool reads = kt == kMaxRowTiles - 2;
+                const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
+                if (reads) wait_tile_landed();
+                const uint32_t next_at = frag_addr(next_slot, lane);
+                f32x16 nxt = zero_acc();
+                sum[kt] += exp2_sum_stage<9>(
+                    [&](int i) __attribute__((always_inline)) {
+                        nxt = i < 8 ? mfma_bf16(qf[i & 7], kf[(kt + 1) % kMaxRowTiles][i & 7], nxt) : mfma_bf16(qaug, ones, nxt);
+                        pin(nxt);
+                        if (reads && i < 8) qf[i & 7] = lds_get_frag(next_at, i);  // its last use was this MFMA
+                    },
+                    [&](int v) __attribute__((always_inline)) { return acc[v] * c; });
+                if (reads) {
+                    wait_frags_read();
+                    qaug = aug_of(aug_next);
+                    if (k + 2 < n_mine) {
+                        fetch_rows(k + 2);
+                        aug_next = aug[(wv + (k + 2) * kScoreWaves) * kRowTile];
+                    }
                 }
+                acc = nxt;
             }
-            __builtin_amdgcn_sched_barrier(0);
-            acc = nxt;
         }
     }
 #pragma unroll
@@ -1056,7 +1101,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
             a.scores[o] = v;
         }
     }
-    if (DIFF) {  // butterfly within waves 0 and 1, then their two sums: a fixed order
+    if constexpr (DIFF) {  // butterfly within waves 0 and 1, then their two sums: a fixed order
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) dacc += __shfl_xor(dacc, off);
         if (lane == 0 && wv < 2) diff_s[wv] = dacc;
@@ -1130,12 +1175,6 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.n_layers = p.n_layers; a.n_seq = p.n_seq; a.n_q = p.n_q; a.h_q = p.h_q; a.h_kv = p.h_kv;
     a.group = p.group; a.rows = p.rows; a.RP = p.row_tiles * kRowTile;
     a.window = p.window;
-    // Key tiles a wave keeps in flight: one.  The next tile is requested as soon as the current one's fragments are
-    // in registers and arrives while the wave computes; a second tile in flight only queues in the memory system
-    // (both passes already move data at the rate a plain read of K reaches) and costs the second pass 2.5 us on
-    // the 128K layer (46.7 -> 44.2 us; first pass 47.3 -> 46.8).
-    const int depth_cold = knobs().depth1, depth_second = knobs().depth2;  // ablation knobs (default 1)
-    a.depth = depth_cold;
     a.group_shift = -1;
     for (int sh = 0; sh < 16; ++sh)
         if (p.group == (1 << sh)) a.group_shift = sh;
@@ -1193,7 +1232,6 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         a.n_cgrp = p.cu_cgrp2[p.n_seq];
         a.one_waves = p.n_seq == 1 ? p.cu_chunk2[1] : 0;
         grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
-        a.depth = depth_second;
     }
     if (many_rows) {
         if (lse) {  // the second pass's own tables and the -beta/c terms, which a combine launch provides otherwise
