@@ -324,6 +324,7 @@ int jq_select_topk(const jq_shape* shape, const float* pooled, int32_t* idx, voi
                              overlaps(ws, p.ws_bytes, p.layer_budgets, lb_bytes(p)))))
         return JQ_ERR_ALIAS;
     hipStream_t st = (hipStream_t)stream;
+    if (select_small(p)) return launch_status(launch_pool_select(p, pooled, nullptr, false, (char*)ws, idx, st));
     uint32_t* hist = (uint32_t*)((char*)ws + p.off_hist);
     hipError_t e = launch_fill_u32(hist, (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride, 0u, st);
     if (e == hipSuccess) e = launch_hist(p, pooled, hist, (char*)ws, st);
@@ -375,6 +376,34 @@ int jq_compact_inplace(const jq_shape* shape, void* K, void* V, const int32_t* i
     return launch_status(launch_compact_inplace(p, K, V, idx, ws, (hipStream_t)stream));
 }
 
+// Everything of an eviction after its arguments have been checked: scores -> pooling -> selection -> kept rows, in K_out /
+// V_out, or (`stage`: in place) over K and V themselves.
+static hipError_t evict_launches(const Plan& p, const void* Q, const void* K, const void* V, const float* lse, const void* k_tail,
+                                 void* K_out, void* V_out, int32_t* idx_out, float* scores_out, char* w, hipStream_t st, void* stage = nullptr,
+                                 const int32_t* pos_in = nullptr, int32_t* pos_out = nullptr, const uint32_t* dest_bits = nullptr) {
+    uint32_t* hist = (uint32_t*)(w + p.off_hist);
+    float* raw = (float*)(w + p.off_scores);
+    int32_t* idx = idx_out ? idx_out : (int32_t*)(w + p.off_idx);
+    hipError_t e;
+    bool gathered = true;  // the selection's last kernel gathers (or, in place, stages) the kept rows itself unless it had to stream
+    if (select_small(p) && !p.marks) {  // (a traced call reports pooling and selection apart: it takes the two kernels)
+        e = launch_score(p, Q, K, raw, w, st, nullptr, 0, lse, k_tail);
+        if (e == hipSuccess) e = launch_pool_select(p, raw, scores_out, true, w, idx, st, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
+    } else {
+        float* pooled = scores_out ? scores_out : (float*)(w + p.off_pooled);
+        const size_t zero_words = (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride;
+        e = launch_score(p, Q, K, raw, w, st, hist, zero_words, lse, k_tail);  // also clears the selection histograms
+        if (e == hipSuccess) e = launch_pool(p, raw, pooled, hist, w, st);
+        if (e == hipSuccess) e = launch_select(p, pooled, hist, w, idx, st, K, V, K_out, V_out, &gathered, stage, pos_in, pos_out, dest_bits);
+    }
+    if (e != hipSuccess) return e;
+    if (!stage) return gathered ? hipSuccess : launch_compact(p, K, V, idx, K_out, V_out, st);
+    // In place: the selection has saved the kept rows that are about to be overwritten; one more launch writes every kept
+    // row.  (A streaming selection saves nothing: both launches of the stand-alone in-place gather run.)
+    void *Kw = const_cast<void*>(K), *Vw = const_cast<void*>(V);
+    return gathered ? launch_compact_inplace_write(p, Kw, Vw, idx, stage, st, dest_bits) : launch_compact_inplace(p, Kw, Vw, idx, stage, st, dest_bits);
+}
+
 static int evict_impl(const jq_shape* shape, const void* Q, const void* K, const void* V, const float* lse,
                       const void* k_tail, void* K_out, void* V_out, int32_t* idx_out, float* scores_out, void* ws,
                       size_t ws_bytes, void* stream, void* const* marks, const jq_pages* pages = nullptr,
@@ -407,20 +436,9 @@ static int evict_impl(const jq_shape* shape, const void* Q, const void* K, const
             if (outs[o2] && overlaps(outs[o], out_bytes[o], outs[o2], out_bytes[o2])) return JQ_ERR_ALIAS;
     }
 
-    hipStream_t st = (hipStream_t)stream;
-    char* w = (char*)ws;
-    uint32_t* hist = (uint32_t*)(w + p.off_hist);
-    float* raw = (float*)(w + p.off_scores);
-    float* pooled = scores_out ? scores_out : (float*)(w + p.off_pooled);
-    int32_t* idx = idx_out ? idx_out : (int32_t*)(w + p.off_idx);
     p.marks = marks;
-    const size_t zero_words = (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride;
-    hipError_t e = launch_score(p, Q, K, raw, w, st, hist, zero_words, lse, k_tail);  // also clears the selection histograms
-    if (e == hipSuccess) e = launch_pool(p, raw, pooled, hist, w, st);
-    bool gathered = false;  // the selection's last kernel gathers the kept rows itself unless it had to stream
-    if (e == hipSuccess) e = launch_select(p, pooled, hist, w, idx, st, K, V, K_out, V_out, &gathered, nullptr, pos_in, pos_out);
-    if (e == hipSuccess && !gathered) e = launch_compact(p, K, V, idx, K_out, V_out, st);
-    return launch_status(e);
+    return launch_status(evict_launches(p, Q, K, V, lse, k_tail, K_out, V_out, idx_out, scores_out, (char*)ws, (hipStream_t)stream, nullptr,
+                                        pos_in, pos_out));
 }
 
 int jq_evict_inplace_workspace_bytes(const jq_shape* shape, size_t* bytes) {
@@ -452,23 +470,8 @@ int jq_evict_inplace(const jq_shape* shape, const void* Q, void* K, void* V, con
             if (bufs[i] && bufs[j] && (i == 1 || i == 2 || j == 1 || j == 2 || j >= 5) && overlaps(bufs[i], sizes[i], bufs[j], sizes[j]))
                 return JQ_ERR_ALIAS;
 
-    hipStream_t st = (hipStream_t)stream;
     char* w = (char*)ws;
-    char* stage = w + p.ws_bytes;
-    uint32_t* hist = (uint32_t*)(w + p.off_hist);
-    float* raw = (float*)(w + p.off_scores);
-    float* pooled = scores_out ? scores_out : (float*)(w + p.off_pooled);
-    int32_t* idx = idx_out ? idx_out : (int32_t*)(w + p.off_idx);
-    const size_t zero_words = (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride;
-    hipError_t e = launch_score(p, Q, K, raw, w, st, hist, zero_words, lse, nullptr);
-    if (e == hipSuccess) e = launch_pool(p, raw, pooled, hist, w, st);
-    // The selection kernel saves the kept rows that are about to be overwritten; one more launch then writes every
-    // kept row over the front of K and V.  (A streaming selection saves nothing: both launches of the stand-alone
-    // in-place gather run.)
-    bool staged = false;
-    if (e == hipSuccess) e = launch_select(p, pooled, hist, w, idx, st, K, V, nullptr, nullptr, &staged, stage);
-    if (e == hipSuccess) e = staged ? launch_compact_inplace_write(p, K, V, idx, stage, st) : launch_compact_inplace(p, K, V, idx, stage, st);
-    return launch_status(e);
+    return launch_status(evict_launches(p, Q, K, V, lse, nullptr, nullptr, nullptr, idx_out, scores_out, w, (hipStream_t)stream, w + p.ws_bytes));
 }
 
 // workspace of the paged in-place eviction: the scratch of jq_evict, the staged rows, the destination-page bitmap
@@ -519,19 +522,8 @@ int jq_evict_paged_inplace(const jq_shape* shape, const jq_pages* pages, const j
     char* w = (char*)ws;
     char* stage = w + off_stage;
     uint32_t* dest_bits = (uint32_t*)(w + off_bits);
-    uint32_t* hist = (uint32_t*)(w + p.off_hist);
-    float* raw = (float*)(w + p.off_scores);
-    float* pooled = scores_out ? scores_out : (float*)(w + p.off_pooled);
-    int32_t* idx = idx_out ? idx_out : (int32_t*)(w + p.off_idx);
-    const size_t zero_words = (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride;
     hipError_t e = launch_mark_dest_pages(p, dest_bits, st);  // which pages receive kept rows (read by the last two kernels)
-    if (e == hipSuccess) e = launch_score(p, Q, K_pool, raw, w, st, hist, zero_words, lse, nullptr);
-    if (e == hipSuccess) e = launch_pool(p, raw, pooled, hist, w, st);
-    bool staged = false;
-    if (e == hipSuccess) e = launch_select(p, pooled, hist, w, idx, st, K_pool, V_pool, nullptr, nullptr, &staged, stage, nullptr, nullptr, dest_bits);
-    if (e == hipSuccess)
-        e = staged ? launch_compact_inplace_write(p, K_pool, V_pool, idx, stage, st, dest_bits)
-                   : launch_compact_inplace(p, K_pool, V_pool, idx, stage, st, dest_bits);
+    if (e == hipSuccess) e = evict_launches(p, Q, K_pool, V_pool, lse, nullptr, nullptr, nullptr, idx_out, scores_out, w, st, stage, nullptr, nullptr, dest_bits);
     return launch_status(e);
 }
 

@@ -240,6 +240,18 @@ hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t v, hipStream_t st);
 hipError_t launch_hist(const Plan& p, const float* pooled, uint32_t* hist, char* ws_or_null, hipStream_t st);
 // Whether every sequence of the plan fits the selection's fast path (LDS bitmaps); otherwise it streams.
 bool select_fast_path(const Plan& p);
+// Calls whose sequences all have at most kSmallMax positions: pooling (unless `pool` is false: `in` then holds the values
+// to select by), selection and gather in ONE kernel, which needs no histogram and no lists.  `out` (nullable) takes the
+// pooled scores; the other arguments as launch_select.  Why the line lies at 32768: the staged scores of a longer sequence
+// do not fit a workgroup's LDS, and there the two ways meet -- whole eviction calls of one layer with 8 KV heads and 256
+// kept rows, one kernel against two: 22.4 / 34.0 us at 2048 tokens, 29.2 / 36.3 at 8192, 36.7 / 41.7 at 16384, 50.3 / 50.6
+// at 32768 (every slice repeats the problem's selection, whose cost grows with the length).
+constexpr int kSmallMax = 32768;
+bool select_small(const Plan& p);
+hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool pool, char* ws, int32_t* idx, hipStream_t st,
+                              const void* K = nullptr, const void* V = nullptr, void* K_out = nullptr, void* V_out = nullptr,
+                              void* stage = nullptr, const int32_t* pos_in = nullptr, int32_t* pos_out = nullptr,
+                              const uint32_t* dest_bits = nullptr);
 // With K, V, K_out, V_out (all or none) the selection also gathers the kept rows when its fast path runs;
 // `*gathered` tells whether it did (otherwise launch_compact is still due).  With K, V and `stage` (in-place
 // eviction, dense layouts, no K_out / V_out) it copies the kept rows whose sources are about to be overwritten to

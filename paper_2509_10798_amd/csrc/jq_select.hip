@@ -17,6 +17,7 @@
 // order.  Several workgroups ("slices") work on one problem: each repeats the (cheap, cache-resident)
 // resolution and emits its own range of output slots; in the fused eviction call it also gathers the K/V
 // rows of those slots, so the pruned cache needs no further kernel.
+// Short sequences (every one of the call up to kSmallMax tokens): pooling, selection and gather in one kernel.
 // General path (very long sequences): one workgroup per problem streams the row three times.
 #include <atomic>
 
@@ -223,6 +224,253 @@ __global__ __launch_bounds__(kSelectThreads) void jq_select_stream_kernel(Select
         eq_done += total >> 16;
         if (gt_done + min(eq_done, need) >= p.B) break;  // uniform: everything kept already
     }
+}
+
+// Pruned cache (paper Section 4.3): the kept rows of output slots o0 .. o0 + n_rows - 1 of a problem, whose positions are
+// in slot_pos[0 .. n_rows - 1] (LDS); 16 lanes x 16 B per 256-byte head row.  Every thread takes kGatherRows rows at a time,
+// so that that many K and V loads are in flight together: one pair per thread left a workgroup with 1024 rows to gather
+// waiting for 32 round trips to memory.
+constexpr int kGatherRows = 4;
+template <int THREADS>
+__device__ __forceinline__ void gather_slots(const SelectArgs& a, const Problem& p, const uint32_t* slot_pos, uint32_t o0, uint32_t n_rows) {
+    const int part = threadIdx.x & 15;
+    constexpr uint32_t kStep = THREADS / 16;
+    if (a.stage) {  // uniform
+        const int64_t v_stage = (int64_t)a.n_layers * a.TB * a.h_kv * (kHeadDim * 2);
+        for (uint32_t rr = threadIdx.x >> 4; rr < n_rows; rr += kStep) {
+            const int64_t src_row = (int64_t)p.tok0 + slot_pos[rr];  // within the layer (dense layout)
+            if (!row_is_overwritten(a.pm, a.dest_bits, src_row, a.TB, p.s, (int)slot_pos[rr])) continue;  // read in place later
+            const int64_t src = ((kv_row_from(a.pm, p.tok0, a.T, p.layer, p.s, (int)slot_pos[rr]) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
+            const int64_t stg = ((((int64_t)p.layer * a.TB + p.bud0 + o0 + rr) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
+            *(uint4*)(a.stage + stg) = *(const uint4*)(a.K + src);
+            *(uint4*)(a.stage + v_stage + stg) = *(const uint4*)(a.V + src);
+        }
+        return;
+    }
+    for (uint32_t r0 = threadIdx.x >> 4; r0 < n_rows; r0 += kGatherRows * kStep) {
+        uint4 kv[kGatherRows], vv[kGatherRows];
+#pragma unroll
+        for (int u = 0; u < kGatherRows; ++u) {
+            const uint32_t rr = min(r0 + u * kStep, n_rows - 1);  // past the end: the last row again, not stored
+            const int64_t src = ((kv_row_from(a.pm, p.tok0, a.T, p.layer, p.s, (int)slot_pos[rr]) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
+            kv[u] = *(const uint4*)(a.K + src);
+            vv[u] = *(const uint4*)(a.V + src);
+        }
+#pragma unroll
+        for (int u = 0; u < kGatherRows; ++u) {
+            const uint32_t rr = r0 + u * kStep;
+            if (rr >= n_rows) continue;
+            const int64_t dst = ((kv_row_from(a.pm_out, p.bud0, a.TB, p.layer, p.s, (int)(o0 + rr)) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
+            store_stream16(a.K_out + dst, kv[u]);
+            store_stream16(a.V_out + dst, vv[u]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// short sequences: pooling, selection and gather in one kernel
+// ------------------------------------------------------------------------------------------------
+// A problem of up to THREADS * VPT positions fits one workgroup: its scores are staged in LDS, thread t pools the run of
+// VPT consecutive positions t * VPT .. and keeps their keys in registers.  The threshold is found by a radix descent over
+// the range that the problem's own keys span -- 2048 bins over [lowest, highest], then over the bin that holds the B-th
+// largest -- so that crowded scores spread over many bins, and runs in thread order are runs in position order, so one
+// block-wide scan of the threads' kept counts gives every kept position its slot: no histogram or lists in memory and no
+// kernel (and no boundary between kernels) of its own for the pooling.  The slices of a problem repeat the selection and
+// share the output (pooled scores by thread, kept rows by slot).  Latency-bound: a chain of about ten barriers.
+struct PoolSelectArgs {
+    const float* in;   // [n_layers][h_kv][T]: unpooled scores, or (K == 1) the values to select by
+    float* out;        // pooled scores, or null
+    int32_t pool_k;
+    float inv_k;
+    SelectArgs sel;
+};
+constexpr int kSmallBins = 2048;
+constexpr int kSmallFixedWords = kSmallBins + 32 + 32 + 64;  // bins, scan scratch, pick results, per-wave extremes
+// Runs are VPT words apart from thread to thread: four words of padding per 32 spread the 16-byte reads of eight
+// neighbouring threads over all banks.
+__host__ __device__ constexpr int small_pad(int i) { return i + ((i >> 5) << 2); }
+
+// K: pooling width 5 or 7 with unrolled taps, 1 for no pooling, 0 for any width
+template <int THREADS, int VPT, int K>
+__global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs pa) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    uint32_t* bins = lds;
+    uint32_t* tmp = bins + kSmallBins;
+    uint32_t* res = tmp + 32;
+    uint32_t* ext = res + 32;                          // per wave: lowest, highest free key
+    float* tile = (float*)(ext + 64);                  // staged scores; later the kept positions of the slice's slots
+    uint32_t* slot_pos = ext + 64;
+    const SelectArgs& a = pa.sel;
+    const Problem p = problem_of(a, blockIdx.x);
+    const int L = p.L, tid = (int)threadIdx.x;
+    const int64_t row = ((int64_t)p.layer * a.h_kv + p.g) * a.T + p.tok0;
+    const float* in_row = pa.in + row;
+    constexpr int kHalo = K > 1 ? 4 : 0;               // staged in front of and behind the sequence, zeros
+    float raw[VPT];
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        raw[u] = in_row[min((uint32_t)(u * THREADS + tid), (uint32_t)L - 1u)];
+    }
+    for (int b = tid; b < kSmallBins; b += THREADS) bins[b] = 0u;
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        const int j = u * THREADS + tid;
+        tile[small_pad(tid + kHalo) + u * small_pad(THREADS)] = j < L ? raw[u] : 0.f;  // THREADS is a multiple of 32
+    }
+    if (kHalo && tid < 2 * kHalo) tile[small_pad(tid < kHalo ? tid : THREADS * VPT + tid)] = 0.f;
+    lds_barrier();
+
+    const int j0 = tid * VPT;  // this thread's run of positions
+    float v[VPT];
+    if constexpr (K > 1) {
+        float x[VPT + 2 * kHalo];
+#pragma unroll
+        for (int q = 0; q < VPT + 2 * kHalo; q += 4) {
+            const float4 f = *(const float4*)&tile[small_pad(j0 + q)];
+            x[q] = f.x; x[q + 1] = f.y; x[q + 2] = f.z; x[q + 3] = f.w;
+        }
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            float acc = 0.f;
+#pragma unroll
+            for (int k = 0; k < K; ++k) acc += x[u + kHalo - K / 2 + k];  // ascending position order, as jq_pool_kernel
+            v[u] = acc * pa.inv_k;
+        }
+    } else if (K == 1) {
+#pragma unroll
+        for (int q = 0; q < VPT; q += 4) {
+            const float4 f = *(const float4*)&tile[small_pad(j0 + q)];
+            v[q] = f.x; v[q + 1] = f.y; v[q + 2] = f.z; v[q + 3] = f.w;
+        }
+    } else {
+        const int r = (pa.pool_k - 1) / 2;
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int q0 = max(0, j0 + u - r), q1 = min(L - 1, j0 + u + r);
+            float acc = 0.f;
+            for (int q = q0; q <= q1 && j0 + u < L; ++q) acc += tile[small_pad(q)];
+            v[u] = acc * pa.inv_k;
+        }
+    }
+    if (pa.out && (uint32_t)tid * gridDim.y / THREADS == blockIdx.y && j0 < L) {  // this slice's share of the pooled scores
+        float* o = pa.out + row + j0;
+        if (j0 + VPT <= L && (((uintptr_t)o) & 15u) == 0) {
+#pragma unroll
+            for (int q = 0; q < VPT; q += 4) *(float4*)(o + q) = make_float4(v[q], v[q + 1], v[q + 2], v[q + 3]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < VPT; ++u)
+                if (j0 + u < L) o[u] = v[u];
+        }
+    }
+
+    // Keys.  Always-kept positions get the largest key and positions past the end key 0; all others keep to 1 .. 2^32 - 2,
+    // so that every later test of a position is one comparison.
+    const int f0 = a.keep_first, f1 = L - a.keep_last;  // free positions: [f0, f1)
+    uint32_t key[VPT];
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;                 // lowest free key - 1, highest free key + 1
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) key[u] = min(max(sortable_key(v[u]), 1u), 0xFFFFFFFEu);
+    if (j0 < f0 || j0 + VPT > f1) {  // runs that are not all free
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int j = j0 + u;
+            if (j < f0 || j >= f1) key[u] = j < L ? 0xFFFFFFFFu : 0u;
+            lo = min(lo, j < f0 || j >= f1 ? 0xFFFFFFFFu : key[u] - 1u);
+            hi = max(hi, key[u] + 1u);  // the largest key wraps to 0
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) { lo = min(lo, key[u]); hi = max(hi, key[u]); }
+        lo -= 1u; hi += 1u;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
+    }
+    if ((tid & 63) == 0) { ext[tid >> 6] = lo; ext[32 + (tid >> 6)] = hi; }
+    lds_barrier();
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) { lo = min(lo, ext[w]); hi = max(hi, ext[32 + w]); }
+    const uint32_t n_forced = (uint32_t)(a.keep_first + a.keep_last);
+    uint32_t need = p.B - min(p.B, n_forced);  // places for free positions
+    uint32_t tau = 0xFFFFFFFEu;                // kept: key > tau, and the first `need` positions with key == tau
+    if (need > 0) {                            // uniform; there are free positions then
+        lo += 1u; hi -= 1u;
+        uint32_t base = lo, span = hi - lo;    // the need-th largest free key lies in [base, base + span]
+        // Long runs: a lower bound first.  The largest key of every group of kGroup positions goes into the histogram; the
+        // bin of the need-th largest of THEM has at least `need` keys at or above its lowest key, so only those few enter
+        // the descent -- counting all 32 keys of every thread took longer than everything else here, LDS atomics of a wave
+        // being served a few lanes at a time.
+        constexpr int kGroup = 8;
+        if (VPT >= 2 * kGroup && need <= (uint32_t)(THREADS * VPT / kGroup / 2)) {  // uniform
+            const int shift = max(0, 32 - __clz((int)(span | 1u)) - 11);
+#pragma unroll
+            for (int u = 0; u < VPT; u += kGroup) {
+                uint32_t top = 0u;
+#pragma unroll
+                for (int e = 0; e < kGroup; ++e) top = max(top, key[u + e] + 1u);  // + 1: see hi
+                if (top > base) atomicAdd(&bins[(top - 1u - base) >> shift], 1u);  // a group without free positions has 0 or 1
+            }
+            if (tid == 0) res[8] = 0u;  // stays 0 when there are fewer groups than `need`
+            lds_barrier();
+            uint32_t* found = res + 8;
+            pick_bin<THREADS, kSmallBins / THREADS>(bins, kSmallBins, need, tmp, found);
+            base += found[0] << shift;
+            span = hi - base;
+            for (int b = tid; b < kSmallBins; b += THREADS) bins[b] = 0u;
+            lds_barrier();
+        }
+        for (;;) {
+            const int shift = max(0, 32 - __clz((int)(span | 1u)) - 11);
+#pragma unroll
+            for (int u = 0; u < VPT; ++u) {
+                const uint32_t d = key[u] - base;
+                if (d <= span) atomicAdd(&bins[d >> shift], 1u);  // (a key below base wraps above span; so do 0 and 2^32 - 1)
+            }
+            lds_barrier();
+            pick_bin<THREADS, kSmallBins / THREADS>(bins, kSmallBins, need, tmp, res);
+            base += res[0] << shift;
+            need -= res[1];
+            tau = base;
+            if (shift == 0) break;
+            if (res[2] == need) {  // the whole bin is kept: everything from its lowest key (>= 1) on, no tie to trim
+                tau = base - 1u;
+                need = 0u;
+                break;
+            }
+            span = min((1u << shift) - 1u, hi - base);
+            for (int b = tid; b < kSmallBins; b += THREADS) bins[b] = 0u;
+            lds_barrier();
+        }
+    }
+
+    uint32_t m_gt = 0, m_eq = 0;  // bit u: position j0 + u
+#pragma unroll
+    for (int u = 0; u < VPT; ++u) {
+        m_gt |= key[u] > tau ? 1u << u : 0u;
+        m_eq |= key[u] == tau ? 1u << u : 0u;
+    }
+    const uint32_t n_gt = __popc(m_gt), n_eq = __popc(m_eq);
+    uint32_t total;
+    const uint32_t packed = n_gt | (n_eq << 16);  // at most 32768 per field
+    const uint32_t incl = block_scan_incl<THREADS>(packed, tmp, &total);
+    uint32_t gt = (incl - packed) & 0xFFFFu, eq = (incl - packed) >> 16;  // before this thread's run
+    const uint32_t per_slice = (p.B + gridDim.y - 1) / gridDim.y;
+    const uint32_t o_begin = min(p.B, blockIdx.y * per_slice), n_rows = min(p.B, o_begin + per_slice) - o_begin;
+    for (uint32_t m = m_gt | (eq < need ? m_eq : 0u); m != 0u; m &= m - 1u) {
+        const uint32_t bit = m & (0u - m);
+        const bool is_eq = (m_eq & bit) != 0u;
+        if (is_eq && eq >= need) continue;
+        const uint32_t slot = gt + min(eq, need) - o_begin;
+        if (slot < n_rows) slot_pos[slot] = (uint32_t)(j0 + __builtin_ctz(m));  // the staged scores are dead
+        gt += !is_eq;
+        eq += is_eq;
+    }
+    lds_barrier();
+    for (uint32_t o = threadIdx.x; o < n_rows; o += THREADS) p.emit(o_begin + o, (int)slot_pos[o]);
+    if (a.K_out != nullptr || a.stage != nullptr) gather_slots<THREADS>(a, p, slot_pos, o_begin, n_rows);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -432,31 +680,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     const uint32_t per_slice = (p.B + gridDim.y - 1) / gridDim.y;
     const uint32_t o_begin = min(p.B, blockIdx.y * per_slice), o_end = min(p.B, o_begin + per_slice);
     uint32_t* slot_pos = bins2;  // the histograms are dead: kept positions of (a batch of) the slice's output slots
-    // Pruned cache (paper Section 4.3): the kept rows of output slots o0 .. o0 + n_rows - 1, whose positions are in
-    // slot_pos; 16 lanes x 16 B per 256-byte head row.
-    auto gather_rows = [&](uint32_t o0, uint32_t n_rows) __attribute__((always_inline)) {
-        const int part = threadIdx.x & 15;
-        if (a.stage) {  // uniform
-            const int64_t v_stage = (int64_t)a.n_layers * a.TB * a.h_kv * (kHeadDim * 2);
-            for (uint32_t rr = threadIdx.x >> 4; rr < n_rows; rr += kFinThreads / 16) {
-                const int64_t src_row = (int64_t)p.tok0 + slot_pos[rr];  // within the layer (dense layout)
-                if (!row_is_overwritten(a.pm, a.dest_bits, src_row, a.TB, p.s, (int)slot_pos[rr])) continue;  // read in place later
-                const int64_t src = ((kv_row_from(a.pm, p.tok0, a.T, p.layer, p.s, (int)slot_pos[rr]) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
-                const int64_t stg = ((((int64_t)p.layer * a.TB + p.bud0 + o0 + rr) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
-                *(uint4*)(a.stage + stg) = *(const uint4*)(a.K + src);
-                *(uint4*)(a.stage + v_stage + stg) = *(const uint4*)(a.V + src);
-            }
-            return;
-        }
-        for (uint32_t rr = threadIdx.x >> 4; rr < n_rows; rr += kFinThreads / 16) {
-            const int64_t src = ((kv_row_from(a.pm, p.tok0, a.T, p.layer, p.s, (int)slot_pos[rr]) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
-            const int64_t dst = ((kv_row_from(a.pm_out, p.bud0, a.TB, p.layer, p.s, (int)(o0 + rr)) * a.h_kv + p.g) * kHeadDim) * 2 + part * 16;
-            const uint4 kv = *(const uint4*)(a.K + src);
-            const uint4 vv = *(const uint4*)(a.V + src);
-            store_stream16(a.K_out + dst, kv);
-            store_stream16(a.V_out + dst, vv);
-        }
-    };
+    auto gather_rows = [&](uint32_t o0, uint32_t n_rows) __attribute__((always_inline)) { gather_slots<kFinThreads>(a, p, slot_pos, o0, n_rows); };
     const bool want_rows = a.K_out != nullptr || a.stage != nullptr;  // uniform
     if (listed && o_end - o_begin <= 3072u) {
         // Every kept element sits in the flat list, and its output slot is its rank among the kept positions:
@@ -533,32 +757,28 @@ bool select_fast_path(const Plan& p) {
     return qual_cap >= kQualCapMin;  // otherwise the bitmaps (nearly) fill LDS: stream instead
 }
 
-// Launches of the finalize kernel with more than 64 KiB of dynamic LDS need the function's limit raised.  That
+// Launches with more than 64 KiB of dynamic LDS need the function's limit raised.  That
 // is done once per device, to the fixed maximum any call can ask for (never to a call's own size: the attribute is
 // process-wide, and two host threads with different sequence lengths must not undo each other's setting).
-static hipError_t allow_large_lds() {
-    static std::atomic<uint64_t> done{0};  // bit d: device d has the limit raised
+static hipError_t allow_large_lds(const void* kernel, std::atomic<uint64_t>& done) {  // done, bit d: device d has the limit raised
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
     if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-    e = hipFuncSetAttribute((const void*)jq_select_finalize_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(kMaxLds - 1024));
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kMaxLds - 1024));
     if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
     return e;
 }
 
-hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, char* ws, int32_t* idx, hipStream_t st,
-                         const void* K, const void* V, void* K_out, void* V_out, bool* gathered, void* stage,
-                         const int32_t* pos_in, int32_t* pos_out, const uint32_t* dest_bits) {
+static SelectArgs select_args(const Plan& p, const float* pooled, uint32_t* hist, char* ws, int32_t* idx, const void* K, const void* V,
+                              void* K_out, void* V_out, void* stage, const int32_t* pos_in, int32_t* pos_out, const uint32_t* dest_bits) {
     SelectArgs a;
     a.dest_bits = dest_bits;
     a.pooled = pooled; a.hist = hist; a.idx = idx;
     a.pos_in = pos_in; a.pos_out = pos_out;
     a.K = (const char*)K; a.V = (const char*)V; a.K_out = (char*)K_out; a.V_out = (char*)V_out;
     a.stage = (char*)stage;
-    if (gathered) *gathered = false;
     a.seg = (const uint2*)(ws + p.off_seg);
     a.seg_hdr = (const uint4*)(ws + p.off_seghdr);
     a.head = p.seg_head;
@@ -572,6 +792,68 @@ hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, cha
     a.n_seg = p.n_seg;
     for (int s = 0; s <= p.n_seq; ++s) a.cu_seg[s] = p.cu_seg[s];
     a.tab = p.tab;
+    return a;
+}
+
+// Slices per problem: enough workgroups to spread the emission (and the gather) over the chip, each with at least 64
+// output slots.
+static unsigned slices_of(const Plan& p, int64_t target) {
+    const int64_t n_prob = (int64_t)p.n_layers * p.n_seq * p.h_kv;
+    int64_t min_budget = INT32_MAX;
+    for (int s = 0; s < p.n_seq; ++s) min_budget = min(min_budget, (int64_t)(p.tab.cu_bud[s + 1] - p.tab.cu_bud[s]));
+    int64_t slices = (target + n_prob - 1) / n_prob;
+    slices = min(slices, (min_budget + 63) / 64);
+    return (unsigned)max((int64_t)1, min(slices, (int64_t)64));
+}
+
+static int longest_sequence(const Plan& p) {
+    int max_len = 0;
+    for (int s = 0; s < p.n_seq; ++s) max_len = max(max_len, p.tab.cu_seq[s + 1] - p.tab.cu_seq[s]);
+    return max_len;
+}
+
+bool select_small(const Plan& p) { return longest_sequence(p) <= kSmallMax; }
+
+template <int THREADS, int VPT, int K>
+static hipError_t launch_small_k(const Plan& p, const PoolSelectArgs& a, hipStream_t st) {
+    static std::atomic<uint64_t> done{0};
+    const int words = kSmallFixedWords + small_pad(THREADS * VPT + 8) + 4;
+    const size_t lds_bytes = (size_t)words * sizeof(uint32_t);
+    if (lds_bytes > 64 * 1024) {
+        const hipError_t e = allow_large_lds((const void*)jq_pool_select_kernel<THREADS, VPT, K>, done);
+        if (e != hipSuccess) return e;
+    }
+    const unsigned n_prob = (unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv);
+    return launch_kernel(jq_pool_select_kernel<THREADS, VPT, K>, dim3(n_prob, slices_of(p, 256)), dim3(THREADS), lds_bytes, st, nullptr, -1, a);
+}
+template <int K>
+static hipError_t launch_small(const Plan& p, const PoolSelectArgs& a, hipStream_t st) {
+    const int L = longest_sequence(p);
+    if (L <= 512 * 4) return launch_small_k<512, 4, K>(p, a, st);
+    if (L <= 512 * 8) return launch_small_k<512, 8, K>(p, a, st);
+    if (L <= 512 * 16) return launch_small_k<512, 16, K>(p, a, st);
+    if (L <= 1024 * 16) return launch_small_k<1024, 16, K>(p, a, st);
+    return launch_small_k<1024, 32, K>(p, a, st);
+}
+
+hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool pool, char* ws, int32_t* idx, hipStream_t st, const void* K,
+                              const void* V, void* K_out, void* V_out, void* stage, const int32_t* pos_in, int32_t* pos_out,
+                              const uint32_t* dest_bits) {
+    PoolSelectArgs a;
+    a.in = in; a.out = out;
+    a.pool_k = p.pool_k; a.inv_k = 1.0f / (float)p.pool_k;
+    a.sel = select_args(p, nullptr, (uint32_t*)(ws + p.off_hist), ws, idx, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
+    if (!pool || p.pool_k == 1) return launch_small<1>(p, a, st);
+    if (p.pool_k == 7) return launch_small<7>(p, a, st);
+    if (p.pool_k == 5) return launch_small<5>(p, a, st);
+    return launch_small<0>(p, a, st);
+}
+
+hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, char* ws, int32_t* idx, hipStream_t st,
+                         const void* K, const void* V, void* K_out, void* V_out, bool* gathered, void* stage,
+                         const int32_t* pos_in, int32_t* pos_out, const uint32_t* dest_bits) {
+    const SelectArgs a = select_args(p, pooled, hist, ws, idx, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
+    if (gathered) *gathered = false;
     const unsigned n_prob = (unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv);
 
     if (!select_fast_path(p))  // bitmaps do not fit: stream instead
@@ -580,22 +862,13 @@ hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, cha
     int words_cap, qual_cap;
     const size_t lds_bytes = finalize_lds(p, &words_cap, &qual_cap);
     if (lds_bytes > 64 * 1024) {
-        const hipError_t e = allow_large_lds();
+        static std::atomic<uint64_t> done{0};
+        const hipError_t e = allow_large_lds((const void*)jq_select_finalize_kernel, done);
         if (e != hipSuccess) return e;
     }
-    // Slices per problem: enough workgroups to spread the emission (and the gather) over the chip, each with
-    // at least 64 output slots.
-    int64_t min_budget = INT32_MAX;
-    for (int s = 0; s < p.n_seq; ++s) {
-        const int64_t b = p.tab.cu_bud[s + 1] - p.tab.cu_bud[s];
-        if (b < min_budget) min_budget = b;
-    }
-    int64_t slices = (256 + n_prob - 1) / n_prob;
-    if (slices > (min_budget + 63) / 64) slices = (min_budget + 63) / 64;
-    if (slices > 64) slices = 64;
-    if (slices < 1) slices = 1;
+    const unsigned slices = slices_of(p, 256);
     if (gathered) *gathered = K_out != nullptr || stage != nullptr;
-    return launch_kernel(jq_select_finalize_kernel, dim3(n_prob, (unsigned)slices), dim3(kFinThreads), lds_bytes, st, p.marks,
+    return launch_kernel(jq_select_finalize_kernel, dim3(n_prob, slices), dim3(kFinThreads), lds_bytes, st, p.marks,
                          kTrFinalize, a, words_cap, qual_cap);
 }
 
