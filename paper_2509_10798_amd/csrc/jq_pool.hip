@@ -21,7 +21,9 @@ constexpr int kPoolBlockPos = kPoolThreads * kPoolPerThread;  // 1024 positions 
 static_assert(kPoolBlockPos == kSegLen, "one segment of the selection's lists per pooling workgroup");
 constexpr int kPoolMaxHalo = 32;                               // (pool_k - 1) / 2 up to here uses the LDS path
 constexpr int kWinBins = 128;                                  // histogram window below the block's top bin
-constexpr int kWinCopies = 16;
+constexpr int kWinCopies = 8;                                  // interleaved copies of the window's counters; 16, with room for 1024 sorted
+                                                              // pairs whatever `head`, left room for six workgroups per CU (8 x 64K scores:
+                                                              // 23.6 us); eight fit now (19.6)
 constexpr int kWinStride = kWinBins + 1;                       // +1: copies of one bin fall into different banks
 
 struct PoolArgs {
@@ -46,8 +48,8 @@ struct PoolArgs {
 // pooling windows stop at sequence ends and every count goes to its own problem's histogram).
 //
 // Histogram of the block's values: neighbouring scores crowd into a few bins, which would serialise
-// LDS atomics on one word; so the 128 bins below the block's highest bin are kept in 16 interleaved
-// copies (lane & 15 picks the copy) and merged into the problem's global histogram with one
+// LDS atomics on one word; so the 128 bins below the block's highest bin are kept in kWinCopies interleaved
+// copies (the lane's low bits pick the copy) and merged into the problem's global histogram with one
 // device-scope atomic per non-empty bin.  Values more than 32 octaves below the block's maximum
 // (the far tail of a peaked softmax, exact zeros) are counted in a single full-width LDS histogram
 // that is cleared, filled and flushed only by blocks that meet such a value.
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     __shared__ uint32_t win[kWinCopies * kWinStride];
     __shared__ uint32_t wave_top[kPoolThreads / 64], wave_bottom[kPoolThreads / 64];
     __shared__ uint32_t scan_tmp[kPoolThreads / 64 + 1];
-    __shared__ __attribute__((aligned(16))) uint2 sorted[kSegLen];  // head of the block's segment, assembled before it is written out
+    extern __shared__ __attribute__((aligned(16))) uint2 sorted[];  // [head] of the block's segment, assembled before it is written out
     // staged inputs; once the block's values are in registers the same memory serves as the full-width
     // histogram `low` of the far tail
     __shared__ __attribute__((aligned(16))) float tile[(POOL ? kPoolBlockPos + 2 * kPoolMaxHalo + 8 : 4) > kHistBins
@@ -194,8 +196,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     }
     if (a.seg == nullptr) return;  // uniform
 
-    // Counting sort by (bin, highest first; copy): thread t owns bin 127 - t/2 of the window and eight of its
-    // sixteen copies, so thread order is slot order.  The counters become running offsets.
+    // Counting sort by (bin, highest first; copy): thread t owns bin 127 - t/2 of the window and half of its
+    // copies, so thread order is slot order.  The counters become running offsets.
     const int brel = kWinBins - 1 - (int)(threadIdx.x >> 1);
     const int c0 = (int)(threadIdx.x & 1) * (kWinCopies / 2);
     lds_barrier();  // the flush above has read the counters
@@ -335,14 +337,14 @@ hipError_t launch_pool(const Plan& p, const float* scores, float* pooled, uint32
                        hipStream_t st) {
     const PoolArgs a = make_args(p, scores, pooled, hist_or_null, ws_or_null);
     dim3 grid((unsigned)p.n_seg, p.h_kv, p.n_layers);
-    if (p.pool_k == 7) return launch_kernel(jq_pool_kernel<true, 7>, grid, dim3(kPoolThreads), 0, st, p.marks, kTrPool, a);
-    return launch_kernel(jq_pool_kernel<true, 0>, grid, dim3(kPoolThreads), 0, st, p.marks, kTrPool, a);
+    if (p.pool_k == 7) return launch_kernel(jq_pool_kernel<true, 7>, grid, dim3(kPoolThreads), a.seg ? a.head * sizeof(uint2) : 0, st, p.marks, kTrPool, a);
+    return launch_kernel(jq_pool_kernel<true, 0>, grid, dim3(kPoolThreads), a.seg ? a.head * sizeof(uint2) : 0, st, p.marks, kTrPool, a);
 }
 
 hipError_t launch_hist(const Plan& p, const float* pooled, uint32_t* hist, char* ws_or_null, hipStream_t st) {
     const PoolArgs a = make_args(p, pooled, nullptr, hist, ws_or_null);
     dim3 grid((unsigned)p.n_seg, p.h_kv, p.n_layers);
-    return launch_kernel(jq_pool_kernel<false, 0>, grid, dim3(kPoolThreads), 0, st, nullptr, -1, a);
+    return launch_kernel(jq_pool_kernel<false, 0>, grid, dim3(kPoolThreads), a.seg ? a.head * sizeof(uint2) : 0, st, nullptr, -1, a);
 }
 
 hipError_t launch_fill_u32(uint32_t* dst, size_t n, uint32_t v, hipStream_t st) {
