@@ -1,5 +1,6 @@
 // C ABI of libjq: argument validation, planning (wave counts, workspace layout) and the launch
 // sequences.  Everything here runs on the host; no HIP call is made before validation succeeds.
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
@@ -96,38 +97,74 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
     }
     p.TB = tb;
 
-    // A sequence of L keys is worked on by ceil(L / chunk_keys) waves per head (which share its 32-key tiles
-    // round-robin).  Small calls aim at one wave per SIMD (256 CUs x 4) in the pass that reads K cold (the
-    // first pass, or the only one when the normalisers are supplied): one wave with two tiles in flight keeps
-    // its SIMD busy and the window of K in flight stays small.  The second pass finds part of K in the
-    // Infinity Cache and has more arithmetic per tile; it does better with two waves per SIMD.  The cap makes
-    // big calls run in several rounds.
-    // (groups of 128 query rows beyond the first are further workgroups of the first pass's one launch)
-    const int64_t keys = (int64_t)p.n_layers * p.h_kv * p.T * p.row_groups;
-    auto plan_waves = [&](int64_t target_waves, int32_t knob, int32_t* cu_chunk, int32_t* cu_cgrp, int32_t* chunk_keys,
-                          int32_t* n_chunks) {
-        int64_t chunk = (keys + target_waves - 1) / target_waves;
-        chunk = (chunk + kKeyTile - 1) / kKeyTile * kKeyTile;
-        if (chunk < 64) chunk = 64;
-        if (chunk > 1024) chunk = 1024;
-        if (knob) chunk = knob;  // ablation knob
+    // How the sequences are cut into workgroups of four waves for the passes over K: ceil(L / (4 * chunk)) workgroups per
+    // (layer, sequence, head, group of 128 query rows), whose waves share the sequence's 32-key tiles round-robin.  The
+    // `chunk` is chosen by an estimate of either pass's time in units of the 1.3 us that 1024 waves (one per SIMD: 256 CUs,
+    // one workgroup each) take for a tile each at the rate memory delivers:
+    //   tiles / 1024                      all waves busy
+    //   + what the last, partly filled round of the 512 resident workgroups wastes: per tile of its longest wave it takes
+    //     at least 0.75 (the arithmetic of a wave alone on its SIMD) with at most one workgroup per CU, 1.5 with two on
+    //     some, 1.0 when the few of a later round start as the CUs fall free
+    //   + the longest wave's lead over the average
+    //   + 2 per further workgroup and CU  another start-up (query rows, normalisers), 2-4 us that its neighbour hides in part
+    //   + 3 for the launch that merges the statistics of a sequence with more than 64 workgroups.
+    // One workgroup per CU wins where the sequences divide evenly -- 128K layer, keys per wave 512 / 1024: 48.7 + 44.9 /
+    // 45.2 + 41.5 us; 8 layers x 64K, 1024 / 4096: 180 + 194 / 174 + 189; 32 x 8K, 1024 / 2048: 95.7 + 94.5 / 90.2 + 92.1
+    // -- and a count just over a multiple of 512 loses: a paged batch of 8 with 528 workgroups in the second pass took 218
+    // us per call, with 400 204.  (Candidates only grow from the smallest sensible chunk: workspaces hold one set of
+    // statistics per workgroup.)
+    const int64_t per_key = (int64_t)p.n_layers * p.h_kv * p.row_groups;
+    const int64_t keys = per_key * p.T;
+    auto wgs_of = [](int64_t L, int64_t chunk) { return (L + kScoreWaves * chunk - 1) / (kScoreWaves * chunk); };
+    auto estimate = [&](int64_t chunk) {
+        int64_t wgs = 0, tiles = 0, waves = 0, t_max = 0, wgs_max = 0;
+        for (int s = 0; s < sh->n_seq; ++s) {
+            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
+            const int64_t n = (L + kKeyTile - 1) / kKeyTile, g = wgs_of(L, chunk), w = std::min(kScoreWaves * g, n);
+            wgs += g; tiles += n; waves += w;
+            t_max = std::max(t_max, (n + w - 1) / w);
+            wgs_max = std::max(wgs_max, g);
+        }
+        const double N = (double)per_key * (double)wgs, rest = N - 512.0 * std::floor(N / 512.0);
+        const double t_avg = (double)tiles / (double)waves;
+        const double last = rest > 256.0 ? 1.5 : N > 512.0 ? 1.0 : 0.75;
+        double cost = (double)per_key * (double)tiles / 1024.0 + 2.0 * std::max(0.0, N / 256.0 - 1.0) + ((double)t_max - t_avg);
+        if (rest > 0.0) cost += std::max(0.0, last * (double)t_max - rest / 256.0 * t_avg);
+        if (wgs_max > 64 && p.row_groups == 1) cost += 3.0;
+        return cost;
+    };
+    auto round_tile = [](int64_t x) { return (x + kKeyTile - 1) / kKeyTile * kKeyTile; };
+    const int64_t smallest = std::min<int64_t>(std::max<int64_t>(round_tile((keys + 1023) / 1024), 64), 1024);
+    int64_t best = smallest;
+    if (!knobs().chunk_keys || !knobs().chunk_keys2) {
+        double best_cost = estimate(smallest);
+        auto consider = [&](int64_t chunk) {
+            if (chunk <= smallest || chunk > 8192) return;
+            const double cost = estimate(chunk);
+            if (cost < best_cost) { best_cost = cost; best = chunk; }
+        };
+        for (int f = 5; f <= 32; f += f < 8 ? 1 : f < 16 ? 4 : 8) consider(round_tile(smallest * f / 4));  // 1.25, 1.5, 1.75, 2, 3, 4, 6, 8 times
+        if (sh->n_seq == 1)  // cut evenly into as many workgroups as fill the chip once, twice, four times
+            for (int k = 1; k <= 4; k *= 2) {
+                const int64_t g = 256 * k / per_key;
+                if (g >= 1) consider(round_tile((p.T + kScoreWaves * g - 1) / (kScoreWaves * g)));
+            }
+    }
+    auto cut = [&](int64_t chunk, int32_t* cu_chunk, int32_t* cu_cgrp) {
         int64_t nc = 0, ng = 0;
         cu_chunk[0] = 0;
         cu_cgrp[0] = 0;
         for (int s = 0; s < sh->n_seq; ++s) {
-            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
-            const int64_t waves = (L + chunk - 1) / chunk;
-            nc += waves;
-            ng += (waves + kScoreWaves - 1) / kScoreWaves;
+            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s], g = wgs_of(L, chunk);
+            nc += std::min(kScoreWaves * g, (L + kKeyTile - 1) / kKeyTile);
+            ng += g;
             cu_chunk[s + 1] = (int32_t)nc;
             cu_cgrp[s + 1] = (int32_t)ng;
         }
-        *chunk_keys = (int32_t)chunk;
-        *n_chunks = (int32_t)nc;
         return ng;
     };
-    const int64_t ng = plan_waves(1024, knobs().chunk_keys, p.tab.cu_chunk, p.tab.cu_cgrp, &p.chunk_keys, &p.n_chunks);
-    int64_t ng2 = plan_waves(2048, knobs().chunk_keys2, p.cu_chunk2, p.cu_cgrp2, &p.chunk_keys2, &p.n_chunks2);
+    const int64_t ng = cut(knobs().chunk_keys ? knobs().chunk_keys : best, p.tab.cu_chunk, p.tab.cu_cgrp);
+    int64_t ng2 = cut(knobs().chunk_keys2 ? knobs().chunk_keys2 : best, p.cu_chunk2, p.cu_cgrp2);
     if (p.row_groups > 1) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
         ng2 = 0;
         for (int s = 0; s < sh->n_seq; ++s) {

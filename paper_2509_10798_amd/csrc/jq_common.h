@@ -25,7 +25,7 @@ struct SeqTab {
     int32_t n_seq;
     int32_t cu_seq[JQ_MAX_SEQ + 1];    // token offsets
     int32_t cu_bud[JQ_MAX_SEQ + 1];    // kept-row offsets
-    int32_t cu_chunk[JQ_MAX_SEQ + 1];  // score-wave offsets (ceil(L / chunk_keys) waves per sequence and head)
+    int32_t cu_chunk[JQ_MAX_SEQ + 1];  // score-wave offsets (waves per sequence and head that have tiles)
     int32_t cu_cgrp[JQ_MAX_SEQ + 1];   // score-workgroup offsets (ceil(waves / 4) workgroups per sequence and head)
 };
 
@@ -45,10 +45,7 @@ struct Plan {
     int32_t rows;         // n_q * group: query rows that share one KV head
     int32_t row_tiles;    // ceil(rows / 32)
     int32_t row_groups;   // ceil(row_tiles / 4): 1, or the groups of rows that the first pass handles side by side
-    int32_t chunk_keys;   // a sequence of L keys gets ceil(L / chunk_keys) score waves per head (multiple of 32)
-    int32_t n_chunks;     // such waves per layer and head, over all sequences (tab.cu_chunk counts them)
-    // the same for the second K pass when a first one has run (tab holds the first pass's tables)
-    int32_t chunk_keys2, n_chunks2;
+    // tab.cu_chunk / cu_cgrp: waves and workgroups of the first pass over K (or the only one); for a second pass:
     int32_t cu_chunk2[JQ_MAX_SEQ + 1], cu_cgrp2[JQ_MAX_SEQ + 1];
     double scale;         // logit scale actually used
     // paged cache (block_table null: dense K, V): page = 1 << page_shift tokens, n_pages per layer's pool

@@ -49,7 +49,7 @@ struct ScoreArgs {
     float2* stats;    // [n_layers][n_cgrp of pass 1][h_kv][RP]: (m, Z) per pass-1 workgroup
     uint2* aug;       // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
     float* scores;    // [n_layers][h_kv][T]
-    int32_t n_layers, n_seq, n_q, h_q, h_kv, group, rows, RP, chunk_keys, n_chunks;
+    int32_t n_layers, n_seq, n_q, h_q, h_kv, group, rows, RP;
     int32_t n_cgrp;       // workgroups per layer and head: sum over sequences of ceil(waves / 4)
     // pass 2 only: where pass 1 left its per-workgroup statistics (its own n_cgrp and per-sequence offsets),
     // and whether this launch merges them itself (otherwise jq_combine_kernel has filled `aug`)
@@ -1189,7 +1189,6 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.diff_ref = nullptr; a.diff_part = nullptr; a.diff_inv_ref = a.diff_inv_own = 0.0f;
     const bool paged = p.block_table != nullptr;
     if (fuse && (paged || lse)) return hipErrorInvalidValue;  // the fused comparison exists for dense two-pass calls
-    a.chunk_keys = p.chunk_keys; a.n_chunks = p.n_chunks;
     a.n_cgrp = p.tab.cu_cgrp[p.n_seq];
     a.one_L = p.n_seq == 1 ? p.tab.cu_seq[1] : 0;
     a.one_waves = p.n_seq == 1 ? p.tab.cu_chunk[1] : 0;
@@ -1227,7 +1226,6 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         // the second pass cuts the sequences into its own number of waves
         a.n_part = a.n_cgrp;
         for (int s = 0; s <= p.n_seq; ++s) a.cu_part[s] = p.tab.cu_cgrp[s];
-        a.chunk_keys = p.chunk_keys2; a.n_chunks = p.n_chunks2;
         for (int s = 0; s <= p.n_seq; ++s) { a.tab.cu_chunk[s] = p.cu_chunk2[s]; a.tab.cu_cgrp[s] = p.cu_cgrp2[s]; }
         a.n_cgrp = p.cu_cgrp2[p.n_seq];
         a.one_waves = p.n_seq == 1 ? p.cu_chunk2[1] : 0;
