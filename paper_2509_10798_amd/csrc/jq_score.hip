@@ -966,8 +966,10 @@ template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  //
 // order and stored once.  Before, every 128 rows took a launch of each pass that read K and added to the scores in
 // memory: launches of 64..256 keys per wave that were mostly start-up.  The work is a contraction that K does not
 // bound (every key is used by all rows): 9 MFMA per 32 x 32 logits against 16 exp2/mul/add per lane.  Measured at 16384
-// keys x 8 heads x 1024 rows: eight launches of 12.4 us and eight first passes of 10.9 us before, 46 + 45 us + 5 us for
-// the combine launch now.
+// keys x 8 heads x 1024 rows: eight launches of 12.4 us and eight first passes of 10.9 us before, 37 + 37 us + 5 us for
+// the combine launch now (1.05 PFLOP/s; a plain library product of 8192^3 reaches 1.2 on this card, which lowers its
+// clock under matrix work).  Two waves per key group instead of four: 42.9 against 41.5 us there, 5 % better only with
+// thousands of workgroups: not kept.
 // -beta/c comes from `aug`, which a combine launch (or jq_lse_aug_kernel) has filled.
 template <bool PAGED, bool DIFF>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(ScoreArgs a) {
@@ -993,9 +995,25 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...
     const uint2* aug = a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + (lane & 31);
     const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
+    // With a power-of-two group of up to 32 heads a tile's rows lie where a key tile's would: a lane part that never changes
+    // and a uniform part per load (4 i + a, a < 4, splits without carry), so a request costs no vector arithmetic -- the
+    // general addresses below cost 400 of a tile's 1800 cycles (training forward 101 -> 97.5 us, response tokens 104.5 -> 101).
+    const int gs = a.group_shift;
+    const bool regular = gs >= 0 && gs <= 5 && tok_bytes < (1 << 25);  // uniform; a tile's bytes fit a 32-bit offset
+    const uint32_t rl = (uint32_t)lane >> 4, tok32 = (uint32_t)tok_bytes;
+    const uint32_t tq = (rl >> (gs & 31)) * tok32 + (rl & (uint32_t)(a.group - 1)) * (kHeadDim * 2) + ((((uint32_t)lane & 15u) ^ rl) << 4);
     auto fetch_rows = [&](int k) __attribute__((always_inline)) {
         const int r0 = (wv + k * kScoreWaves) * kRowTile;
         char* slot = slots + (k & 1) * kSlotBytes;
+        if (regular && r0 + kRowTile <= a.rows) {
+            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(qbase + (int64_t)(r0 >> gs) * tok_bytes), 0,
+                (int)((uint32_t)((kRowTile - 1) >> gs) * tok32 + (uint32_t)min(a.group, kRowTile) * (kHeadDim * 2)), 0x00020000);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                lds_dma16(rsrc, slot + 1024 * i, tq ^ (64u * (i & 3)), ((uint32_t)(4 * i) >> gs) * tok32 + ((uint32_t)(4 * i) & (uint32_t)(a.group - 1)) * (kHeadDim * 2));
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int r = 4 * i + (lane >> 4);
