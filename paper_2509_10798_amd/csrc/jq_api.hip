@@ -167,12 +167,14 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
     // workgroups, the first (whose workgroups each leave a set of statistics) with up to 64.  Whole calls, two tiles / one:
     // 2048 tokens with 2 KV heads 20.6 / 19.4 us, with 8 22.8 / 21.9; with 512 workgroups 28.3 / 29.7.
     int64_t best2 = best;
+    const int64_t split = best;
     if (best == 64 && p.row_groups == 1) {
         int64_t wgs = 0;
         for (int s = 0; s < sh->n_seq; ++s) wgs += wgs_of(sh->cu_seqlens[s + 1] - sh->cu_seqlens[s], kKeyTile);
         if (per_key * wgs <= 256) best2 = kKeyTile;
         if (per_key * wgs <= 64) best = kKeyTile;
     }
+    const int64_t ng_ws = cut(knobs().chunk_keys ? knobs().chunk_keys : split, p.tab.cu_chunk, p.tab.cu_cgrp);  // for the workspace
     const int64_t ng = cut(knobs().chunk_keys ? knobs().chunk_keys : best, p.tab.cu_chunk, p.tab.cu_cgrp);
     int64_t ng2 = cut(knobs().chunk_keys2 ? knobs().chunk_keys2 : best2, p.cu_chunk2, p.cu_cgrp2);
     if (p.row_groups > 1) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
@@ -210,14 +212,19 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
 
     const size_t RP = (size_t)p.row_tiles * kRowTile;
     size_t off = 0;
-    p.off_stats = off;  off += align_up((size_t)p.n_layers * ng * p.h_kv * RP * sizeof(float2));  // one per pass-1 workgroup
-    p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
-    p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
-    p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
+    // The statistics (one set of RP per first-pass workgroup) have room for `split`; with one tile per wave they run on into
+    // the pooled scores and the block heads behind them, which pooling writes when both passes are done.  That always fits:
+    // ceil(L / 128) - ceil(L / 256) <= (L + 255) / 256 sets of at most 1 KB against 4 L bytes of pooled scores and 1 KB of
+    // block heads.  So the finer split asks callers for no larger workspace.
+    p.off_stats = off;  off += align_up((size_t)p.n_layers * ng_ws * p.h_kv * RP * sizeof(float2));
     p.off_pooled = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
     p.off_idx = off;    off += align_up((size_t)p.n_layers * p.h_kv * p.TB * sizeof(int32_t));
     p.off_seg = off;    off += align_up((size_t)p.n_layers * p.h_kv * p.n_seg * p.seg_head * sizeof(uint2));
     p.off_seghdr = off; off += align_up((size_t)p.n_layers * p.h_kv * p.n_seg * sizeof(uint4));
+    p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
+    p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
+    p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
+    if (p.off_stats + (size_t)p.n_layers * ng * p.h_kv * RP * sizeof(float2) > p.off_aug) return JQ_ERR_UNSUPPORTED;  // never
     p.ws_bytes = off;
     *out = p;
     return JQ_OK;
@@ -709,8 +716,11 @@ static int mse_fused_plans(const jq_shape* shape, int32_t n_q_b, Plan* pa, Plan*
     sb.n_q = n_q_b;
     if ((rc = make_plan(&sb, false, pb)) != JQ_OK) return rc;
     *off_b = pa->ws_bytes;
-    *off_part = *off_b + pb->ws_bytes;
-    *total = *off_part + align_up((size_t)pb->n_layers * pb->cu_cgrp2[pb->n_seq] * pb->h_kv * sizeof(double));
+    // the partial sums (8 bytes per workgroup of at least 128 keys, or a sequence's end) lie in the first plan's pooled
+    // scores and positions (4 L + 4 bytes per sequence and head at least), which this call has no other use for
+    *off_part = pa->off_pooled;
+    if (*off_part + (size_t)pb->n_layers * pb->cu_cgrp2[pb->n_seq] * pb->h_kv * sizeof(double) > pa->off_seg) return JQ_ERR_UNSUPPORTED;  // never
+    *total = *off_b + pb->ws_bytes;
     return JQ_OK;
 }
 
