@@ -221,7 +221,7 @@ int jq_map_mse(const jq_shape* shape, const float* scores_a, float rows_a, const
 /* The same value (Section 4.2: the maps of Eq. 3 and Eq. 4, the loss of Eq. 5) straight from the two query sets,
  * without handing the maps to the caller: Q_a [n_layers, n_seq, shape->n_q, h_q, d] are the soft tokens' queries,
  * Q_b [n_layers, n_seq, n_q_b, h_q, d] the response tokens' (any n_q_b >= 1; rows beyond 128 per KV head take
- * further passes over K), K the prompt's keys as in jq_score.  The soft tokens' map is computed first; the
+ * further statistics sweeps over K), K the prompt's keys as in jq_score.  The soft tokens' map is computed first; the
  * launch that completes the response's map does not store it but accumulates
  *   ( map_a[t] / (n_q * G) - map_b[t] / (n_q_b * G) )^2,  G = h_q / h_kv,
  * per workgroup in fp64, and a last small launch adds the workgroups' sums in a fixed order:

@@ -9,10 +9,13 @@
 //   pass 2 (score):  score_j = sum_r 2^(c * (q_r.k_j - beta_r / c)).  The -beta_r/c term enters
 //                    through one extra MFMA step whose key-side operand is 1.0, so the epilogue is one
 //                    multiply, one exp2 and one add per logit.
+// With more than 128 query rows per KV head pass 1 takes a grid slice per 128 rows, the merge is a kernel of its own, and
+// pass 2 turns around: jq_score_rows_kernel keeps 128 keys in registers and streams the query rows past them, so that a
+// key's score is complete in one launch whatever the number of rows.
 // Variants of the same kernels: supplied normalisers (pass 2 alone), the soft tokens' own keys or the prompt's
 // own last tokens as causally masked tiles of pass 1, keys read out of a paged pool.
 //
-// One wave owns one (layer, sequence, KV head) and a strided set of that sequence's 32-key tiles, and
+// Otherwise one wave owns one (layer, sequence, KV head) and a strided set of that sequence's 32-key tiles, and
 // keeps the head's (up to) 128 query rows in registers as MFMA operands.  The four waves of a workgroup
 // work on the same head and fetch its query rows together (one row tile each, whole rows, turned into
 // operand order through LDS) -- gathering them one row per lane would cost every wave 32 row-strided
