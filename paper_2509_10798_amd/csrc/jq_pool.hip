@@ -71,6 +71,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     __shared__ __attribute__((aligned(16))) float tile[(POOL ? kPoolBlockPos + 2 * kPoolMaxHalo + 8 : 4) > kHistBins
                                                            ? (POOL ? kPoolBlockPos + 2 * kPoolMaxHalo + 8 : 4) : kHistBins];
     uint32_t* low = (uint32_t*)tile;
+    static_assert(sizeof(tile) >= sizeof(float) * (kPoolBlockPos + kPoolThreads), "a whole round of loads for the halo");
+    static_assert(2 * kPoolMaxHalo <= kPoolThreads, "one round of loads for the halo");
     const int g = blockIdx.y, layer = blockIdx.z;
     const int s = a.one_L ? 0 : find_seq(a.cu_seg, a.tab.n_seq, blockIdx.x);
     const int64_t lo = a.one_L ? 0 : a.tab.cu_seq[s], hi = a.one_L ? a.one_L : a.tab.cu_seq[s + 1];
@@ -84,15 +86,29 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     const int r = K ? (K - 1) / 2 : (a.pool_k - 1) / 2;
     const bool staged = POOL && r <= kPoolMaxHalo;  // uniform
 
-    if (do_hist) {
-        for (int b = threadIdx.x; b < kWinCopies * kWinStride; b += kPoolThreads) win[b] = 0;
-    }
     if (staged) {
         const int n = cnt + 2 * r;
-        for (int i = threadIdx.x; i < n; i += kPoolThreads) {
-            const int64_t q = p0 - r + i;
-            tile[i] = (q >= lo && q < hi) ? in_row[q] : 0.f;
+        // All requests of a thread first, then their stores to LDS: as one loop of load, bounds test and store they were up to
+        // five memory latencies in a row, half of the kernel's duration, whatever the occupancy (8 x 64K scores 19.4 -> 15.5 us,
+        // 128K layer 8.0 -> 6.6).
+        constexpr int kLoads = kPoolPerThread + (2 * kPoolMaxHalo + kPoolThreads - 1) / kPoolThreads;
+        const float* seq = in_row + lo;
+        float x[kLoads];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {  // clamped addresses: nothing stands between the requests
+            const int i = u * kPoolThreads + (int)threadIdx.x;
+            if (u < kPoolPerThread || i < n) x[u] = seq[(uint32_t)min(max(jblk - r + i, 0), Ls - 1)];
         }
+        if (do_hist) {  // while they are on their way
+            for (int b = threadIdx.x; b < kWinCopies * kWinStride; b += kPoolThreads) win[b] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int i = u * kPoolThreads + (int)threadIdx.x, j = jblk - r + i;
+            if (u < kPoolPerThread || i < n) tile[i] = j >= 0 && j < Ls ? x[u] : 0.f;  // (`tile` has room for kLoads * kPoolThreads)
+        }
+    } else if (do_hist) {
+        for (int b = threadIdx.x; b < kWinCopies * kWinStride; b += kPoolThreads) win[b] = 0;
     }
     lds_barrier();
     // Thread t owns the run of four consecutive positions 4t ..: with the taps unrolled a run reads its 4 + 2r
