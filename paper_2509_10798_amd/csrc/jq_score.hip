@@ -414,6 +414,13 @@ __device__ __forceinline__ f32x16 stats_chain(const bf16x8 (&kf)[8], const bf16x
     return acc;
 }
 
+// The largest Z that a lane hands on with an offset that is not the maximum of its logits.  The merges that follow (two
+// lane halves, the waves of a workgroup, a sequence's workgroups) add lanes' Z without looking again, at equal offsets in
+// the worst case: a row has at most two lanes per 32-key tile, 2^20 of them (a sequence is below 2^24 tokens: 256 bytes a
+// row in a 32-bit buffer offset), and 2^20 * 2^96 is still finite.  With the limit at infinity a group of late keys 111..128
+// octaves above every wave's first tile left each lane finite and the merged Z infinite, hence NaN scores.
+constexpr float kLargestZ = 0x1p96f;
+
 // The general tile: masked, and `keep` says whether the offsets stay as they are (any offset gives the same (m, Z) pair
 // up to rounding as long as no term overflows; terms that underflow are negligible next to the contribution of the
 // offset's own key) or follow the running maximum.
@@ -551,8 +558,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
         }
     };
     // First sweep: the wave's first tile sets each lane's offset m (to the largest of four of its 16 logits), later tiles
-    // keep it -- no maximum to track.  A logit more than 2^7 (base 2) above that offset overflows 2^(t - m) to infinity,
-    // which cannot be repaired afterwards, so such a wave (wave-uniform decision) sweeps again with the running maximum.
+    // keep it -- no maximum to track.  Logits far above that offset overflow Z to infinity, which cannot be repaired
+    // afterwards, so a wave with a Z of kLargestZ or more (wave-uniform decision) sweeps again with the running maximum.
     int k = 0;
     if (n_full > 0) {
         // The hot sweep, tiles 0 .. n_full - 1, software-pipelined across tiles: while query tile qt's logits are
@@ -605,7 +612,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
         }
         bool overflow = false;
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) overflow |= !(z[qt] < INFINITY);
+        for (int qt = 0; qt < NQT; ++qt) overflow |= !(z[qt] < kLargestZ);
         if (repeat || !__builtin_expect(__any(overflow), 0)) break;
         repeat = true;
 #pragma unroll

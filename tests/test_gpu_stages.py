@@ -93,6 +93,32 @@ def test_score_with_one_dominant_key(knobs, alpha, where, chunk):
     assert ref[0, where] > 0.99 and got[0, where] > 0.99   # that query row's whole mass sits on the planted key
 
 
+@pytest.mark.parametrize("n_q", [16, 80])        # 64 rows per head; 320: statistics merged by a launch of their own
+@pytest.mark.parametrize("octaves", [90, 100, 113, 118, 124, 131])
+def test_score_with_late_keys_far_above_every_first_tile(knobs, octaves, n_q):
+    # Every wave's offset comes from keys with logits near 0, all later keys (many per lane, in every wave) lie the same
+    # number of octaves above it.  A lane sums 2^octaves about 500 times: up to some 118 octaves that stays finite, but the
+    # sum over lanes, waves and workgroups does not.
+    print("score late keys", octaves, n_q, flush=True)
+    torch = torch_()
+    knobs(JQ_CHUNK_KEYS="1024")                            # two workgroups of four waves with 32 tiles each
+    rng = np.random.default_rng(16)
+    L, first, h_q, h_kv, d = 8192, 8 * 32, 8, 2, 128
+    Qf = 0.05 * rng.standard_normal((1, 1, n_q, h_q, d)).astype(np.float32)
+    Kf = 0.05 * rng.standard_normal((1, L, h_kv, d)).astype(np.float32)
+    Qf[..., 0] = 32.0
+    Kf[..., 0] = 0.0
+    Kf[:, first:, :, 0] = octaves * np.log(2.0) * np.sqrt(d) / 32.0
+    Q, K = f32_to_bf16_bits(Qf), f32_to_bf16_bits(Kf)
+    sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=n_q, h_q=h_q, h_kv=h_kv)
+    got = jq.score(sh, to_dev_bf16(Q), to_dev_bf16(K))
+    torch.cuda.synchronize()
+    got = got.cpu().numpy()[0]
+    assert np.isfinite(got).all()
+    assert_scores_close(got, oracle.score(Q[0, 0], K[0]), n_q * (h_q // h_kv) / L, "late keys")
+    np.testing.assert_allclose(got.sum(axis=1), n_q * (h_q // h_kv), rtol=1e-4)
+
+
 def test_score_several_chunks_per_sequence(knobs):
     # force 64-key chunks so that one sequence is split over many waves and partial statistics merge
     print("score chunked", flush=True)
