@@ -99,15 +99,19 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
 
     // How the sequences are cut into workgroups of four waves for the passes over K: ceil(L / (4 * chunk)) workgroups per
     // (layer, sequence, head, group of 128 query rows), whose waves share the sequence's 32-key tiles round-robin.  The
-    // `chunk` is chosen by an estimate of either pass's time in units of the 1.3 us that 1024 waves (one per SIMD: 256 CUs,
-    // one workgroup each) take for a tile each at the rate memory delivers:
+    // `chunk` is chosen by an estimate of either pass's time, in units of the time that 1024 waves (one per SIMD: 256 CUs,
+    // one workgroup each) take for a tile each at the rate memory delivers (1.3..1.6 us):
     //   tiles / 1024                      all waves busy
-    //   + what the last, partly filled round of the 512 resident workgroups wastes: per tile of its longest wave it takes
-    //     at least 0.75 (the arithmetic of a wave alone on its SIMD) with at most one workgroup per CU, 1.5 with two on
-    //     some, 1.0 when the few of a later round start as the CUs fall free
-    //   + the longest wave's lead over the average
+    //   + what the last, partly filled round of the 512 resident workgroups wastes: with x = workgroups / 256 in it, each
+    //     tile of its longest wave takes 0.38 + 0.62 x with at most one workgroup per CU, 0.58 + 0.75 x with two on some
+    //     (or where the workgroups start as the CUs fall free), against the x that full rates would give
+    //   + or at least the longest wave's lead over the average
     //   + 2 per further workgroup and CU  another start-up (query rows, normalisers), 2-4 us that its neighbour hides in part
     //   + 3 for the launch that merges the statistics of a sequence with more than 64 workgroups.
+    // One cold pass, 4 layers x 123490 keys, 128 query rows, 128 / 192 / 256 / 320 / 384 / 448 / 512 workgroups: 264.6 / 216.3
+    // / 192.8 / 233.6 / 218.1 / 208.1 / 200.7 us, 640 / 768 / 1024 / 1952: 220.3 / 219.3 / 195.8 / 198.6; 32 rows, 100000
+    // and 65536 keys run alike.  (With 0.75 for everything up to one per CU, 192 workgroups counted as good as 256: 4 x
+    // 123490 took 218 us in one pass and 394 in two, now 193 and 355; 4 layers x 60000 keys x 2 heads 53.5, now 49.)
     // One workgroup per CU wins where the sequences divide evenly -- 128K layer, keys per wave 512 / 1024: 48.7 + 44.9 /
     // 45.2 + 41.5 us; 8 layers x 64K, 1024 / 4096: 180 + 194 / 174 + 189; 32 x 8K, 1024 / 2048: 95.7 + 94.5 / 90.2 + 92.1
     // -- and a count just over a multiple of 512 loses: a paged batch of 8 with 528 workgroups in the second pass took 218
@@ -125,11 +129,11 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
             t_max = std::max(t_max, (n + w - 1) / w);
             wgs_max = std::max(wgs_max, g);
         }
-        const double N = (double)per_key * (double)wgs, rest = N - 512.0 * std::floor(N / 512.0);
-        const double t_avg = (double)tiles / (double)waves;
-        const double last = rest > 256.0 ? 1.5 : N > 512.0 ? 1.0 : 0.75;
-        double cost = (double)per_key * (double)tiles / 1024.0 + 2.0 * std::max(0.0, N / 256.0 - 1.0) + ((double)t_max - t_avg);
-        if (rest > 0.0) cost += std::max(0.0, last * (double)t_max - rest / 256.0 * t_avg);
+        const double N = (double)per_key * (double)wgs, x = (N - 512.0 * std::floor(N / 512.0)) / 256.0;
+        const double t_avg = (double)tiles / (double)waves, last = N <= 256.0 ? 0.38 + 0.62 * x : 0.58 + 0.75 * x;
+        double wasted = (double)t_max - t_avg;
+        if (x > 0.0) wasted = std::max(wasted, last * (double)t_max - x * t_avg);
+        double cost = (double)per_key * (double)tiles / 1024.0 + 2.0 * std::max(0.0, N / 256.0 - 1.0) + wasted;
         if (wgs_max > 64 && p.row_groups == 1) cost += 3.0;
         return cost;
     };
@@ -167,14 +171,12 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
     // workgroups, the first (whose workgroups each leave a set of statistics) with up to 64.  Whole calls, two tiles / one:
     // 2048 tokens with 2 KV heads 20.6 / 19.4 us, with 8 22.8 / 21.9; with 512 workgroups 28.3 / 29.7.
     int64_t best2 = best;
-    const int64_t split = best;
     if (best == 64 && p.row_groups == 1) {
         int64_t wgs = 0;
         for (int s = 0; s < sh->n_seq; ++s) wgs += wgs_of(sh->cu_seqlens[s + 1] - sh->cu_seqlens[s], kKeyTile);
         if (per_key * wgs <= 256) best2 = kKeyTile;
         if (per_key * wgs <= 64) best = kKeyTile;
     }
-    const int64_t ng_ws = cut(knobs().chunk_keys ? knobs().chunk_keys : split, p.tab.cu_chunk, p.tab.cu_cgrp);  // for the workspace
     const int64_t ng = cut(knobs().chunk_keys ? knobs().chunk_keys : best, p.tab.cu_chunk, p.tab.cu_cgrp);
     int64_t ng2 = cut(knobs().chunk_keys2 ? knobs().chunk_keys2 : best2, p.cu_chunk2, p.cu_cgrp2);
     if (p.row_groups > 1) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
@@ -212,19 +214,22 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out) {
 
     const size_t RP = (size_t)p.row_tiles * kRowTile;
     size_t off = 0;
-    // The statistics (one set of RP per first-pass workgroup) have room for `split`; with one tile per wave they run on into
-    // the pooled scores and the block heads behind them, which pooling writes when both passes are done.  That always fits:
-    // ceil(L / 128) - ceil(L / 256) <= (L + 255) / 256 sets of at most 1 KB against 4 L bytes of pooled scores and 1 KB of
-    // block heads.  So the finer split asks callers for no larger workspace.
-    p.off_stats = off;  off += align_up((size_t)p.n_layers * ng_ws * p.h_kv * RP * sizeof(float2));
-    p.off_pooled = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
-    p.off_idx = off;    off += align_up((size_t)p.n_layers * p.h_kv * p.TB * sizeof(int32_t));
-    p.off_seg = off;    off += align_up((size_t)p.n_layers * p.h_kv * p.n_seg * p.seg_head * sizeof(uint2));
-    p.off_seghdr = off; off += align_up((size_t)p.n_layers * p.h_kv * p.n_seg * sizeof(uint4));
+    // The statistics (one set of RP per first-pass workgroup) have room of their own for an eighth of the workgroups (a cut
+    // differs from the next build's by at most that, see the candidates) and run on into what pooling and selection write when
+    // both passes are done, so that a finer cut asks callers for no larger workspace than a coarser one did.  What does not fit
+    // there either (many query rows, the smallest calls) gets room too.
+    const size_t stats = (size_t)p.n_layers * ng * p.h_kv * RP * sizeof(float2), n_heads = (size_t)p.n_layers * p.h_kv;
+    const size_t pooled = align_up(n_heads * p.T * sizeof(float)), idx = align_up(n_heads * p.TB * sizeof(int32_t));
+    const size_t seg = align_up(n_heads * p.n_seg * p.seg_head * sizeof(uint2)), seghdr = align_up(n_heads * p.n_seg * sizeof(uint4));
+    const size_t later = pooled + idx + seg + seghdr;
+    p.off_stats = off;  off += align_up(std::max(stats / 8, stats > later ? stats - later : 0));
+    p.off_pooled = off; off += pooled;
+    p.off_idx = off;    off += idx;
+    p.off_seg = off;    off += seg;
+    p.off_seghdr = off; off += seghdr;
     p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
     p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
     p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
-    if (p.off_stats + (size_t)p.n_layers * ng * p.h_kv * RP * sizeof(float2) > p.off_aug) return JQ_ERR_UNSUPPORTED;  // never
     p.ws_bytes = off;
     *out = p;
     return JQ_OK;
