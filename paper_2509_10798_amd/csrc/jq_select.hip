@@ -800,13 +800,20 @@ static SelectArgs select_args(const Plan& p, const float* pooled, uint32_t* hist
     return a;
 }
 
-// Slices per problem: enough workgroups to spread the emission (and the gather) over the chip, each with at least 64
-// output slots.
-static unsigned slices_of(const Plan& p, int64_t target) {
+// Slices per problem: enough workgroups to spread the emission (and the gather) over the chip's 256 CUs, each with at least
+// 64 output slots.  Where only one workgroup fits a CU (`alone`), some more than 256 of them are a second round of the whole
+// selection: then as many as fit in one, unless that leaves a slice more than 1000 rows to gather -- whole calls, rounded up /
+// down: 30000 + 8 x 9000 tokens, 256 kept 124.5 / 108.1 us, 3000 kept 135.9 / 129.3; 3 x 20000, 2048 kept 96.2 / 79.3; but
+// 6 x 24000 + 6 x 3000 (96 problems), 1024 kept 161.2 / 154.4, 2048 kept 163.4 / 169.8.
+static unsigned slices_of(const Plan& p, bool alone) {
     const int64_t n_prob = (int64_t)p.n_layers * p.n_seq * p.h_kv;
-    int64_t min_budget = INT32_MAX;
-    for (int s = 0; s < p.n_seq; ++s) min_budget = min(min_budget, (int64_t)(p.tab.cu_bud[s + 1] - p.tab.cu_bud[s]));
-    int64_t slices = (target + n_prob - 1) / n_prob;
+    int64_t min_budget = INT32_MAX, max_budget = 0;
+    for (int s = 0; s < p.n_seq; ++s) {
+        min_budget = min(min_budget, (int64_t)(p.tab.cu_bud[s + 1] - p.tab.cu_bud[s]));
+        max_budget = max(max_budget, (int64_t)(p.tab.cu_bud[s + 1] - p.tab.cu_bud[s]));
+    }
+    int64_t slices = (256 + n_prob - 1) / n_prob;
+    if (alone && max_budget <= 1000 * (256 / n_prob)) slices = 256 / n_prob;
     slices = min(slices, (min_budget + 63) / 64);
     return (unsigned)max((int64_t)1, min(slices, (int64_t)64));
 }
@@ -829,7 +836,7 @@ static hipError_t launch_small_k(const Plan& p, const PoolSelectArgs& a, hipStre
         if (e != hipSuccess) return e;
     }
     const unsigned n_prob = (unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv);
-    return launch_kernel(jq_pool_select_kernel<THREADS, VPT, K>, dim3(n_prob, slices_of(p, 256)), dim3(THREADS), lds_bytes, st, nullptr, -1, a);
+    return launch_kernel(jq_pool_select_kernel<THREADS, VPT, K>, dim3(n_prob, slices_of(p, lds_bytes > kMaxLds / 2)), dim3(THREADS), lds_bytes, st, nullptr, -1, a);
 }
 template <int K>
 static hipError_t launch_small(const Plan& p, const PoolSelectArgs& a, hipStream_t st) {
@@ -871,7 +878,7 @@ hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, cha
         const hipError_t e = allow_large_lds((const void*)jq_select_finalize_kernel, done);
         if (e != hipSuccess) return e;
     }
-    const unsigned slices = slices_of(p, 256);
+    const unsigned slices = slices_of(p, false);
     if (gathered) *gathered = K_out != nullptr || stage != nullptr;
     return launch_kernel(jq_select_finalize_kernel, dim3(n_prob, slices), dim3(kFinThreads), lds_bytes, st, p.marks,
                          kTrFinalize, a, words_cap, qual_cap);

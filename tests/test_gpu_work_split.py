@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
     (1, [32768], 32, 8),                     # 256 workgroups, eight tiles per wave
     (5, [9999], 16, 8),                      # an odd length over five layers: uneven waves, a partial last tile
     (3, [20011, 31, 4099, 1, 12345], 8, 8),  # ragged, with sequences of less than a tile and of less than a workgroup's waves
+    (2, [9999, 70], 8, 8),                   # one query-row tile
     (16, [4097], 8, 2),                      # one key past a whole number of tiles
     (2, [54579], 16, 8),                     # 256 workgroups, 27 tiles in some waves and 26 in others
     (2, [65536], 8, 1),                      # one KV head: more than 64 workgroups per sequence (merged by a launch of their own)
