@@ -239,12 +239,32 @@ hipError_t launch_hist(const Plan& p, const float* pooled, uint32_t* hist, char*
 bool select_fast_path(const Plan& p);
 // Calls whose sequences all have at most kSmallMax positions: pooling (unless `pool` is false: `in` then holds the values
 // to select by), selection and gather in ONE kernel, which needs no histogram and no lists.  `out` (nullable) takes the
-// pooled scores; the other arguments as launch_select.  Why the line lies at 32768: the staged scores of a longer sequence
-// do not fit a workgroup's LDS, and there the two ways meet -- whole eviction calls of one layer with 8 KV heads and 256
-// kept rows, one kernel against two: 22.4 / 34.0 us at 2048 tokens, 29.2 / 36.3 at 8192, 36.7 / 41.7 at 16384, 50.3 / 50.6
-// at 32768 (every slice repeats the problem's selection, whose cost grows with the length).
+// pooled scores; the other arguments as launch_select.  The scores of a longer sequence do not fit a workgroup's LDS.
+// A selection alone always takes it (32768 values, 512 kept: 14.9 us against 35.6 for the three launches of the other way).
+// An eviction weighs it against the pooling kernel followed by the selection's (evict_tail_small): every slice of a problem
+// repeats pooling and selection in its one workgroup, which costs more the longer the sequence, while the lists of the other
+// way cost more the more is kept.  Whole calls of one layer with 8 KV heads, one kernel / two, in us:
+//   kept:          256          512          1024         2048         3072
+//    2048     22.4 / 34.0
+//   12000     32.9 / 36.2               33.0 / 37.3
+//   16384     35.1 / 38.7               35.6 / 40.0
+//   20000     43.1 / 41.4  42.8 / 42.0  43.2 / 43.4  44.5 / 45.7
+//   28000     49.0 / 48.0  49.2 / 48.5  49.4 / 49.6  50.8 / 52.2  51.0 / 55.8
+//   32768     51.7 / 51.0  51.4 / 51.3  51.7 / 52.5  52.9 / 55.0  53.5 / 58.1
+// 4 layers: 20000, 256 kept 81.5 / 82.2; 32768 110.4 / 111.8, 3072 kept 125 / 132.  Above 16384 positions one workgroup fills a
+// CU's LDS, and more than 256 problems take turns: 32768 + 63 x 300 (512 problems) 111.4 / 106.7, 4 layers of 32768 + 31 x
+// 500 272 / 257, 36 x 18000 598 / 585, 20000 + 35 x 500 93.1 / 84.3 -- two kernels then, except without pooling (36 x 18000
+// 591 / 621).  Up to 16384 it wins there too (48 x 9000 435 / 447, 40 x 16000 569 / 579).
+// Widths 1, 5 and 7 are compiled in; any other is summed tap by tap out of LDS, for 4 to 32 positions per thread:
+//   width:        3            9            13           31           63           129
+//    2048     22.3 / 32.3  23.4 / 32.3  24.1 / 32.9  27.5 / 33.8  35.0 / 37.3  48.3 / 68.9
+//    4096     24.3 / 33.0  26.5 / 33.3  27.9 / 34.1  34.8 / 35.1  48.5 / 38.7  73.7 / 70.9
+//    8192     30.4 / 34.8  34.8 / 34.8  37.8 / 35.4  51.4 / 36.7  77.7 / 40.2   127 / 76.4
+//   16384     37.6 / 39.6  42.4 / 39.9  45.8 / 40.6  61.1 / 41.5  90.4 / 44.3   147 / 88.0
+//   32768     56.9 / 52.8  67.3 / 52.9  74.2 / 53.6   104 / 54.7   163 / 56.9   277 / 103
 constexpr int kSmallMax = 32768;
 bool select_small(const Plan& p);
+bool evict_tail_small(const Plan& p);
 hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool pool, char* ws, int32_t* idx, hipStream_t st,
                               const void* K = nullptr, const void* V = nullptr, void* K_out = nullptr, void* V_out = nullptr,
                               void* stage = nullptr, const int32_t* pos_in = nullptr, int32_t* pos_out = nullptr,

@@ -826,6 +826,14 @@ static int longest_sequence(const Plan& p) {
 
 bool select_small(const Plan& p) { return longest_sequence(p) <= kSmallMax; }
 
+bool evict_tail_small(const Plan& p) {
+    const int L = longest_sequence(p);
+    if (L > kSmallMax) return false;
+    if (p.pool_k != 1 && p.pool_k != 5 && p.pool_k != 7)
+        return L <= 2048 || p.pool_k <= (L <= 4096 ? 31 : L <= 8192 ? 9 : L <= 16384 ? 3 : 0);
+    return p.pool_k == 1 || L <= 16384 || (int64_t)p.n_layers * p.n_seq * p.h_kv <= 256;
+}
+
 template <int THREADS, int VPT, int K>
 static hipError_t launch_small_k(const Plan& p, const PoolSelectArgs& a, hipStream_t st) {
     static std::atomic<uint64_t> done{0};
@@ -845,7 +853,8 @@ static hipError_t launch_small(const Plan& p, const PoolSelectArgs& a, hipStream
     if (L <= 512 * 8) return launch_small_k<512, 8, K>(p, a, st);
     if (L <= 512 * 16) return launch_small_k<512, 16, K>(p, a, st);
     if (L <= 1024 * 16) return launch_small_k<1024, 16, K>(p, a, st);
-    return launch_small_k<1024, 32, K>(p, a, st);
+    if constexpr (K == 0) return hipErrorInvalidValue;  // no caller pools so long a sequence here
+    else return launch_small_k<1024, 32, K>(p, a, st);
 }
 
 hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool pool, char* ws, int32_t* idx, hipStream_t st, const void* K,

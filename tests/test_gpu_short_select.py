@@ -36,6 +36,9 @@ def test_select_is_exact_at_the_edges(L, kind):
 @pytest.mark.parametrize("seq_lens,budgets,pool_k,kf,kl", [
     ([2048], [256], 7, 0, 0), ([2049, 5, 2048], [100, 5, 64], 7, 2, 1), ([4097], [3000], 5, 0, 0), ([4097], [70], 13, 4, 32),
     ([9000, 31], [1000, 1], 1, 0, 0), ([700], [200], 1399, 0, 0), ([16385], [513], 7, 4, 8), ([32768, 100], [2048, 50], 5, 0, 16),
+    ([2048], [300], 63, 0, 0), ([4096], [300], 31, 3, 0), ([4096, 9], [300, 2], 63, 0, 2), ([8192], [300], 9, 0, 0), ([8193], [700], 3, 0, 0),
+    ([8193], [700], 13, 0, 0), ([16384], [400], 3, 0, 5), ([16385], [400], 3, 0, 5), ([16385, 70], [400, 7], 63, 2, 0), ([32768], [1100], 13, 0, 0),
+    ([16400] + [40] * 64, [300] + [3] * 64, 7, 0, 0),      # more than 256 problems above 16384 positions
     ([16400] + [5000] * 8, [1500] + [600] * 8, 7, 0, 0)])  # 36 problems: seven slices each, not eight
 def test_evict_equals_the_two_kernel_path_bit_for_bit(seq_lens, budgets, pool_k, kf, kl):
     torch = torch_()
