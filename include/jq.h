@@ -354,9 +354,10 @@ int jq_evict_paged_inplace(const jq_shape* shape, const jq_pages* pages, const j
  * (when a stage needs several launches the last one is reported; sequences too long
  * for the selection's fast path take a streaming selection, reported in slot 3, and an
  * untimed separate gather; sequences long enough to leave hundreds of partial
- * statistics get an untimed merge launch between slots 0 and 1; sequences of up to 32768
- * tokens, which jq_evict pools inside the selection's kernel, take the two kernels of longer
- * ones here).  Results are those of jq_evict. */
+ * statistics get an untimed merge launch between slots 0 and 1; short sequences, up to
+ * 32768 tokens, are pooled by the selection's kernel, which slot 3 then reports, and slot 2
+ * is an empty interval of a few microseconds in front of it).  The kernels are those of
+ * jq_evict, and so are the results. */
 #define JQ_TRACE_MARKS 8
 int jq_evict_traced(const jq_shape* shape, const void* Q, const void* K, const void* V,
                     void* K_out, void* V_out, int32_t* idx_out, float* scores_out,

@@ -246,7 +246,8 @@ def evict(shape: Shape, Q, K, V, K_out=None, V_out=None, idx_out=None, scores_ou
 
     `marks`: optional list of TRACE_MARKS torch.cuda.Event(enable_timing=True) objects that have been
     recorded once (so that their handles exist); events 2i / 2i+1 receive the start / stop time of
-    kernel TRACE_KERNELS[i]."""
+    kernel TRACE_KERNELS[i] (short sequences: the last one's is the kernel that also pools, and the pooling
+    kernel's hold an empty interval)."""
     import torch
     dev = K.device
     if K_out is None:

@@ -445,7 +445,7 @@ static hipError_t evict_launches(const Plan& p, const void* Q, const void* K, co
     int32_t* idx = idx_out ? idx_out : (int32_t*)(w + p.off_idx);
     hipError_t e;
     bool gathered = true;  // the selection's last kernel gathers (or, in place, stages) the kept rows itself unless it had to stream
-    if (evict_tail_small(p) && !p.marks) {  // (a traced call reports pooling and selection apart: it takes the two kernels)
+    if (evict_tail_small(p)) {
         e = launch_score(p, Q, K, raw, w, st, nullptr, 0, lse, k_tail);
         if (e == hipSuccess) e = launch_pool_select(p, raw, scores_out, true, w, idx, st, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
     } else {

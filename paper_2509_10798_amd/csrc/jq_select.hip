@@ -844,7 +844,7 @@ static hipError_t launch_small_k(const Plan& p, const PoolSelectArgs& a, hipStre
         if (e != hipSuccess) return e;
     }
     const unsigned n_prob = (unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv);
-    return launch_kernel(jq_pool_select_kernel<THREADS, VPT, K>, dim3(n_prob, slices_of(p, lds_bytes > kMaxLds / 2)), dim3(THREADS), lds_bytes, st, nullptr, -1, a);
+    return launch_kernel(jq_pool_select_kernel<THREADS, VPT, K>, dim3(n_prob, slices_of(p, lds_bytes > kMaxLds / 2)), dim3(THREADS), lds_bytes, st, p.marks, kTrFinalize, a);
 }
 template <int K>
 static hipError_t launch_small(const Plan& p, const PoolSelectArgs& a, hipStream_t st) {
@@ -863,6 +863,11 @@ hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool p
     PoolSelectArgs a;
     a.in = in; a.out = out;
     a.pool_k = p.pool_k; a.inv_k = 1.0f / (float)p.pool_k;
+    if (p.marks)  // no pooling kernel of its own: an interval with nothing in it
+        for (int i = 0; i < 2; ++i) {
+            const hipError_t e = hipEventRecord((hipEvent_t)p.marks[2 * kTrPool + i], st);
+            if (e != hipSuccess) return e;
+        }
     a.sel = select_args(p, nullptr, (uint32_t*)(ws + p.off_hist), ws, idx, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
     if (!pool || p.pool_k == 1) return launch_small<1>(p, a, st);
     if (p.pool_k == 7) return launch_small<7>(p, a, st);

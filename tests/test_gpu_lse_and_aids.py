@@ -112,6 +112,32 @@ def test_traced_evict_equals_evict_and_times_every_kernel():
         assert 0.0 < ms < 50.0, (name, ms)
 
 
+@pytest.mark.parametrize("L,pool_k", [(4096, 7), (20000, 7), (20000, 31), (40000, 7)])
+def test_traced_evict_times_the_kernels_that_evict_runs(L, pool_k):
+    # short sequences in one kernel, at a width that is not compiled in and above 32768 tokens in two
+    torch = torch_()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    Q = torch.randn((1, 1, 8, 8, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((1, L, 2, 128), generator=gen, device="cuda").bfloat16()
+    sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=8, h_q=8, h_kv=2, pool_k=pool_k, budgets=[256])
+    marks = [torch.cuda.Event(enable_timing=True) for _ in range(jq.TRACE_MARKS)]
+    for ev in marks:
+        ev.record()
+    plain = jq.evict(sh, Q, K, K)
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        out = jq.evict(sh, Q, K, K, marks=marks)
+        torch.cuda.synchronize()
+    ran = [e.name for e in prof.events() if "jq_" in e.name]  # (the profiler may miss one)
+    for x, y in zip(out, plain):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+    assert ran
+    other = ("jq_pool_kernel", "jq_select_finalize_kernel") if L <= 32768 and pool_k == 7 else ("jq_pool_select_kernel",)
+    assert not [n for n in ran if any(o in n for o in other)]
+    assert all(0.0 < marks[2 * j].elapsed_time(marks[2 * j + 1]) < 50.0 for j in range(len(jq.TRACE_KERNELS)))
+
+
 def test_copy_probe_copies():
     torch = torch_()
     src = torch.randint(0, 255, (1 << 20,), dtype=torch.uint8, device="cuda")

@@ -1,6 +1,6 @@
 """Sequences of up to 32768 tokens: pooling, selection and gather in one kernel, at the edges of its instances (runs of
 4 / 8 / 16 / 32 positions per thread, 512 and 1024 threads), against the oracle and against the two kernels that longer
-sequences (and traced calls) take, whose results must be the same bits."""
+sequences take, whose results must be the same bits."""
 import numpy as np
 import pytest
 
@@ -40,19 +40,24 @@ def test_select_is_exact_at_the_edges(L, kind):
     ([8193], [700], 13, 0, 0), ([16384], [400], 3, 0, 5), ([16385], [400], 3, 0, 5), ([16385, 70], [400, 7], 63, 2, 0), ([32768], [1100], 13, 0, 0),
     ([16400] + [40] * 64, [300] + [3] * 64, 7, 0, 0),      # more than 256 problems above 16384 positions
     ([16400] + [5000] * 8, [1500] + [600] * 8, 7, 0, 0)])  # 36 problems: seven slices each, not eight
-def test_evict_equals_the_two_kernel_path_bit_for_bit(seq_lens, budgets, pool_k, kf, kl):
+def test_evict_equals_the_two_kernel_path_bit_for_bit(knobs, seq_lens, budgets, pool_k, kf, kl):
+    # a sequence of 32769 tokens in the same batch sends the others through the two kernels; one number of keys per wave for
+    # both calls, so that their scores are the same bits
     torch = torch_()
     print("short evict", seq_lens, budgets, pool_k, kf, kl, flush=True)
+    knobs(JQ_CHUNK_KEYS="1024")
     rng = np.random.default_rng(5)
     T, ns = sum(seq_lens), len(seq_lens)
     Q = to_dev_bf16(f32_to_bf16_bits(rng.standard_normal((2, ns, 8, 8, 128)).astype(np.float32)))
     K = to_dev_bf16(f32_to_bf16_bits(rng.standard_normal((2, T, 2, 128)).astype(np.float32)))
     V = to_dev_bf16(f32_to_bf16_bits(rng.standard_normal((2, T, 2, 128)).astype(np.float32)))
     sh = jq.Shape(n_layers=2, seq_lens=seq_lens, n_q=8, h_q=8, h_kv=2, pool_k=pool_k, budgets=budgets, keep_first=kf, keep_last=kl)
-    marks = [torch.cuda.Event(enable_timing=True) for _ in range(jq.TRACE_MARKS)]
-    for ev in marks:
-        ev.record()
-    want = jq.evict(sh, Q, K, V, marks=marks)
+    long = jq.Shape(n_layers=2, seq_lens=seq_lens + [32769], n_q=8, h_q=8, h_kv=2, pool_k=pool_k, budgets=budgets + [max(1, kf + kl)], keep_first=kf, keep_last=kl)
+    more = torch.randn((2, 32769, 2, 128), device="cuda").bfloat16()
+    wide = jq.evict(long, torch.cat([Q, Q[:, :1]], dim=1), torch.cat([K, more], dim=1), torch.cat([V, more], dim=1))
+    TB = sum(budgets)
+    want = wide[0][:, :TB], wide[1][:, :TB], wide[2][:, :, :TB], wide[3][:, :, :T]
+    want = [x.contiguous() for x in want]
     got = jq.evict(sh, Q, K, V)
     bare = jq.evict(sh, Q, K, V, want_idx=False, want_scores=False)  # pooled scores are not stored then
     Ki, Vi = K.clone(), V.clone()
@@ -61,5 +66,4 @@ def test_evict_equals_the_two_kernel_path_bit_for_bit(seq_lens, budgets, pool_k,
     for a, b in zip(got, want):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     assert torch.equal(bare[0].view(torch.int16), want[0].view(torch.int16)) and torch.equal(bare[1].view(torch.int16), want[1].view(torch.int16))
-    TB = sum(budgets)
     assert torch.equal(Ki[:, :TB].view(torch.int16), want[0].view(torch.int16)) and torch.equal(Vi[:, :TB].view(torch.int16), want[1].view(torch.int16))
