@@ -1002,7 +1002,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     // ---- query-row tiles: global -> LDS, laid out as key tiles are (see fetch_tile) ----
     const char* qbase = (const char*)a.Q + (((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q) * a.h_q + (int64_t)w.g * a.group) * kHeadDim * 2;
     const int n_rt = (a.rows + kRowTile - 1) / kRowTile;
-    const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...
+    const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...: at least
+                                                                     // one (the kernel runs with more than kScoreWaves)
     const uint2* aug = a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + (lane & 31);
     const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
     // With a power-of-two group of up to 32 heads a tile's rows lie where a key tile's would: a lane part that never changes
@@ -1045,11 +1046,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         const uint32_t off = tile_offset<PAGED>(ks, t, tile_page<PAGED>(ks, t));
         fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, w.L - t * kKeyTile), lane);
     }
-    uint2 aug_next = make_uint2(0u, 0u);
-    if (n_mine > 0) {  // uniform; at least wave 0 has tiles
-        fetch_rows(0);
-        aug_next = aug[wv * kRowTile];
-    }
+    fetch_rows(0);
+    uint2 aug_next = aug[wv * kRowTile];
     wait_tile_landed();
     bare_barrier();
     bf16x8 kf[kMaxRowTiles][8];
@@ -1071,41 +1069,39 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         if (half == 0) { av[0] = t.x; av[1] = t.y; }
         return as_bf16x8(av);
     };
-    if (n_mine > 0) {
-        bf16x8 qf[8];
-        lds_get_frags(slots, qf, lane);
-        bf16x8 qaug = aug_of(aug_next);
-        wait_frags_read();
-        if (n_mine > 1) {
-            fetch_rows(1);
-            aug_next = aug[(wv + kScoreWaves) * kRowTile];
-        }
-        f32x16 acc = score_chain(qf, qaug, kf[0], ones);
-        for (int k = 0; k < n_mine; ++k) {
+    bf16x8 qf[8];
+    lds_get_frags(slots, qf, lane);
+    bf16x8 qaug = aug_of(aug_next);
+    wait_frags_read();
+    if (n_mine > 1) {
+        fetch_rows(1);
+        aug_next = aug[(wv + kScoreWaves) * kRowTile];
+    }
+    f32x16 acc = score_chain(qf, qaug, kf[0], ones);
+    for (int k = 0; k < n_mine; ++k) {
 #pragma unroll
-            for (int kt = 0; kt < kMaxRowTiles; ++kt) {
-                const bool reads = kt == kMaxRowTiles - 2;
-                const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
-                if (reads) wait_tile_landed();
-                const uint32_t next_at = frag_addr(next_slot, lane);
-                f32x16 nxt = zero_acc();
-                sum[kt] += exp2_sum_stage<9>(
-                    [&](int i) __attribute__((always_inline)) {
-                        nxt = i < 8 ? mfma_bf16(qf[i & 7], kf[(kt + 1) % kMaxRowTiles][i & 7], nxt) : mfma_bf16(qaug, ones, nxt);
-                        pin(nxt);
-                        if (reads && i < 8) qf[i & 7] = lds_get_frag(next_at, i);  // its last use was this MFMA
-                    },
-                    [&](int v) __attribute__((always_inline)) { return acc[v] * c; });
-                if (reads) {
-                    wait_frags_read();
-                    qaug = aug_of(aug_next);
-                    if (k + 2 < n_mine) {
-                        fetch_rows(k + 2);
-                        aug_next = aug[(wv + (k + 2) * kScoreWaves) * kRowTile];
-                    }
+        for (int kt = 0; kt < kMaxRowTiles; ++kt) {
+            const bool reads = kt == kMaxRowTiles - 2;
+            const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
+            if (reads) wait_tile_landed();
+            const uint32_t next_at = frag_addr(next_slot, lane);
+            f32x16 nxt = zero_acc();
+            sum[kt] += exp2_sum_stage<9>(
+                [&](int i) __attribute__((always_inline)) {
+                    nxt = i < 8 ? mfma_bf16(qf[i & 7], kf[(kt + 1) % kMaxRowTiles][i & 7], nxt) : mfma_bf16(qaug, ones, nxt);
+                    pin(nxt);
+                    if (reads && i < 8) qf[i & 7] = lds_get_frag(next_at, i);  // its last use was this MFMA
+                },
+                [&](int v) __attribute__((always_inline)) { return acc[v] * c; });
+            if (reads) {
+                wait_frags_read();
+                qaug = aug_of(aug_next);
+                if (k + 2 < n_mine) {
+                    fetch_rows(k + 2);
+                    aug_next = aug[(wv + (k + 2) * kScoreWaves) * kRowTile];
                 }
-                acc = nxt;
             }
+            acc = nxt;
         }
     }
 #pragma unroll

@@ -17,7 +17,7 @@
 // order.  Several workgroups ("slices") work on one problem: each repeats the (cheap, cache-resident)
 // resolution and emits its own range of output slots; in the fused eviction call it also gathers the K/V
 // rows of those slots, so the pruned cache needs no further kernel.
-// Short sequences (every one of the call up to kSmallMax tokens): pooling, selection and gather in one kernel.
+// Short sequences (up to kSmallMax tokens; evict_tail_small says which calls): pooling, selection and gather in one kernel.
 // General path (very long sequences): one workgroup per problem streams the row three times.
 #include <atomic>
 
