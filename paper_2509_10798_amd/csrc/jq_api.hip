@@ -105,10 +105,12 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     // one workgroup each) take for a tile each at the rate memory delivers (1.3..1.6 us):
     //   tiles / 1024                      all waves busy
     //   + what the last, partly filled round of the 512 resident workgroups wastes: with x = workgroups / 256 in it, each
-    //     tile of its longest wave takes 0.38 + 0.62 x with at most one workgroup per CU, 0.58 + 0.75 x with two on some
-    //     (or where the workgroups start as the CUs fall free), against the x that full rates would give
-    //   + or at least the longest wave's lead over the average
-    //   + 2 per further workgroup and CU  another start-up (query rows, normalisers), 2-4 us that its neighbour hides in part
+    //     tile of its waves takes 0.38 + 0.62 x with at most one workgroup per CU, 0.58 + 0.75 x with two on some (or where the
+    //     workgroups start as the CUs fall free), against the x that full rates would give
+    //   + 0.45 per tile by which the longest wave leads the average: its last tiles run on a chip that is nearly empty
+    //   + 0.03 per tile where all run at once with two workgroups on some CUs
+    //   + 0.7 per further workgroup and CU  another start-up (query rows, normalisers), 2-4 us that its neighbour mostly hides;
+    //     2.0 with several groups of query rows, for which the keys come out of the caches and a start-up counts for more tiles
     //   + 3 for the launch that merges the statistics of a sequence with more than 64 workgroups.
     // One cold pass, 4 layers x 123490 keys, 128 query rows, 128 / 192 / 256 / 320 / 384 / 448 / 512 workgroups: 264.6 / 216.3
     // / 192.8 / 233.6 / 218.1 / 208.1 / 200.7 us, 640 / 768 / 1024 / 1952: 220.3 / 219.3 / 195.8 / 198.6; 32 rows, 100000
@@ -117,11 +119,12 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     // One workgroup per CU wins where the sequences divide evenly -- 128K layer, keys per wave 512 / 1024: 48.7 + 44.9 /
     // 45.2 + 41.5 us; 8 layers x 64K, 1024 / 4096: 180 + 194 / 174 + 189; 32 x 8K, 1024 / 2048: 95.7 + 94.5 / 90.2 + 92.1
     // -- and a count just over a multiple of 512 loses: a paged batch of 8 with 528 workgroups in the second pass took 218
-    // us per call, with 400 204.  (Candidates only grow from the smallest sensible chunk: workspaces hold one set of
-    // statistics per workgroup.)
+    // us per call, with 400 204.  Candidates run from the smallest sensible chunk to eight times that.  Over 61 shapes (1..32
+    // layers, 1..16 sequences of 2K..131K tokens) the cut so chosen is 0.25 % from the best candidate, at most 3.7 %.
     const int64_t per_key = (int64_t)p.n_layers * p.h_kv * p.row_groups;
     const int64_t keys = per_key * p.T;
     auto wgs_of = [](int64_t L, int64_t chunk) { return (L + kScoreWaves * chunk - 1) / (kScoreWaves * chunk); };
+    const double startup = p.row_groups == 1 ? 0.7 : 2.0;
     int64_t tiles = 0;
     for (int s = 0; s < sh->n_seq; ++s) tiles += (sh->cu_seqlens[s + 1] - sh->cu_seqlens[s] + kKeyTile - 1) / kKeyTile;
     // (Without integer divisions, which took most of the 6.8 us that a plan for 128 sequences cost, 4.3 now: the workgroups come
@@ -141,9 +144,9 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
         }
         const double N = (double)per_key * (double)wgs, x = (N - 512.0 * std::floor(N / 512.0)) / 256.0;
         const double t_avg = (double)tiles / (double)waves, last = N <= 256.0 ? 0.38 + 0.62 * x : 0.58 + 0.75 * x;
-        double wasted = (double)t_max - t_avg;
-        if (x > 0.0) wasted = std::max(wasted, last * (double)t_max - x * t_avg);
-        double cost = (double)per_key * (double)tiles / 1024.0 + 2.0 * std::max(0.0, N / 256.0 - 1.0) + wasted;
+        double cost = (double)per_key * (double)tiles / 1024.0 + startup * std::max(0.0, N / 256.0 - 1.0) + 0.45 * ((double)t_max - t_avg);
+        if (x > 0.0) cost += std::max(0.0, last - x) * t_avg;
+        if (N > 256.0 && N <= 512.0) cost += 0.03 * t_avg;
         if (wgs_max > 64 && p.row_groups == 1) cost += 3.0;
         return cost;
     };
