@@ -21,7 +21,7 @@
  *   jq_score_paged, jq_evict_paged  the same on a paged cache (pools + block table)
  *   jq_hit_rate     critical-KV hit rate between two kept sets (Eq. 6)
  *   jq_map_mse      forward value of the training objective (Eq. 5) from two score maps
- *   jq_map_mse_fused  the same from the two query sets, the second map never stored
+ *   jq_map_mse_fused  the same from the two query sets, neither map ever stored
  *
  * Conventions common to every entry point
  * ---------------------------------------
@@ -220,9 +220,9 @@ int jq_map_mse(const jq_shape* shape, const float* scores_a, float rows_a, const
 
 /* The same value (Section 4.2: the maps of Eq. 3 and Eq. 4, the loss of Eq. 5) straight from the two query sets,
  * without handing the maps to the caller: Q_a [n_layers, n_seq, shape->n_q, h_q, d] are the soft tokens' queries,
- * Q_b [n_layers, n_seq, n_q_b, h_q, d] the response tokens' (any n_q_b >= 1; rows beyond 128 per KV head take
- * further statistics sweeps over K), K the prompt's keys as in jq_score.  The soft tokens' map is computed first; the
- * launch that completes the response's map does not store it but accumulates
+ * Q_b [n_layers, n_seq, n_q_b, h_q, d] the response tokens' (any n_q_b >= 1; each 128 rows per KV head of both sets
+ * together take a statistics sweep over K), K the prompt's keys as in jq_score.  Both maps form in the same launch,
+ * which stores neither but accumulates
  *   ( map_a[t] / (n_q * G) - map_b[t] / (n_q_b * G) )^2,  G = h_q / h_kv,
  * per workgroup in fp64, and a last small launch adds the workgroups' sums in a fixed order:
  *   mse[l,s,g] as in jq_map_mse, [n_layers, n_seq, h_kv] fp32 (DEVICE).

@@ -443,7 +443,7 @@ def map_mse(shape: Shape, scores_a, rows_a: float, scores_b, rows_b: float, mse=
 
 def map_mse_fused(shape: Shape, Q_a, Q_b, K, mse=None, ws=None, stream=None):
     """Eq. 3-5 forward from the two query sets (Q_a [.., shape.n_q, h_q, d] soft tokens, Q_b [.., n_q_b, h_q, d] response
-    tokens): the second map is compared with the first inside the launch that completes it and never stored."""
+    tokens): both maps form in one launch, which compares them and stores neither."""
     import torch
     n_q_b = int(Q_b.shape[2])
     if mse is None:

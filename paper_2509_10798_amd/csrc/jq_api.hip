@@ -43,8 +43,8 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 
 // Validates `shape` and derives the plan.  `need_budgets`: the entry point uses budgets.
 // (`sweeps` false: a call that neither passes over K nor shares a workspace with one that does; how the sequences are cut
-// is of no account then and not looked for.)
-int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = true) {
+// is of no account then and not looked for.)  `n_q2`: tokens of a second query set over the same keys, or 0.
+int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = true, int32_t n_q2 = 0) {
     if (!sh || !sh->cu_seqlens) return JQ_ERR_NULL;
     if (need_budgets && !sh->budgets) return JQ_ERR_NULL;
     if (sh->n_layers < 1 || sh->n_seq < 1 || sh->n_q < 1 || sh->h_q < 1 || sh->h_kv < 1 || sh->d < 1) return JQ_ERR_SHAPE;
@@ -76,8 +76,13 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     const int64_t rows = (int64_t)p.n_q * p.group;
     if (rows > (1 << 20)) return JQ_ERR_UNSUPPORTED;
     p.rows = (int32_t)rows;
-    p.row_tiles = (p.rows + kRowTile - 1) / kRowTile;
+    p.row_tiles1 = (p.rows + kRowTile - 1) / kRowTile;
+    if ((int64_t)n_q2 * p.group > (1 << 20)) return JQ_ERR_UNSUPPORTED;
+    p.n_q2 = n_q2;
+    p.rows2 = n_q2 * p.group;
+    p.row_tiles = p.row_tiles1 + (p.rows2 + kRowTile - 1) / kRowTile;
     p.row_groups = (p.row_tiles + kMaxRowTiles - 1) / kMaxRowTiles;
+    p.by_rows = p.row_groups > 1 || n_q2 > 0;
     p.T = sh->cu_seqlens[sh->n_seq];
     p.tab.n_seq = sh->n_seq;
     int64_t tb = 0;
@@ -192,7 +197,7 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     }
     const int64_t ng = cut(knobs().chunk_keys ? knobs().chunk_keys : best, p.tab.cu_chunk, p.tab.cu_cgrp);
     int64_t ng2 = cut(knobs().chunk_keys2 ? knobs().chunk_keys2 : best2, p.cu_chunk2, p.cu_cgrp2);
-    if (p.row_groups > 1) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
+    if (p.by_rows) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
         ng2 = 0;
         for (int s = 0; s < sh->n_seq; ++s) {
             const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
@@ -242,7 +247,7 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     p.off_seghdr = off; off += seghdr;
     p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
     p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
-    p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
+    p.off_scores = off; off += n_q2 ? 0 : align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));  // two sets: no map is stored
     p.ws_bytes = off;
     *out = p;
     return JQ_OK;
@@ -724,59 +729,48 @@ int jq_map_mse(const jq_shape* shape, const float* scores_a, float rows_a, const
     return launch_status(launch_map_mse(p, scores_a, rows_a, scores_b, rows_b, mse, (hipStream_t)stream));
 }
 
-// Layout of the fused forward's workspace: the plan of either query set in full, then the partial sums.
-static int mse_fused_plans(const jq_shape* shape, int32_t n_q_b, Plan* pa, Plan* pb, size_t* off_b, size_t* off_part, size_t* total) {
-    int rc = make_plan(shape, false, pa);
+// The fused forward: one plan whose rows are those of both query sets.  The partial sums (8 bytes per workgroup of 128 keys, or
+// a sequence's end) lie in the pooled scores and positions (4 L + 4 bytes per sequence and head at least), where the statistics
+// that may have run on into them have been merged by then.
+static int mse_fused_plan(const jq_shape* shape, int32_t n_q_b, Plan* p) {
+    int rc = make_plan(shape, false, p, false);  // the errors of the first query set come first
     if (rc != JQ_OK) return rc;
     if (n_q_b < 1) return JQ_ERR_SHAPE;
-    if (pa->window) return JQ_ERR_SHAPE;  // the maps of Eq. 3 / Eq. 4 have no window mode
-    jq_shape sb = *shape;
-    sb.n_q = n_q_b;
-    if ((rc = make_plan(&sb, false, pb)) != JQ_OK) return rc;
-    *off_b = pa->ws_bytes;
-    // the partial sums (8 bytes per workgroup of at least 128 keys, or a sequence's end) lie in the first plan's pooled
-    // scores and positions (4 L + 4 bytes per sequence and head at least), which this call has no other use for
-    *off_part = pa->off_pooled;
-    if (*off_part + (size_t)pb->n_layers * pb->cu_cgrp2[pb->n_seq] * pb->h_kv * sizeof(double) > pa->off_seg) return JQ_ERR_UNSUPPORTED;  // never
-    *total = *off_b + pb->ws_bytes;
+    if (p->window) return JQ_ERR_SHAPE;  // the maps of Eq. 3 / Eq. 4 have no window mode
+    if ((rc = make_plan(shape, false, p, true, n_q_b)) != JQ_OK) return rc;
+    if ((size_t)p->n_layers * p->cu_cgrp2[p->n_seq] * p->h_kv * sizeof(double) > p->off_seg - p->off_pooled) return JQ_ERR_UNSUPPORTED;  // never
     return JQ_OK;
 }
 
 int jq_map_mse_fused_workspace_bytes(const jq_shape* shape, int32_t n_q_b, size_t* bytes) {
     if (!bytes) return JQ_ERR_NULL;
-    Plan pa, pb;
-    size_t off_b, off_part;
-    return mse_fused_plans(shape, n_q_b, &pa, &pb, &off_b, &off_part, bytes);
+    Plan p;
+    const int rc = mse_fused_plan(shape, n_q_b, &p);
+    if (rc != JQ_OK) return rc;
+    *bytes = p.ws_bytes;
+    return JQ_OK;
 }
 
 int jq_map_mse_fused(const jq_shape* shape, const void* Q_a, const void* Q_b, int32_t n_q_b, const void* K, float* mse,
                      void* ws, size_t ws_bytes, void* stream) {
-    Plan pa, pb;
-    size_t off_b, off_part, total;
-    const int rc = mse_fused_plans(shape, n_q_b, &pa, &pb, &off_b, &off_part, &total);
+    Plan p;
+    const int rc = mse_fused_plan(shape, n_q_b, &p);
     if (rc != JQ_OK) return rc;
     if (!Q_a || !Q_b || !K || !mse) return JQ_ERR_NULL;
     if (!ws) return JQ_ERR_NULL;
-    if (misaligned(ws, 16) || ws_bytes < total) return JQ_ERR_WORKSPACE;
+    if (misaligned(ws, 16) || ws_bytes < p.ws_bytes) return JQ_ERR_WORKSPACE;
     if (misaligned(Q_a, 16) || misaligned(Q_b, 16) || misaligned(K, 16) || misaligned(mse, 4)) return JQ_ERR_UNSUPPORTED;
-    const size_t out_bytes = (size_t)pa.n_layers * pa.n_seq * pa.h_kv * sizeof(float);
+    const size_t out_bytes = (size_t)p.n_layers * p.n_seq * p.h_kv * sizeof(float);
     const void* ins[3] = {Q_a, Q_b, K};
-    const size_t in_bytes[3] = {q_bytes(pa), q_bytes(pb), kv_bytes(pa)};
+    const size_t in_bytes[3] = {q_bytes(p), (size_t)p.n_layers * p.n_seq * n_q_b * p.h_q * p.d * 2, kv_bytes(p)};
     for (int i = 0; i < 3; ++i)
-        if (overlaps(ws, total, ins[i], in_bytes[i]) || overlaps(mse, out_bytes, ins[i], in_bytes[i])) return JQ_ERR_ALIAS;
-    if (overlaps(mse, out_bytes, ws, total)) return JQ_ERR_ALIAS;
+        if (overlaps(ws, p.ws_bytes, ins[i], in_bytes[i]) || overlaps(mse, out_bytes, ins[i], in_bytes[i])) return JQ_ERR_ALIAS;
+    if (overlaps(mse, out_bytes, ws, p.ws_bytes)) return JQ_ERR_ALIAS;
     hipStream_t st = (hipStream_t)stream;
     char* w = (char*)ws;
-    float* map_a = (float*)(w + pa.off_scores);
-    float* map_b = (float*)(w + off_b + pb.off_scores);  // (addresses only: the comparing launch stores no scores)
-    hipError_t e = launch_score(pa, Q_a, K, map_a, w, st);
-    MseFuse fuse;
-    fuse.ref = map_a;
-    fuse.inv_rows_ref = 1.0f / (float)pa.rows;
-    fuse.inv_rows_own = 1.0f / (float)pb.rows;
-    fuse.part = (double*)(w + off_part);
-    if (e == hipSuccess) e = launch_score(pb, Q_b, K, map_b, w + off_b, st, nullptr, 0, nullptr, nullptr, &fuse);
-    if (e == hipSuccess) e = launch_mse_reduce(pb, fuse.part, mse, st);
+    double* part = (double*)(w + p.off_pooled);
+    hipError_t e = launch_score(p, Q_a, K, nullptr, w, st, nullptr, 0, nullptr, nullptr, Q_b, part);
+    if (e == hipSuccess) e = launch_mse_reduce(p, part, mse, st);
     return launch_status(e);
 }
 

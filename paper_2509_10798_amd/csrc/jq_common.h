@@ -43,8 +43,11 @@ struct Plan {
     int32_t window;                 // 1: the queries are the last n_q tokens of every sequence (causal inside them)
     const int32_t* layer_budgets;   // DEVICE [n_layers][n_seq] or null: per-layer budgets (tab.cu_bud then holds the largest)
     int32_t rows;         // n_q * group: query rows that share one KV head
-    int32_t row_tiles;    // ceil(rows / 32)
+    int32_t n_q2, rows2;  // second query set of the call (jq_map_mse_fused): its tokens and rows, 0 elsewhere
+    int32_t row_tiles1;   // ceil(rows / 32)
+    int32_t row_tiles;    // ... and those of the second set, which follow
     int32_t row_groups;   // ceil(row_tiles / 4): 1, or the groups of rows that the first pass handles side by side
+    bool by_rows;         // the second pass streams query rows past keys held in registers (jq_score_rows_kernel)
     // tab.cu_chunk / cu_cgrp: waves and workgroups of the first pass over K (or the only one); for a second pass:
     int32_t cu_chunk2[JQ_MAX_SEQ + 1], cu_cgrp2[JQ_MAX_SEQ + 1];
     double scale;         // logit scale actually used
@@ -215,16 +218,12 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
 // `zero_words` words at `zero` (nullable) are cleared on the way (between the two K passes).
 // With `lse` (nullable, [n_layers, n_seq, n_q, h_q] natural-log normalisers) the statistics pass is skipped.
 // With `k_tail` (nullable, [n_layers, n_seq, n_q, h_kv, d] bf16) the normalisers also cover those keys, causally.
-// With `fuse` the last launch of the second pass does not store its scores: it compares them with a reference
-// map and leaves one partial sum of squared differences per workgroup (Eq. 5 forward, see launch_mse_reduce).
-struct MseFuse {
-    const float* ref;         // [n_layers][h_kv][T] scores of the other query set
-    float inv_rows_ref, inv_rows_own;
-    double* part;             // [n_layers][workgroups of the second pass per layer and head][h_kv]
-};
+// With two query sets in the plan, Q2 and `diff_part` ([n_layers][workgroups of the second pass per layer and head][h_kv]) the
+// last launch stores no scores: it leaves one partial sum per workgroup of the squared differences of the sets' maps (Eq. 5
+// forward, see launch_mse_reduce).
 hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scores, char* ws, hipStream_t st,
                         uint32_t* zero = nullptr, size_t zero_words = 0, const float* lse = nullptr,
-                        const void* k_tail = nullptr, const MseFuse* fuse = nullptr);
+                        const void* k_tail = nullptr, const void* Q2 = nullptr, double* diff_part = nullptr);
 // Sums the per-workgroup partials of a fused launch in workgroup order and divides by the sequence length.
 hipError_t launch_mse_reduce(const Plan& p, const double* part, float* mse, hipStream_t st);
 // With `hist` the pooling kernel also builds the selection's level-1 histograms, and with `ws` on top of that

@@ -73,12 +73,15 @@ struct ScoreArgs {
     // arguments, which a wave fetches in one go
     int32_t cu_part[JQ_MAX_SEQ + 1];
     SeqTab tab;
-    // DIFF kernels (training-side forward, Eq. 3-5): instead of storing its scores the launch compares them with
-    // the map of the other query set and leaves one partial sum of squared differences per workgroup
-    const float* diff_ref;    // [n_layers][h_kv][T]
-    double* diff_part;        // [n_layers][n_cgrp][h_kv]
-    float diff_inv_ref, diff_inv_own;  // 1 / summed probability rows of either map
+    // Two query sets in one call (training-side forward, Eq. 3-5): row tiles tiles1 .. of a head hold the rows of the second
+    // set.  Their launch of jq_score_rows_kernel compares the two maps instead of storing either and leaves one partial sum
+    // of squared differences per workgroup.  (tiles1: past all row tiles where there is one set.)
+    const uint16_t* Q2;
+    int32_t n_q2, rows2, tiles1;
+    float inv_rows1, inv_rows2;  // 1 / summed probability rows of either map
+    double* diff_part;           // [n_layers][n_cgrp][h_kv]
 };
+constexpr int kOneSet = 0x7FFFFFFF;  // tiles1 of a call with one query set
 
 constexpr int kSlotBytes = kKeyTile * kHeadDim * 2;  // 8 KiB
 
@@ -272,13 +275,16 @@ __device__ __forceinline__ void bare_barrier() {
 template <int NQT>
 __device__ __forceinline__ void q_rows_where(const ScoreArgs& a, const WaveItem& w, int lane, const u32x4* (&src)[8], uint32_t& pad) {
     const int wv = min(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), NQT - 1);
-    const char* qbase = (const char*)a.Q + ((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q) * a.h_q * kHeadDim * 2;
+    const int rt = w.rg * NQT + wv;  // (uniform)
+    const bool second = rt >= a.tiles1;
+    const int n_q = second ? a.n_q2 : a.n_q, rows = second ? a.rows2 : a.rows;
+    const char* qbase = (const char*)(second ? a.Q2 : a.Q) + ((int64_t)(w.layer * a.n_seq + w.seq) * n_q) * a.h_q * kHeadDim * 2;
     pad = 0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + (lane >> 4);
-        const int row = (w.rg * NQT + wv) * kRowTile + r;
-        const bool valid = row < a.rows;
+        const int row = (second ? rt - a.tiles1 : rt) * kRowTile + r;
+        const bool valid = row < rows;
         const int rowc = valid ? row : 0;
         int it, hh;
         if (a.group_shift >= 0) { it = rowc >> a.group_shift; hh = rowc & (a.group - 1); }
@@ -725,7 +731,8 @@ __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(Sc
                 Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz.y * __builtin_amdgcn_exp2f(mz.x - mm);
                 M = mm;
             }
-            a.aug[((int64_t)(layer * a.n_seq + s) * a.h_kv + g) * a.RP + row] = row < a.rows ? neg_beta_terms(M, Z, a.inv_c) : split_bf16x3(kPadTerm);
+            const bool real = rt < a.tiles1 ? row < a.rows : row - a.tiles1 * kRowTile < a.rows2;
+            a.aug[((int64_t)(layer * a.n_seq + s) * a.h_kv + g) * a.RP + row] = real ? neg_beta_terms(M, Z, a.inv_c) : split_bf16x3(kPadTerm);
         }
     }
 }
@@ -743,13 +750,9 @@ __device__ __forceinline__ f32x16 score_chain(const bf16x8 (&q)[8], bf16x8 qaug,
 
 // FROM_LSE: the caller supplied the normalisers and no statistics pass has run: lse becomes the -beta/c terms
 // on the fly (beta = lse * log2 e, c = scale * log2 e, so -beta/c = -lse / scale), and the launch also clears the words the selection stage needs cleared.
-// DIFF: the scores are not stored; (ref / rows_ref - score / rows_own)^2 is summed instead (Eq. 5 of the paper on
-// the maps of Eq. 3 and Eq. 4), in fp64 per lane, then in a fixed order over lanes and waves.
-template <int NQT, bool FROM_LSE, bool PAGED, bool DIFF = false>
+template <int NQT, bool FROM_LSE, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs a) {
     __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
-    __shared__ double diff_s[DIFF ? kScoreWaves : 1];
-    if (DIFF && threadIdx.x < kScoreWaves) diff_s[threadIdx.x] = 0.0;  // before the start-up's barriers
     WaveItem w;
     wave_item(a, true, w);  // reversed order: the keys pass 1 read last are fetched first
     const int lane = threadIdx.x & 63;
@@ -881,10 +884,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
         const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
         for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
     }
-    if (w.n_tiles == 0) {  // surplus wave of the sequence's last workgroup
-        if (DIFF) __syncthreads();  // the workgroup's final merge
-        return;
-    }
+    if (w.n_tiles == 0) return;  // surplus wave of the sequence's last workgroup
     u32x4 ones_bits = {0u, 0u, 0u, 0u};
     if (half == 0) { ones_bits[0] = 0x3F803F80u; ones_bits[1] = 0x00003F80u; }  // 1.0 at elements 0..2
     const bf16x8 ones = as_bf16x8(ones_bits);
@@ -894,18 +894,11 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
     float pending = 0.f;  // previous tile's result, stored one iteration late so that the store has a
                           // whole tile of compute to retire before the next wait on outstanding loads
     const int n_scored = a.window ? w.L - a.n_q : w.L;  // the window's own positions report 0
-    double dacc = 0.0;  // DIFF: this lane's sum of squared map differences
     auto store_tile = [&](int k, float v) {  // only the sequence's last tile can be partial
         const int t = tile_of(k);
         if (lane < 32 && t * kKeyTile + lane < w.L) {
-            float* o = out + t * kKeyTile + lane;
             if (t * kKeyTile + lane >= n_scored) v = 0.f;
-            if (DIFF) {
-                const double d = (double)a.diff_ref[o - a.scores] * (double)a.diff_inv_ref - (double)v * (double)a.diff_inv_own;
-                dacc += d * d;
-            } else {
-                *o = v;
-            }
+            out[t * kKeyTile + lane] = v;
         }
     };
 
@@ -947,23 +940,9 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
         pending = sum;
     }
     store_tile(w.n_tiles - 1, pending);
-    if (DIFF) {  // lanes 0..31 hold the sums: butterfly within the half wave, then the four waves in wave order
-#pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) dacc += __shfl_xor(dacc, off);
-        const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        if (lane == 0) diff_s[wv] = dacc;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const int cg = (a.one_L ? 0 : a.tab.cu_cgrp[w.seq]) + w.wave / kScoreWaves;  // wave 0 always has tiles
-            double sum = 0.0;
-#pragma unroll
-            for (int i = 0; i < kScoreWaves; ++i) sum += diff_s[i];
-            a.diff_part[((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g] = sum;
-        }
-    }
 }
 
-template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  // placement: see jq_lib.hip
+template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placement: see jq_lib.hip
 
 // ------------------------------------------------------------------------------------------------
 // many query rows (more than kMaxRowTiles tiles per KV head): keys stationary, query rows streamed
@@ -981,6 +960,10 @@ template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  //
 // clock under matrix work).  Two waves per key group instead of four: 42.9 against 41.5 us there, 5 % better only with
 // thousands of workgroups: not kept.
 // -beta/c comes from `aug`, which a combine launch (or jq_lse_aug_kernel) has filled.
+// DIFF: two query sets, whose row tiles follow each other (tiles1).  A key's two sums form in the same sweep, and instead of
+// storing either map the workgroup leaves its sum of (sum1 / rows1 - sum2 / rows2)^2 (Eq. 5 of the paper on the maps of Eq. 3
+// and Eq. 4), in fp64 per key, then in a fixed order over lanes and waves.  The first set has four tiles where the second has
+// sixteen in the usual sizes, so sweeping them here costs less than the launches of both passes that stored its map before.
 template <bool PAGED, bool DIFF>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(ScoreArgs a) {
     __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
@@ -1000,11 +983,13 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     const int tile0 = (cg - a.tab.cu_cgrp[w.seq]) * kMaxRowTiles;  // first key tile of the group
 
     // ---- query-row tiles: global -> LDS, laid out as key tiles are (see fetch_tile) ----
-    const char* qbase = (const char*)a.Q + (((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q) * a.h_q + (int64_t)w.g * a.group) * kHeadDim * 2;
-    const int n_rt = (a.rows + kRowTile - 1) / kRowTile;
-    const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...: at least
-                                                                     // one (the kernel runs with more than kScoreWaves)
-    const uint2* aug = a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + (lane & 31);
+    const int64_t head0 = (int64_t)w.g * a.group * kHeadDim * 2, prob = w.layer * a.n_seq + w.seq;
+    const char* qbase1 = (const char*)a.Q + prob * a.n_q * a.h_q * kHeadDim * 2 + head0;
+    const char* qbase2 = (const char*)a.Q2 + prob * a.n_q2 * a.h_q * kHeadDim * 2 + head0;  // DIFF only
+    const int n_rt = a.RP / kRowTile;
+    const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...; none of few
+    const int n_first = DIFF ? min(n_mine, (a.tiles1 - wv + kScoreWaves - 1) / kScoreWaves) : 0;  // ... of them of the first set
+    const uint2* aug = a.aug + prob * a.h_kv * a.RP + (int64_t)w.g * a.RP + (lane & 31);
     const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
     // With a power-of-two group of up to 32 heads a tile's rows lie where a key tile's would: a lane part that never changes
     // and a uniform part per load (4 i + a, a < 4, splits without carry), so a request costs no vector arithmetic -- the
@@ -1014,9 +999,12 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     const uint32_t rl = (uint32_t)lane >> 4, tok32 = (uint32_t)tok_bytes;
     const uint32_t tq = (rl >> (gs & 31)) * tok32 + (rl & (uint32_t)(a.group - 1)) * (kHeadDim * 2) + ((((uint32_t)lane & 15u) ^ rl) << 4);
     auto fetch_rows = [&](int k) __attribute__((always_inline)) {
-        const int r0 = (wv + k * kScoreWaves) * kRowTile;
+        const int rt = wv + k * kScoreWaves;
+        const bool second = DIFF && rt >= a.tiles1;  // uniform
+        const char* qbase = second ? qbase2 : qbase1;
+        const int rows = second ? a.rows2 : a.rows, r0 = (second ? rt - a.tiles1 : rt) * kRowTile;
         char* slot = slots + (k & 1) * kSlotBytes;
-        if (regular && r0 + kRowTile <= a.rows) {
+        if (regular && r0 + kRowTile <= rows) {
             const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
                 (void*)(qbase + (int64_t)(r0 >> gs) * tok_bytes), 0,
                 (int)((uint32_t)((kRowTile - 1) >> gs) * tok32 + (uint32_t)min(a.group, kRowTile) * (kHeadDim * 2)), 0x00020000);
@@ -1028,7 +1016,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int r = 4 * i + (lane >> 4);
-            const int row = min(r0 + r, a.rows - 1);  // rows past the end re-read the last one: their aug makes every term 0
+            const int row = min(r0 + r, rows - 1);  // rows past the end re-read the last one: their aug makes every term 0
             int it, hh;
             if (a.group_shift >= 0) { it = row >> a.group_shift; hh = row & (a.group - 1); }
             else { it = row / a.group; hh = row % a.group; }
@@ -1047,7 +1035,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, w.L - t * kKeyTile), lane);
     }
     fetch_rows(0);
-    uint2 aug_next = aug[wv * kRowTile];
+    uint2 aug_next = aug[min(wv, n_rt - 1) * kRowTile];
     wait_tile_landed();
     bare_barrier();
     bf16x8 kf[kMaxRowTiles][8];
@@ -1059,9 +1047,13 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     if (half == 0) { ones_bits[0] = 0x3F803F80u; ones_bits[1] = 0x00003F80u; }  // 1.0 at elements 0..2
     const bf16x8 ones = as_bf16x8(ones_bits);
     const float c = a.c;
-    float sum[kMaxRowTiles];
+    float sum[kMaxRowTiles], sum1[kMaxRowTiles];  // sum1: DIFF, the first set's
 #pragma unroll
-    for (int kt = 0; kt < kMaxRowTiles; ++kt) sum[kt] = 0.f;
+    for (int kt = 0; kt < kMaxRowTiles; ++kt) sum[kt] = sum1[kt] = 0.f;
+    auto next_set = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int kt = 0; kt < kMaxRowTiles; ++kt) { sum1[kt] = sum[kt]; sum[kt] = 0.f; }
+    };
     // as in the other sweeps: the next key tile's MFMA chain runs between the exp2 work of this one, and behind the last
     // one the first chain of the next row tile, read a stage earlier
     auto aug_of = [&](uint2 t) __attribute__((always_inline)) {
@@ -1079,6 +1071,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     }
     f32x16 acc = score_chain(qf, qaug, kf[0], ones);
     for (int k = 0; k < n_mine; ++k) {
+        if (DIFF && k == n_first) next_set();
 #pragma unroll
         for (int kt = 0; kt < kMaxRowTiles; ++kt) {
             const bool reads = kt == kMaxRowTiles - 2;
@@ -1104,25 +1097,33 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
             acc = nxt;
         }
     }
+    if (DIFF && n_first == n_mine) next_set();  // a wave with tiles of the first set alone
+    constexpr int kKeys = kMaxRowTiles * kKeyTile;
 #pragma unroll
     for (int kt = 0; kt < kMaxRowTiles; ++kt) {
         sum[kt] += __shfl_xor(sum[kt], 32);  // the two lane halves hold complementary query rows of the same key
-        if (half == 0) ((float*)slots)[kt * kKeyTile + lane] = sum[kt];  // the wave's slots are idle by now
+        if (DIFF) sum1[kt] += __shfl_xor(sum1[kt], 32);
+        if (half == 0) {  // the wave's slots are idle by now
+            ((float*)slots)[kt * kKeyTile + lane] = sum[kt];
+            if (DIFF) ((float*)slots)[kKeys + kt * kKeyTile + lane] = sum1[kt];
+        }
     }
     __syncthreads();
     const int key = tile0 * kKeyTile + (int)threadIdx.x;  // threads 0..127: one key each
     double dacc = 0.0;
-    if (threadIdx.x < kMaxRowTiles * kKeyTile && key < w.L) {
-        float v = 0.f;
+    if (threadIdx.x < kKeys && key < w.L) {
+        float v = 0.f, v1 = 0.f;
 #pragma unroll
-        for (int i = 0; i < kScoreWaves; ++i) v += ((const float*)&lds[i][0][0])[threadIdx.x];
-        if (a.window && key >= w.L - a.n_q) v = 0.f;  // the window's own positions report 0
-        const int64_t o = ((int64_t)w.layer * a.h_kv + w.g) * a.T + w.tok0 + key;
+        for (int i = 0; i < kScoreWaves; ++i) {
+            v += ((const float*)&lds[i][0][0])[threadIdx.x];
+            if (DIFF) v1 += ((const float*)&lds[i][0][0])[kKeys + threadIdx.x];
+        }
         if (DIFF) {
-            const double d = (double)a.diff_ref[o] * (double)a.diff_inv_ref - (double)v * (double)a.diff_inv_own;
+            const double d = (double)v1 * (double)a.inv_rows1 - (double)v * (double)a.inv_rows2;
             dacc = d * d;
         } else {
-            a.scores[o] = v;
+            if (a.window && key >= w.L - a.n_q) v = 0.f;  // the window's own positions report 0
+            a.scores[((int64_t)w.layer * a.h_kv + w.g) * a.T + w.tok0 + key] = v;
         }
     }
     if constexpr (DIFF) {  // butterfly within waves 0 and 1, then their two sums: a fixed order
@@ -1176,18 +1177,8 @@ static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
     }
 }
 
-static hipError_t launch_score_diff_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st) {
-    dim3 block(kScoreWaves * 64);
-    switch (nqt) {
-        case 1: return launch_kernel(jq_score_kernel<1, false, false, true>, grid, block, 0, st, nullptr, -1, a);
-        case 2: return launch_kernel(jq_score_kernel<2, false, false, true>, grid, block, 0, st, nullptr, -1, a);
-        case 3: return launch_kernel(jq_score_kernel<3, false, false, true>, grid, block, 0, st, nullptr, -1, a);
-        default: return launch_kernel(jq_score_kernel<4, false, false, true>, grid, block, 0, st, nullptr, -1, a);
-    }
-}
-
 hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scores, char* ws, hipStream_t st,
-                        uint32_t* zero, size_t zero_words, const float* lse, const void* k_tail, const MseFuse* fuse) {
+                        uint32_t* zero, size_t zero_words, const float* lse, const void* k_tail, const void* Q2, double* diff_part) {
     void* const* marks = p.marks;
     ScoreArgs a;
     a.Q = (const uint16_t*)Q;
@@ -1210,9 +1201,11 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.zero = zero; a.zero_words = zero_words;
     a.tab = p.tab;
     a.block_table = p.block_table; a.page_shift = p.page_shift; a.n_pages = p.n_pages; a.max_pages = p.max_pages;
-    a.diff_ref = nullptr; a.diff_part = nullptr; a.diff_inv_ref = a.diff_inv_own = 0.0f;
+    a.Q2 = (const uint16_t*)Q2; a.diff_part = diff_part;
+    a.n_q2 = p.n_q2; a.rows2 = p.rows2; a.tiles1 = p.n_q2 ? p.row_tiles1 : kOneSet;
+    a.inv_rows1 = 1.0f / (float)p.rows; a.inv_rows2 = p.n_q2 ? 1.0f / (float)p.rows2 : 0.0f;
     const bool paged = p.block_table != nullptr;
-    if (fuse && (paged || lse)) return hipErrorInvalidValue;  // the fused comparison exists for dense two-pass calls
+    if ((diff_part != nullptr) != (p.n_q2 != 0) || (diff_part && (paged || lse))) return hipErrorInvalidValue;  // two sets: dense two-pass calls
     a.n_cgrp = p.tab.cu_cgrp[p.n_seq];
     a.one_L = p.n_seq == 1 ? p.tab.cu_seq[1] : 0;
     a.one_waves = p.n_seq == 1 ? p.tab.cu_chunk[1] : 0;
@@ -1222,9 +1215,9 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.lse = lse;
     a.n_part = 0; a.fuse_combine = 0;
     for (int s = 0; s <= p.n_seq; ++s) a.cu_part[s] = 0;
-    const bool many_rows = p.row_groups > 1;  // more query rows per KV head than a wave holds: jq_score_rows_kernel
+    const bool many_rows = p.by_rows;  // more query rows per KV head than a wave holds, or two sets of them: jq_score_rows_kernel
     if (!lse) {
-        const int nqt = many_rows ? kMaxRowTiles : p.row_tiles;
+        const int nqt = min(p.row_tiles, kMaxRowTiles);
         // all row groups in one launch (in several where the grid would get too large for one)
         const int64_t wgs = grid.x;
         const int per_launch = (int)max((int64_t)1, min((int64_t)p.row_groups, ((int64_t)1 << 23) / wgs));
@@ -1265,18 +1258,9 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
             grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
         }
         const dim3 block(kScoreWaves * 64);
-        if (fuse) {
-            a.diff_ref = fuse->ref; a.diff_part = fuse->part;
-            a.diff_inv_ref = fuse->inv_rows_ref; a.diff_inv_own = fuse->inv_rows_own;
-            return launch_kernel(jq_score_rows_kernel<false, true>, grid, block, 0, st, nullptr, -1, a);
-        }
+        if (diff_part) return launch_kernel(jq_score_rows_kernel<false, true>, grid, block, 0, st, nullptr, -1, a);
         if (paged) return launch_kernel(jq_score_rows_kernel<true, false>, grid, block, 0, st, marks, kTrScore, a);
         return launch_kernel(jq_score_rows_kernel<false, false>, grid, block, 0, st, marks, kTrScore, a);
-    }
-    if (fuse) {  // compare the scores instead of storing them
-        a.diff_ref = fuse->ref; a.diff_part = fuse->part;
-        a.diff_inv_ref = fuse->inv_rows_ref; a.diff_inv_own = fuse->inv_rows_own;
-        return launch_score_diff_n(p.row_tiles, a, grid, st);
     }
     if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);
     return lse ? launch_score_n<true, false>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, false>(p.row_tiles, a, grid, st, marks);
