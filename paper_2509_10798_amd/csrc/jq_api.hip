@@ -247,7 +247,7 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     p.off_seghdr = off; off += seghdr;
     p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
     p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
-    p.off_scores = off; off += n_q2 ? 0 : align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));  // two sets: no map is stored
+    p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
     p.ws_bytes = off;
     *out = p;
     return JQ_OK;
