@@ -46,8 +46,9 @@
  *   averaged) over the n_q soft tokens and the h_q/h_kv heads of the group, so
  *   the unpooled scores of a (layer, sequence, KV head) sum to n_q * h_q / h_kv.
  * - The caller owns every buffer.  The library allocates nothing, keeps no
- *   state between calls (apart from the knobs below, read once, and a one-time
- *   per-device raise of one kernel's LDS limit), never synchronises the stream
+ *   state between calls (apart from the knobs below, read once, a one-time
+ *   per-device raise of some kernels' LDS limit, and a counter that gives every
+ *   call a number of its own), never synchronises the stream
  *   and may be called from several host threads at once.  `stream` is a hipStream_t passed as void*
  *   (NULL = the default stream).  Work is only enqueued; results are ready when
  *   the stream reaches the end of the enqueued work.
@@ -357,7 +358,8 @@ int jq_evict_paged_inplace(const jq_shape* shape, const jq_pages* pages, const j
  * statistics get an untimed merge launch between slots 0 and 1; short sequences, up to
  * 32768 tokens, are pooled by the selection's kernel, which slot 3 then reports, and slot 2
  * is an empty interval of a few microseconds in front of it).  The kernels are those of
- * jq_evict, and so are the results. */
+ * jq_evict, except that it runs both passes over K in one launch; the results are the same
+ * bits. */
 #define JQ_TRACE_MARKS 8
 int jq_evict_traced(const jq_shape* shape, const void* Q, const void* K, const void* V,
                     void* K_out, void* V_out, int32_t* idx_out, float* scores_out,
@@ -370,7 +372,8 @@ int jq_copy_probe(const void* src, void* dst, size_t bytes, void* stream);
 
 /* Ablation and diagnosis knobs.  The library reads a few environment variables ONCE per process, at its first
  * call (never on the path of a later call): JQ_CHUNK_KEYS / JQ_CHUNK_KEYS_2 (keys per wave in the first / second
- * pass over K, multiples of 32 up to 8192), JQ_LOG (print the HIP error string when a launch is refused).  Results do
+ * pass over K, multiples of 32 up to 8192), JQ_WAIT_US (how long a workgroup that does both passes waits for the statistics
+ * of others before it forms them itself, 0..1000000 microseconds, 1000 by default), JQ_LOG (print the HIP error string when a launch is refused).  Results do
  * not depend on them beyond rounding order.  jq_reload_knobs reads the environment again; it must not run
  * concurrently with other calls (tests use it to force rarely taken code paths at small sizes).  Always returns JQ_OK. */
 int jq_reload_knobs(void);

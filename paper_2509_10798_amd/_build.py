@@ -15,6 +15,9 @@ SOURCES = ["jq_lib.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # matrix results in ordinary registers also in a kernel of one wave per SIMD (jq_passes_kernel), which may use more than 256:
+    # every result goes through vector instructions next, and out of accumulation registers that costs two moves each
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 

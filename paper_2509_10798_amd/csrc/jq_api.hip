@@ -20,6 +20,8 @@ static Knobs read_knobs() {
     k.chunk_keys = chunk("JQ_CHUNK_KEYS");
     k.chunk_keys2 = chunk("JQ_CHUNK_KEYS_2");
     if (!std::getenv("JQ_CHUNK_KEYS_2")) k.chunk_keys2 = k.chunk_keys;
+    const char* wait = std::getenv("JQ_WAIT_US");
+    k.wait_us = wait ? (int32_t)std::min(std::max(std::atol(wait), 0l), 1000000l) : 1000;
     k.log = std::getenv("JQ_LOG") != nullptr;
     return k;
 }
@@ -39,6 +41,71 @@ bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0;
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
     return a0 < b0 + nb && b0 < a0 + na;
+}
+
+// How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
+// with about that many; without it the quads are dealt evenly: as many workgroups as make one per CU.
+Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
+    Split x{};
+    const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
+    if (chunk) {
+        for (int s = 0; s < p.n_seq; ++s) {
+            const int32_t L = p.tab.cu_seq[s + 1] - p.tab.cu_seq[s], n = (L - 1) / (kScoreWaves * chunk) + 1;
+            x.cu[s + 1] = x.cu[s] + n;
+            x.max_sets = std::max(x.max_sets, n);
+        }
+        x.args.whole = 1;
+        x.args.per_layer = x.cu[p.n_seq];
+        x.args.inv_layer = inverse(x.args.per_layer);
+        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
+        return x;
+    }
+    const int64_t per = (int64_t)p.h_kv * p.row_groups;
+    int64_t n = std::max<int64_t>(1, 256 / per);
+    n = std::min(n, n_quads);
+    if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
+    if (p.n_seq == 1 && n % units == 0) {  // whole workgroups for every layer
+        x.args.whole = 1;
+        x.args.per_layer = x.cu[1] = (int32_t)(n / units);
+        x.args.inv_layer = x.args.inv_n = inverse(x.args.per_layer);
+        x.n_wg = x.n_sets = (int32_t)n;
+        x.max_sets = x.args.per_layer;
+        return x;
+    }
+    // Where workgroups come to more than one sequence, those that do take fewer keys, if that makes the longest one shorter:
+    // a change of sequence costs about as much as kStartUp quads in either pass.
+    constexpr int kStartUp = 5;
+    auto longest = [&](int64_t gap) {
+        const int64_t total = n_quads + (units - 1) * gap;
+        int64_t worst = 0, u0 = 0;
+        int32_t s = 0;
+        for (int64_t c = 0, b0 = 0; c < n; ++c) {
+            const int64_t b1 = (c + 1) * total / n;
+            int64_t cost = 0;
+            for (;;) {
+                const int64_t nq = p.cu_quad[s + 1] - p.cu_quad[s], lo = std::max(b0, u0), hi = std::min(b1, u0 + nq);
+                if (hi > lo) cost += hi - lo + kStartUp;
+                if (b1 < u0 + nq + gap || (b1 == total && u0 + nq >= total)) break;
+                u0 += nq + gap;
+                if (++s == p.n_seq) s = 0;
+                if (u0 >= b1) break;
+            }
+            worst = std::max(worst, cost);
+            b0 = b1;
+        }
+        return worst;
+    };
+    if (units > 1 && units <= 1024 && n > 1 && n_quads / n > kStartUp && longest(kStartUp) < longest(0)) x.args.gap = kStartUp;
+    x.args.n = (int32_t)n;
+    x.args.total = (int32_t)(n_quads + (units - 1) * x.args.gap);
+    x.args.per_layer = p.cu_quad[p.n_seq] + p.n_seq * x.args.gap;
+    for (int s = 0; s < p.n_seq; ++s) x.cu[s + 1] = p.cu_quad[s + 1] + (s + 1) * x.args.gap;
+    x.args.q = x.args.total / x.args.n;
+    x.args.inv_n = inverse(x.args.n); x.args.inv_total = inverse(x.args.total); x.args.inv_layer = inverse(x.args.per_layer);
+    x.n_wg = (int32_t)n;
+    x.n_sets = (int32_t)(units + n - 1);
+    x.max_sets = (int32_t)std::min<int64_t>(n, max_quads < 2 ? 1 : (max_quads - 2) / x.args.q + 2);
+    return x;
 }
 
 // Validates `shape` and derives the plan.  `need_budgets`: the entry point uses budgets.
@@ -104,109 +171,28 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     }
     p.TB = tb;
 
-    // How the sequences are cut into workgroups of four waves for the passes over K: ceil(L / (4 * chunk)) workgroups per
-    // (layer, sequence, head, group of 128 query rows), whose waves share the sequence's 32-key tiles round-robin.  The
-    // `chunk` is chosen by an estimate of either pass's time, in units of the time that 1024 waves (one per SIMD: 256 CUs,
-    // one workgroup each) take for a tile each at the rate memory delivers (1.3..1.6 us):
-    //   tiles / 1024                      all waves busy
-    //   + what the last, partly filled round of the 512 resident workgroups wastes: with x = workgroups / 256 in it, each
-    //     tile of its waves takes 0.38 + 0.62 x with at most one workgroup per CU, 0.58 + 0.75 x with two on some (or where the
-    //     workgroups start as the CUs fall free), against the x that full rates would give
-    //   + 0.45 per tile by which the longest wave leads the average: its last tiles run on a chip that is nearly empty
-    //   + 0.03 per tile where all run at once with two workgroups on some CUs
-    //   + 0.7 per further workgroup and CU  another start-up (query rows, normalisers), 2-4 us that its neighbour mostly hides;
-    //     2.0 with several groups of query rows, for which the keys come out of the caches and a start-up counts for more tiles
-    //   + 3 for the launch that merges the statistics of a sequence with more than 64 workgroups.
-    // One cold pass, 4 layers x 123490 keys, 128 query rows, 128 / 192 / 256 / 320 / 384 / 448 / 512 workgroups: 264.6 / 216.3
-    // / 192.8 / 233.6 / 218.1 / 208.1 / 200.7 us, 640 / 768 / 1024 / 1952: 220.3 / 219.3 / 195.8 / 198.6; 32 rows, 100000
-    // and 65536 keys run alike.  (With 0.75 for everything up to one per CU, 192 workgroups counted as good as 256: 4 x
-    // 123490 took 218 us in one pass and 394 in two, now 193 and 355; 4 layers x 60000 keys x 2 heads 53.5, now 49.)
-    // One workgroup per CU wins where the sequences divide evenly -- 128K layer, keys per wave 512 / 1024: 48.7 + 44.9 /
-    // 45.2 + 41.5 us; 8 layers x 64K, 1024 / 4096: 180 + 194 / 174 + 189; 32 x 8K, 1024 / 2048: 95.7 + 94.5 / 90.2 + 92.1
-    // -- and a count just over a multiple of 512 loses: a paged batch of 8 with 528 workgroups in the second pass took 218
-    // us per call, with 400 204.  Candidates run from the smallest sensible chunk to eight times that.  Over 61 shapes (1..32
-    // layers, 1..16 sequences of 2K..131K tokens) the cut so chosen is 0.25 % from the best candidate, at most 3.7 %.
-    const int64_t per_key = (int64_t)p.n_layers * p.h_kv * p.row_groups;
-    const int64_t keys = per_key * p.T;
-    auto wgs_of = [](int64_t L, int64_t chunk) { return (L + kScoreWaves * chunk - 1) / (kScoreWaves * chunk); };
-    const double startup = p.row_groups == 1 ? 0.7 : 2.0;
-    int64_t tiles = 0;
-    for (int s = 0; s < sh->n_seq; ++s) tiles += (sh->cu_seqlens[s + 1] - sh->cu_seqlens[s] + kKeyTile - 1) / kKeyTile;
-    // (Without integer divisions, which took most of the 6.8 us that a plan for 128 sequences cost, 4.3 now: the workgroups come
-    // from a reciprocal -- exact, half a key away from any whole number -- and the longest wave is divided out only where it is
-    // longer than those before.)
-    auto estimate = [&](int64_t chunk) {
-        int64_t wgs = 0, waves = 0;
-        int32_t t_max = 0, wgs_max = 0;
-        const double per_wg = 1.0 / (double)(kScoreWaves * chunk);
-        for (int s = 0; s < sh->n_seq; ++s) {
-            const int32_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
-            const int32_t n = (int32_t)(((uint32_t)L + kKeyTile - 1) / kKeyTile);
-            const int32_t g = (int32_t)(((double)L - 0.5) * per_wg) + 1, w = std::min(kScoreWaves * g, n);
-            wgs += g; waves += w;
-            if ((int64_t)n > (int64_t)t_max * w) t_max = (n + w - 1) / w;
-            wgs_max = std::max(wgs_max, g);
-        }
-        const double N = (double)per_key * (double)wgs, x = (N - 512.0 * std::floor(N / 512.0)) / 256.0;
-        const double t_avg = (double)tiles / (double)waves, last = N <= 256.0 ? 0.38 + 0.62 * x : 0.58 + 0.75 * x;
-        double cost = (double)per_key * (double)tiles / 1024.0 + startup * std::max(0.0, N / 256.0 - 1.0) + 0.45 * ((double)t_max - t_avg);
-        if (x > 0.0) cost += std::max(0.0, last - x) * t_avg;
-        if (N > 256.0 && N <= 512.0) cost += 0.03 * t_avg;
-        if (wgs_max > 64 && p.row_groups == 1) cost += 3.0;
-        return cost;
-    };
-    auto round_tile = [](int64_t x) { return (x + kKeyTile - 1) / kKeyTile * kKeyTile; };
-    const int64_t smallest = std::min<int64_t>(std::max<int64_t>(round_tile((keys + 1023) / 1024), 64), 1024);
-    int64_t best = smallest;
-    if (sweeps && (!knobs().chunk_keys || !knobs().chunk_keys2)) {
-        double best_cost = estimate(smallest);
-        auto consider = [&](int64_t chunk) {
-            if (chunk <= smallest || chunk > 8192) return;
-            const double cost = estimate(chunk);
-            if (cost < best_cost) { best_cost = cost; best = chunk; }
-        };
-        for (int f = 5; f <= 32; f += f < 8 ? 1 : f < 16 ? 4 : 8) consider(round_tile(smallest * f / 4));  // 1.25, 1.5, 1.75, 2, 3, 4, 6, 8 times
-        if (sh->n_seq == 1)  // cut evenly into as many workgroups as fill the chip once, twice, four times
-            for (int k = 1; k <= 4; k *= 2) {
-                const int64_t g = 256 * k / per_key;
-                if (g >= 1) consider(round_tile((p.T + kScoreWaves * g - 1) / (kScoreWaves * g)));
-            }
+    p.cu_quad[0] = 0;
+    int64_t wg_bound = 0;
+    int32_t max_quads = 0;
+    for (int s = 0; s < sh->n_seq; ++s) {
+        const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
+        const int32_t n = (int32_t)((L + kScoreWaves * kKeyTile - 1) / (kScoreWaves * kKeyTile));
+        p.cu_quad[s + 1] = p.cu_quad[s] + n;
+        max_quads = std::max(max_quads, n);
+        wg_bound += p.by_rows ? n : (L + 4095) / 4096;
     }
-    auto cut = [&](int64_t chunk, int32_t* cu_chunk, int32_t* cu_cgrp) {
-        int64_t nc = 0, ng = 0;
-        cu_chunk[0] = 0;
-        cu_cgrp[0] = 0;
-        for (int s = 0; s < sh->n_seq; ++s) {
-            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s], g = wgs_of(L, chunk);
-            nc += std::min(kScoreWaves * g, (L + kKeyTile - 1) / kKeyTile);
-            ng += g;
-            cu_chunk[s + 1] = (int32_t)nc;
-            cu_cgrp[s + 1] = (int32_t)ng;
-        }
-        return ng;
-    };
-    // Calls that do not fill the chip even with one tile per wave take just that: the second pass with up to 256 such
-    // workgroups, the first (whose workgroups each leave a set of statistics) with up to 64.  Whole calls, two tiles / one:
-    // 2048 tokens with 2 KV heads 20.6 / 19.4 us, with 8 22.8 / 21.9; with 512 workgroups 28.3 / 29.7.
-    int64_t best2 = best;
-    if (best == 64 && p.row_groups == 1) {
-        int64_t wgs = 0;
-        for (int s = 0; s < sh->n_seq; ++s) wgs += wgs_of(sh->cu_seqlens[s + 1] - sh->cu_seqlens[s], kKeyTile);
-        if (per_key * wgs <= 256) best2 = kKeyTile;
-        if (per_key * wgs <= 64) best = kKeyTile;
-    }
-    const int64_t ng = cut(knobs().chunk_keys ? knobs().chunk_keys : best, p.tab.cu_chunk, p.tab.cu_cgrp);
-    int64_t ng2 = cut(knobs().chunk_keys2 ? knobs().chunk_keys2 : best2, p.cu_chunk2, p.cu_cgrp2);
-    if (p.by_rows) {  // jq_score_rows_kernel: one workgroup per 128 keys, whatever the waves per sequence
-        ng2 = 0;
-        for (int s = 0; s < sh->n_seq; ++s) {
-            const int64_t L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
-            ng2 += (L + kMaxRowTiles * kKeyTile - 1) / (kMaxRowTiles * kKeyTile);
-            p.cu_cgrp2[s + 1] = (int32_t)ng2;
-        }
-    }
-    if ((int64_t)p.n_layers * (ng > ng2 ? ng : ng2) * p.h_kv >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
+    if ((int64_t)p.n_layers * wg_bound * p.h_kv >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
     if ((int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
+    if (sweeps) {
+        if (knobs().chunk_keys || knobs().chunk_keys2) {  // whole workgroups per sequence, at least 32 keys a wave
+            int64_t wgs = 0;
+            const int32_t chunk = std::min(knobs().chunk_keys ? knobs().chunk_keys : 8192, knobs().chunk_keys2 ? knobs().chunk_keys2 : 8192);
+            for (int s = 0; s < sh->n_seq; ++s) wgs += (sh->cu_seqlens[s + 1] - sh->cu_seqlens[s] - 1) / (kScoreWaves * chunk) + 1;
+            if ((int64_t)p.n_layers * wgs * p.h_kv >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
+        }
+        p.split = make_split(p, knobs().chunk_keys, max_quads);
+        p.split2 = knobs().chunk_keys2 == knobs().chunk_keys ? p.split : make_split(p, knobs().chunk_keys2, max_quads);
+    }
 
     // pooling workgroups (= segments of the selection's lists): whole sequences in pieces of kSegLen positions
     p.cu_seg[0] = 0;
@@ -232,20 +218,23 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
 
     const size_t RP = (size_t)p.row_tiles * kRowTile;
     size_t off = 0;
-    // The statistics (one set of RP per first-pass workgroup) have room of their own for an eighth of the workgroups (a cut
-    // differs from the next build's by at most that, see the candidates) and run on into what pooling and selection write when
-    // both passes are done, so that a finer cut asks callers for no larger workspace than a coarser one did.  What does not fit
-    // there either (many query rows, the smallest calls) gets room too.
-    const size_t stats = (size_t)p.n_layers * ng * p.h_kv * RP * sizeof(float2), n_heads = (size_t)p.n_layers * p.h_kv;
+    // The statistics (one set of RP per share) lie in what pooling and selection write when both passes are done, so that
+    // more shares ask callers for no larger workspace.  What does not fit there (many query rows, the smallest calls) gets room
+    // of its own, and so does an eighth of them where a knob sets the keys per wave, which can so be told from the size.
+    const size_t set = (size_t)p.h_kv * RP * sizeof(float2), stats = (size_t)p.split.n_sets * set, n_heads = (size_t)p.n_layers * p.h_kv;
     const size_t pooled = align_up(n_heads * p.T * sizeof(float)), idx = align_up(n_heads * p.TB * sizeof(int32_t));
     const size_t seg = align_up(n_heads * p.n_seg * p.seg_head * sizeof(uint2)), seghdr = align_up(n_heads * p.n_seg * sizeof(uint4));
     const size_t later = pooled + idx + seg + seghdr;
-    p.off_stats = off;  off += align_up(std::max(stats / 8, stats > later ? stats - later : 0));
+    p.off_stats = off;  off += align_up(std::max(knobs().chunk_keys ? stats / 8 : 0, stats > later ? stats - later : 0));
     p.off_pooled = off; off += pooled;
     p.off_idx = off;    off += idx;
     p.off_seg = off;    off += seg;
     p.off_seghdr = off; off += seghdr;
     p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
+    // (the flags of a launch that does both passes lie where the merge launch it does without leaves its terms)
+    p.off_flags = p.off_aug;
+    p.one_launch = sweeps && !p.by_rows && p.split.max_sets <= 64 && p.split.n_wg * p.h_kv <= 512 &&
+                   (size_t)p.split.n_sets <= (size_t)p.n_layers * p.n_seq * RP && knobs().chunk_keys == knobs().chunk_keys2;
     p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
     p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));
     p.ws_bytes = off;
@@ -464,12 +453,12 @@ static hipError_t evict_launches(const Plan& p, const void* Q, const void* K, co
     hipError_t e;
     bool gathered = true;  // the selection's last kernel gathers (or, in place, stages) the kept rows itself unless it had to stream
     if (evict_tail_small(p)) {
-        e = launch_score(p, Q, K, raw, w, st, nullptr, 0, lse, k_tail);
+        e = launch_score(p, Q, K, raw, w, st, nullptr, 0, lse, k_tail, nullptr, nullptr, true);
         if (e == hipSuccess) e = launch_pool_select(p, raw, scores_out, true, w, idx, st, K, V, K_out, V_out, stage, pos_in, pos_out, dest_bits);
     } else {
         float* pooled = scores_out ? scores_out : (float*)(w + p.off_pooled);
         const size_t zero_words = (size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride;
-        e = launch_score(p, Q, K, raw, w, st, hist, zero_words, lse, k_tail);  // also clears the selection histograms
+        e = launch_score(p, Q, K, raw, w, st, hist, zero_words, lse, k_tail, nullptr, nullptr, true);  // also clears the selection histograms
         if (e == hipSuccess) e = launch_pool(p, raw, pooled, hist, w, st);
         if (e == hipSuccess) e = launch_select(p, pooled, hist, w, idx, st, K, V, K_out, V_out, &gathered, stage, pos_in, pos_out, dest_bits);
     }
@@ -738,7 +727,7 @@ static int mse_fused_plan(const jq_shape* shape, int32_t n_q_b, Plan* p) {
     if (n_q_b < 1) return JQ_ERR_SHAPE;
     if (p->window) return JQ_ERR_SHAPE;  // the maps of Eq. 3 / Eq. 4 have no window mode
     if ((rc = make_plan(shape, false, p, true, n_q_b)) != JQ_OK) return rc;
-    if ((size_t)p->n_layers * p->cu_cgrp2[p->n_seq] * p->h_kv * sizeof(double) > p->off_seg - p->off_pooled) return JQ_ERR_UNSUPPORTED;  // never
+    if ((size_t)p->n_layers * p->cu_quad[p->n_seq] * p->h_kv * sizeof(double) > p->off_seg - p->off_pooled) return JQ_ERR_UNSUPPORTED;  // never
     return JQ_OK;
 }
 

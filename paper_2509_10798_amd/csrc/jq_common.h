@@ -20,13 +20,29 @@ constexpr int kHistStride = kHistBins + 16;  // per problem: the bins, then [0] 
 constexpr int kSelectThreads = 1024;
 constexpr int kSegLen = 1024;       // positions per pooling workgroup = entries per segment of the selection's sorted lists
 
-// Per-call sequence table, passed to kernels by value (about 2 KiB of kernarg).
+// Per-call sequence table, passed to kernels by value (about 1 KiB of kernarg).
 struct SeqTab {
     int32_t n_seq;
     int32_t cu_seq[JQ_MAX_SEQ + 1];    // token offsets
     int32_t cu_bud[JQ_MAX_SEQ + 1];    // kept-row offsets
-    int32_t cu_chunk[JQ_MAX_SEQ + 1];  // score-wave offsets (waves per sequence and head that have tiles)
-    int32_t cu_cgrp[JQ_MAX_SEQ + 1];   // score-workgroup offsets (ceil(waves / 4) workgroups per sequence and head)
+};
+
+// How the workgroups of a pass over K share the keys out, in quads of 128 keys (four 32-key tiles, one per wave).
+struct SplitArgs {
+    int32_t n, total;   // evenly: workgroup c of n takes positions c * total / n .. (c + 1) * total / n - 1 of the row of all quads,
+    int32_t gap;        // with a gap of this many between sequences, for the start-up that a change of sequence costs
+    int32_t per_layer;  // positions per layer (the gap behind it included), or workgroups per layer
+    int32_t whole;      // 1: whole workgroups for every sequence
+    int32_t q;          // total / n
+    uint32_t inv_n, inv_total, inv_layer;  // inverse() of n, total, per_layer
+};
+inline uint32_t inverse(int32_t d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d); }  // of the device's udiv()
+struct Split {
+    SplitArgs args;
+    int32_t n_wg;       // workgroups per KV head (and group of query rows)
+    int32_t n_sets;     // sets of statistics per KV head that a first pass shared out like this leaves
+    int32_t max_sets;   // ... of one (layer, sequence) at most
+    int32_t cu[JQ_MAX_SEQ + 1];  // first position, or workgroup, of every sequence in a layer
 };
 
 // Where a layer's K / V rows live: dense [T] rows per layer (block_table null), or a pool of n_pages pages of
@@ -48,8 +64,9 @@ struct Plan {
     int32_t row_tiles;    // ... and those of the second set, which follow
     int32_t row_groups;   // ceil(row_tiles / 4): 1, or the groups of rows that the first pass handles side by side
     bool by_rows;         // the second pass streams query rows past keys held in registers (jq_score_rows_kernel)
-    // tab.cu_chunk / cu_cgrp: waves and workgroups of the first pass over K (or the only one); for a second pass:
-    int32_t cu_chunk2[JQ_MAX_SEQ + 1], cu_cgrp2[JQ_MAX_SEQ + 1];
+    Split split, split2;  // the first pass over K (or the only one), and a second launch's
+    bool one_launch;      // both passes may go in one launch (jq_passes_kernel)
+    int32_t cu_quad[JQ_MAX_SEQ + 1];  // groups of 128 keys per sequence
     double scale;         // logit scale actually used
     // paged cache (block_table null: dense K, V): page = 1 << page_shift tokens, n_pages per layer's pool
     const int32_t* block_table;  // DEVICE [n_seq][max_pages]
@@ -64,11 +81,12 @@ struct Plan {
     PageMap out_map;      // where the pruned cache goes (block_table null: dense [n_layers][TB] rows)
     void* const* marks;   // host only: nullptr, or 2 * kTraceKernels events (start, stop) for jq_evict_traced
     // workspace layout (byte offsets, 256-aligned)
-    size_t off_stats, off_aug, off_hist, off_scores, off_pooled, off_idx, off_seg, off_seghdr, ws_bytes;
+    size_t off_stats, off_flags, off_aug, off_hist, off_scores, off_pooled, off_idx, off_seg, off_seghdr, ws_bytes;
 };
 
 // Largest s with cu[s] <= v (cu[0] = 0, strictly increasing, v < cu[n]).
-__host__ __device__ inline int find_seq(const int32_t* cu, int n, int64_t v) {
+template <class Table>  // a pointer to int32_t, in whatever memory
+__host__ __device__ inline int find_seq(Table cu, int n, int64_t v) {
     int lo = 0, hi = n;  // answer in [lo, hi)
     while (hi - lo > 1) {
         int mid = (lo + hi) >> 1;
@@ -134,8 +152,9 @@ __device__ inline uint32_t select_key(float x, int j, int L, int keep_first, int
 // Ablation and diagnosis knobs, read from the environment ONCE per process (first use) -- no entry point touches the
 // environment on its hot path.  jq_reload_knobs() reads them again (tests use it to force rarely taken paths).
 struct Knobs {
-    int32_t chunk_keys;   // JQ_CHUNK_KEYS: keys per wave in the pass that reads K cold (0: planned from the call's size)
+    int32_t chunk_keys;   // JQ_CHUNK_KEYS: keys per wave in the pass that reads K cold, in whole workgroups per sequence (0: planned)
     int32_t chunk_keys2;  // JQ_CHUNK_KEYS_2: the same for the second pass (0: JQ_CHUNK_KEYS if set, else planned)
+    int32_t wait_us;      // JQ_WAIT_US: how long a workgroup waits for others' statistics before it forms them itself (microseconds)
     int32_t log;          // JQ_LOG: print the HIP error string when a launch is refused
 };
 const Knobs& knobs();
@@ -221,9 +240,12 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
 // With two query sets in the plan, Q2 and `diff_part` ([n_layers][workgroups of the second pass per layer and head][h_kv]) the
 // last launch stores no scores: it leaves one partial sum per workgroup of the squared differences of the sets' maps (Eq. 5
 // forward, see launch_mse_reduce).
+// `flags_cleared_later`: the caller launches a kernel behind this that clears the plan's flags (flag_words() words at off_flags),
+// so that both passes may go in one launch.
 hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scores, char* ws, hipStream_t st,
                         uint32_t* zero = nullptr, size_t zero_words = 0, const float* lse = nullptr,
-                        const void* k_tail = nullptr, const void* Q2 = nullptr, double* diff_part = nullptr);
+                        const void* k_tail = nullptr, const void* Q2 = nullptr, double* diff_part = nullptr,
+                        bool flags_cleared_later = false);
 // Sums the per-workgroup partials of a fused launch in workgroup order and divides by the sequence length.
 hipError_t launch_mse_reduce(const Plan& p, const double* part, float* mse, hipStream_t st);
 // With `hist` the pooling kernel also builds the selection's level-1 histograms, and with `ws` on top of that

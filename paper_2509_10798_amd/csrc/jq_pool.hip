@@ -37,6 +37,8 @@ struct PoolArgs {
     int32_t keep_first, keep_last;  // always-kept positions (they land in the histogram's top bin)
     float inv_k;
     int64_t T;
+    uint64_t* flags;   // words to clear: the flags of a launch that did both passes over K (or null)
+    int32_t n_flags;
     int32_t one_L;                   // single-sequence calls: the sequence's length (0 otherwise), next to the other
                                      // scalars so that the first kernel-argument reads do not chain through the tables
     int32_t n_seg;                   // workgroups per layer and head
@@ -74,6 +76,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     static_assert(sizeof(tile) >= sizeof(float) * (kPoolBlockPos + kPoolThreads), "a whole round of loads for the halo");
     static_assert(2 * kPoolMaxHalo <= kPoolThreads, "one round of loads for the halo");
     const int g = blockIdx.y, layer = blockIdx.z;
+    if (a.flags && blockIdx.x == 0)  // the workgroups of a layer's and head's first segment share it
+        for (int i = (layer * a.h_kv + g) * kPoolThreads + (int)threadIdx.x; i < a.n_flags; i += a.n_layers * a.h_kv * kPoolThreads) a.flags[i] = 0;
     const int s = a.one_L ? 0 : find_seq(a.cu_seg, a.tab.n_seq, blockIdx.x);
     const int64_t lo = a.one_L ? 0 : a.tab.cu_seq[s], hi = a.one_L ? a.one_L : a.tab.cu_seq[s + 1];
     const int Ls = (int)(hi - lo);
@@ -299,17 +303,17 @@ hipError_t launch_map_mse(const Plan& p, const float* scores_a, float rows_a, co
 // workgroups of the comparing launch left -- lane i every 64th of them in workgroup order, then a butterfly, the same
 // order in every run -- and divides by the sequence length.
 struct MseReduceArgs {
-    const double* part;  // [n_layers][n_cgrp][h_kv]
+    const double* part;  // [n_layers][layer_quads][h_kv]
     float* mse;          // [n_layers][n_seq][h_kv]
-    int32_t n_layers, n_seq, h_kv, n_cgrp;
-    int32_t cu_cgrp[JQ_MAX_SEQ + 1];
+    int32_t n_layers, n_seq, h_kv, layer_quads;
+    int32_t cu_quad[JQ_MAX_SEQ + 1];
     int32_t cu_seq[JQ_MAX_SEQ + 1];
 };
 __global__ __launch_bounds__(64) void jq_mse_reduce_kernel(MseReduceArgs a) {
     const int i = blockIdx.x;
     const int g = i % a.h_kv, s = (i / a.h_kv) % a.n_seq, layer = i / (a.h_kv * a.n_seq);
     double sum = 0.0;
-    for (int cg = a.cu_cgrp[s] + (int)threadIdx.x; cg < a.cu_cgrp[s + 1]; cg += 64) sum += a.part[((int64_t)layer * a.n_cgrp + cg) * a.h_kv + g];
+    for (int q = a.cu_quad[s] + (int)threadIdx.x; q < a.cu_quad[s + 1]; q += 64) sum += a.part[((int64_t)layer * a.layer_quads + q) * a.h_kv + g];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
     if (threadIdx.x == 0) a.mse[i] = (float)(sum / (double)(a.cu_seq[s + 1] - a.cu_seq[s]));
@@ -318,8 +322,8 @@ __global__ __launch_bounds__(64) void jq_mse_reduce_kernel(MseReduceArgs a) {
 hipError_t launch_mse_reduce(const Plan& p, const double* part, float* mse, hipStream_t st) {
     MseReduceArgs a;
     a.part = part; a.mse = mse;
-    a.n_layers = p.n_layers; a.n_seq = p.n_seq; a.h_kv = p.h_kv; a.n_cgrp = p.cu_cgrp2[p.n_seq];
-    for (int s = 0; s <= p.n_seq; ++s) { a.cu_cgrp[s] = p.cu_cgrp2[s]; a.cu_seq[s] = p.tab.cu_seq[s]; }
+    a.n_layers = p.n_layers; a.n_seq = p.n_seq; a.h_kv = p.h_kv; a.layer_quads = p.cu_quad[p.n_seq];
+    for (int s = 0; s <= p.n_seq; ++s) { a.cu_quad[s] = p.cu_quad[s]; a.cu_seq[s] = p.tab.cu_seq[s]; }
     return launch_kernel(jq_mse_reduce_kernel, dim3((unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv)), dim3(64), 0, st, nullptr, -1, a);
 }
 
@@ -342,6 +346,8 @@ static PoolArgs make_args(const Plan& p, const float* in, float* out, uint32_t* 
     a.keep_first = p.keep_first; a.keep_last = p.keep_last;
     a.inv_k = 1.0f / (float)p.pool_k;
     a.T = p.T;
+    a.flags = p.one_launch && hist && ws && out ? (uint64_t*)(ws + p.off_flags) : nullptr;  // an eviction's pooling
+    a.n_flags = p.split.n_sets * p.h_kv;
     a.one_L = p.n_seq == 1 ? p.tab.cu_seq[1] : 0;
     a.n_seg = p.n_seg;
     for (int s = 0; s <= p.n_seq; ++s) a.cu_seg[s] = p.cu_seg[s];

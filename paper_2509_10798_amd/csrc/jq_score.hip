@@ -6,6 +6,8 @@
 //   merge:           beta_r = m_r + log2 Z_r over a sequence's partials, as -beta_r / c split into three
 //                    bf16 terms -- done by every pass-2 workgroup for its own head in its start-up (a
 //                    separate small kernel only when a sequence leaves more than 64 partials).
+// An eviction runs both passes in one launch, jq_passes_kernel: a workgroup scores the keys it has swept as soon as the others
+// that share their sequence have published their statistics.
 //   pass 2 (score):  score_j = sum_r 2^(c * (q_r.k_j - beta_r / c)).  The -beta_r/c term enters
 //                    through one extra MFMA step whose key-side operand is 1.0, so the epilogue is one
 //                    multiply, one exp2 and one add per logit.
@@ -15,7 +17,7 @@
 // Variants of the same kernels: supplied normalisers (pass 2 alone), the soft tokens' own keys or the prompt's
 // own last tokens as causally masked tiles of pass 1, keys read out of a paged pool.
 //
-// Otherwise one wave owns one (layer, sequence, KV head) and a strided set of that sequence's 32-key tiles, and
+// Otherwise a wave has one (layer, sequence, KV head) at a time and a set of that sequence's 32-key tiles (see Share), and
 // keeps the head's (up to) 128 query rows in registers as MFMA operands.  The four waves of a workgroup
 // work on the same head and fetch its query rows together (one row tile each, whole rows, turned into
 // operand order through LDS) -- gathering them one row per lane would cost every wave 32 row-strided
@@ -30,6 +32,8 @@
 // contraction elements selected by (l >> 5); both operands use the same element order, so any
 // fixed channel permutation cancels.  Result: lane l holds column (l & 31), register v holds row
 // 8*(v/4) + 4*(l>>5) + (v&3).
+#include <atomic>
+#include <random>
 #include <type_traits>
 
 #include "jq_common.h"
@@ -40,48 +44,84 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
+
 struct ScoreArgs {
-    const uint16_t* Q;
-    const uint16_t* K;
-    const uint16_t* K_tail;  // [n_layers][n_seq][n_q][h_kv][d] keys of the soft tokens themselves, or null
-    const float* lse;        // [n_layers][n_seq][n_q][h_q] caller-supplied natural-log normalisers, or null
-    double inv_scale, inv_c;        // 1 / scale, 1 / c
-    int32_t one_L, one_waves;  // single-sequence calls: the sequence's length and its number of waves per head (0
-                               // otherwise), next to the pointers, so that a wave's first kernel-argument reads
-                               // do not chain through the per-sequence tables further down
-    float2* stats;    // [n_layers][n_cgrp of pass 1][h_kv][RP]: (m, Z) per pass-1 workgroup
-    uint2* aug;       // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
-    float* scores;    // [n_layers][h_kv][T]
-    int32_t n_layers, n_seq, n_q, h_q, h_kv, group, rows, RP;
-    int32_t n_cgrp;       // workgroups per layer and head: sum over sequences of ceil(waves / 4)
-    // pass 2 only: where pass 1 left its per-workgroup statistics (its own n_cgrp and per-sequence offsets),
-    // and whether this launch merges them itself (otherwise jq_combine_kernel has filled `aug`)
-    int32_t n_part, fuse_combine;
-    int32_t group_shift;  // log2(group) when group is a power of two, else -1
-    int32_t window;       // 1: the queries are the sequence's own last n_q tokens; query i sees keys 0 .. L - n_q + i
+    // What a workgroup needs to find its share and make its first requests comes first, in the few lines of constant memory that
+    // kernel_lines() has fetched at once: a wave's first reads of its arguments take about 1 us each where they chain.
+    int32_t n_layers, n_seq, h_kv;
+    uint32_t inv_h_kv;    // for udiv()
     int32_t n_rg, rg0;    // first pass: groups of NQT query-row tiles in this launch (1 unless a head has more than
                           // kMaxRowTiles), and the first of them
-    float c;             // scale * log2(e)
+    int32_t one_L;        // single-sequence calls: the sequence's length (0 otherwise): no per-sequence table is read then
+    int32_t layer_quads;  // groups of four tiles (128 keys) per layer and head, rounded up per sequence
+    SplitArgs own;        // how this launch's workgroups share the keys out
+    int32_t n_q, h_q, group, rows, RP;
+    int32_t group_shift;  // log2(group) when group is a power of two, else -1
+    int32_t tiles1;       // two query sets: row tiles of the first (kOneSet: there is one set)
+    const uint16_t* Q;
+    const uint16_t* K;
     int64_t T;
-    uint32_t* zero;      // combine: words to clear for the later selection stage (nullable)
+    const uint16_t* K_tail;  // [n_layers][n_seq][n_q][h_kv][d] keys of the soft tokens themselves, or null
+    uint32_t* zero;      // words to clear for the later selection stage (nullable)
     uint64_t zero_words;
+    float2* stats;    // [sets][h_kv][RP]: (m, Z) of every share of a (layer, sequence), see Share
+    float c;             // scale * log2(e)
+    int32_t window;       // 1: the queries are the sequence's own last n_q tokens; query i sees keys 0 .. L - n_q + i
+    // both passes in one launch: flags[h_kv][n_sets], set to `token` when a set of statistics is complete, and how long (ticks of
+    // 10 ns) a workgroup waits for others' before it forms them itself
+    uint64_t* flags;
+    uint64_t token;
+    int64_t wait_ticks;
+    int32_t n_sets;
+    float* scores;        // [n_layers][h_kv][T]
+    const float* lse;     // [n_layers][n_seq][n_q][h_q] caller-supplied natural-log normalisers, or null
+    uint2* aug;           // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
+    double inv_scale, inv_c;  // 1 / scale, 1 / c
+    SplitArgs part;       // how the workgroups that left the statistics shared the keys out (second pass alone, merge)
+    int32_t fuse_combine; // second pass alone: it merges the statistics itself (otherwise jq_combine_kernel has filled `aug`)
     // paged K (PAGED kernels): K is [n_layers][n_pages][1 << page_shift][h_kv][d]; token t of sequence s lives in
     // page block_table[s * max_pages + (t >> page_shift)]
-    const int32_t* block_table;
     int32_t page_shift, n_pages, max_pages;
-    // the per-sequence tables come last: every scalar above sits in the first few hundred bytes of the kernel
-    // arguments, which a wave fetches in one go
-    int32_t cu_part[JQ_MAX_SEQ + 1];
-    SeqTab tab;
+    const int32_t* block_table;
     // Two query sets in one call (training-side forward, Eq. 3-5): row tiles tiles1 .. of a head hold the rows of the second
     // set.  Their launch of jq_score_rows_kernel compares the two maps instead of storing either and leaves one partial sum
-    // of squared differences per workgroup.  (tiles1: past all row tiles where there is one set.)
+    // of squared differences per workgroup.
     const uint16_t* Q2;
-    int32_t n_q2, rows2, tiles1;
+    int32_t n_q2, rows2;
     float inv_rows1, inv_rows2;  // 1 / summed probability rows of either map
-    double* diff_part;           // [n_layers][n_cgrp][h_kv]
+    double* diff_part;           // [n_layers][layer_quads][h_kv]
+    int32_t cu_seq[JQ_MAX_SEQ + 1], cu_quad[JQ_MAX_SEQ + 1];
+    int32_t cu_wg[JQ_MAX_SEQ + 1], cu_part[JQ_MAX_SEQ + 1];  // Split::cu of `own` and `part`
 };
 constexpr int kOneSet = 0x7FFFFFFF;  // tiles1 of a call with one query set
+
+// A kernel's own arguments, which lie in constant memory, reached through a pointer that the compiler knows nothing about: what is
+// read through it is read where it is used.  A workgroup with several shares repeats everything below; without this the
+// compiler keeps every scalar of every phase in registers across all of them (200 spilled).
+typedef const ScoreArgs __attribute__((address_space(4))) KArgs;
+typedef const SplitArgs __attribute__((address_space(4))) KSplit;
+__device__ __forceinline__ KArgs& kernel_args() {
+    KArgs* p = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *p;
+}
+// The first lines of a kernel's arguments, requested together.
+__device__ __forceinline__ void kernel_lines() {
+    const_i32_ptr p = (const_i32_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    const int32_t a = p[0], b = p[16], c = p[32], d = p[48], e = p[64];
+    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
+}
+// x / d for the d that `inv` was made of (ceil(2^32 / d), 0 for 1): the product is at most one too large
+__device__ __forceinline__ uint32_t udiv(uint32_t x, uint32_t d, uint32_t inv) {
+    const uint32_t q = __umulhi(x, inv), less = (int32_t)(x - q * d) < 0 ? 1u : 0u;
+    return inv ? q - less : x;
+}
+__device__ __forceinline__ int lane_again() {  // the same for what derives from the lane
+    int lane = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 
 constexpr int kSlotBytes = kKeyTile * kHeadDim * 2;  // 8 KiB
 
@@ -96,6 +136,13 @@ __device__ __forceinline__ void wait_tile_landed() {
     asm volatile("" ::: "memory");
 }
 
+// The same with one younger request, a store, that may still be on its way (vector memory operations complete in order).
+__device__ __forceinline__ void wait_tile_landed_before_store() {
+    __builtin_amdgcn_s_waitcnt(0x0F71);  // vmcnt(1)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
 // The fragments just read from an LDS slot must be in registers before the slot is refilled.
 __device__ __forceinline__ void wait_frags_read() {
     asm volatile("" ::: "memory");
@@ -105,53 +152,150 @@ __device__ __forceinline__ void wait_frags_read() {
     asm volatile("" ::: "memory");
 }
 
-// Which (layer, sequence, head) and which of its key tiles this wave owns.  A sequence of L keys gets
-// W = ceil(L / chunk_keys) waves per head; wave w of them takes the 32-key tiles w, w + W, w + 2W, ...
-// Interleaving the tiles (instead of giving each wave one contiguous range) makes all waves that run
-// at the same time sweep one window of the key tensor, which DRAM serves at close to its streaming rate.
-// The four waves of a workgroup are consecutive waves of ONE (layer, sequence, head), so they can share
-// the head's query rows; a sequence whose W is not a multiple of four leaves the last workgroup's
-// surplus waves without tiles (they only help with the query rows).
-struct WaveItem {
-    int layer, seq, g;
-    int rg;                           // group of query-row tiles (0 unless the launch has several)
-    int wave, n_waves;                // w and W
-    int L;                            // keys in the sequence
-    int n_tiles;                      // tiles this wave owns (0: surplus wave)
-    int64_t tok0;                     // first token of the sequence in the flattened T axis
+// ---- which keys a workgroup sweeps ----------------------------------------------------------------
+// The keys of a head, over all layers and sequences of the call, are shared out in steps of four tiles (one per wave), called
+// quads; a quad never straddles sequences.  Either every sequence gets whole workgroups, or (evenly) all quads in a row are
+// dealt to the workgroups in equal, contiguous portions, whatever sequences those touch: then all finish together, and a
+// workgroup has a SHARE of one (layer, sequence) or of several in turn.
+// The workgroups that share a (layer, sequence) take its quads in the order in which they reach them, counted in steps on
+// every workgroup's own clock, so that all waves that run at the same time sweep one moving window of the key tensor, which
+// DRAM serves at close to its streaming rate (one contiguous range per workgroup instead took 49 us cold against 45 on the
+// 128K layer).  Dealt evenly, a (layer, sequence) has at most one workgroup that comes to it late (the first), workgroups that
+// work on nothing else, and one that leaves early (the last), so the number of quads taken before a workgroup's step i has a
+// closed form.
+struct Share {
+    int layer, seq, L, seq_tiles;  // seq_tiles: 32-key tiles of the sequence
+    int64_t tok0;                  // first token of the sequence in the flattened T axis
+    int set0, n_sets, rank;        // sets of statistics of the (layer, sequence): set0 .. set0 + n_sets - 1, here set0 + rank
+    int x, len;                    // the workgroup's steps for it: x .. x + len - 1
+    int full, at, at_last, q;      // workgroups with nothing else; of those, how many come before this one in a step; in step q
+    int late_from, late_n, early;  // first step (counted with its place in a step) and steps of the late one; steps of the early one
+    __device__ __forceinline__ int quad(int i) const {
+        return (i < q ? full * i + at : full * q + at_last) + min(max(i - late_from, 0), late_n) + min(i, early);
+    }
+};
+__device__ __forceinline__ int split_start(KSplit& sp, int c) { return (int)udiv((uint32_t)c * (uint32_t)sp.total, (uint32_t)sp.n, sp.inv_n); }
+__device__ __forceinline__ int split_owner(KSplit& sp, int pos) {  // the largest c with split_start(c) <= pos
+    return (int)udiv(((uint32_t)pos + 1u) * (uint32_t)sp.n - 1u, (uint32_t)sp.total, sp.inv_total);
+}
+__device__ __forceinline__ int quads_of(KArgs& a, int seq) { return a.one_L ? a.layer_quads : a.cu_quad[seq + 1] - a.cu_quad[seq]; }
+// sets of statistics of a (layer, sequence); `cu`: the split's table
+__device__ __forceinline__ void sets_of(KArgs& a, KSplit& sp, const_i32_ptr cu, int layer, int seq, int& set0, int& n) {
+    const int at = layer * sp.per_layer + (a.one_L ? 0 : cu[seq]);
+    if (sp.whole) {
+        set0 = at;
+        n = a.one_L ? sp.per_layer : cu[seq + 1] - cu[seq];
+        return;
+    }
+    const int ca = split_owner(sp, at), cb = split_owner(sp, at + quads_of(a, seq) - 1);
+    set0 = layer * a.n_seq + seq + ca;  // along the row either the sequence or the workgroup (or both) steps on: no number twice
+    n = cb - ca + 1;
+}
+// the first (or last) (layer, sequence) of workgroup c
+__device__ __forceinline__ void first_share(KArgs& a, int c, bool last, int& layer, int& seq) {
+    KSplit& sp = a.own;
+    const int pos = sp.whole ? c : last ? split_start(sp, c + 1) - 1 : split_start(sp, c);
+    layer = a.n_layers == 1 ? 0 : (int)udiv((uint32_t)pos, (uint32_t)sp.per_layer, sp.inv_layer);
+    seq = a.one_L ? 0 : find_seq(a.cu_wg, a.n_seq, pos - layer * sp.per_layer);
+    if (!last && !sp.whole && pos - layer * sp.per_layer - (a.one_L ? 0 : a.cu_wg[seq]) >= quads_of(a, seq))  // in the gap behind it
+        if (++seq == a.n_seq) { seq = 0; ++layer; }
+}
+__device__ __forceinline__ Share share_of(KArgs& a, int c, int layer, int seq) {
+    KSplit& sp = a.own;
+    Share h;
+    h.layer = layer; h.seq = seq;
+    h.tok0 = a.one_L ? 0 : a.cu_seq[seq];
+    h.L = a.one_L ? a.one_L : a.cu_seq[seq + 1] - a.cu_seq[seq];
+    h.seq_tiles = (h.L + kKeyTile - 1) / kKeyTile;
+    const int nq = (h.seq_tiles + kScoreWaves - 1) / kScoreWaves;
+    sets_of(a, sp, a.cu_wg, layer, seq, h.set0, h.n_sets);
+    h.late_from = h.late_n = h.early = h.at_last = 0;
+    if (sp.whole) {
+        h.rank = c - h.set0;
+        h.x = 0;
+        const uint32_t steps = (uint32_t)(nq - h.rank + h.n_sets - 1);  // >= n_sets: no more workgroups than quads
+        h.len = (int)(sp.inv_n ? udiv(steps, (uint32_t)h.n_sets, sp.inv_n) : steps / (uint32_t)h.n_sets);
+        h.full = h.n_sets; h.at = h.rank; h.q = 0x7FFFFFFF;
+        return h;
+    }
+    const int ca = h.set0 - (layer * a.n_seq + seq), cb = ca + h.n_sets - 1;
+    const int q0 = layer * sp.per_layer + (a.one_L ? 0 : a.cu_wg[seq]), b0 = split_start(sp, c), b1 = split_start(sp, c + 1);
+    h.rank = c - ca;
+    h.x = max(b0, q0) - b0;
+    h.len = min(b1, q0 + nq) - b0 - h.x;
+    h.q = sp.q;
+    if (h.n_sets == 1) {
+        h.full = h.at = 0;
+        h.late_from = h.x; h.late_n = h.len;
+    } else {
+        h.full = h.n_sets - 2;
+        h.at = min(max(h.rank - 1, 0), h.full);
+        const int s1 = split_start(sp, ca + 1);
+        h.at_last = c == ca ? 0 : b0 - s1 - h.q * h.at;
+        h.late_from = q0 - split_start(sp, ca) - (c > ca ? 1 : 0);
+        h.late_n = s1 - q0;
+        h.early = q0 + nq - split_start(sp, cb);
+    }
+    return h;
+}
+
+// The tiles of one wave of a share in the order in which it takes them, forwards or backwards: their numbers rise evenly but for
+// the few steps at which another workgroup joins or leaves (Share::quad for every tile cost the sweeps a twentieth: a wave
+// issues in order, and the matrix core waits meanwhile).
+template <bool BACK>
+struct Walk {
+    int i, t, stride, left;  // step, its tile, distance to the next step's and for how many more steps it holds
+    __device__ __forceinline__ void turn(const Share& h) {
+        const int at[5] = {h.q - 1, h.q, h.late_from, h.late_from + h.late_n, h.early};
+        int next = BACK ? -1 : 0x7FFFFFFF;
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            if (BACK ? at[k] < i : at[k] > i) next = BACK ? max(next, at[k]) : min(next, at[k]);
+        stride = kScoreWaves * (BACK ? h.quad(i - 1) - h.quad(i) : h.quad(i + 1) - h.quad(i));
+        left = BACK ? i - next : next - i;
+    }
+    __device__ __forceinline__ void start(const Share& h, int from, int wave) {
+        i = from;
+        t = kScoreWaves * h.quad(i) + wave;
+        turn(h);
+    }
+    __device__ __forceinline__ void step(const Share& h) {
+        i += BACK ? -1 : 1;
+        t += stride;
+        if (__builtin_expect(--left == 0, 0)) turn(h);
+    }
 };
 
-__device__ __forceinline__ void wave_item(const ScoreArgs& a, bool reverse, WaveItem& w) {
-    uint32_t b = blockIdx.x;  // the grid is exactly n_layers * n_cgrp * n_rg * h_kv workgroups (below 2^31: 32-bit arithmetic)
-    if (reverse) b = gridDim.x - 1 - b;
-    // readfirstlane makes the wave index (and everything derived from it) a scalar for the compiler
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    w.g = (int)(b % (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row
-    uint32_t rest = b / (uint32_t)a.h_kv;
-    w.rg = 0;
+// Where a workgroup starts: its KV head, group of query rows, number among their workgroups, and its first share (`last`: it takes
+// its shares, and the launch its workgroups, from the end).
+struct Place { int g, rg, c, layer, seq; };
+__device__ __forceinline__ Place place_of(KArgs& a, bool last) {
+    uint32_t b = blockIdx.x;  // below 2^31: 32-bit arithmetic
+    if (last) b = gridDim.x - 1 - b;
+    Place at;
+    uint32_t rest = udiv(b, (uint32_t)a.h_kv, a.inv_h_kv);
+    at.g = (int)(b - rest * (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row
+    at.rg = a.rg0;
     if (a.n_rg > 1) {  // row groups next: the workgroups that read the same keys run side by side (with eight heads on one XCD)
-        w.rg = a.rg0 + (int)(rest % (uint32_t)a.n_rg);
+        at.rg += (int)(rest % (uint32_t)a.n_rg);
         rest /= (uint32_t)a.n_rg;
-    } else {
-        w.rg = a.rg0;
     }
-    const int cg = (int)(rest % (uint32_t)a.n_cgrp);
-    w.layer = (int)(rest / (uint32_t)a.n_cgrp);
-    if (a.one_L) {  // one sequence: nothing to look up
-        w.seq = 0;
-        w.L = a.one_L;
-        w.n_waves = a.one_waves;
-        w.wave = cg * kScoreWaves + wv;
-        w.tok0 = 0;
+    at.c = (int)rest;
+    first_share(a, at.c, last, at.layer, at.seq);
+    return at;
+}
+// on to the workgroup's next share (the one before it with `last`); false if `h` was the final one
+__device__ __forceinline__ bool next_share(KArgs& a, const Share& h, bool last, Place& at) {
+    KSplit& sp = a.own;
+    if (sp.whole) return false;
+    if (last) {
+        if (h.x <= sp.gap) return false;  // what precedes the (layer, sequence) here is a gap at most
+        if (--at.seq < 0) { at.seq = a.n_seq - 1; --at.layer; }
     } else {
-        w.seq = find_seq(a.tab.cu_cgrp, a.tab.n_seq, cg);
-        w.L = a.tab.cu_seq[w.seq + 1] - a.tab.cu_seq[w.seq];
-        w.n_waves = a.tab.cu_chunk[w.seq + 1] - a.tab.cu_chunk[w.seq];
-        w.wave = (cg - a.tab.cu_cgrp[w.seq]) * kScoreWaves + wv;
-        w.tok0 = a.tab.cu_seq[w.seq];
+        if (h.x + h.len + sp.gap >= split_start(sp, at.c + 1) - split_start(sp, at.c)) return false;
+        if (++at.seq == a.n_seq) { at.seq = 0; ++at.layer; }
     }
-    const int seq_tiles = (w.L + kKeyTile - 1) / kKeyTile;  // >= n_waves, since a chunk is at least one tile
-    w.n_tiles = w.wave < w.n_waves ? (seq_tiles - w.wave + w.n_waves - 1) / w.n_waves : 0;
+    return true;
 }
 
 // ---- key tiles: global -> LDS -------------------------------------------------------------------
@@ -268,49 +412,69 @@ __device__ __forceinline__ void bare_barrier() {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
-// Where the query rows that this wave stages live (every wave computes addresses, so that the loads themselves
-// can be issued unconditionally; waves beyond the row tiles take the last tile's and never store them).  Rows past
-// the end take the address of row 0 of the head, in bounds, and are zeroed when staged -- `pad`, bit i: load i is
-// such a row.
+// The query rows that this wave stages: requested into registers, 16 B per lane, four whole 256-byte rows per instruction.  Every
+// wave requests (those beyond the row tiles the last tile's, and they never store them), so that the requests sit in one basic
+// block with others.  Rows past the end are zeros.  With a power-of-two group of up to 32 heads a tile's rows lie where
+// a key tile's would: a lane part that never changes and a uniform part per request (4 i + a, a < 4, splits without carry),
+// through a resource that ends with the last token, behind which the hardware returns zeros.
 template <int NQT>
-__device__ __forceinline__ void q_rows_where(const ScoreArgs& a, const WaveItem& w, int lane, const u32x4* (&src)[8], uint32_t& pad) {
+__device__ __forceinline__ void q_rows_request(KArgs& a, const Share& h, int g, int rg, int lane, u32x4 (&raw)[8]) {
     const int wv = min(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), NQT - 1);
-    const int rt = w.rg * NQT + wv;  // (uniform)
+    const int rt = rg * NQT + wv;  // (uniform)
     const bool second = rt >= a.tiles1;
-    const int n_q = second ? a.n_q2 : a.n_q, rows = second ? a.rows2 : a.rows;
-    const char* qbase = (const char*)(second ? a.Q2 : a.Q) + ((int64_t)(w.layer * a.n_seq + w.seq) * n_q) * a.h_q * kHeadDim * 2;
-    pad = 0;
+    const int n_q = second ? a.n_q2 : a.n_q, r0 = (second ? rt - a.tiles1 : rt) * kRowTile;
+    const char* qbase = (const char*)(second ? a.Q2 : a.Q) + (((int64_t)(h.layer * a.n_seq + h.seq) * n_q) * a.h_q + g * a.group) * kHeadDim * 2;
+    const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
+    const int gs = a.group_shift;
+    const uint32_t rl = (uint32_t)lane >> 4, piece = ((uint32_t)lane & 15u) ^ rl;
+    if (gs >= 0 && gs <= 5 && tok_bytes < (1 << 25)) {  // uniform; a tile's bytes fit a 32-bit offset
+        const int it0 = r0 >> gs, left = min(n_q - it0, kRowTile);  // tokens that the tile reaches, none past the end
+        const uint32_t tok32 = (uint32_t)tok_bytes, group = (uint32_t)a.group;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(qbase + it0 * tok_bytes), 0,
+            left > 0 ? (int)((uint32_t)(left - 1) * tok32 + group * (kHeadDim * 2)) : 0, 0x00020000);
+        const uint32_t tq = (rl >> gs) * tok32 + (rl & (group - 1)) * (kHeadDim * 2) + (piece << 4);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = 4 * i + (lane >> 4);
-        const int row = (second ? rt - a.tiles1 : rt) * kRowTile + r;
-        const bool valid = row < rows;
-        const int rowc = valid ? row : 0;
-        int it, hh;
-        if (a.group_shift >= 0) { it = rowc >> a.group_shift; hh = rowc & (a.group - 1); }
-        else { it = rowc / a.group; hh = rowc % a.group; }
-        const int c = (lane & 15) ^ (r & 15);
-        src[i] = (const u32x4*)(qbase + ((int64_t)it * a.h_q + (w.g * a.group + hh)) * kHeadDim * 2 + c * 16);
-        pad |= valid ? 0u : 1u << i;
+        for (int i = 0; i < 8; ++i)
+            raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(tq ^ (64u * (i & 3))),
+                                                           (int)(((uint32_t)(4 * i) >> gs) * tok32 + ((uint32_t)(4 * i) & (group - 1)) * (kHeadDim * 2)), 0);
+    } else {
+        const int rows = second ? a.rows2 : a.rows;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = 4 * i + (lane >> 4), row = r0 + r, rowc = row < rows ? row : 0;
+            int it, hh;
+            if (gs >= 0) { it = rowc >> gs; hh = rowc & (a.group - 1); }
+            else { it = rowc / a.group; hh = rowc % a.group; }
+            const u32x4 v = *(const u32x4*)(qbase + it * tok_bytes + (int64_t)hh * (kHeadDim * 2) + (((lane & 15) ^ (r & 15)) << 4));
+            raw[i] = row < rows ? v : u32x4{0u, 0u, 0u, 0u};
+        }
     }
 }
 // ... and their way through LDS into operand order, with the first key tile in flight.  Every wave of the
 // workgroup must call this (two barriers).
 template <int NQT>
-__device__ __forceinline__ void q_rows_stage(int lane, char* lds_base, const u32x4 (&raw)[8], uint32_t pad, bf16x8 (&qf)[NQT][8]) {
+__device__ __forceinline__ void q_rows_stage(int lane, char* area, int stride, const u32x4 (&raw)[8], bf16x8 (&qf)[NQT][8]) {
     static_assert(NQT <= kScoreWaves, "one wave per query-row tile");
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (wv < NQT) {
-        const uint32_t slot = lds_addr(lds_base + (wv * 2 + 1) * kSlotBytes);
+        const uint32_t slot = lds_addr(area + wv * stride);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lds_put16(slot + 1024u * i + 16u * lane, (pad >> i) & 1u ? u32x4{0u, 0u, 0u, 0u} : raw[i]);
+        for (int i = 0; i < 8; ++i) lds_put16(slot + 1024u * i + 16u * lane, raw[i]);
         lds_wait_all();
     }
     bare_barrier();
 #pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds_base + (qt * 2 + 1) * kSlotBytes), qf[qt], lane);
+    for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(area + qt * stride), qf[qt], lane);
     bare_barrier();
 }
+
+// LDS of a pass: every wave's two tile slots; the kernel of both passes keeps more behind them.
+constexpr int kSlotsBytes = kScoreWaves * 2 * kSlotBytes;
+constexpr int kLdsQ = kSlotsBytes;                                  // query rows of the present (layer, sequence), one slot per row tile
+constexpr int kLdsSet = kLdsQ + kMaxRowTiles * kSlotBytes;          // the set of statistics formed last (a float2 per row)
+constexpr int kLdsAug = kLdsSet + kMaxRowTiles * kRowTile * 8;     // the rows' normalisers
+constexpr int kLdsWord = kLdsAug + kMaxRowTiles * kRowTile * 8;
+constexpr int kLdsBoth = kLdsWord + 16;
 
 struct KeyStream {
     __amdgpu_buffer_rsrc_t rsrc;  // this head's rows of the whole sequence (PAGED: of the layer's whole pool)
@@ -320,21 +484,26 @@ struct KeyStream {
 };
 
 template <bool PAGED>
-__device__ __forceinline__ KeyStream key_stream(const ScoreArgs& a, const WaveItem& w) {
+__device__ __forceinline__ KeyStream key_stream(KArgs& a, int layer, int seq, int64_t tok0, int L, int g) {
     KeyStream ks;
     ks.row_bytes = (uint32_t)a.h_kv * kHeadDim * 2;
     // the resource covers exactly this head's rows of the sequence, or of the layer's pool (the host checks
     // that this is below 4 GiB); every generated offset stays inside it
-    const int64_t first_row = PAGED ? ((int64_t)w.layer * a.n_pages) << a.page_shift : (int64_t)w.layer * a.T + w.tok0;
-    const uint32_t n_rows = PAGED ? (uint32_t)a.n_pages << a.page_shift : (uint32_t)w.L;
-    const char* kseq = (const char*)a.K + (first_row * a.h_kv + w.g) * kHeadDim * 2;
+    const int64_t first_row = PAGED ? ((int64_t)layer * a.n_pages) << a.page_shift : (int64_t)layer * a.T + tok0;
+    const uint32_t n_rows = PAGED ? (uint32_t)a.n_pages << a.page_shift : (uint32_t)L;
+    const char* kseq = (const char*)a.K + (first_row * a.h_kv + g) * kHeadDim * 2;
     const uint32_t bytes = (n_rows - 1) * ks.row_bytes + kHeadDim * 2;
     ks.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kseq, 0, (int)bytes, 0x00020000);
-    ks.pages = PAGED ? a.block_table + (int64_t)w.seq * a.max_pages : nullptr;
+    ks.pages = PAGED ? a.block_table + (int64_t)seq * a.max_pages : nullptr;
     ks.page_shift = (uint32_t)a.page_shift;
     ks.page_mask = (1u << a.page_shift) - 1u;
     ks.last_page = (uint32_t)a.n_pages - 1u;
     return ks;
+}
+
+template <bool PAGED>
+__device__ __forceinline__ KeyStream key_stream(KArgs& a, const Share& h, int g) {
+    return key_stream<PAGED>(a, h.layer, h.seq, h.tok0, h.L, g);
 }
 
 // Byte offset of sequence tile t inside the key stream's resource.  A page holds a whole number of 32-key
@@ -350,7 +519,6 @@ __device__ __forceinline__ uint32_t tile_offset(const KeyStream& ks, int t, int 
 // One table word per tile, at a wave-uniform address.  The table is read-only for the whole launch, so it is
 // read through the constant address space: that makes the load a scalar one with a wait of its own -- a
 // vector load would have to be waited for together with every key tile in flight.
-typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
 template <bool PAGED>
 __device__ __forceinline__ int tile_page(const KeyStream& ks, int t) {
     return PAGED ? ((const_i32_ptr)ks.pages)[((uint32_t)t * kKeyTile) >> ks.page_shift] : 0;
@@ -414,9 +582,9 @@ __device__ __forceinline__ float exp2_sum_stage(Step step, Arg arg) {
 __device__ __forceinline__ f32x16 mfma_bf16(bf16x8 a, bf16x8 b, f32x16 acc) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0); }
 __device__ __forceinline__ f32x16 zero_acc() { return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; }
 __device__ __forceinline__ f32x16 stats_chain(const bf16x8 (&kf)[8], const bf16x8 (&q)[8]) {
-    f32x16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    f32x16 acc = zero_acc();
 #pragma unroll
-    for (int k8 = 0; k8 < 8; ++k8) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[k8], q[k8], acc, 0, 0, 0);
+    for (int k8 = 0; k8 < 8; ++k8) acc = mfma_bf16(kf[k8], q[k8], acc);
     return acc;
 }
 
@@ -456,41 +624,42 @@ __device__ __forceinline__ void stats_tile(const bf16x8 (&kf)[8], const bf16x8 (
     }
 }
 
-template <int NQT, bool PAGED>
-__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs a) {
-    __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
-    WaveItem w;
-    wave_item(a, false, w);
-    const int lane = threadIdx.x & 63;
-    const int half = lane >> 5;
-    char* slots = &lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))][0][0];
+// A workgroup's share of one (layer, sequence): its waves sweep their tiles and leave one set of statistics, in a.stats.
+// SHARED: the launch does both passes (see jq_passes_kernel): others read the set, the query rows stay in LDS (`q_there`: they are).
+template <int NQT, bool PAGED, bool SHARED>
+__device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int rg, char* lds, bool q_there = false) {
+    const int lane = lane_again(), half = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char* slots = lds + wv * 2 * kSlotBytes;
+    auto tile_of = [&](int k) __attribute__((always_inline)) { return kScoreWaves * h.quad(h.x + k) + wv; };
+    const int n_tiles = h.len - (tile_of(h.len - 1) >= h.seq_tiles ? 1 : 0);  // only the sequence's last quad may lack tiles
 
-    const KeyStream ks = key_stream<PAGED>(a, w);
+    const KeyStream ks = key_stream<PAGED>(a, h, g);
     const uint32_t tl = tile_lane(lane, ks.row_bytes);
     // With the soft tokens' own keys in the softmax, the sequence's first wave takes them as further tiles
     // after its prompt tiles (same row stride, n_q rows), masked causally per query row.
-    const int n_tail = (a.K_tail && w.wave == 0) ? (a.n_q + kKeyTile - 1) / kKeyTile : 0;  // wave 0 always has tiles
-    const int n_all = w.n_tiles + n_tail;
+    const int n_tail = (a.K_tail && h.rank == 0 && wv == 0) ? (a.n_q + kKeyTile - 1) / kKeyTile : 0;  // wave 0 always has tiles
+    const int n_all = n_tiles + n_tail;
     __amdgpu_buffer_rsrc_t tail_rsrc = ks.rsrc;
     if (n_tail) {
-        const char* kt = (const char*)a.K_tail + ((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q * a.h_kv + w.g) * kHeadDim * 2;
+        const char* kt = (const char*)a.K_tail + ((int64_t)(h.layer * a.n_seq + h.seq) * a.n_q * a.h_kv + g) * kHeadDim * 2;
         tail_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kt, 0, (int)((uint32_t)(a.n_q - 1) * ks.row_bytes + kHeadDim * 2),
                                                       0x00020000);
     }
-    // the wave's k-th tile is tile w.wave + k * w.n_waves of the sequence and uses slot k & 1.  PAGED: tiles are
+    // The wave's k-th tile is tile_of(k) of the sequence and uses slot k & 1.  PAGED: tiles are
     // requested in the order k = 0, 1, 2, ...; the table word of the NEXT request is loaded while this one is
-    // issued, so its latency never sits in front of a tile's loads (`first_page` primes the sequence).
+    // issued, so its latency never sits in front of a tile's loads (primed where a sweep starts).
     int page_next = 0;
-    auto first_page = [&]() __attribute__((always_inline)) { if (PAGED && w.n_tiles > 0) page_next = tile_page<PAGED>(ks, w.wave); };
+    Walk<false> walk;  // at the next tile to request
     auto fetch = [&](int k) __attribute__((always_inline)) {
-        if (k < w.n_tiles) {
-            const int t = w.wave + k * w.n_waves;
-            const int page = page_next;
-            if (PAGED && k + 1 < w.n_tiles) page_next = tile_page<PAGED>(ks, t + w.n_waves);
+        if (k < n_tiles) {
+            const int t = walk.t, page = page_next;
+            walk.step(h);
+            if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
             fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes,
-                       w.L - t * kKeyTile, tl, lane);
+                       h.L - t * kKeyTile, tl, lane);
         } else {
-            const int t = k - w.n_tiles;
+            const int t = k - n_tiles;
             fetch_tile(tail_rsrc, slots + (k & 1) * kSlotBytes, (uint32_t)t * kKeyTile * ks.row_bytes, ks.row_bytes,
                        a.n_q - t * kKeyTile, tl, lane);
         }
@@ -501,39 +670,41 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
     // As in the second pass the query rows are requested first, into registers, the key tile after them, and the
     // rows pass through LDS while the tile is in flight (explicit LDS instructions, every request unconditional in
     // one basic block: see lds_addr()).  A wave without tiles requests the sequence's first tile and drops it.
+    walk.start(h, h.x, wv);
+    const int t_first = n_tiles > 0 ? walk.t : 0;
+    const int page_first = PAGED ? tile_page<PAGED>(ks, t_first) : 0;
+    walk.step(h);
+    if (PAGED && n_tiles > 1) page_next = tile_page<PAGED>(ks, walk.t);
+    const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
+    const int valid_first = min(kKeyTile, h.L - t_first * kKeyTile);
     bf16x8 qf[NQT][8];
-    {
-        const u32x4* qsrc[8];
-        uint32_t qpad;
-        q_rows_where<NQT>(a, w, lane, qsrc, qpad);
-        const int t_first = w.n_tiles > 0 ? w.wave : 0;
-        const int page_first = PAGED ? tile_page<PAGED>(ks, t_first) : 0;
-        if (PAGED && w.n_tiles > 1) page_next = tile_page<PAGED>(ks, t_first + w.n_waves);
-        const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
-        const int valid_first = min(kKeyTile, w.L - t_first * kKeyTile);
-        __builtin_amdgcn_sched_barrier(0);
-        u32x4 qraw[8];
+    if (SHARED && q_there) {
+        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) qraw[i] = *qsrc[i];
+        for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
+    } else {
+        u32x4 qraw[8];
+        q_rows_request<NQT>(a, h, g, rg, lane, qraw);
         __builtin_amdgcn_sched_barrier(0);
         fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
         __builtin_amdgcn_sched_barrier(0);
-        q_rows_stage<NQT>(lane, &lds[0][0][0], qraw, qpad, qf);
+        q_rows_stage<NQT>(lane, SHARED ? lds + kLdsQ : lds + kSlotBytes, SHARED ? kSlotBytes : 2 * kSlotBytes, qraw, qf);
     }
     const float c = a.c;
     float m[NQT], z[NQT];
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) { m[qt] = -1.0e30f; z[qt] = 0.0f; }
-    if (n_all > 0) {  // not a surplus wave of the sequence's last workgroup
+    if (n_all > 0) {  // not a wave without tiles in the sequence's last quad
 
     // Every load older than the second tile's eight (first tile, query rows) is covered
     // by the first wait of the sweep.  Tiles that lie entirely inside the keys every query row sees (all L
     // prompt keys, or the L - n_q keys in front of the window when the queries are the prompt's own last
     // tokens) need no mask; the others -- the sequence's partial last tile, the window's tiles -- are the
     // last of the tiles of whichever waves own them.
-    const int n_common = a.window ? w.L - a.n_q : w.L;
+    const int n_common = a.window ? h.L - a.n_q : h.L;
     const int common_tiles = n_common / kKeyTile;  // sequence tiles 0 .. common_tiles - 1 are unmasked
-    const int n_full = common_tiles > w.wave ? min(w.n_tiles, (common_tiles - 1 - w.wave) / w.n_waves + 1) : 0;
+    int n_full = n_tiles;
+    while (n_full > 0 && tile_of(n_full - 1) >= common_tiles) --n_full;
     // Besides the hot sweep's body the kernel holds ONE general one, for the few masked tiles (partial last tile, window,
     // soft tokens' own keys) and the rare repeat of a sweep.  (A copy per case made the kernel 45 KB of code, for no
     // gain in time.)
@@ -554,12 +725,12 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
             // soft token of the lane's row (row r = i * group + hh): it sees soft tokens 0..i
-            const int soft_i = a.window || k >= w.n_tiles ? ((w.rg * NQT + qt) * kRowTile + l) / a.group : 0;
-            if (k < w.n_tiles) {
-                const int t0 = (w.wave + k * w.n_waves) * kKeyTile;
-                valid[qt] = (a.window ? n_common + soft_i + 1 : w.L) - t0;
+            const int soft_i = a.window || k >= n_tiles ? ((rg * NQT + qt) * kRowTile + l) / a.group : 0;
+            if (k < n_tiles) {
+                const int t0 = tile_of(k) * kKeyTile;
+                valid[qt] = (a.window ? n_common + soft_i + 1 : h.L) - t0;
             } else {  // soft token t * 32 + j is visible to the row of soft token i iff it is <= i
-                valid[qt] = soft_i + 1 - (k - w.n_tiles) * kKeyTile;
+                valid[qt] = soft_i + 1 - (k - n_tiles) * kKeyTile;
             }
         }
     };
@@ -624,7 +795,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) { m[qt] = -1.0e30f; z[qt] = 0.0f; }
         wait_frags_read();
-        first_page();
+        walk.start(h, h.x, wv);
+        if (PAGED && n_tiles > 0) page_next = tile_page<PAGED>(ks, walk.t);
         fetch(0);
         k = 0;
     }
@@ -633,7 +805,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
 
     // Lanes l and l+32 hold the same query rows over complementary keys: merge them; then the four waves of
     // the workgroup merge their rows through LDS (every slot is idle by now), in wave order, into the one
-    // partial the workgroup leaves per query row.
+    // set the share leaves.
     float2* mine = (float2*)slots;  // [NQT * 32] of this wave
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
@@ -643,18 +815,43 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs
         if (half == 0) mine[qt * kRowTile + lane] = make_float2(mm, zz);
     }
     __syncthreads();
-    const int row = w.rg * NQT * kRowTile + (int)threadIdx.x;  // the last group may reach past the head's row tiles
+    const int row = rg * NQT * kRowTile + (int)threadIdx.x;  // the last group may reach past the head's row tiles
+    const int set = h.set0 + h.rank;
     if (threadIdx.x < NQT * kRowTile && row < a.RP) {
         float M = -1.0e30f, Z = 0.f;
 #pragma unroll
-        for (int wv = 0; wv < kScoreWaves; ++wv) {
-            const float2 mz = ((const float2*)&lds[wv][0][0])[threadIdx.x];
+        for (int w = 0; w < kScoreWaves; ++w) {
+            const float2 mz = ((const float2*)(lds + w * 2 * kSlotBytes))[threadIdx.x];
             const float mm = fmaxf(M, mz.x);
             Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz.y * __builtin_amdgcn_exp2f(mz.x - mm);
             M = mm;
         }
-        const int cg = (a.one_L ? 0 : a.tab.cu_cgrp[w.seq]) + w.wave / kScoreWaves;  // this workgroup among the layer's, per head
-        a.stats[(((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g) * a.RP + row] = make_float2(M, Z);
+        float2* to = &a.stats[((int64_t)set * a.h_kv + g) * a.RP + row];
+        if (SHARED) {
+            __hip_atomic_store((uint64_t*)to, (uint64_t)__float_as_uint(M) | (uint64_t)__float_as_uint(Z) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ((float2*)(lds + kLdsSet))[threadIdx.x] = make_float2(M, Z);
+        } else {
+            *to = make_float2(M, Z);
+        }
+    }
+    if (SHARED) {  // the set has to be where every XCD sees it before its flag is
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        bare_barrier();
+        if (threadIdx.x == 0 && h.n_sets > 1) __hip_atomic_store(&a.flags[(int64_t)g * a.n_sets + set], a.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+template <int NQT, bool PAGED>
+__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
+    __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
+    kernel_lines();
+    Place at = place_of(kernel_args(), false);
+    for (;;) {
+        KArgs& a = kernel_args();
+        const Share h = share_of(a, at.c, at.layer, at.seq);
+        stats_share<NQT, PAGED, false>(a, h, at.g, at.rg, lds);
+        if (!next_share(a, h, false, at)) break;
+        bare_barrier();  // the statistics have left the slots
     }
 }
 
@@ -683,7 +880,8 @@ __device__ __forceinline__ uint2 neg_beta_terms(float m, float z, double inv_c) 
 constexpr float kPadTerm = -1.0e30f;  // for padded rows: 2^(c * x) = 0
 
 constexpr int kCombineLanes = 32;  // partial-lanes per query row
-__global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(ScoreArgs) {
+    KArgs& a = kernel_args();
     // one workgroup per (layer, sequence, head, tile of 32 rows); thread = (row r, partial-lane kl)
     __shared__ float2 part[kCombineLanes][kRowTile];
     const int r = threadIdx.x & (kRowTile - 1), kl = threadIdx.x / kRowTile;
@@ -704,16 +902,17 @@ __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(Sc
         const int layer = (int)(rest / a.n_seq);
         const int row = rt * kRowTile + r;
         if (item != blockIdx.x) __syncthreads();  // `part` is still being read
-        const int c0 = a.tab.cu_cgrp[s], c1 = a.tab.cu_cgrp[s + 1];
-        const float2* p = a.stats + (((int64_t)layer * a.n_cgrp + c0) * a.h_kv + g) * a.RP + row;
+        int set0, n_sets;
+        sets_of(a, a.part, a.cu_part, layer, s, set0, n_sets);
+        const float2* p = a.stats + ((int64_t)set0 * a.h_kv + g) * a.RP + row;
         const int64_t step = (int64_t)a.h_kv * a.RP;
         float M = -1.0e30f, Z = 0.f;
-        for (int k0 = kl; k0 < c1 - c0; k0 += 8 * kCombineLanes) {  // 8 independent loads in flight per thread
+        for (int k0 = kl; k0 < n_sets; k0 += 8 * kCombineLanes) {  // 8 independent loads in flight per thread
             float2 mz[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int k = k0 + u * kCombineLanes;
-                mz[u] = k < c1 - c0 ? p[k * step] : make_float2(-1.0e30f, 0.f);
+                mz[u] = k < n_sets ? p[k * step] : make_float2(-1.0e30f, 0.f);
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -748,177 +947,233 @@ __device__ __forceinline__ f32x16 score_chain(const bf16x8 (&q)[8], bf16x8 qaug,
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(qaug, ones, acc, 0, 0, 0);  // - beta_r / c
 }
 
-// FROM_LSE: the caller supplied the normalisers and no statistics pass has run: lse becomes the -beta/c terms
-// on the fly (beta = lse * log2 e, c = scale * log2 e, so -beta/c = -lse / scale), and the launch also clears the words the selection stage needs cleared.
-template <int NQT, bool FROM_LSE, bool PAGED>
-__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs a) {
-    __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
-    WaveItem w;
-    wave_item(a, true, w);  // reversed order: the keys pass 1 read last are fetched first
-    const int lane = threadIdx.x & 63;
-    const int half = lane >> 5;
-    char* slots = &lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))][0][0];
+// Where a second pass gets its normalisers from.
+enum Norms {
+    kNormsMerged,  // sets of statistics that an earlier launch has left (or `aug`, if a combine launch has merged them)
+    kNormsLse,     // the caller: lse becomes the -beta/c terms on the fly (beta = lse * log2 e, c = scale * log2 e, so
+                   // -beta/c = -lse / scale)
+    kNormsShared,  // sets of statistics that this launch's workgroups form and publish
+};
 
-    const KeyStream ks = key_stream<PAGED>(a, w);
+// A workgroup's share of one (layer, sequence): its waves score their tiles, from the share's last to its first (the first pass went
+// the other way, and the caches still hold what it read last: front to back it takes 1.7 us longer on the 128K layer).
+// Returns -1, or (kNormsShared) the number of a set that others have not published within `patience` ticks; nothing is scored then.
+template <int NQT, Norms NORMS, bool PAGED>
+__device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char* lds, int64_t patience, bool q_there = false) {
+    const int lane = lane_again(), half = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char* slots = lds + wv * 2 * kSlotBytes;
+    const int x_last = h.x + h.len - 1;
+    const int skip = kScoreWaves * h.quad(x_last) + wv >= h.seq_tiles ? 1 : 0;  // no tile for this wave in the sequence's last quad
+    const int n_tiles = h.len - skip;
+
+    const KeyStream ks = key_stream<PAGED>(a, h, g);
     const uint32_t tl = tile_lane(lane, ks.row_bytes);
-    // The wave walks its tiles from the last to the first (pass 1 swept the keys front to back, so the end
-    // of the sequence is what the caches still hold): its k-th tile here is sequence tile tile_of(k).
-    auto tile_of = [&](int k) { return w.wave + (w.n_tiles - 1 - k) * w.n_waves; };
     // PAGED: as in the first pass, the table word of the next request (k + 1) is loaded one request ahead
     int page_next = 0;  // set by the start-up's first request
-    auto fetch = [&](int k) __attribute__((always_inline)) {
-        const int t = tile_of(k);
-        const int page = page_next;
-        if (PAGED && k + 1 < w.n_tiles) page_next = tile_page<PAGED>(ks, t - w.n_waves);
+    Walk<true> walk;    // at the next tile to request
+    auto fetch = [&](int k) __attribute__((always_inline)) {  // returns the tile
+        const int t = walk.t, page = page_next;
+        walk.step(h);
+        if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
         fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes,
-                   w.L - t * kKeyTile, tl, lane);
+                   h.L - t * kKeyTile, tl, lane);
+        return t;
     };
     bf16x8 qf[NQT][8];
-    bf16x8 qaug[NQT];
-    // Start-up.  Requested first, into registers: the query rows, the first pass's partial statistics (or the
+    // Start-up.  Requested first, into registers: the query rows, the first pass's statistics (or the
     // normalisers themselves); then the first key tile, straight into LDS.  Everything up to the sweep works on the
     // former while the latter is in flight (see lds_addr() above for why the LDS instructions here are explicit).
     // The compiler can only count on loads that are certain to have been issued, so every request below is
     // unconditional -- addresses are clamped, values that turn out not to be needed are dropped -- and all of them
     // sit in one basic block: then each wait is exactly "everything older than this value", never the key tile.
-    const bool fused = !FROM_LSE && a.fuse_combine;  // uniform
-    constexpr int kFirstParts = 16;  // partials per thread requested up front: all of them for up to 32 per row
+    const bool merging = NORMS == kNormsShared || (NORMS == kNormsMerged && a.fuse_combine);  // uniform
+    constexpr int kFirstParts = 16;  // sets per thread requested up front: all of them for up to 32 per row
     const int p0 = (int)(threadIdx.x & 1);
-    // Pass 1 left one (m, Z) partial per workgroup; unless a combine launch has merged them already, this
-    // workgroup merges the partials of its head's rows itself: thread t takes row t / 2 and every second
-    // partial; pairs meet by shuffle, and the rows' -beta/c terms pass through LDS.
+    // Unless a combine launch has merged them already, this
+    // workgroup merges the sets of its head's rows itself: thread t takes row t / 2 and every second
+    // set; pairs meet by shuffle, and the rows' -beta/c terms pass through LDS.
     const int mrow = min((int)(threadIdx.x >> 1), NQT * kRowTile - 1);
-    const int c0 = (a.one_L || !fused) ? 0 : a.cu_part[w.seq];
-    const int n_p = !fused ? 1 : a.one_L ? a.n_part : a.cu_part[w.seq + 1] - c0;
-    const float2* pp = a.stats + (((int64_t)w.layer * a.n_part + c0) * a.h_kv + w.g) * a.RP + mrow;
+    int set0 = h.set0, n_p = h.n_sets;
+    if (NORMS == kNormsMerged) {
+        set0 = 0; n_p = 1;
+        if (merging) sets_of(a, a.part, a.cu_part, h.layer, h.seq, set0, n_p);
+    }
+    const float2* pp = a.stats + ((int64_t)set0 * a.h_kv + g) * a.RP + mrow;
     const int64_t pstep = (int64_t)a.h_kv * a.RP;
-    const u32x4* qsrc[8];
-    uint32_t qpad;
-    q_rows_where<NQT>(a, w, lane, qsrc, qpad);
-    const float* nsrc[NQT];  // FROM_LSE: the lane's rows' normalisers; otherwise the merged -beta/c terms of a combine launch
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-        const int row = min(qt * kRowTile + (lane & 31), a.rows - 1);
-        if (FROM_LSE) {
-            const int i = row / a.group, h = w.g * a.group + row % a.group;
-            nsrc[qt] = a.lse + ((int64_t)(w.layer * a.n_seq + w.seq) * a.n_q + i) * a.h_q + h;
-        } else {
-            nsrc[qt] = (const float*)(a.aug + ((int64_t)(w.layer * a.n_seq + w.seq) * a.h_kv + w.g) * a.RP + qt * kRowTile + (lane & 31));
-        }
-    }
-    const int t_first = w.n_tiles > 0 ? tile_of(0) : 0;  // a surplus wave requests the sequence's first tile and drops it
+    walk.start(h, x_last - skip, wv);
+    const int t_first = n_tiles > 0 ? walk.t : 0;  // a wave without tiles requests the sequence's first tile and drops it
     const int page_first = PAGED ? tile_page<PAGED>(ks, t_first) : 0;
-    if (PAGED && w.n_tiles > 1) page_next = tile_page<PAGED>(ks, t_first - w.n_waves);
+    walk.step(h);
+    if (PAGED && n_tiles > 1) page_next = tile_page<PAGED>(ks, walk.t);
     const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
-    const int valid_first = min(kKeyTile, w.L - t_first * kKeyTile);
-    __builtin_amdgcn_sched_barrier(0);
-    u32x4 qraw[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) qraw[i] = *qsrc[i];
+    const int valid_first = min(kKeyTile, h.L - t_first * kKeyTile);
     float2 mz[kFirstParts];
+    uint2 aug_direct[NQT];  // the terms of the lane's rows where no merging is due
+    if (NORMS == kNormsShared && q_there) {
+        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
 #pragma unroll
-    for (int u = 0; u < kFirstParts; ++u) mz[u] = pp[min(p0 + 2 * u, n_p - 1) * pstep];
-    uint2 aug_direct[NQT];
-#pragma unroll
-    for (int qt = 0; qt < NQT; ++qt) {
-        if (FROM_LSE) aug_direct[qt] = make_uint2(__float_as_uint(*nsrc[qt]), 0u);
-        else aug_direct[qt] = *(const uint2*)nsrc[qt];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < kFirstParts; ++u)
-        if (!fused || p0 + 2 * u >= n_p) mz[u] = make_float2(-1.0e30f, 0.f);
-    const bool merges = fused && (threadIdx.x >> 1) < NQT * kRowTile;
-    if (FROM_LSE) {
+        for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
+    } else {
+        const float* nsrc[NQT];  // kNormsLse: the lane's rows' normalisers; kNormsMerged: the terms of a combine launch
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
-            const int row = qt * kRowTile + (lane & 31);
-            aug_direct[qt] = split_bf16x3(row < a.rows ? (float)(-(double)__uint_as_float(aug_direct[qt].x) * a.inv_scale) : kPadTerm);
+            const int row = min(qt * kRowTile + (lane & 31), a.rows - 1);
+            if (NORMS == kNormsLse) {
+                const int i = row / a.group, hd = g * a.group + row % a.group;
+                nsrc[qt] = a.lse + ((int64_t)(h.layer * a.n_seq + h.seq) * a.n_q + i) * a.h_q + hd;
+            } else if (NORMS == kNormsMerged) {
+                nsrc[qt] = (const float*)(a.aug + ((int64_t)(h.layer * a.n_seq + h.seq) * a.h_kv + g) * a.RP + qt * kRowTile + (lane & 31));
+            }
+        }
+        u32x4 qraw[8];
+        q_rows_request<NQT>(a, h, g, 0, lane, qraw);
+        if (NORMS == kNormsMerged) {
+#pragma unroll
+            for (int u = 0; u < kFirstParts; ++u) mz[u] = pp[min(p0 + 2 * u, n_p - 1) * pstep];
+        }
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt) {
+            if (NORMS == kNormsLse) aug_direct[qt] = make_uint2(__float_as_uint(*nsrc[qt]), 0u);
+            else if (NORMS == kNormsMerged) aug_direct[qt] = *(const uint2*)nsrc[qt];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
+        __builtin_amdgcn_sched_barrier(0);
+        if (NORMS == kNormsLse) {
+#pragma unroll
+            for (int qt = 0; qt < NQT; ++qt) {
+                const int row = qt * kRowTile + (lane & 31);
+                aug_direct[qt] = split_bf16x3(row < a.rows ? (float)(-(double)__uint_as_float(aug_direct[qt].x) * a.inv_scale) : kPadTerm);
+            }
+        }
+        q_rows_stage<NQT>(lane, NORMS == kNormsShared ? lds + kLdsQ : lds + kSlotBytes, NORMS == kNormsShared ? kSlotBytes : 2 * kSlotBytes, qraw, qf);
+    }
+    // the rows' -beta/c terms pass through LDS; in a launch of the second pass alone through wave 0's second slot, free until its second tile
+    const uint32_t aug_s = lds_addr(NORMS == kNormsShared ? lds + kLdsAug : lds + kSlotBytes);
+    const bool own_set = NORMS == kNormsShared && q_there && n_p == 1;  // nobody else has keys of the sequence, and LDS holds the set
+    if (NORMS == kNormsShared && !own_set) {
+        if (n_p > 1) {
+            // Wave 0 watches the flags of the (layer, sequence), one per lane (at most 64, the host has seen to it); the other
+            // waves wait at the barrier, where they take no issue slots.  The wait ends after `patience` ticks whatever happens.
+            const uint32_t word = lds_addr(lds + kLdsWord);
+            if (wv == 0) {
+                const uint64_t* flag = a.flags + (int64_t)g * a.n_sets + set0 + min(lane, n_p - 1);
+                const int64_t t0 = wall_clock64();
+                uint32_t missing = 0u;  // number of a missing set + 1
+                for (;;) {
+                    const uint64_t late = __ballot(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.token);
+                    if (late == 0u) break;
+                    if (wall_clock64() - t0 >= patience) { missing = 1u + (uint32_t)__builtin_ctzll(late); break; }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                if (lane == 0) lds_put8(word, make_uint2(missing, 0u));
+                lds_wait_all();
+            }
+            bare_barrier();
+            const uint32_t missing = __builtin_amdgcn_readfirstlane(lds_get8_waited(word).x);
+            if (missing) {  // uniform
+                wait_tile_landed();  // the request above must not land in a slot that is in use again
+                bare_barrier();
+                return (int)missing - 1;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kFirstParts; ++u) {  // formed and stored by other workgroups of this launch: read past the caches that are not shared
+            const uint64_t v = __hip_atomic_load((const uint64_t*)(pp + min(p0 + 2 * u, n_p - 1) * pstep), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            mz[u] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
         }
     }
-    q_rows_stage<NQT>(lane, &lds[0][0][0], qraw, qpad, qf);
     float cM = -1.0e30f, cZ = 0.f;
-    auto merge_in = [&](float2 t) __attribute__((always_inline)) {
-        const float mm = fmaxf(cM, t.x);
-        cZ = cZ * __builtin_amdgcn_exp2f(cM - mm) + t.y * __builtin_amdgcn_exp2f(t.x - mm);
-        cM = mm;
-    };
-    if (merges) {  // ascending partial index, the same order whatever their number
+    if (own_set) {
+        const uint2 v = lds_get8_waited(lds_addr(lds + kLdsSet) + 8u * (uint32_t)mrow);
+        if (p0 == 0) { cM = __uint_as_float(v.x); cZ = __uint_as_float(v.y); }
+    } else if (merging && (threadIdx.x >> 1) < NQT * kRowTile) {  // the same order of additions whatever the number of sets
+        auto merge_in = [&](const float2* t, int n, int from) __attribute__((always_inline)) {  // sets from, from + 2, ...
+            float mm = cM;
 #pragma unroll
-        for (int u = 0; u < kFirstParts; ++u) merge_in(mz[u]);
-        for (int k0 = p0 + 2 * kFirstParts; k0 < n_p; k0 += 16) {  // a sequence that left more than 32 partials
+            for (int u = 0; u < n; ++u) mm = fmaxf(mm, from + 2 * u < n_p ? t[u].x : -1.0e30f);
+            cZ *= __builtin_amdgcn_exp2f(cM - mm);
+#pragma unroll
+            for (int u = 0; u < n; ++u) cZ = fmaf(t[u].y, from + 2 * u < n_p ? __builtin_amdgcn_exp2f(t[u].x - mm) : 0.f, cZ);
+            cM = mm;
+        };
+        merge_in(mz, kFirstParts, p0);
+        for (int k0 = p0 + 2 * kFirstParts; k0 < n_p; k0 += 16) {  // more than 32 sets
             float2 more[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) more[u] = k0 + 2 * u < n_p ? pp[(k0 + 2 * u) * pstep] : make_float2(-1.0e30f, 0.f);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) merge_in(more[u]);
+            for (int u = 0; u < 8; ++u) {
+                const float2* src = pp + min(k0 + 2 * u, n_p - 1) * pstep;
+                if (NORMS == kNormsShared) {
+                    const uint64_t v = __hip_atomic_load((const uint64_t*)src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    more[u] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+                } else {
+                    more[u] = *src;
+                }
+            }
+            merge_in(more, 8, k0);
         }
     }
+    bf16x8 qaug[NQT];
     auto set_aug = [&](int qt, uint2 t) {  // the three bf16 terms sit in k-elements 0..2 of the extra MFMA step (lane half 0)
         u32x4 v = {0u, 0u, 0u, 0u};
         if (half == 0) { v[0] = t.x; v[1] = t.y; }
         qaug[qt] = as_bf16x8(v);
     };
-    if (fused) {
+    if (merging) {
         const float oM = __shfl_xor(cM, 1), oZ = __shfl_xor(cZ, 1);  // the odd neighbour's half; even threads finish the row
         const float mm = fmaxf(cM, oM);
         const float zz = cZ * __builtin_amdgcn_exp2f(cM - mm) + oZ * __builtin_amdgcn_exp2f(oM - mm);
         const int crow = (int)(threadIdx.x >> 1);
-        const uint32_t aug_s = lds_addr(&lds[0][1][0]);  // the query rows have left this slot (second barrier of q_rows_stage)
-        if (!(threadIdx.x & 1) && (threadIdx.x >> 1) < NQT * kRowTile) {
-            lds_put8(aug_s + 8u * (threadIdx.x >> 1), crow < a.rows ? neg_beta_terms(mm, zz, a.inv_c) : split_bf16x3(kPadTerm));
+        if (!(threadIdx.x & 1) && crow < NQT * kRowTile) {
+            lds_put8(aug_s + 8u * crow, crow < a.rows ? neg_beta_terms(mm, zz, a.inv_c) : split_bf16x3(kPadTerm));
             lds_wait_all();
         }
         bare_barrier();
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) set_aug(qt, lds_get8_waited(aug_s + 8u * (qt * kRowTile + (lane & 31))));
-        bare_barrier();  // the slot is refilled with a key tile next
+        if (NORMS != kNormsShared) bare_barrier();  // the slot is refilled with a key tile next
     } else {
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) set_aug(qt, aug_direct[qt]);
     }
-    if (a.zero) {  // words the selection needs cleared (stores: they only join the loads the sweep's first wait covers)
-        const uint64_t per = (a.zero_words + gridDim.x - 1) / gridDim.x;
-        const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
-        for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
-    }
-    if (w.n_tiles == 0) return;  // surplus wave of the sequence's last workgroup
+    wait_tile_landed();
+    if (n_tiles == 0) return -1;  // a wave without tiles in the sequence's last quad
     u32x4 ones_bits = {0u, 0u, 0u, 0u};
     if (half == 0) { ones_bits[0] = 0x3F803F80u; ones_bits[1] = 0x00003F80u; }  // 1.0 at elements 0..2
     const bf16x8 ones = as_bf16x8(ones_bits);
 
-    float* out = a.scores + ((int64_t)w.layer * a.h_kv + w.g) * a.T + w.tok0;
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc((void*)(a.scores + ((int64_t)h.layer * a.h_kv + g) * a.T + h.tok0), 0,
+                                                                          h.L * 4, 0x00020000);
     const float c = a.c;
-    float pending = 0.f;  // previous tile's result, stored one iteration late so that the store has a
-                          // whole tile of compute to retire before the next wait on outstanding loads
-    const int n_scored = a.window ? w.L - a.n_q : w.L;  // the window's own positions report 0
-    auto store_tile = [&](int k, float v) {  // only the sequence's last tile can be partial
-        const int t = tile_of(k);
-        if (lane < 32 && t * kKeyTile + lane < w.L) {
-            if (t * kKeyTile + lane >= n_scored) v = 0.f;
-            out[t * kKeyTile + lane] = v;
-        }
+    float pending = 0.f;  // previous tile's result, stored one iteration late
+    const int n_scored = a.window ? h.L - a.n_q : h.L;  // the window's own positions report 0
+    // Always one store instruction: the upper lane half (which holds the same sums), rows past the end of the sequence's last
+    // tile and whatever goes to kNowhere fall behind the end of the resource, where the hardware drops them.
+    constexpr int kNowhere = 0x40000000 / (4 * kKeyTile);  // (the resource has at most 2^26 bytes)
+    const uint32_t out_lane = half == 0 ? 4u * (uint32_t)lane : 0x40000000u;
+    auto store_tile = [&](int t, float v) {
+        if (t * kKeyTile + kKeyTile > n_scored && t * kKeyTile + (lane & 31) >= n_scored) v = 0.f;
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, (int)(out_lane + 4u * (uint32_t)(t * kKeyTile)), 0, 0);
     };
 
     // Software pipeline over the query-row tiles and across key tiles, as in the first pass: while one tile's logits are
     // exponentiated the MFMA chain of the next runs, and behind the last one that of the next key tile's first, whose
     // fragments were read a stage earlier.  At an iteration's end tile k + 1 sits in registers and tile k + 2 is in
     // flight; the last iteration's look-ahead reads whatever its slot holds and drops it.
-    wait_tile_landed();
     bf16x8 kf[8];
     lds_get_frags(slots, kf, lane);
     wait_frags_read();
-    if (w.n_tiles > 1) fetch(1);
+    int t_done = kNowhere, t_here = t_first, t_next = n_tiles > 1 ? fetch(1) : 0;  // the tiles k - 1, k, k + 1
+    store_tile(kNowhere, 0.f);  // for the sweep's first wait
     f32x16 acc = score_chain(qf[0], qaug[0], kf, ones);
-    for (int k = 0; k < w.n_tiles; ++k) {
+    for (int k = 0; k < n_tiles; ++k) {
         float sum = 0.f;
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
             const bool reads = qt == (NQT > 1 ? NQT - 2 : 0);
             const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
-            if (reads) wait_tile_landed();
+            if (reads) wait_tile_landed_before_store();  // tile k + 1, behind which tile k - 2's scores were stored
             const uint32_t next_at = frag_addr(next_slot, lane);
             if (NQT == 1) lds_get_frags(next_slot, kf, lane);
             f32x16 nxt = zero_acc();
@@ -931,18 +1186,97 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs
                 [&](int v) __attribute__((always_inline)) { return acc[v] * c; });
             if (reads) {
                 wait_frags_read();
-                if (k > 0) store_tile(k - 1, pending);
-                if (k + 2 < w.n_tiles) fetch(k + 2);
+                const int t_stored = t_done;
+                t_done = t_here; t_here = t_next;
+                if (k + 2 < n_tiles) t_next = fetch(k + 2);
+                store_tile(t_stored, pending);
             }
             acc = nxt;
         }
         sum += __shfl_xor(sum, 32);  // the two lane halves hold complementary query rows of the same key
         pending = sum;
     }
-    store_tile(w.n_tiles - 1, pending);
+    store_tile(t_done, pending);
+    return -1;
+}
+
+__device__ __forceinline__ void clear_words(KArgs& a) {  // what the selection needs cleared: every workgroup its part
+    if (!a.zero) return;
+    const uint64_t per = (a.zero_words + gridDim.x - 1) / gridDim.x;
+    const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
+    for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
+}
+
+template <int NQT, bool FROM_LSE, bool PAGED>
+__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
+    __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
+    kernel_lines();
+    Place at = place_of(kernel_args(), true);  // from the end: the keys pass 1 read last are fetched first
+    clear_words(kernel_args());
+    for (;;) {
+        KArgs& a = kernel_args();
+        const Share h = share_of(a, at.c, at.layer, at.seq);
+        score_share<NQT, FROM_LSE ? kNormsLse : kNormsMerged, PAGED>(a, h, at.g, lds, 0);
+        if (!next_share(a, h, true, at)) break;
+    }
 }
 
 template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placement: see jq_lib.hip
+
+// ------------------------------------------------------------------------------------------------
+// both passes in one launch
+// ------------------------------------------------------------------------------------------------
+// Every workgroup sweeps its shares for their statistics, publishes each set -- the set past its XCD's L2, then a flag -- and scores
+// the same shares, last one first, as soon as the other workgroups of the (layer, sequence) have published theirs.  Against a
+// launch per pass that saves the boundary between two dependent kernels (2.2 us), the second request for the query rows
+// (they wait in LDS) and, where one workgroup has a whole (layer, sequence), the way of the statistics through memory; and no
+// workgroup waits for any other sequence's.  Device timestamps, 32768 tokens, 8 heads, from a workgroup's last tile of the
+// first pass to its first of the second: set stored 0.8 us, flag 0.4, share and query rows 1.5, all flags seen 0.5,
+// sets read and merged 1.2, terms exchanged 0.4.  Whole calls, two launches / one: 2048 tokens and 2 heads 18.7 / 17.0 us, 32768 tokens
+// 48.3 / 44.8, 128K layer 114.7 / 113.0, 32 layers of 8192 246 / 240, 8 x 12345 with window queries 97.3 / 92.8; together with the
+// even shares a paged batch of 8 196 / 187, 16 ragged sequences 821 / 779.
+// No workgroup depends on another one running: a wait ends after `wait_ticks` (or the time the workgroup has run itself, if that
+// is longer), and what is missing then is formed here, from the same keys in the same order -- the same bits, whoever
+// stores them.  The flags need no clearing before the launch: they are compared with a 64-bit token that is the call's
+// own.  A captured call has the same token in every replay, so a later kernel of the call clears them.
+// One workgroup per CU (99 KB of LDS).
+template <int NQT, bool PAGED>
+__global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArgs) {
+    __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
+    kernel_lines();
+    const int64_t t_entry = wall_clock64();
+    Place at = place_of(kernel_args(), false);
+    clear_words(kernel_args());
+    bool scoring = false, q_there = false;  // uniform
+    int help = -1;                          // another workgroup, whose set this one forms in its stead
+    int64_t patience = kernel_args().wait_ticks;
+    for (;;) {
+        KArgs& a = kernel_args();
+        if (!scoring || help >= 0) {
+            const Share h = share_of(a, help < 0 ? at.c : help, at.layer, at.seq);
+            stats_share<NQT, PAGED, true>(a, h, at.g, 0, lds, q_there);
+            if (scoring) {
+                help = -1;
+            } else {
+                scoring = !next_share(a, h, false, at);
+                if (scoring && patience) patience = max(patience, (int64_t)(wall_clock64() - t_entry));
+            }
+            q_there = scoring;
+        } else {
+            const Share h = share_of(a, at.c, at.layer, at.seq);
+            const int missing = score_share<NQT, kNormsShared, PAGED>(a, h, at.g, lds, patience, q_there);
+            q_there = true;
+            if (missing >= 0) {
+                help = at.c - h.rank + missing;
+            } else {
+                if (!next_share(a, h, true, at)) break;
+                q_there = false;
+            }
+        }
+    }
+}
+
+template __global__ void jq_passes_kernel<4, false>(ScoreArgs);
 
 // ------------------------------------------------------------------------------------------------
 // many query rows (more than kMaxRowTiles tiles per KV head): keys stationary, query rows streamed
@@ -965,31 +1299,31 @@ template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placem
 // and Eq. 4), in fp64 per key, then in a fixed order over lanes and waves.  The first set has four tiles where the second has
 // sixteen in the usual sizes, so sweeping them here costs less than the launches of both passes that stored its map before.
 template <bool PAGED, bool DIFF>
-__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(ScoreArgs) {
+    KArgs& a = kernel_args();
     __shared__ __attribute__((aligned(1024))) char lds[kScoreWaves][2][kSlotBytes];
     __shared__ double diff_s[DIFF ? 2 : 1];
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     char* slots = &lds[wv][0][0];
     // one workgroup per (layer, group of 128 keys, head), heads fastest: with eight heads an XCD's L2 holds one head's rows
-    WaveItem w;
-    w.g = (int)(blockIdx.x % (uint32_t)a.h_kv);
+    const int g = (int)(blockIdx.x % (uint32_t)a.h_kv);
     const uint32_t rest = blockIdx.x / (uint32_t)a.h_kv;
-    const int cg = (int)(rest % (uint32_t)a.n_cgrp);
-    w.layer = (int)(rest / (uint32_t)a.n_cgrp);
-    w.seq = a.one_L ? 0 : find_seq(a.tab.cu_cgrp, a.tab.n_seq, cg);
-    w.tok0 = a.tab.cu_seq[w.seq];
-    w.L = a.tab.cu_seq[w.seq + 1] - a.tab.cu_seq[w.seq];
-    const int tile0 = (cg - a.tab.cu_cgrp[w.seq]) * kMaxRowTiles;  // first key tile of the group
+    const int quad = (int)(rest % (uint32_t)a.layer_quads), layer = (int)(rest / (uint32_t)a.layer_quads);
+    const int seq = a.one_L ? 0 : find_seq(a.cu_quad, a.n_seq, quad);
+    const int64_t tok0 = a.cu_seq[seq];
+    const int L = a.cu_seq[seq + 1] - a.cu_seq[seq];
+    static_assert(kMaxRowTiles == kScoreWaves, "the keys of a workgroup are a quad");
+    const int tile0 = (quad - a.cu_quad[seq]) * kMaxRowTiles;  // first key tile of the group
 
     // ---- query-row tiles: global -> LDS, laid out as key tiles are (see fetch_tile) ----
-    const int64_t head0 = (int64_t)w.g * a.group * kHeadDim * 2, prob = w.layer * a.n_seq + w.seq;
+    const int64_t head0 = (int64_t)g * a.group * kHeadDim * 2, prob = layer * a.n_seq + seq;
     const char* qbase1 = (const char*)a.Q + prob * a.n_q * a.h_q * kHeadDim * 2 + head0;
     const char* qbase2 = (const char*)a.Q2 + prob * a.n_q2 * a.h_q * kHeadDim * 2 + head0;  // DIFF only
     const int n_rt = a.RP / kRowTile;
     const int n_mine = (n_rt - wv + kScoreWaves - 1) / kScoreWaves;  // this wave sweeps row tiles wv, wv + 4, ...; none of few
     const int n_first = DIFF ? min(n_mine, (a.tiles1 - wv + kScoreWaves - 1) / kScoreWaves) : 0;  // ... of them of the first set
-    const uint2* aug = a.aug + prob * a.h_kv * a.RP + (int64_t)w.g * a.RP + (lane & 31);
+    const uint2* aug = a.aug + prob * a.h_kv * a.RP + (int64_t)g * a.RP + (lane & 31);
     const int64_t tok_bytes = (int64_t)a.h_q * kHeadDim * 2;  // from one query token to the next
     // With a power-of-two group of up to 32 heads a tile's rows lie where a key tile's would: a lane part that never changes
     // and a uniform part per load (4 i + a, a < 4, splits without carry), so a request costs no vector arithmetic -- the
@@ -1027,12 +1361,12 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     };
 
     // ---- start-up: wave wv fetches key tile wv into its second slot, its first row tile into its first ----
-    const KeyStream ks = key_stream<PAGED>(a, w);
-    const int last_tile = (w.L - 1) / kKeyTile;
+    const KeyStream ks = key_stream<PAGED>(a, layer, seq, tok0, L, g);
+    const int last_tile = (L - 1) / kKeyTile;
     {
         const int t = min(tile0 + wv, last_tile);  // tiles past the sequence's end repeat its last one and are not stored
         const uint32_t off = tile_offset<PAGED>(ks, t, tile_page<PAGED>(ks, t));
-        fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, w.L - t * kKeyTile), lane);
+        fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, L - t * kKeyTile), lane);
     }
     fetch_rows(0);
     uint2 aug_next = aug[min(wv, n_rt - 1) * kRowTile];
@@ -1111,7 +1445,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     __syncthreads();
     const int key = tile0 * kKeyTile + (int)threadIdx.x;  // threads 0..127: one key each
     double dacc = 0.0;
-    if (threadIdx.x < kKeys && key < w.L) {
+    if (threadIdx.x < kKeys && key < L) {
         float v = 0.f, v1 = 0.f;
 #pragma unroll
         for (int i = 0; i < kScoreWaves; ++i) {
@@ -1122,8 +1456,8 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
             const double d = (double)v1 * (double)a.inv_rows1 - (double)v * (double)a.inv_rows2;
             dacc = d * d;
         } else {
-            if (a.window && key >= w.L - a.n_q) v = 0.f;  // the window's own positions report 0
-            a.scores[((int64_t)w.layer * a.h_kv + w.g) * a.T + w.tok0 + key] = v;
+            if (a.window && key >= L - a.n_q) v = 0.f;  // the window's own positions report 0
+            a.scores[((int64_t)layer * a.h_kv + g) * a.T + tok0 + key] = v;
         }
     }
     if constexpr (DIFF) {  // butterfly within waves 0 and 1, then their two sums: a fixed order
@@ -1131,7 +1465,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         for (int off = 32; off >= 1; off >>= 1) dacc += __shfl_xor(dacc, off);
         if (lane == 0 && wv < 2) diff_s[wv] = dacc;
         __syncthreads();
-        if (threadIdx.x == 0) a.diff_part[((int64_t)w.layer * a.n_cgrp + cg) * a.h_kv + w.g] = diff_s[0] + diff_s[1];
+        if (threadIdx.x == 0) a.diff_part[((int64_t)layer * a.layer_quads + quad) * a.h_kv + g] = diff_s[0] + diff_s[1];
     }
 }
 
@@ -1177,8 +1511,32 @@ static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
     }
 }
 
+template <bool PAGED>
+static hipError_t launch_passes_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st) {
+    dim3 block(kScoreWaves * 64);
+    switch (nqt) {
+        case 1: return launch_kernel(jq_passes_kernel<1, PAGED>, grid, block, 0, st, nullptr, -1, a);
+        case 2: return launch_kernel(jq_passes_kernel<2, PAGED>, grid, block, 0, st, nullptr, -1, a);
+        case 3: return launch_kernel(jq_passes_kernel<3, PAGED>, grid, block, 0, st, nullptr, -1, a);
+        default: return launch_kernel(jq_passes_kernel<4, PAGED>, grid, block, 0, st, nullptr, -1, a);
+    }
+}
+
+// A value that no flag holds by chance (2^-64): every call's is another one.
+static uint64_t next_token() {
+    static std::atomic<uint64_t> count{[] {
+        std::random_device rd;
+        return ((uint64_t)rd() << 32) ^ (uint64_t)rd();
+    }()};
+    uint64_t x = count.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);  // splitmix64 (Steele, Lea, Flood 2014): a bijection of the count
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    return x ^ (x >> 31);
+}
+
 hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scores, char* ws, hipStream_t st,
-                        uint32_t* zero, size_t zero_words, const float* lse, const void* k_tail, const void* Q2, double* diff_part) {
+                        uint32_t* zero, size_t zero_words, const float* lse, const void* k_tail, const void* Q2, double* diff_part,
+                        bool flags_cleared_later) {
     void* const* marks = p.marks;
     ScoreArgs a;
     a.Q = (const uint16_t*)Q;
@@ -1199,69 +1557,73 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.inv_c = 1.0 / (double)a.c;
     a.T = p.T;
     a.zero = zero; a.zero_words = zero_words;
-    a.tab = p.tab;
     a.block_table = p.block_table; a.page_shift = p.page_shift; a.n_pages = p.n_pages; a.max_pages = p.max_pages;
     a.Q2 = (const uint16_t*)Q2; a.diff_part = diff_part;
     a.n_q2 = p.n_q2; a.rows2 = p.rows2; a.tiles1 = p.n_q2 ? p.row_tiles1 : kOneSet;
     a.inv_rows1 = 1.0f / (float)p.rows; a.inv_rows2 = p.n_q2 ? 1.0f / (float)p.rows2 : 0.0f;
     const bool paged = p.block_table != nullptr;
     if ((diff_part != nullptr) != (p.n_q2 != 0) || (diff_part && (paged || lse))) return hipErrorInvalidValue;  // two sets: dense two-pass calls
-    a.n_cgrp = p.tab.cu_cgrp[p.n_seq];
     a.one_L = p.n_seq == 1 ? p.tab.cu_seq[1] : 0;
-    a.one_waves = p.n_seq == 1 ? p.tab.cu_chunk[1] : 0;
-
-    dim3 grid((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
-    hipError_t e;
+    a.layer_quads = p.cu_quad[p.n_seq];
+    for (int s = 0; s <= p.n_seq; ++s) { a.cu_seq[s] = p.tab.cu_seq[s]; a.cu_quad[s] = p.cu_quad[s]; }
+    auto share_out = [&](const Split& from, SplitArgs& to, int32_t* cu) {
+        to = from.args;
+        for (int s = 0; s <= p.n_seq; ++s) cu[s] = from.cu[s];
+    };
+    share_out(p.split, a.own, a.cu_wg);
+    a.inv_h_kv = inverse(p.h_kv);
     a.lse = lse;
-    a.n_part = 0; a.fuse_combine = 0;
-    for (int s = 0; s <= p.n_seq; ++s) a.cu_part[s] = 0;
-    const bool many_rows = p.by_rows;  // more query rows per KV head than a wave holds, or two sets of them: jq_score_rows_kernel
+    a.part = a.own; a.fuse_combine = 0;
+    a.flags = nullptr; a.token = 0; a.wait_ticks = 0; a.n_sets = p.split.n_sets;
+
+    const dim3 block(kScoreWaves * 64);
+    const unsigned wgs = (unsigned)(p.split.n_wg * p.h_kv);
+    hipError_t e;
+    if (!lse && p.one_launch && flags_cleared_later && !marks) {
+        a.flags = (uint64_t*)(ws + p.off_flags);
+        a.token = next_token();
+        a.wait_ticks = (int64_t)knobs().wait_us * 100;
+        const int nqt = p.row_tiles;
+        return paged ? launch_passes_n<true>(nqt, a, dim3(wgs), st) : launch_passes_n<false>(nqt, a, dim3(wgs), st);
+    }
     if (!lse) {
         const int nqt = min(p.row_tiles, kMaxRowTiles);
         // all row groups in one launch (in several where the grid would get too large for one)
-        const int64_t wgs = grid.x;
         const int per_launch = (int)max((int64_t)1, min((int64_t)p.row_groups, ((int64_t)1 << 23) / wgs));
         for (a.rg0 = 0; a.rg0 < p.row_groups; a.rg0 += per_launch) {
             a.n_rg = min(per_launch, p.row_groups - a.rg0);
-            const dim3 g1((unsigned)(wgs * a.n_rg));
+            const dim3 g1(wgs * a.n_rg);
             e = paged ? launch_stats_n<true>(nqt, a, g1, st, marks) : launch_stats_n<false>(nqt, a, g1, st, marks);
             if (e != hipSuccess) return e;
         }
         a.n_rg = 1; a.rg0 = 0;
-        // Pass 1 leaves one partial per workgroup.  With few of them per sequence every pass-2 workgroup merges
-        // its head's partials itself; a very long sequence has hundreds, and then one small launch merges them
+        // Pass 1 leaves one set of statistics per share.  With few of them per sequence every pass-2 workgroup merges
+        // its head's sets itself; a very long sequence has hundreds, and then one small launch merges them
         // once (and clears the selection's words on the way).
-        int max_parts = 0;
-        for (int s = 0; s < p.n_seq; ++s) max_parts = max(max_parts, p.tab.cu_cgrp[s + 1] - p.tab.cu_cgrp[s]);
-        a.fuse_combine = max_parts <= 64 && !many_rows;
+        share_out(p.split, a.part, a.cu_part);
+        a.fuse_combine = p.split.max_sets <= 64 && !p.by_rows;
         if (!a.fuse_combine) {
             const int64_t n_row_tiles = (int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles;
             e = launch_kernel(jq_combine_kernel, dim3((unsigned)min(n_row_tiles, (int64_t)1 << 20)), dim3(kRowTile * kCombineLanes), 0, st, nullptr, -1, a);
             if (e != hipSuccess) return e;
             a.zero = nullptr;  // done by the combine launch
         }
-        // the second pass cuts the sequences into its own number of waves
-        a.n_part = a.n_cgrp;
-        for (int s = 0; s <= p.n_seq; ++s) a.cu_part[s] = p.tab.cu_cgrp[s];
-        for (int s = 0; s <= p.n_seq; ++s) { a.tab.cu_chunk[s] = p.cu_chunk2[s]; a.tab.cu_cgrp[s] = p.cu_cgrp2[s]; }
-        a.n_cgrp = p.cu_cgrp2[p.n_seq];
-        a.one_waves = p.n_seq == 1 ? p.cu_chunk2[1] : 0;
-        grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
     }
-    if (many_rows) {
-        if (lse) {  // the second pass's own tables and the -beta/c terms, which a combine launch provides otherwise
+    if (p.by_rows) {  // more query rows per KV head than a wave holds, or two sets of them
+        if (lse) {  // the -beta/c terms, which a combine launch provides otherwise
             const int64_t n = (int64_t)p.n_layers * p.n_seq * p.h_kv * a.RP;
             e = launch_kernel(jq_lse_aug_kernel, dim3((unsigned)min((n + 255) / 256, (int64_t)2048)), dim3(256), 0, st, nullptr, -1, a, n);
             if (e != hipSuccess) return e;
-            for (int s = 0; s <= p.n_seq; ++s) a.tab.cu_cgrp[s] = p.cu_cgrp2[s];
-            a.n_cgrp = p.cu_cgrp2[p.n_seq];
-            grid = dim3((unsigned)((int64_t)p.n_layers * a.n_cgrp * p.h_kv));
         }
-        const dim3 block(kScoreWaves * 64);
+        const dim3 grid((unsigned)((int64_t)p.n_layers * a.layer_quads * p.h_kv));
         if (diff_part) return launch_kernel(jq_score_rows_kernel<false, true>, grid, block, 0, st, nullptr, -1, a);
         if (paged) return launch_kernel(jq_score_rows_kernel<true, false>, grid, block, 0, st, marks, kTrScore, a);
         return launch_kernel(jq_score_rows_kernel<false, false>, grid, block, 0, st, marks, kTrScore, a);
     }
+    // the second pass may share the keys out in its own way
+    const Split& own = lse ? p.split : p.split2;
+    share_out(own, a.own, a.cu_wg);
+    const dim3 grid((unsigned)(own.n_wg * p.h_kv));
     if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);
     return lse ? launch_score_n<true, false>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, false>(p.row_tiles, a, grid, st, marks);
 }

@@ -282,6 +282,8 @@ struct PoolSelectArgs {
     float* out;        // pooled scores, or null
     int32_t pool_k;
     float inv_k;
+    uint64_t* flags;   // words to clear: the flags of a launch that did both passes over K (or null)
+    int32_t n_flags;
     SelectArgs sel;
 };
 constexpr int kSmallBins = 2048;
@@ -312,6 +314,8 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
         raw[u] = in_row[min((uint32_t)(u * THREADS + tid), (uint32_t)L - 1u)];
     }
     for (int b = tid; b < kSmallBins; b += THREADS) bins[b] = 0u;
+    if (pa.flags && blockIdx.y == 0)
+        for (int i = (int)blockIdx.x * THREADS + tid; i < pa.n_flags; i += (int)gridDim.x * THREADS) pa.flags[i] = 0;
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
         const int j = u * THREADS + tid;
@@ -863,6 +867,8 @@ hipError_t launch_pool_select(const Plan& p, const float* in, float* out, bool p
     PoolSelectArgs a;
     a.in = in; a.out = out;
     a.pool_k = p.pool_k; a.inv_k = 1.0f / (float)p.pool_k;
+    a.flags = p.one_launch && pool ? (uint64_t*)(ws + p.off_flags) : nullptr;  // an eviction's
+    a.n_flags = p.split.n_sets * p.h_kv;
     if (p.marks)  // no pooling kernel of its own: an interval with nothing in it
         for (int i = 0; i < 2; ++i) {
             const hipError_t e = hipEventRecord((hipEvent_t)p.marks[2 * kTrPool + i], st);

@@ -1,0 +1,93 @@
+"""Both passes over K in one launch (every eviction but the traced one, up to 64 workgroups per sequence and head), and how its
+workgroups share the keys: contiguous, equal portions of all sequences in a row, so that workgroups come to several sequences
+and sequences to several workgroups."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2509_10798_amd as jq
+from parity import assert_scores_close, to_dev_bf16
+from workloads import f32_to_bf16_bits
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(n_layers, seq_lens, n_q, h_q, h_kv, seed=21):
+    rng = np.random.default_rng(seed)
+    Q = f32_to_bf16_bits(rng.standard_normal((n_layers, len(seq_lens), n_q, h_q, 128)).astype(np.float32))
+    K = f32_to_bf16_bits(rng.standard_normal((n_layers, sum(seq_lens), h_kv, 128)).astype(np.float32))
+    return Q, K
+
+
+def _evict(sh, Q, K):
+    """Scores (unpooled: pool_k is 1) and kept positions through the fused call."""
+    _, _, idx, scores = jq.evict(sh, Q, K, K)
+    return scores, idx
+
+
+SHAPES = [
+    (1, [129], 8, 8, 8),                      # two quads of 128 keys, the second with one key
+    (1, [4099], 32, 8, 2),                    # whole workgroups for the one sequence, a partial last quad
+    (3, [1000, 127, 1, 128, 2049], 16, 8, 8),  # portions that end inside sequences; sequences of a key, of less than and of exactly a quad
+    (40, [300], 32, 8, 8),                    # more layers than workgroups per head
+    (2, [70] * 30, 4, 4, 1),                  # thirty sequences of less than a quad: a workgroup has many shares
+    (5, [9999], 32, 12, 4),                   # layers that do not divide the workgroups; a group of three
+    (1, [5000, 200, 3000], 7, 9, 3),          # 21 rows; heads that do not divide the chip
+]
+
+
+@pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv", SHAPES)
+@pytest.mark.parametrize("wait_us", [None, 0])
+def test_one_launch_equals_two_and_the_oracle(knobs, n_layers, seq_lens, n_q, h_q, h_kv, wait_us):
+    # jq_score runs the passes one after the other on the same shares: the same bits.  Without patience a workgroup forms the
+    # missing statistics itself, from the same keys in the same order: the same bits again.
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("one launch", n_layers, seq_lens, n_q, h_q, h_kv, wait_us, flush=True)
+    Q, K = _inputs(n_layers, seq_lens, n_q, h_q, h_kv)
+    Qd, Kd = to_dev_bf16(Q), to_dev_bf16(K)
+    sh = jq.Shape(n_layers=n_layers, seq_lens=seq_lens, n_q=n_q, h_q=h_q, h_kv=h_kv, pool_k=1, budgets=[max(1, L // 8) for L in seq_lens])
+    if wait_us is not None:
+        knobs(JQ_WAIT_US=str(wait_us))
+    got, _ = _evict(sh, Qd, Kd)
+    two = jq.score(sh, Qd, Kd)
+    torch.cuda.synchronize()
+    assert torch.equal(got, two)
+    got = got.cpu().numpy()
+    cu = np.concatenate([[0], np.cumsum(seq_lens)])
+    for layer in {0, n_layers - 1}:
+        for s, L in enumerate(seq_lens):
+            ref = oracle.score(Q[layer, s], K[layer, cu[s]:cu[s + 1]])
+            assert_scores_close(got[layer, :, cu[s]:cu[s + 1]], ref, n_q * (h_q // h_kv) / L, "layer %d seq %d" % (layer, s))
+
+
+@pytest.mark.parametrize("L", [3000, 40000])  # the flags are cleared by the short tail's kernel, by the pooling kernel
+def test_replays_of_a_captured_eviction_wait_for_their_own_statistics(L):
+    # A replay's flags have the same value as the one before it: they have to be cleared in between, or the second pass would
+    # take the statistics of the keys that the buffers held before.
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("captured eviction", L, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def new(*size):
+        return torch.randn(size, generator=gen, device="cuda").bfloat16()
+    sh = jq.Shape(n_layers=2, seq_lens=[L], n_q=16, h_q=16, h_kv=8, budgets=[200])
+    Q, K = new(2, 1, 16, 16, 128), new(2, L, 8, 128)
+    out = dict(zip(("K_out", "V_out", "idx_out", "scores_out"), jq.evict(sh, Q, K, K)))
+    ws = jq.alloc_workspace(sh)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        jq.evict(sh, Q, K, K, ws=ws, **out)
+    for i in range(4):
+        Q.copy_(new(2, 1, 16, 16, 128) * (1.0 + i))  # other logits, other normalisers
+        K.copy_(new(2, L, 8, 128))
+        graph.replay()
+        torch.cuda.synchronize()
+        want = jq.evict(sh, Q, K, K)
+        torch.cuda.synchronize()
+        for a, b in zip(("K_out", "V_out", "idx_out", "scores_out"), want):
+            assert torch.equal(out[a].view(torch.int16), b.view(torch.int16)), (i, a)
