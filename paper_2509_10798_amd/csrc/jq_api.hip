@@ -44,7 +44,8 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 }
 
 // How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
-// with about that many; without it the quads are dealt evenly: as many workgroups as make one per CU.
+// with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
+// as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
 Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
     Split x{};
     const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
@@ -64,17 +65,23 @@ Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
     int64_t n = std::max<int64_t>(1, 256 / per);
     n = std::min(n, n_quads);
     if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
-    if (p.n_seq == 1 && n % units == 0) {  // whole workgroups for every layer
-        x.args.whole = 1;
-        x.args.per_layer = x.cu[1] = (int32_t)(n / units);
-        x.args.inv_layer = x.args.inv_n = inverse(x.args.per_layer);
-        x.n_wg = x.n_sets = (int32_t)n;
-        x.max_sets = x.args.per_layer;
-        return x;
-    }
-    // Where workgroups come to more than one sequence, those that do take fewer keys, if that makes the longest one shorter:
-    // a change of sequence costs about as much as kStartUp quads in either pass.
+    // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
+    // kStartUp of them (5.6 us in the first pass, 7 in the second, 1.25 us a quad).
     constexpr int kStartUp = 5;
+    auto whole = [&](int64_t steps) {  // workgroups per layer with at most that many quads each
+        int64_t wgs = 0;
+        for (int s = 0; s < p.n_seq; ++s) wgs += (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps;
+        return wgs;
+    };
+    int64_t steps = 0;  // the fewest that n workgroups can do with; 0: more (layer, sequence)s than workgroups
+    if (units <= n) {
+        int64_t lo = (n_quads + n - 1) / n, hi = max_quads;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (p.n_layers * whole(mid) <= n) hi = mid; else lo = mid + 1;
+        }
+        steps = lo;
+    }
     auto longest = [&](int64_t gap) {
         const int64_t total = n_quads + (units - 1) * gap;
         int64_t worst = 0, u0 = 0;
@@ -95,7 +102,29 @@ Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
         }
         return worst;
     };
-    if (units > 1 && units <= 1024 && n > 1 && n_quads / n > kStartUp && longest(kStartUp) < longest(0)) x.args.gap = kStartUp;
+    // (A workgroup that comes to more than one sequence may take fewer keys: a gap between sequences in the row that is dealt.)
+    int64_t dealt = INT64_MAX;
+    if (units > 1 && units <= 1024 && n > 1) {
+        dealt = longest(0);
+        const int64_t gapped = n_quads / n > kStartUp ? longest(kStartUp) : INT64_MAX;
+        if (gapped < dealt) { dealt = gapped; x.args.gap = kStartUp; }
+    } else if (units > 1) {
+        dealt = n_quads / n + kStartUp;  // many sequences, a few to every workgroup
+    }
+    if (steps && steps + kStartUp <= dealt) {
+        x.args = SplitArgs{};
+        x.args.whole = 1;
+        for (int s = 0; s < p.n_seq; ++s) {
+            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps);
+            x.cu[s + 1] = x.cu[s] + w;
+            x.max_sets = std::max(x.max_sets, w);
+        }
+        x.args.per_layer = x.cu[p.n_seq];
+        x.args.inv_layer = inverse(x.args.per_layer);
+        if (p.n_seq == 1) x.args.inv_n = inverse(x.args.per_layer);
+        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
+        return x;
+    }
     x.args.n = (int32_t)n;
     x.args.total = (int32_t)(n_quads + (units - 1) * x.args.gap);
     x.args.per_layer = p.cu_quad[p.n_seq] + p.n_seq * x.args.gap;
