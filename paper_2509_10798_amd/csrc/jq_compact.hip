@@ -179,6 +179,9 @@ hipError_t launch_mark_dest_pages(const Plan& p, uint32_t* dest_bits, hipStream_
 // Critical-KV hit rate (paper Eq. 6): |I_cur & I_ref| / |I_ref| per (layer, sequence, KV head) for two kept
 // sets given as ascending position lists.  One workgroup per problem; every position of the reference
 // list is looked up in the current list by binary search.  Integer work; the quotient is the only rounding.
+// One workgroup per problem is a chain of latencies: searching in memory, nine dependent reads for 512 kept positions.  The
+// current list therefore goes to LDS first, all requests together (lists beyond kHitLds positions, which fill a quarter of a CU's
+// LDS, are searched in memory as before).
 struct HitArgs {
     const int32_t* cur;  // [n_layers][h_kv][TB_cur]
     const int32_t* ref;  // [n_layers][h_kv][TB_ref]
@@ -188,8 +191,10 @@ struct HitArgs {
     int32_t cu_cur[JQ_MAX_SEQ + 1], cu_ref[JQ_MAX_SEQ + 1];
 };
 
+constexpr int kHitLds = 10240;
 __global__ __launch_bounds__(256) void jq_hit_rate_kernel(HitArgs a) {
     __shared__ uint32_t wave_hits[4];
+    __shared__ int32_t list[kHitLds];
     const int g = blockIdx.x % a.h_kv;
     const int s = (blockIdx.x / a.h_kv) % a.n_seq;
     const int layer = blockIdx.x / (a.h_kv * a.n_seq);
@@ -197,14 +202,23 @@ __global__ __launch_bounds__(256) void jq_hit_rate_kernel(HitArgs a) {
     const int32_t* cur = a.cur + ((int64_t)layer * a.h_kv + g) * a.TB_cur + a.cu_cur[s];
     const int32_t* ref = a.ref + ((int64_t)layer * a.h_kv + g) * a.TB_ref + a.cu_ref[s];
     uint32_t hits = 0;
-    for (int i = threadIdx.x; i < nr; i += 256) {
-        const int32_t want = ref[i];
-        int lo = 0, hi = nc;  // first position of cur that is >= want
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cur[mid] < want) lo = mid + 1; else hi = mid;
+    auto count = [&](const auto* sorted) __attribute__((always_inline)) {
+        for (int i = threadIdx.x; i < nr; i += 256) {
+            const int32_t want = ref[i];
+            int lo = 0, hi = nc;  // first position of the current list that is >= want
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (sorted[mid] < want) lo = mid + 1; else hi = mid;
+            }
+            hits += (lo < nc && sorted[lo] == want);
         }
-        hits += (lo < nc && cur[lo] == want);
+    };
+    if (nc <= kHitLds) {  // uniform
+        for (int i = threadIdx.x; i < nc; i += 256) list[i] = cur[i];
+        __syncthreads();
+        count(list);
+    } else {
+        count(cur);
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) hits += __shfl_xor(hits, d);
