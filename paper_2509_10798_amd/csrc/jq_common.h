@@ -177,6 +177,19 @@ __device__ __forceinline__ void store_stream16(void* p, uint4 v) {
     __builtin_nontemporal_store(x, (jq_u32x4*)p);
 }
 
+typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
+// The first lines of a kernel's arguments, which lie in memory, requested together: read where they are used, they arrive one
+// after the other, up to 1 us each.
+template <int LINES>
+__device__ __forceinline__ void argument_lines() {
+    const_i32_ptr p = (const_i32_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    int32_t x[LINES];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) x[i] = p[16 * i];
+#pragma unroll
+    for (int i = 0; i < LINES; ++i) asm volatile("" ::"s"(x[i]));
+}
+
 // Workgroup barrier that orders LDS traffic only: global loads and stores that are still outstanding stay in
 // flight across it (a plain __syncthreads() waits for all of them first).  For workgroups that communicate
 // through LDS alone.

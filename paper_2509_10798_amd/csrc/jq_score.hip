@@ -44,11 +44,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
-
 struct ScoreArgs {
     // What a workgroup needs to find its share and make its first requests comes first, in the few lines of constant memory that
-    // kernel_lines() has fetched at once: a wave's first reads of its arguments take about 1 us each where they chain.
+    // argument_lines() has fetched at once: a wave's first reads of its arguments take about 1 us each where they chain.
     int32_t n_layers, n_seq, h_kv;
     uint32_t inv_h_kv;    // for udiv()
     int32_t n_rg, rg0;    // first pass: groups of NQT query-row tiles in this launch (1 unless a head has more than
@@ -105,12 +103,6 @@ __device__ __forceinline__ KArgs& kernel_args() {
     KArgs* p = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *p;
-}
-// The first lines of a kernel's arguments, requested together.
-__device__ __forceinline__ void kernel_lines() {
-    const_i32_ptr p = (const_i32_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-    const int32_t a = p[0], b = p[16], c = p[32], d = p[48], e = p[64];
-    asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e));
 }
 // x / d for the d that `inv` was made of (ceil(2^32 / d), 0 for 1): the product is at most one too large
 __device__ __forceinline__ uint32_t udiv(uint32_t x, uint32_t d, uint32_t inv) {
@@ -844,7 +836,7 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
 template <int NQT, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
-    kernel_lines();
+    argument_lines<5>();
     Place at = place_of(kernel_args(), false);
     for (;;) {
         KArgs& a = kernel_args();
@@ -1210,7 +1202,7 @@ __device__ __forceinline__ void clear_words(KArgs& a) {  // what the selection n
 template <int NQT, bool FROM_LSE, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
-    kernel_lines();
+    argument_lines<5>();
     Place at = place_of(kernel_args(), true);  // from the end: the keys pass 1 read last are fetched first
     clear_words(kernel_args());
     for (;;) {
@@ -1243,7 +1235,7 @@ template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placem
 template <int NQT, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
-    kernel_lines();
+    argument_lines<5>();
     const int64_t t_entry = wall_clock64();
     Place at = place_of(kernel_args(), false);
     clear_words(kernel_args());
