@@ -199,34 +199,49 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Inclusive prefix sum over a block of THREADS threads (thread order); `tmp` (LDS) holds THREADS/64 + 1 words.
+// Wave-wide scans and reductions in the vector ALU (DPP): lane i takes the value of lane i - 1, - 2, - 4, - 8 of its row of 16,
+// then whole rows take the last lane of the row, of the half before them.  Through LDS (shuffles) each of the six steps was a
+// round trip of some 120 cycles in kernels that are chains of such steps.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t otherwise, uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)otherwise, (int)x, CTRL, ROWS, 0xF, false);
+}
+template <class Op>  // lane 63 (and in ROW every lane of it) ends with everything up to it: an inclusive scan
+__device__ __forceinline__ uint32_t row_scan(uint32_t x, uint32_t identity, Op op) {
+    x = op(x, dpp_or<0x111, 0xF>(identity, x));
+    x = op(x, dpp_or<0x112, 0xF>(identity, x));
+    x = op(x, dpp_or<0x114, 0xF>(identity, x));
+    return op(x, dpp_or<0x118, 0xF>(identity, x));
+}
+template <class Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
+    x = row_scan(x, identity, op);
+    x = op(x, dpp_or<0x142, 0xA>(identity, x));  // the last lane of rows 0 and 2 for rows 1 and 3
+    return op(x, dpp_or<0x143, 0xC>(identity, x));  // the last lane of the lower half for the upper
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(x, 0xFFFFFFFFu, [](uint32_t a, uint32_t b) { return a < b ? a : b; }), 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan(x, 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; }), 63);
+}
+
+// Inclusive prefix sum over a block of THREADS threads (thread order); `tmp` (LDS) holds THREADS/64 words.  Every wave scans the
+// waves' totals itself.
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t* tmp, uint32_t* total) {
     constexpr int kW = THREADS / 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
+    static_assert(kW <= 16, "the totals fill a row at most");
+    auto add = [](uint32_t a, uint32_t b) { return a + b; };
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t x = wave_scan(v, 0u, add);
     lds_barrier();  // tmp may still be read from a previous call
     if (lane == 63) tmp[wave] = x;
     lds_barrier();
-    if (wave == 0) {
-        const uint32_t w = lane < kW ? tmp[lane] : 0u;
-        uint32_t wi = w;
-#pragma unroll
-        for (int d = 1; d < kW; d <<= 1) {
-            const uint32_t y = __shfl_up(wi, d);
-            if (lane >= d) wi += y;
-        }
-        if (lane < kW) tmp[lane] = wi - w;  // exclusive wave offsets
-        if (lane == kW - 1) tmp[kW] = wi;
-    }
-    lds_barrier();
-    *total = tmp[kW];
-    return x + tmp[wave];
+    const uint32_t w = row_scan(lane < kW ? tmp[lane] : 0u, 0u, add);
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)w, kW - 1);
+    const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)w, wave > 0 ? wave - 1 : 0);
+    return x + (wave > 0 ? before : 0u);
 }
 
 // Kernels whose start/stop timestamps jq_evict_traced reports, in launch order.

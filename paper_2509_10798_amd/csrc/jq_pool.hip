@@ -178,11 +178,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
         bin[u] = in ? key[u] >> 21 : 0xFFFFFFFFu;  // 0xFFFFFFFF: no element
         if (in) { top = max(top, bin[u]); bottom = min(bottom, bin[u]); }
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        top = max(top, (uint32_t)__shfl_xor((int)top, d));
-        bottom = min(bottom, (uint32_t)__shfl_xor((int)bottom, d));
-    }
+    top = wave_max(top);
+    bottom = wave_min(bottom);
     if ((threadIdx.x & 63) == 0) { wave_top[threadIdx.x >> 6] = top; wave_bottom[threadIdx.x >> 6] = bottom; }
     lds_barrier();
 #pragma unroll

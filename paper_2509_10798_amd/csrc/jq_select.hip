@@ -404,11 +404,8 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
         for (int u = 0; u < VPT; ++u) { lo = min(lo, key[u]); hi = max(hi, key[u]); }
         lo -= 1u; hi += 1u;
     }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        lo = min(lo, (uint32_t)__shfl_xor((int)lo, d));
-        hi = max(hi, (uint32_t)__shfl_xor((int)hi, d));
-    }
+    lo = wave_min(lo);
+    hi = wave_max(hi);
     if ((tid & 63) == 0) { ext[tid >> 6] = lo; ext[32 + (tid >> 6)] = hi; }
     lds_barrier();
 #pragma unroll
@@ -481,16 +478,20 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
     const uint32_t per_slice = (p.B + gridDim.y - 1) / gridDim.y;
     const uint32_t o_begin = min(p.B, blockIdx.y * per_slice), n_rows = min(p.B, o_begin + per_slice) - o_begin;
     // (Slots rise with the positions: most threads' kept positions belong to other slices, and whole waves have nothing to
-    // list.  Without the test every wave went through its fullest thread's: 2.2 us with 32 positions per thread.)
-    const bool mine = gt + min(eq, need) < o_begin + n_rows && gt + n_gt + min(eq + n_eq, need) > o_begin;
-    for (uint32_t m = mine ? m_gt | (eq < need ? m_eq : 0u) : 0u; m != 0u; m &= m - 1u) {
-        const uint32_t bit = m & (0u - m);
-        const bool is_eq = (m_eq & bit) != 0u;
-        if (is_eq && eq >= need) continue;
-        const uint32_t slot = gt + min(eq, need) - o_begin;
-        if (slot < n_rows) slot_pos[slot] = (uint32_t)(j0 + __builtin_ctz(m));  // the staged scores are dead
-        gt += !is_eq;
-        eq += is_eq;
+    // list.  The others test a bit per position: going from set bit to set bit, a wave went through its fullest thread's, 2 us
+    // with 32 positions per thread.)
+    uint32_t kept = m_gt, slot = gt + min(eq, need) - o_begin;
+    if (eq < need) {
+        uint32_t ties = m_eq;
+        for (uint32_t room = need - eq, n = n_eq; n > room; --n) ties &= ~(0x80000000u >> __builtin_clz(ties));  // the highest ones go
+        kept |= ties;
+    }
+    if (kept != 0u && (int)slot < (int)n_rows && (int)(slot + __popc(kept)) > 0) {
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            if (((kept >> u) & 1u) && slot < n_rows) slot_pos[slot] = (uint32_t)(j0 + u);  // the staged scores are dead
+            slot += (kept >> u) & 1u;
+        }
     }
     lds_barrier();
     for (uint32_t o = threadIdx.x; o < n_rows; o += THREADS) p.emit(o_begin + o, (int)slot_pos[o]);
