@@ -75,6 +75,7 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     uint32_t* low = (uint32_t*)tile;
     static_assert(sizeof(tile) >= sizeof(float) * (kPoolBlockPos + kPoolThreads), "a whole round of loads for the halo");
     static_assert(2 * kPoolMaxHalo <= kPoolThreads, "one round of loads for the halo");
+    argument_lines<2>();
     const int g = blockIdx.y, layer = blockIdx.z;
     if (a.flags && blockIdx.x == 0)  // the workgroups of a layer's and head's first segment share it
         for (int i = (layer * a.h_kv + g) * kPoolThreads + (int)threadIdx.x; i < a.n_flags; i += a.n_layers * a.h_kv * kPoolThreads) a.flags[i] = 0;

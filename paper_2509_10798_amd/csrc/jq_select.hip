@@ -506,6 +506,7 @@ constexpr int kFinWaves = kFinThreads / 64;
 constexpr int kSegBatch = 16;  // segments whose first 64 entries a wave requests before it knows the threshold bin
 
 __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectArgs a, int words_cap, int qual_cap) {
+    argument_lines<5>();
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
     uint32_t* bins2 = lds;                        // 2048: level-2 histogram
     uint32_t* bins3 = bins2 + 2048;               // 1024: level-3 histogram
