@@ -46,7 +46,7 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
 // How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
 // with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
 // as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
-Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
+Split make_split(const Plan& p, int32_t chunk, int32_t max_quads, bool tight) {
     Split x{};
     const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
     if (chunk) {
@@ -62,7 +62,9 @@ Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
         return x;
     }
     const int64_t per = (int64_t)p.h_kv * p.row_groups;
-    int64_t n = std::max<int64_t>(1, 256 / per);
+    // (With many query rows the keys come out of the caches and arithmetic is the bound: two workgroups per CU hide each other's
+    // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
+    int64_t n = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per);
     n = std::min(n, n_quads);
     if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
     // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
@@ -140,7 +142,8 @@ Split make_split(const Plan& p, int32_t chunk, int32_t max_quads) {
 // Validates `shape` and derives the plan.  `need_budgets`: the entry point uses budgets.
 // (`sweeps` false: a call that neither passes over K nor shares a workspace with one that does; how the sequences are cut
 // is of no account then and not looked for.)  `n_q2`: tokens of a second query set over the same keys, or 0.
-int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = true, int32_t n_q2 = 0) {
+// `tight`: the smallest workspace that will do, whatever it costs.
+int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = true, int32_t n_q2 = 0, bool tight = false) {
     if (!sh || !sh->cu_seqlens) return JQ_ERR_NULL;
     if (need_budgets && !sh->budgets) return JQ_ERR_NULL;
     if (sh->n_layers < 1 || sh->n_seq < 1 || sh->n_q < 1 || sh->h_q < 1 || sh->h_kv < 1 || sh->d < 1) return JQ_ERR_SHAPE;
@@ -219,8 +222,8 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
             for (int s = 0; s < sh->n_seq; ++s) wgs += (sh->cu_seqlens[s + 1] - sh->cu_seqlens[s] - 1) / (kScoreWaves * chunk) + 1;
             if ((int64_t)p.n_layers * wgs * p.h_kv >= INT32_MAX) return JQ_ERR_UNSUPPORTED;
         }
-        p.split = make_split(p, knobs().chunk_keys, max_quads);
-        p.split2 = knobs().chunk_keys2 == knobs().chunk_keys ? p.split : make_split(p, knobs().chunk_keys2, max_quads);
+        p.split = make_split(p, knobs().chunk_keys, max_quads, tight);
+        p.split2 = knobs().chunk_keys2 == knobs().chunk_keys ? p.split : make_split(p, knobs().chunk_keys2, max_quads, tight);
     }
 
     // pooling workgroups (= segments of the selection's lists): whole sequences in pieces of kSegLen positions
@@ -503,9 +506,9 @@ static int evict_impl(const jq_shape* shape, const void* Q, const void* K, const
                       const void* k_tail, void* K_out, void* V_out, int32_t* idx_out, float* scores_out, void* ws,
                       size_t ws_bytes, void* stream, void* const* marks, const jq_pages* pages = nullptr,
                       bool paged = false, const jq_pages* out_pages = nullptr, const int32_t* pos_in = nullptr,
-                      int32_t* pos_out = nullptr) {
+                      int32_t* pos_out = nullptr, bool tight = false) {
     Plan p;
-    int rc = make_plan(shape, true, &p);
+    int rc = make_plan(shape, true, &p, true, 0, tight);
     if (rc != JQ_OK) return rc;
     if (paged && (rc = apply_pages(pages, &p)) != JQ_OK) return rc;
     if (out_pages && (rc = apply_out_pages(out_pages, &p)) != JQ_OK) return rc;
@@ -674,8 +677,11 @@ int static_scratch(void** out) {
 int jq_evict_static(const jq_shape* shape, const void* Q, const void* K, const void* V, void* K_out, void* V_out,
                     int32_t* idx_out, float* scores_out, void* stream) {
     Plan p;
-    const int rc = make_plan(shape, true, &p);
+    int rc = make_plan(shape, true, &p);
     if (rc != JQ_OK) return rc;
+    // Many query rows and few keys: statistics of fewer workgroups may still fit.
+    const bool tight = p.ws_bytes > (size_t)JQ_STATIC_WS_BYTES;
+    if (tight && (rc = make_plan(shape, true, &p, true, 0, true)) != JQ_OK) return rc;
     if (p.ws_bytes > (size_t)JQ_STATIC_WS_BYTES) return JQ_ERR_WORKSPACE;  // the problem needs more scratch than the array holds
     if (!Q || !K || !V || !K_out || !V_out) return JQ_ERR_NULL;
     void* ws = nullptr;
@@ -684,7 +690,7 @@ int jq_evict_static(const jq_shape* shape, const void* Q, const void* K, const v
     // Nothing in the scratch area has to survive from, or be cleared before, a call: the first kernels write the
     // partial statistics and clear the histograms and list counters before anything reads them.
     return evict_impl(shape, Q, K, V, nullptr, nullptr, K_out, V_out, idx_out, scores_out, ws, JQ_STATIC_WS_BYTES, stream,
-                      nullptr);
+                      nullptr, nullptr, false, nullptr, nullptr, nullptr, tight);
 }
 
 int jq_score_paged(const jq_shape* shape, const jq_pages* pages, const void* Q, const void* K_pool, const float* lse,
