@@ -308,33 +308,13 @@ __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, char* dst
                                              (int)soff, 0, 0);
 }
 
-// `tile_off` = byte offset of the tile's first key row inside the buffer resource (uniform).
-__device__ __forceinline__ void fetch_tile(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off,
-                                           uint32_t row_bytes, int valid, uint32_t tl, int lane) {
-    if (valid >= kKeyTile) {
+// `tile_off` = byte offset of the tile's first key row inside the buffer resource (uniform), `tl` = tile_lane().  Rows past the
+// end of a sequence arrive as zeros -- its resource ends there, and the hardware's check covers the scalar offset -- or, in a
+// paged pool, as whatever the rest of the page holds; the first pass masks those keys, the second does not store them, and
+// no other key's values meet them.
+__device__ __forceinline__ void fetch_tile(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off, uint32_t row_bytes, uint32_t tl) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl ^ (64u * (i & 3)), tile_off + 4 * i * row_bytes);
-    } else {  // last, partial tile of a sequence: rows past the end re-read the last valid key (masked later)
-        asm volatile("" : "+v"(lane));  // keep this rarely taken path's address arithmetic out of the caller's loop
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = 4 * i + (lane >> 4);
-            const uint32_t voff = (uint32_t)min(r, valid - 1) * row_bytes + (((lane & 15) ^ (r & 15)) << 4);
-            lds_dma16(rsrc, slot + 1024 * i, voff, tile_off);
-        }
-    }
-}
-
-// The same with the general addressing whatever `valid` (>= 1) is: no branch, for requests that have to sit in one
-// basic block with other loads.
-__device__ __forceinline__ void fetch_tile_any(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off,
-                                               uint32_t row_bytes, int valid, int lane) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = 4 * i + (lane >> 4);
-        const uint32_t voff = (uint32_t)min(r, valid - 1) * row_bytes + (((lane & 15) ^ (r & 15)) << 4);
-        lds_dma16(rsrc, slot + 1024 * i, voff, tile_off);
-    }
+    for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl ^ (64u * (i & 3)), tile_off + 4 * i * row_bytes);
 }
 
 // MFMA operand fragments of the tile in `slot`: lane l takes key row (l & 31), logical chunks
@@ -648,12 +628,10 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
             const int t = walk.t, page = page_next;
             walk.step(h);
             if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
-            fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes,
-                       h.L - t * kKeyTile, tl, lane);
+            fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl);
         } else {
             const int t = k - n_tiles;
-            fetch_tile(tail_rsrc, slots + (k & 1) * kSlotBytes, (uint32_t)t * kKeyTile * ks.row_bytes, ks.row_bytes,
-                       a.n_q - t * kKeyTile, tl, lane);
+            fetch_tile(tail_rsrc, slots + (k & 1) * kSlotBytes, (uint32_t)t * kKeyTile * ks.row_bytes, ks.row_bytes, tl);
         }
     };
     // The first key tile goes to slot 0 at once; the second slots first serve as the staging area that turns
@@ -668,17 +646,16 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
     walk.step(h);
     if (PAGED && n_tiles > 1) page_next = tile_page<PAGED>(ks, walk.t);
     const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
-    const int valid_first = min(kKeyTile, h.L - t_first * kKeyTile);
     bf16x8 qf[NQT][8];
     if (SHARED && q_there) {
-        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
     } else {
         u32x4 qraw[8];
         q_rows_request<NQT>(a, h, g, rg, lane, qraw);
         __builtin_amdgcn_sched_barrier(0);
-        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
         __builtin_amdgcn_sched_barrier(0);
         q_rows_stage<NQT>(lane, SHARED ? lds + kLdsQ : lds + kSlotBytes, SHARED ? kSlotBytes : 2 * kSlotBytes, qraw, qf);
     }
@@ -968,8 +945,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
         const int t = walk.t, page = page_next;
         walk.step(h);
         if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
-        fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes,
-                   h.L - t * kKeyTile, tl, lane);
+        fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl);
         return t;
     };
     bf16x8 qf[NQT][8];
@@ -999,11 +975,10 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     walk.step(h);
     if (PAGED && n_tiles > 1) page_next = tile_page<PAGED>(ks, walk.t);
     const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
-    const int valid_first = min(kKeyTile, h.L - t_first * kKeyTile);
     float2 mz[kFirstParts];
     uint2 aug_direct[NQT];  // the terms of the lane's rows where no merging is due
     if (NORMS == kNormsShared && q_there) {
-        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
     } else {
@@ -1030,7 +1005,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
             else if (NORMS == kNormsMerged) aug_direct[qt] = *(const uint2*)nsrc[qt];
         }
         __builtin_amdgcn_sched_barrier(0);
-        fetch_tile_any(ks.rsrc, slots, off_first, ks.row_bytes, valid_first, lane);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
         __builtin_amdgcn_sched_barrier(0);
         if (NORMS == kNormsLse) {
 #pragma unroll
@@ -1358,7 +1333,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     {
         const int t = min(tile0 + wv, last_tile);  // tiles past the sequence's end repeat its last one and are not stored
         const uint32_t off = tile_offset<PAGED>(ks, t, tile_page<PAGED>(ks, t));
-        fetch_tile_any(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, min(kKeyTile, L - t * kKeyTile), lane);
+        fetch_tile(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, tile_lane(lane, ks.row_bytes));
     }
     fetch_rows(0);
     uint2 aug_next = aug[min(wv, n_rt - 1) * kRowTile];

@@ -91,3 +91,34 @@ def test_replays_of_a_captured_eviction_wait_for_their_own_statistics(L):
         torch.cuda.synchronize()
         for a, b in zip(("K_out", "V_out", "idx_out", "scores_out"), want):
             assert torch.equal(out[a].view(torch.int16), b.view(torch.int16)), (i, a)
+
+
+@pytest.mark.parametrize("seq_lens,n_q", [([70, 33, 129], 8), ([1], 8), ([200], 40)])  # 16 and 80 query rows per head; 160: streamed rows
+@pytest.mark.parametrize("h_q", [4, 8])
+def test_rest_of_a_page_may_hold_anything(seq_lens, n_q, h_q):
+    # the last tile of a sequence is fetched whole: keys behind the sequence's end, NaN here, must not reach any score
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("rest of a page", seq_lens, n_q, h_q, flush=True)
+    h_kv, page = 2, 64
+    Q, K = _inputs(1, seq_lens, n_q, h_q, h_kv, seed=22)
+    n_pages = sum(-(-L // page) for L in seq_lens) + 1
+    pool = torch.full((1, n_pages, page, h_kv, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    table = torch.zeros((len(seq_lens), max(-(-L // page) for L in seq_lens)), dtype=torch.int32)
+    Kd, at, nxt = to_dev_bf16(K), 0, 1
+    for s, L in enumerate(seq_lens):
+        for j in range(0, L, page):
+            table[s, j // page] = nxt
+            n = min(page, L - j)
+            pool[0, nxt, :n] = Kd[0, at + j:at + j + n]
+            nxt += 1
+        at += L
+    sh = jq.Shape(n_layers=1, seq_lens=seq_lens, n_q=n_q, h_q=h_q, h_kv=h_kv, pool_k=1, budgets=[max(1, L // 4) for L in seq_lens])
+    pages = jq.Pages(page, n_pages, table.cuda())
+    two = jq.score_paged(sh, pages, to_dev_bf16(Q), pool)
+    got = jq.evict_paged(sh, pages, to_dev_bf16(Q), pool, pool)[3]
+    torch.cuda.synchronize()
+    cu = np.concatenate([[0], np.cumsum(seq_lens)])
+    for x in (two.cpu().numpy(), got.cpu().numpy()):
+        for s, L in enumerate(seq_lens):
+            assert_scores_close(x[0, :, cu[s]:cu[s + 1]], oracle.score(Q[0, s], K[0, cu[s]:cu[s + 1]]), n_q * (h_q // h_kv) / L, "seq %d" % s)
