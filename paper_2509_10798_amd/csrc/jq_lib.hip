@@ -1,11 +1,11 @@
 // libjq.so is built from this ONE translation unit.
 //
-// Why: the four kernels of an eviction step over more than 32768 tokens (both passes over K, pooling, selection +
+// Why: the kernels of an eviction step over more than 32768 tokens (both passes over K in one, pooling, selection +
 // gather) run back to back, thousands of times, and the instruction cache of a compute-unit pair (64 KB) keeps its
-// contents across kernel launches.  Their code is 61.4 KB together (21.7 + 13.3 + 4.3 + 22.2; a shorter call runs
-// three kernels of at most 53 KB: both passes and jq_pool_select_kernel).  Compiled as separate translation units every file becomes a code
+// contents across kernel launches.  Their code is 63.2 KB together (38.0 + 4.0 + 21.2; a shorter call runs
+// two kernels of at most 57.6 KB: both passes and jq_pool_select_kernel).  Compiled as separate translation units every file becomes a code
 // object of its own and the loader decides where each one goes; in one code object the kernels lie where the
-// order of definitions and instantiations puts them, and that order is chosen so that those four are neighbours:
+// order of definitions and instantiations puts them, and that order is chosen so that they are neighbours:
 // the non-template kernels come first in the order of the includes below (the selection's last), then the
 // kernel templates in the order of their first instantiation -- which is why jq_score.hip and jq_pool.hip
 // instantiate the instances of the headline shape explicitly, ahead of their launch switches.  A contiguous
