@@ -268,7 +268,7 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
 // With two query sets in the plan, Q2 and `diff_part` ([n_layers][workgroups of the second pass per layer and head][h_kv]) the
 // last launch stores no scores: it leaves one partial sum per workgroup of the squared differences of the sets' maps (Eq. 5
 // forward, see launch_mse_reduce).
-// `flags_cleared_later`: the caller launches a kernel behind this that clears the plan's flags (flag_words() words at off_flags),
+// `flags_cleared_later`: the caller launches a kernel behind this that clears the plan's flags (split.n_sets * h_kv 64-bit words at off_flags),
 // so that both passes may go in one launch.
 hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scores, char* ws, hipStream_t st,
                         uint32_t* zero = nullptr, size_t zero_words = 0, const float* lse = nullptr,
@@ -294,23 +294,22 @@ bool select_fast_path(const Plan& p);
 // repeats pooling and selection in its one workgroup, which costs more the longer the sequence, while the lists of the other
 // way cost more the more is kept.  Whole calls of one layer with 8 KV heads, one kernel / two, in us:
 //   kept:          256          512          1024         2048         3072
-//    2048     22.4 / 34.0
-//   12000     32.9 / 36.2               33.0 / 37.3
-//   16384     35.1 / 38.7               35.6 / 40.0
-//   20000     43.1 / 41.4  42.8 / 42.0  43.2 / 43.4  44.5 / 45.7
-//   28000     49.0 / 48.0  49.2 / 48.5  49.4 / 49.6  50.8 / 52.2  51.0 / 55.8
-//   32768     51.7 / 51.0  51.4 / 51.3  51.7 / 52.5  52.9 / 55.0  53.5 / 58.1
-// 4 layers: 20000, 256 kept 81.5 / 82.2; 32768 110.4 / 111.8, 3072 kept 125 / 132.  Above 16384 positions one workgroup fills a
-// CU's LDS, and more than 256 problems take turns: 32768 + 63 x 300 (512 problems) 111.4 / 106.7, 4 layers of 32768 + 31 x
-// 500 272 / 257, 36 x 18000 598 / 585, 20000 + 35 x 500 93.1 / 84.3 -- two kernels then, except without pooling (36 x 18000
-// 591 / 621).  Up to 16384 it wins there too (48 x 9000 435 / 447, 40 x 16000 569 / 579).
+//    2048     18.4 / 28.1
+//   12000     26.2 / 31.5               26.3 / 32.8
+//   16384     28.6 / 34.6               28.4 / 35.4
+//   20000     34.4 / 36.9                            35.3 / 39.2
+//   28000     39.1 / 41.7                                         40.1 / 47.0
+//   32768     41.9 / 43.8  40.3 / 44.1  40.4 / 44.7               42.1 / 48.8
+// 4 layers: 20000, 256 kept 70.7 / 73.7; 32768 105.6 / 109.7, 3072 kept 123.9 / 133.3.  Above 16384 positions one workgroup fills a
+// CU's LDS, and more than 256 problems take turns: 32768 + 63 x 300 (512 problems) 88.7 / 88.1, 36 x 18000 557.5 / 551.6,
+// 20000 + 35 x 500 68.6 / 67.4 -- two kernels then, except without pooling (earlier builds: 36 x 18000 591 / 621).  Up to
+// 16384 it wins there too (earlier builds: 48 x 9000 435 / 447, 40 x 16000 569 / 579).
 // Widths 1, 5 and 7 are compiled in; any other is summed tap by tap out of LDS, for 4 to 32 positions per thread:
-//   width:        3            9            13           31           63           129
-//    2048     22.3 / 32.3  23.4 / 32.3  24.1 / 32.9  27.5 / 33.8  35.0 / 37.3  48.3 / 68.9
-//    4096     24.3 / 33.0  26.5 / 33.3  27.9 / 34.1  34.8 / 35.1  48.5 / 38.7  73.7 / 70.9
-//    8192     30.4 / 34.8  34.8 / 34.8  37.8 / 35.4  51.4 / 36.7  77.7 / 40.2   127 / 76.4
-//   16384     37.6 / 39.6  42.4 / 39.9  45.8 / 40.6  61.1 / 41.5  90.4 / 44.3   147 / 88.0
-//   32768     56.9 / 52.8  67.3 / 52.9  74.2 / 53.6   104 / 54.7   163 / 56.9   277 / 103
+//   width:        3            9            13           31           63
+//    2048                               20.6 / 29.5  24.0 / 30.2  31.2 / 33.7
+//    4096                               23.9 / 28.9  30.7 / 29.9  44.1 / 32.8
+//    8192                  29.1 / 30.4  32.2 / 30.9  45.6 / 31.8
+//   16384     30.9 / 34.9  35.9 / 35.1  39.1 / 35.7
 constexpr int kSmallMax = 32768;
 bool select_small(const Plan& p);
 bool evict_tail_small(const Plan& p);
