@@ -43,102 +43,6 @@ bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     return a0 < b0 + nb && b0 < a0 + na;
 }
 
-// How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
-// with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
-// as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
-Split make_split(const Plan& p, int32_t chunk, int32_t max_quads, bool tight) {
-    Split x{};
-    const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
-    if (chunk) {
-        for (int s = 0; s < p.n_seq; ++s) {
-            const int32_t L = p.tab.cu_seq[s + 1] - p.tab.cu_seq[s], n = (L - 1) / (kScoreWaves * chunk) + 1;
-            x.cu[s + 1] = x.cu[s] + n;
-            x.max_sets = std::max(x.max_sets, n);
-        }
-        x.args.whole = 1;
-        x.args.per_layer = x.cu[p.n_seq];
-        x.args.inv_layer = inverse(x.args.per_layer);
-        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
-        return x;
-    }
-    const int64_t per = (int64_t)p.h_kv * p.row_groups;
-    // (With many query rows the keys come out of the caches and arithmetic is the bound: two workgroups per CU hide each other's
-    // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
-    int64_t n = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per);
-    n = std::min(n, n_quads);
-    if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
-    // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
-    // kStartUp of them (5.6 us in the first pass, 7 in the second, 1.25 us a quad).
-    constexpr int kStartUp = 5;
-    auto whole = [&](int64_t steps) {  // workgroups per layer with at most that many quads each
-        int64_t wgs = 0;
-        for (int s = 0; s < p.n_seq; ++s) wgs += (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps;
-        return wgs;
-    };
-    int64_t steps = 0;  // the fewest that n workgroups can do with; 0: more (layer, sequence)s than workgroups
-    if (units <= n) {
-        int64_t lo = (n_quads + n - 1) / n, hi = max_quads;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (p.n_layers * whole(mid) <= n) hi = mid; else lo = mid + 1;
-        }
-        steps = lo;
-    }
-    auto longest = [&](int64_t gap) {
-        const int64_t total = n_quads + (units - 1) * gap;
-        int64_t worst = 0, u0 = 0;
-        int32_t s = 0;
-        for (int64_t c = 0, b0 = 0; c < n; ++c) {
-            const int64_t b1 = (c + 1) * total / n;
-            int64_t cost = 0;
-            for (;;) {
-                const int64_t nq = p.cu_quad[s + 1] - p.cu_quad[s], lo = std::max(b0, u0), hi = std::min(b1, u0 + nq);
-                if (hi > lo) cost += hi - lo + kStartUp;
-                if (b1 < u0 + nq + gap || (b1 == total && u0 + nq >= total)) break;
-                u0 += nq + gap;
-                if (++s == p.n_seq) s = 0;
-                if (u0 >= b1) break;
-            }
-            worst = std::max(worst, cost);
-            b0 = b1;
-        }
-        return worst;
-    };
-    // (A workgroup that comes to more than one sequence may take fewer keys: a gap between sequences in the row that is dealt.)
-    int64_t dealt = INT64_MAX;
-    if (units > 1 && units <= 1024 && n > 1) {
-        dealt = longest(0);
-        const int64_t gapped = n_quads / n > kStartUp ? longest(kStartUp) : INT64_MAX;
-        if (gapped < dealt) { dealt = gapped; x.args.gap = kStartUp; }
-    } else if (units > 1) {
-        dealt = n_quads / n + kStartUp;  // many sequences, a few to every workgroup
-    }
-    if (steps && steps + kStartUp <= dealt) {
-        x.args = SplitArgs{};
-        x.args.whole = 1;
-        for (int s = 0; s < p.n_seq; ++s) {
-            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps);
-            x.cu[s + 1] = x.cu[s] + w;
-            x.max_sets = std::max(x.max_sets, w);
-        }
-        x.args.per_layer = x.cu[p.n_seq];
-        x.args.inv_layer = inverse(x.args.per_layer);
-        if (p.n_seq == 1) x.args.inv_n = inverse(x.args.per_layer);
-        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
-        return x;
-    }
-    x.args.n = (int32_t)n;
-    x.args.total = (int32_t)(n_quads + (units - 1) * x.args.gap);
-    x.args.per_layer = p.cu_quad[p.n_seq] + p.n_seq * x.args.gap;
-    for (int s = 0; s < p.n_seq; ++s) x.cu[s + 1] = p.cu_quad[s + 1] + (s + 1) * x.args.gap;
-    x.args.q = x.args.total / x.args.n;
-    x.args.inv_n = inverse(x.args.n); x.args.inv_total = inverse(x.args.total); x.args.inv_layer = inverse(x.args.per_layer);
-    x.n_wg = (int32_t)n;
-    x.n_sets = (int32_t)(units + n - 1);
-    x.max_sets = (int32_t)std::min<int64_t>(n, max_quads < 2 ? 1 : (max_quads - 2) / x.args.q + 2);
-    return x;
-}
-
 // Validates `shape` and derives the plan.  `need_budgets`: the entry point uses budgets.
 // (`sweeps` false: a call that neither passes over K nor shares a workspace with one that does; how the sequences are cut
 // is of no account then and not looked for.)  `n_q2`: tokens of a second query set over the same keys, or 0.

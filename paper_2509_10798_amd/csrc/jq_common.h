@@ -6,15 +6,13 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include "jq.h"
+#include "jq_sweep.h"
 
 namespace jq {
 
-constexpr int kKeyTile = 32;        // keys per MFMA tile (one 32x32 block column)
 constexpr int kRowTile = 32;        // query rows per MFMA tile
 constexpr int kMaxRowTiles = 4;     // query-row tiles one wave keeps in registers (128 rows)
 constexpr int kHeadDim = 128;
-constexpr int kScoreWaves = 4;      // waves per workgroup in the score kernels
 constexpr int kHistBins = 2048;     // level-1 radix bins (top 11 bits of the sortable key)
 constexpr int kHistStride = kHistBins + 16;  // per problem: the bins, then [0] #sure and [1] #candidate counters
 constexpr int kSelectThreads = 1024;
@@ -25,24 +23,6 @@ struct SeqTab {
     int32_t n_seq;
     int32_t cu_seq[JQ_MAX_SEQ + 1];    // token offsets
     int32_t cu_bud[JQ_MAX_SEQ + 1];    // kept-row offsets
-};
-
-// How the workgroups of a pass over K share the keys out, in quads of 128 keys (four 32-key tiles, one per wave).
-struct SplitArgs {
-    int32_t n, total;   // evenly: workgroup c of n takes positions c * total / n .. (c + 1) * total / n - 1 of the row of all quads,
-    int32_t gap;        // with a gap of this many between sequences, for the start-up that a change of sequence costs
-    int32_t per_layer;  // positions per layer (the gap behind it included), or workgroups per layer
-    int32_t whole;      // 1: whole workgroups for every sequence
-    int32_t q;          // total / n
-    uint32_t inv_n, inv_total, inv_layer;  // inverse() of n, total, per_layer
-};
-inline uint32_t inverse(int32_t d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d); }  // of the device's udiv()
-struct Split {
-    SplitArgs args;
-    int32_t n_wg;       // workgroups per KV head (and group of query rows)
-    int32_t n_sets;     // sets of statistics per KV head that a first pass shared out like this leaves
-    int32_t max_sets;   // ... of one (layer, sequence) at most
-    int32_t cu[JQ_MAX_SEQ + 1];  // first position, or workgroup, of every sequence in a layer
 };
 
 // Where a layer's K / V rows live: dense [T] rows per layer (block_table null), or a pool of n_pages pages of
@@ -83,17 +63,6 @@ struct Plan {
     // workspace layout (byte offsets, 256-aligned)
     size_t off_stats, off_flags, off_aug, off_hist, off_scores, off_pooled, off_idx, off_seg, off_seghdr, ws_bytes;
 };
-
-// Largest s with cu[s] <= v (cu[0] = 0, strictly increasing, v < cu[n]).
-template <class Table>  // a pointer to int32_t, in whatever memory
-__host__ __device__ inline int find_seq(Table cu, int n, int64_t v) {
-    int lo = 0, hi = n;  // answer in [lo, hi)
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if ((int64_t)cu[mid] <= v) lo = mid; else hi = mid;
-    }
-    return lo;
-}
 
 // Order-preserving map from fp32 to uint32 (larger float <=> larger key); -0 is folded onto +0.
 __device__ inline uint32_t sortable_key(float x) {

@@ -98,16 +98,10 @@ constexpr int kOneSet = 0x7FFFFFFF;  // tiles1 of a call with one query set
 // read through it is read where it is used.  A workgroup with several shares repeats everything below; without this the
 // compiler keeps every scalar of every phase in registers across all of them (200 spilled).
 typedef const ScoreArgs __attribute__((address_space(4))) KArgs;
-typedef const SplitArgs __attribute__((address_space(4))) KSplit;
 __device__ __forceinline__ KArgs& kernel_args() {
     KArgs* p = (KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *p;
-}
-// x / d for the d that `inv` was made of (ceil(2^32 / d), 0 for 1): the product is at most one too large
-__device__ __forceinline__ uint32_t udiv(uint32_t x, uint32_t d, uint32_t inv) {
-    const uint32_t q = __umulhi(x, inv), less = (int32_t)(x - q * d) < 0 ? 1u : 0u;
-    return inv ? q - less : x;
 }
 __device__ __forceinline__ int lane_again() {  // the same for what derives from the lane
     int lane = (int)threadIdx.x & 63;
@@ -142,152 +136,6 @@ __device__ __forceinline__ void wait_frags_read() {
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-}
-
-// ---- which keys a workgroup sweeps ----------------------------------------------------------------
-// The keys of a head, over all layers and sequences of the call, are shared out in steps of four tiles (one per wave), called
-// quads; a quad never straddles sequences.  Either every sequence gets whole workgroups, or (evenly) all quads in a row are
-// dealt to the workgroups in equal, contiguous portions, whatever sequences those touch: then all finish together, and a
-// workgroup has a SHARE of one (layer, sequence) or of several in turn.
-// The workgroups that share a (layer, sequence) take its quads in the order in which they reach them, counted in steps on
-// every workgroup's own clock, so that all waves that run at the same time sweep one moving window of the key tensor, which
-// DRAM serves at close to its streaming rate (one contiguous range per workgroup instead took 49 us cold against 45 on the
-// 128K layer).  Dealt evenly, a (layer, sequence) has at most one workgroup that comes to it late (the first), workgroups that
-// work on nothing else, and one that leaves early (the last), so the number of quads taken before a workgroup's step i has a
-// closed form.
-struct Share {
-    int layer, seq, L, seq_tiles;  // seq_tiles: 32-key tiles of the sequence
-    int64_t tok0;                  // first token of the sequence in the flattened T axis
-    int set0, n_sets, rank;        // sets of statistics of the (layer, sequence): set0 .. set0 + n_sets - 1, here set0 + rank
-    int x, len;                    // the workgroup's steps for it: x .. x + len - 1
-    int full, at, at_last, q;      // workgroups with nothing else; of those, how many come before this one in a step; in step q
-    int late_from, late_n, early;  // first step (counted with its place in a step) and steps of the late one; steps of the early one
-    __device__ __forceinline__ int quad(int i) const {
-        return (i < q ? full * i + at : full * q + at_last) + min(max(i - late_from, 0), late_n) + min(i, early);
-    }
-};
-__device__ __forceinline__ int split_start(KSplit& sp, int c) { return (int)udiv((uint32_t)c * (uint32_t)sp.total, (uint32_t)sp.n, sp.inv_n); }
-__device__ __forceinline__ int split_owner(KSplit& sp, int pos) {  // the largest c with split_start(c) <= pos
-    return (int)udiv(((uint32_t)pos + 1u) * (uint32_t)sp.n - 1u, (uint32_t)sp.total, sp.inv_total);
-}
-__device__ __forceinline__ int quads_of(KArgs& a, int seq) { return a.one_L ? a.layer_quads : a.cu_quad[seq + 1] - a.cu_quad[seq]; }
-// sets of statistics of a (layer, sequence); `cu`: the split's table
-__device__ __forceinline__ void sets_of(KArgs& a, KSplit& sp, const_i32_ptr cu, int layer, int seq, int& set0, int& n) {
-    const int at = layer * sp.per_layer + (a.one_L ? 0 : cu[seq]);
-    if (sp.whole) {
-        set0 = at;
-        n = a.one_L ? sp.per_layer : cu[seq + 1] - cu[seq];
-        return;
-    }
-    const int ca = split_owner(sp, at), cb = split_owner(sp, at + quads_of(a, seq) - 1);
-    set0 = layer * a.n_seq + seq + ca;  // along the row either the sequence or the workgroup (or both) steps on: no number twice
-    n = cb - ca + 1;
-}
-// the first (or last) (layer, sequence) of workgroup c
-__device__ __forceinline__ void first_share(KArgs& a, int c, bool last, int& layer, int& seq) {
-    KSplit& sp = a.own;
-    const int pos = sp.whole ? c : last ? split_start(sp, c + 1) - 1 : split_start(sp, c);
-    layer = a.n_layers == 1 ? 0 : (int)udiv((uint32_t)pos, (uint32_t)sp.per_layer, sp.inv_layer);
-    seq = a.one_L ? 0 : find_seq(a.cu_wg, a.n_seq, pos - layer * sp.per_layer);
-    if (!last && !sp.whole && pos - layer * sp.per_layer - (a.one_L ? 0 : a.cu_wg[seq]) >= quads_of(a, seq))  // in the gap behind it
-        if (++seq == a.n_seq) { seq = 0; ++layer; }
-}
-__device__ __forceinline__ Share share_of(KArgs& a, int c, int layer, int seq) {
-    KSplit& sp = a.own;
-    Share h;
-    h.layer = layer; h.seq = seq;
-    h.tok0 = a.one_L ? 0 : a.cu_seq[seq];
-    h.L = a.one_L ? a.one_L : a.cu_seq[seq + 1] - a.cu_seq[seq];
-    h.seq_tiles = (h.L + kKeyTile - 1) / kKeyTile;
-    const int nq = (h.seq_tiles + kScoreWaves - 1) / kScoreWaves;
-    sets_of(a, sp, a.cu_wg, layer, seq, h.set0, h.n_sets);
-    h.late_from = h.late_n = h.early = h.at_last = 0;
-    if (sp.whole) {
-        h.rank = c - h.set0;
-        h.x = 0;
-        const uint32_t steps = (uint32_t)(nq - h.rank + h.n_sets - 1);  // >= n_sets: no more workgroups than quads
-        h.len = (int)(sp.inv_n ? udiv(steps, (uint32_t)h.n_sets, sp.inv_n) : steps / (uint32_t)h.n_sets);
-        h.full = h.n_sets; h.at = h.rank; h.q = 0x7FFFFFFF;
-        return h;
-    }
-    const int ca = h.set0 - (layer * a.n_seq + seq), cb = ca + h.n_sets - 1;
-    const int q0 = layer * sp.per_layer + (a.one_L ? 0 : a.cu_wg[seq]), b0 = split_start(sp, c), b1 = split_start(sp, c + 1);
-    h.rank = c - ca;
-    h.x = max(b0, q0) - b0;
-    h.len = min(b1, q0 + nq) - b0 - h.x;
-    h.q = sp.q;
-    if (h.n_sets == 1) {
-        h.full = h.at = 0;
-        h.late_from = h.x; h.late_n = h.len;
-    } else {
-        h.full = h.n_sets - 2;
-        h.at = min(max(h.rank - 1, 0), h.full);
-        const int s1 = split_start(sp, ca + 1);
-        h.at_last = c == ca ? 0 : b0 - s1 - h.q * h.at;
-        h.late_from = q0 - split_start(sp, ca) - (c > ca ? 1 : 0);
-        h.late_n = s1 - q0;
-        h.early = q0 + nq - split_start(sp, cb);
-    }
-    return h;
-}
-
-// The tiles of one wave of a share in the order in which it takes them, forwards or backwards: their numbers rise evenly but for
-// the few steps at which another workgroup joins or leaves (Share::quad for every tile cost the sweeps a twentieth: a wave
-// issues in order, and the matrix core waits meanwhile).
-template <bool BACK>
-struct Walk {
-    int i, t, stride, left;  // step, its tile, distance to the next step's and for how many more steps it holds
-    __device__ __forceinline__ void turn(const Share& h) {
-        const int at[5] = {h.q - 1, h.q, h.late_from, h.late_from + h.late_n, h.early};
-        int next = BACK ? -1 : 0x7FFFFFFF;
-#pragma unroll
-        for (int k = 0; k < 5; ++k)
-            if (BACK ? at[k] < i : at[k] > i) next = BACK ? max(next, at[k]) : min(next, at[k]);
-        stride = kScoreWaves * (BACK ? h.quad(i - 1) - h.quad(i) : h.quad(i + 1) - h.quad(i));
-        left = BACK ? i - next : next - i;
-    }
-    __device__ __forceinline__ void start(const Share& h, int from, int wave) {
-        i = from;
-        t = kScoreWaves * h.quad(i) + wave;
-        turn(h);
-    }
-    __device__ __forceinline__ void step(const Share& h) {
-        i += BACK ? -1 : 1;
-        t += stride;
-        if (__builtin_expect(--left == 0, 0)) turn(h);
-    }
-};
-
-// Where a workgroup starts: its KV head, group of query rows, number among their workgroups, and its first share (`last`: it takes
-// its shares, and the launch its workgroups, from the end).
-struct Place { int g, rg, c, layer, seq; };
-__device__ __forceinline__ Place place_of(KArgs& a, bool last) {
-    uint32_t b = blockIdx.x;  // below 2^31: 32-bit arithmetic
-    if (last) b = gridDim.x - 1 - b;
-    Place at;
-    uint32_t rest = udiv(b, (uint32_t)a.h_kv, a.inv_h_kv);
-    at.g = (int)(b - rest * (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row
-    at.rg = a.rg0;
-    if (a.n_rg > 1) {  // row groups next: the workgroups that read the same keys run side by side (with eight heads on one XCD)
-        at.rg += (int)(rest % (uint32_t)a.n_rg);
-        rest /= (uint32_t)a.n_rg;
-    }
-    at.c = (int)rest;
-    first_share(a, at.c, last, at.layer, at.seq);
-    return at;
-}
-// on to the workgroup's next share (the one before it with `last`); false if `h` was the final one
-__device__ __forceinline__ bool next_share(KArgs& a, const Share& h, bool last, Place& at) {
-    KSplit& sp = a.own;
-    if (sp.whole) return false;
-    if (last) {
-        if (h.x <= sp.gap) return false;  // what precedes the (layer, sequence) here is a gap at most
-        if (--at.seq < 0) { at.seq = a.n_seq - 1; --at.layer; }
-    } else {
-        if (h.x + h.len + sp.gap >= split_start(sp, at.c + 1) - split_start(sp, at.c)) return false;
-        if (++at.seq == a.n_seq) { at.seq = 0; ++at.layer; }
-    }
-    return true;
 }
 
 // ---- key tiles: global -> LDS -------------------------------------------------------------------
@@ -814,7 +662,7 @@ template <int NQT, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
     argument_lines<5>();
-    Place at = place_of(kernel_args(), false);
+    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, false);
     for (;;) {
         KArgs& a = kernel_args();
         const Share h = share_of(a, at.c, at.layer, at.seq);
@@ -1178,7 +1026,7 @@ template <int NQT, bool FROM_LSE, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
     argument_lines<5>();
-    Place at = place_of(kernel_args(), true);  // from the end: the keys pass 1 read last are fetched first
+    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, true);  // from the end: the keys pass 1 read last are fetched first
     clear_words(kernel_args());
     for (;;) {
         KArgs& a = kernel_args();
@@ -1212,7 +1060,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
     __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
     argument_lines<5>();
     const int64_t t_entry = wall_clock64();
-    Place at = place_of(kernel_args(), false);
+    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, false);
     clear_words(kernel_args());
     bool scoring = false, q_there = false;  // uniform
     int help = -1;                          // another workgroup, whose set this one forms in its stead

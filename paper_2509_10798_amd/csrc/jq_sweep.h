@@ -1,0 +1,320 @@
+// Which keys the workgroups of a pass over K sweep, in which order, and where their requests lie: the index arithmetic of the
+// passes.  Plain integer code without any HIP call, so that a host compiler takes it too and a test can walk every share of any
+// call on the CPU.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "jq.h"
+
+#ifdef __HIPCC__
+#define JQ_HD __host__ __device__ __forceinline__
+#else
+#define JQ_HD inline
+#endif
+
+namespace jq {
+
+constexpr int kKeyTile = 32;        // keys per MFMA tile (one 32x32 block column)
+constexpr int kScoreWaves = 4;      // waves per workgroup in the score kernels
+
+JQ_HD int lesser(int a, int b) { return a < b ? a : b; }
+JQ_HD int greater(int a, int b) { return a > b ? a : b; }
+
+// Largest s with cu[s] <= v (cu[0] = 0, strictly increasing, v < cu[n]).
+template <class Table>  // a pointer to int32_t, in whatever memory
+JQ_HD int find_seq(Table cu, int n, int64_t v) {
+    int lo = 0, hi = n;  // answer in [lo, hi)
+    while (hi - lo > 1) {
+        int mid = (lo + hi) >> 1;
+        if ((int64_t)cu[mid] <= v) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// x / d for the d that `inv` was made of (ceil(2^32 / d), 0 for 1): the product is at most one too large
+JQ_HD uint32_t udiv(uint32_t x, uint32_t d, uint32_t inv) {
+    const uint32_t q = (uint32_t)((uint64_t)x * inv >> 32), less = (int32_t)(x - q * d) < 0 ? 1u : 0u;
+    return inv ? q - less : x;
+}
+
+// How the workgroups of a pass over K share the keys out, in quads of 128 keys (four 32-key tiles, one per wave).
+struct SplitArgs {
+    int32_t n, total;   // evenly: workgroup c of n takes positions c * total / n .. (c + 1) * total / n - 1 of the row of all quads,
+    int32_t gap;        // with a gap of this many between sequences, for the start-up that a change of sequence costs
+    int32_t per_layer;  // positions per layer (the gap behind it included), or workgroups per layer
+    int32_t whole;      // 1: whole workgroups for every sequence
+    int32_t q;          // total / n
+    uint32_t inv_n, inv_total, inv_layer;  // inverse() of n, total, per_layer
+};
+inline uint32_t inverse(int32_t d) { return d == 1 ? 0u : (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d); }  // of the device's udiv()
+struct Split {
+    SplitArgs args;
+    int32_t n_wg;       // workgroups per KV head (and group of query rows)
+    int32_t n_sets;     // sets of statistics per KV head that a first pass shared out like this leaves
+    int32_t max_sets;   // ... of one (layer, sequence) at most
+    int32_t cu[JQ_MAX_SEQ + 1];  // first position, or workgroup, of every sequence in a layer
+};
+
+// How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
+// with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
+// as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
+template <class P>
+Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight) {
+    Split x{};
+    const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
+    auto pieces = [&](int32_t keys) {
+        for (int s = 0; s < p.n_seq; ++s) {
+            const int32_t L = p.tab.cu_seq[s + 1] - p.tab.cu_seq[s], n = (L - 1) / (kScoreWaves * keys) + 1;
+            x.cu[s + 1] = x.cu[s] + n;
+            x.max_sets = std::max(x.max_sets, n);
+        }
+        x.args.whole = 1;
+        x.args.per_layer = x.cu[p.n_seq];
+        x.args.inv_layer = inverse(x.args.per_layer);
+        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
+        return x;
+    };
+    if (chunk) return pieces(chunk);
+    const int64_t per = (int64_t)p.h_kv * p.row_groups;
+    // (With many query rows the keys come out of the caches and arithmetic is the bound: two workgroups per CU hide each other's
+    // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
+    int64_t n = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per);
+    n = std::min(n, n_quads);
+    if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
+    // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
+    // kStartUp of them (5.6 us in the first pass, 7 in the second, 1.25 us a quad).
+    constexpr int kStartUp = 5;
+    auto whole = [&](int64_t steps) {  // workgroups per layer with at most that many quads each
+        int64_t wgs = 0;
+        for (int s = 0; s < p.n_seq; ++s) wgs += (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps;
+        return wgs;
+    };
+    int64_t steps = 0;  // the fewest that n workgroups can do with; 0: more (layer, sequence)s than workgroups
+    if (units <= n) {
+        int64_t lo = (n_quads + n - 1) / n, hi = max_quads;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) / 2;
+            if (p.n_layers * whole(mid) <= n) hi = mid; else lo = mid + 1;
+        }
+        steps = lo;
+    }
+    auto longest = [&](int64_t gap) {
+        const int64_t total = n_quads + (units - 1) * gap;
+        int64_t worst = 0, u0 = 0;
+        int32_t s = 0;
+        for (int64_t c = 0, b0 = 0; c < n; ++c) {
+            const int64_t b1 = (c + 1) * total / n;
+            int64_t cost = 0;
+            for (;;) {
+                const int64_t nq = p.cu_quad[s + 1] - p.cu_quad[s], lo = std::max(b0, u0), hi = std::min(b1, u0 + nq);
+                if (hi > lo) cost += hi - lo + kStartUp;
+                if (b1 < u0 + nq + gap || (b1 == total && u0 + nq >= total)) break;
+                u0 += nq + gap;
+                if (++s == p.n_seq) s = 0;
+                if (u0 >= b1) break;
+            }
+            worst = std::max(worst, cost);
+            b0 = b1;
+        }
+        return worst;
+    };
+    // (A workgroup that comes to more than one sequence may take fewer keys: a gap between sequences in the row that is dealt.)
+    int64_t dealt = INT64_MAX;
+    if (units > 1 && units <= 1024 && n > 1) {
+        dealt = longest(0);
+        const int64_t gapped = n_quads / n > kStartUp ? longest(kStartUp) : INT64_MAX;
+        if (gapped < dealt) { dealt = gapped; x.args.gap = kStartUp; }
+    } else if (units > 1) {
+        dealt = n_quads / n + kStartUp;  // many sequences, a few to every workgroup
+    }
+    if (steps && steps + kStartUp <= dealt) {
+        x.args = SplitArgs{};
+        x.args.whole = 1;
+        for (int s = 0; s < p.n_seq; ++s) {
+            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps);
+            x.cu[s + 1] = x.cu[s] + w;
+            x.max_sets = std::max(x.max_sets, w);
+        }
+        x.args.per_layer = x.cu[p.n_seq];
+        x.args.inv_layer = inverse(x.args.per_layer);
+        if (p.n_seq == 1) x.args.inv_n = inverse(x.args.per_layer);
+        x.n_wg = x.n_sets = p.n_layers * x.args.per_layer;
+        return x;
+    }
+    // The arithmetic of even portions is one of 32 bits: n * total has to stay below 2^32.  A call of 2^24 quads or more (2^31 tokens
+    // over all layers, which a paged cache reaches where sequences share pages) has whole workgroups of 2048 quads instead, some
+    // 2.5 ms of either pass each: thousands of them, at most 64 per sequence, and no start-up that counts.
+    const int64_t total = n_quads + (units - 1) * x.args.gap;
+    if (n * total >= (int64_t)1 << 32) {
+        x.args = SplitArgs{};
+        return pieces(2048 * kKeyTile);
+    }
+    x.args.n = (int32_t)n;
+    x.args.total = (int32_t)total;
+    x.args.per_layer = p.cu_quad[p.n_seq] + p.n_seq * x.args.gap;
+    for (int s = 0; s < p.n_seq; ++s) x.cu[s + 1] = p.cu_quad[s + 1] + (s + 1) * x.args.gap;
+    x.args.q = x.args.total / x.args.n;
+    x.args.inv_n = inverse(x.args.n); x.args.inv_total = inverse(x.args.total); x.args.inv_layer = inverse(x.args.per_layer);
+    x.n_wg = (int32_t)n;
+    x.n_sets = (int32_t)(units + n - 1);
+    x.max_sets = (int32_t)std::min<int64_t>(n, max_quads < 2 ? 1 : (max_quads - 2) / x.args.q + 2);
+    return x;
+}
+
+// ---- which keys a workgroup sweeps ----------------------------------------------------------------
+// The keys of a head, over all layers and sequences of the call, are shared out in steps of four tiles (one per wave), called
+// quads; a quad never straddles sequences.  Either every sequence gets whole workgroups, or (evenly) all quads in a row are
+// dealt to the workgroups in equal, contiguous portions, whatever sequences those touch: then all finish together, and a
+// workgroup has a SHARE of one (layer, sequence) or of several in turn.
+// The workgroups that share a (layer, sequence) take its quads in the order in which they reach them, counted in steps on
+// every workgroup's own clock, so that all waves that run at the same time sweep one moving window of the key tensor, which
+// DRAM serves at close to its streaming rate (one contiguous range per workgroup instead took 49 us cold against 45 on the
+// 128K layer).  Dealt evenly, a (layer, sequence) has at most one workgroup that comes to it late (the first), workgroups that
+// work on nothing else, and one that leaves early (the last), so the number of quads taken before a workgroup's step i has a
+// closed form.
+struct Share {
+    int layer, seq, L, seq_tiles;  // seq_tiles: 32-key tiles of the sequence
+    int64_t tok0;                  // first token of the sequence in the flattened T axis
+    int set0, n_sets, rank;        // sets of statistics of the (layer, sequence): set0 .. set0 + n_sets - 1, here set0 + rank
+    int x, len;                    // the workgroup's steps for it: x .. x + len - 1
+    int full, at, at_last, q;      // workgroups with nothing else; of those, how many come before this one in a step; in step q
+    int late_from, late_n, early;  // first step (counted with its place in a step) and steps of the late one; steps of the early one
+    JQ_HD int quad(int i) const {
+        return (i < q ? full * i + at : full * q + at_last) + lesser(greater(i - late_from, 0), late_n) + lesser(i, early);
+    }
+};
+template <class S>
+JQ_HD int split_start(S& sp, int c) { return (int)udiv((uint32_t)c * (uint32_t)sp.total, (uint32_t)sp.n, sp.inv_n); }
+template <class S>
+JQ_HD int split_owner(S& sp, int pos) {  // the largest c with split_start(c) <= pos
+    return (int)udiv(((uint32_t)pos + 1u) * (uint32_t)sp.n - 1u, (uint32_t)sp.total, sp.inv_total);
+}
+template <class A>
+JQ_HD int quads_of(A& a, int seq) { return a.one_L ? a.layer_quads : a.cu_quad[seq + 1] - a.cu_quad[seq]; }
+// sets of statistics of a (layer, sequence); `cu`: the split's table
+template <class A, class S, class Table>
+JQ_HD void sets_of(A& a, S& sp, Table cu, int layer, int seq, int& set0, int& n) {
+    const int at = layer * sp.per_layer + (a.one_L ? 0 : cu[seq]);
+    if (sp.whole) {
+        set0 = at;
+        n = a.one_L ? sp.per_layer : cu[seq + 1] - cu[seq];
+        return;
+    }
+    const int ca = split_owner(sp, at), cb = split_owner(sp, at + quads_of(a, seq) - 1);
+    set0 = layer * a.n_seq + seq + ca;  // along the row either the sequence or the workgroup (or both) steps on: no number twice
+    n = cb - ca + 1;
+}
+// the first (or last) (layer, sequence) of workgroup c
+template <class A>
+JQ_HD void first_share(A& a, int c, bool last, int& layer, int& seq) {
+    auto& sp = a.own;
+    const int pos = sp.whole ? c : last ? split_start(sp, c + 1) - 1 : split_start(sp, c);
+    layer = a.n_layers == 1 ? 0 : (int)udiv((uint32_t)pos, (uint32_t)sp.per_layer, sp.inv_layer);
+    seq = a.one_L ? 0 : find_seq(a.cu_wg, a.n_seq, pos - layer * sp.per_layer);
+    if (!last && !sp.whole && pos - layer * sp.per_layer - (a.one_L ? 0 : a.cu_wg[seq]) >= quads_of(a, seq))  // in the gap behind it
+        if (++seq == a.n_seq) { seq = 0; ++layer; }
+}
+template <class A>
+JQ_HD Share share_of(A& a, int c, int layer, int seq) {
+    auto& sp = a.own;
+    Share h;
+    h.layer = layer; h.seq = seq;
+    h.tok0 = a.one_L ? 0 : a.cu_seq[seq];
+    h.L = a.one_L ? a.one_L : a.cu_seq[seq + 1] - a.cu_seq[seq];
+    h.seq_tiles = (h.L + kKeyTile - 1) / kKeyTile;
+    const int nq = (h.seq_tiles + kScoreWaves - 1) / kScoreWaves;
+    sets_of(a, sp, a.cu_wg, layer, seq, h.set0, h.n_sets);
+    h.late_from = h.late_n = h.early = h.at_last = 0;
+    if (sp.whole) {
+        h.rank = c - h.set0;
+        h.x = 0;
+        const uint32_t steps = (uint32_t)(nq - h.rank + h.n_sets - 1);  // >= n_sets: no more workgroups than quads
+        h.len = (int)(sp.inv_n ? udiv(steps, (uint32_t)h.n_sets, sp.inv_n) : steps / (uint32_t)h.n_sets);
+        h.full = h.n_sets; h.at = h.rank; h.q = 0x7FFFFFFF;
+        return h;
+    }
+    const int ca = h.set0 - (layer * a.n_seq + seq), cb = ca + h.n_sets - 1;
+    const int q0 = layer * sp.per_layer + (a.one_L ? 0 : a.cu_wg[seq]), b0 = split_start(sp, c), b1 = split_start(sp, c + 1);
+    h.rank = c - ca;
+    h.x = greater(b0, q0) - b0;
+    h.len = lesser(b1, q0 + nq) - b0 - h.x;
+    h.q = sp.q;
+    if (h.n_sets == 1) {
+        h.full = h.at = 0;
+        h.late_from = h.x; h.late_n = h.len;
+    } else {
+        h.full = h.n_sets - 2;
+        h.at = lesser(greater(h.rank - 1, 0), h.full);
+        const int s1 = split_start(sp, ca + 1);
+        h.at_last = c == ca ? 0 : b0 - s1 - h.q * h.at;
+        h.late_from = q0 - split_start(sp, ca) - (c > ca ? 1 : 0);
+        h.late_n = s1 - q0;
+        h.early = q0 + nq - split_start(sp, cb);
+    }
+    return h;
+}
+
+// The tiles of one wave of a share in the order in which it takes them, forwards or backwards: their numbers rise evenly but for
+// the few steps at which another workgroup joins or leaves (Share::quad for every tile cost the sweeps a twentieth: a wave
+// issues in order, and the matrix core waits meanwhile).
+template <bool BACK>
+struct Walk {
+    int i, t, stride, left;  // step, its tile, distance to the next step's and for how many more steps it holds
+    JQ_HD void turn(const Share& h) {
+        const int at[5] = {h.q - 1, h.q, h.late_from, h.late_from + h.late_n, h.early};
+        int next = BACK ? -1 : 0x7FFFFFFF;
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            if (BACK ? at[k] < i : at[k] > i) next = BACK ? greater(next, at[k]) : lesser(next, at[k]);
+        stride = kScoreWaves * (BACK ? h.quad(i - 1) - h.quad(i) : h.quad(i + 1) - h.quad(i));
+        left = BACK ? i - next : next - i;
+    }
+    JQ_HD void start(const Share& h, int from, int wave) {
+        i = from;
+        t = kScoreWaves * h.quad(i) + wave;
+        turn(h);
+    }
+    JQ_HD void step(const Share& h) {
+        i += BACK ? -1 : 1;
+        t += stride;
+        if (__builtin_expect(--left == 0, 0)) turn(h);
+    }
+};
+
+// Where a workgroup starts: its KV head, group of query rows, number among their workgroups, and its first share (`last`: it takes
+// its shares, and the launch its workgroups, from the end).
+struct Place { int g, rg, c, layer, seq; };
+template <class A>
+JQ_HD Place place_of(A& a, uint32_t b, uint32_t n_blocks, bool last) {  // b: number of the workgroup in the launch of n_blocks (below 2^31: 32-bit arithmetic)
+    if (last) b = n_blocks - 1 - b;
+    Place at;
+    uint32_t rest = udiv(b, (uint32_t)a.h_kv, a.inv_h_kv);
+    at.g = (int)(b - rest * (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row
+    at.rg = a.rg0;
+    if (a.n_rg > 1) {  // row groups next: the workgroups that read the same keys run side by side (with eight heads on one XCD)
+        at.rg += (int)(rest % (uint32_t)a.n_rg);
+        rest /= (uint32_t)a.n_rg;
+    }
+    at.c = (int)rest;
+    first_share(a, at.c, last, at.layer, at.seq);
+    return at;
+}
+// on to the workgroup's next share (the one before it with `last`); false if `h` was the final one
+template <class A>
+JQ_HD bool next_share(A& a, const Share& h, bool last, Place& at) {
+    auto& sp = a.own;
+    if (sp.whole) return false;
+    if (last) {
+        if (h.x <= sp.gap) return false;  // what precedes the (layer, sequence) here is a gap at most
+        if (--at.seq < 0) { at.seq = a.n_seq - 1; --at.layer; }
+    } else {
+        if (h.x + h.len + sp.gap >= split_start(sp, at.c + 1) - split_start(sp, at.c)) return false;
+        if (++at.seq == a.n_seq) { at.seq = 0; ++at.layer; }
+    }
+    return true;
+}
+
+}  // namespace jq

@@ -1,0 +1,66 @@
+"""How a pass over K shares the keys out, walked on the CPU: the header that the kernels find their shares by also compiles for
+the host.  Every quad of 128 keys is taken once, every set of statistics has one writer, both passes visit the same shares."""
+import os
+import random
+import subprocess
+
+import pytest
+
+import paper_2509_10798_amd as jq
+from conftest import ROOT
+
+
+@pytest.fixture(scope="module")
+def walk(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("split") / "split_walk")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2509_10798_amd", "csrc"), os.path.join(ROOT, "tests", "split_walk.cpp"), "-o", exe])
+
+    def run(calls):
+        """calls: (n_layers, lens, h_kv, rows, rows2, chunk, every quad); returns (workgroups, sets, longest, quads) of each."""
+        text = "".join("%d %d %d %d %d %d %d %s\n" % (nl, len(lens), h_kv, rows, rows2, chunk, full, " ".join(map(str, lens)))
+                       for nl, lens, h_kv, rows, rows2, chunk, full in calls)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, timeout=300)
+        lines = r.stdout.splitlines()
+        at = calls[len(lines)] if len(lines) < len(calls) else None
+        assert r.returncode == 0 and at is None, "ended (%d) at %s" % (r.returncode, str(at)[:200])
+        for call, line in zip(calls, lines):
+            assert line.startswith("ok"), (line, str(call)[:200])
+        return [tuple(map(int, line.split()[1:])) for line in lines]
+    return run
+
+
+def _call(rng):
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    nl, n_seq = log(1, 64), log(1, 128)
+    top = max(2, min(300000, 40000000 // (nl * n_seq)))
+    lens = [log(1, top) for _ in range(n_seq)] if rng.random() < 0.7 else [log(1, top)] * n_seq
+    rows, rows2 = rng.choice(((16, 0), (128, 0), (128, 0), (500, 0), (128, 512), (32, 32)))
+    return nl, lens, log(1, 256), rows, rows2, rng.choice((0, 0, 0, 0, 64, 2048)), 1
+
+
+def test_every_key_is_taken_once(walk):
+    rng = random.Random(12)
+    walk([_call(rng) for _ in range(3000)])
+
+
+# A paged cache may have its sequences share pages, so the keys of a call can be many times those in memory.
+HUGE = [
+    (3, [16000000] * 128, 1, 128, 0),   # 48 million quads: workgroup number times quads exceeds 32 bits
+    (5, [8000000] * 127, 2, 128, 0),
+    (1, [16777088] * 128, 1, 128, 0),   # 2^24 quads
+    (128, [1000, 16000000], 1, 64, 0),
+    (7, [16000000] * 33 + [1], 1, 128, 512),
+]
+
+
+def test_every_key_is_taken_once_in_the_largest_calls(walk):
+    for (nl, lens, h_kv, rows, rows2), (n_wg, n_sets, longest, quads) in zip(HUGE, walk([c + (0, 0) for c in HUGE])):
+        groups = ((rows + 31) // 32 + (rows2 + 31) // 32 + 3) // 4
+        assert n_wg * h_kv * groups >= 250 and longest * 100 <= quads  # and the whole chip takes part
+
+
+def test_workspace_of_a_call_that_no_card_holds():
+    # 2^32 quads: what a portion is divided by used to come out as zero
+    sh = jq.Shape(n_layers=32768, seq_lens=[131072] * 128, n_q=32, h_q=4, h_kv=1)
+    assert jq.workspace_bytes(sh) > 32768 * 128 * 131072 * 8
