@@ -662,7 +662,7 @@ template <int NQT, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
     argument_lines<5>();
-    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, false);
+    Place at = place_of(kernel_args(), blockIdx.x, false);
     for (;;) {
         KArgs& a = kernel_args();
         const Share h = share_of(a, at.c, at.layer, at.seq);
@@ -1026,7 +1026,7 @@ template <int NQT, bool FROM_LSE, bool PAGED>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
     argument_lines<5>();
-    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, true);  // from the end: the keys pass 1 read last are fetched first
+    Place at = place_of(kernel_args(), gridDim.x - 1 - blockIdx.x, true);  // from the end: the keys pass 1 read last are fetched first
     clear_words(kernel_args());
     for (;;) {
         KArgs& a = kernel_args();
@@ -1060,7 +1060,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
     __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
     argument_lines<5>();
     const int64_t t_entry = wall_clock64();
-    Place at = place_of(kernel_args(), blockIdx.x, gridDim.x, false);
+    Place at = place_of(kernel_args(), blockIdx.x, false);
     clear_words(kernel_args());
     bool scoring = false, q_there = false;  // uniform
     int help = -1;                          // another workgroup, whose set this one forms in its stead

@@ -62,7 +62,7 @@ struct Split {
 // with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
 // as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
 template <class P>
-Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight) {
+static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight) {
     Split x{};
     const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
     auto pieces = [&](int32_t keys) {
@@ -284,12 +284,11 @@ struct Walk {
     }
 };
 
-// Where a workgroup starts: its KV head, group of query rows, number among their workgroups, and its first share (`last`: it takes
-// its shares, and the launch its workgroups, from the end).
+// Where workgroup `b` of the launch (below 2^31: 32-bit arithmetic) starts: its KV head, group of query rows, number among their
+// workgroups, and its first share (`last`: it takes its shares from the end, and `b` counts the launch's workgroups from there).
 struct Place { int g, rg, c, layer, seq; };
 template <class A>
-JQ_HD Place place_of(A& a, uint32_t b, uint32_t n_blocks, bool last) {  // b: number of the workgroup in the launch of n_blocks (below 2^31: 32-bit arithmetic)
-    if (last) b = n_blocks - 1 - b;
+JQ_HD Place place_of(A& a, uint32_t b, bool last) {
     Place at;
     uint32_t rest = udiv(b, (uint32_t)a.h_kv, a.inv_h_kv);
     at.g = (int)(b - rest * (uint32_t)a.h_kv);  // heads vary fastest: neighbouring workgroups read neighbouring 256-byte pieces of a token row

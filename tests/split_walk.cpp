@@ -39,10 +39,9 @@ static std::string walk(const Call& p, const Split& sp, bool full, int64_t& long
     std::vector<uint8_t> quad_seen(full ? (size_t)p.n_layers * a.layer_quads : 0), set_seen((size_t)sp.n_sets);
     std::vector<int64_t> taken((size_t)units);
     longest = 0;
-    const uint32_t n_blocks = (uint32_t)sp.n_wg * (uint32_t)p.h_kv;
     for (int c = 0; c < sp.n_wg; ++c) {
         const uint32_t b = (uint32_t)c * (uint32_t)p.h_kv + (uint32_t)(c % p.h_kv);
-        Place at = place_of(a, b, n_blocks, false);
+        Place at = place_of(a, b, false);
         if (at.c != c || at.g != c % p.h_kv) return "place of a workgroup";
         int64_t len = 0, n_shares = 0;
         std::vector<std::pair<int, int>> order;
@@ -78,7 +77,7 @@ static std::string walk(const Call& p, const Split& sp, bool full, int64_t& long
             if (!next_share(a, h, false, at)) break;
         }
         longest = len > longest ? len : longest;
-        Place back = place_of(a, n_blocks - 1 - b, n_blocks, true);  // the second pass: the same shares, last one first
+        Place back = place_of(a, b, true);  // the second pass: the same shares, last one first
         for (;;) {
             if (order.empty() || back.c != c || order.back() != std::make_pair(back.layer, back.seq)) return "shares from the end";
             order.pop_back();
