@@ -395,13 +395,18 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
 #pragma unroll
         for (int u = 0; u < VPT; ++u) {
             const int j = j0 + u;
-            if (j < f0 || j >= f1) key[u] = j < L ? 0xFFFFFFFFu : 0u;
+            key[u] = j < f0 || j >= f1 ? (j < L ? 0xFFFFFFFFu : 0u) : min(key[u], 0xFFFFFFFEu);
             lo = min(lo, j < f0 || j >= f1 ? 0xFFFFFFFFu : key[u] - 1u);
             hi = max(hi, key[u] + 1u);  // the largest key wraps to 0
         }
     } else {
 #pragma unroll
         for (int u = 0; u < VPT; ++u) { lo = min(lo, key[u]); hi = max(hi, key[u]); }
+        if (__any(hi == 0xFFFFFFFFu)) {  // a NaN of all ones, whose bits make the key of the positions that are always kept
+#pragma unroll
+            for (int u = 0; u < VPT; ++u) key[u] = min(key[u], 0xFFFFFFFEu);
+            lo = min(lo, 0xFFFFFFFEu); hi = min(hi, 0xFFFFFFFEu);
+        }
         lo -= 1u; hi += 1u;
     }
     lo = wave_min(lo);

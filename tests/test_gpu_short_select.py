@@ -33,6 +33,25 @@ def test_select_is_exact_at_the_edges(L, kind):
         np.testing.assert_array_equal(got.cpu().numpy()[0], oracle.select_topk(x[0].astype(np.float64), B, kf, kl))
 
 
+@pytest.mark.parametrize("L", [200, 5000, 20000, 32768])
+@pytest.mark.parametrize("share", [0.01, 0.7, 1.0])
+def test_select_keeps_apart_what_always_stays_and_nan_of_all_ones(L, share):
+    # a caller's values may hold any bits: a NaN of all ones ranks above every number, is counted like any other value, and
+    # the positions that come out are each a position of the sequence
+    torch = torch_()
+    rng = np.random.default_rng(L)
+    bits = rng.random((1, 2, L)).astype(np.float32).view(np.uint32)
+    ones = rng.random((1, 2, L)) < share
+    bits[ones] = 0x7FFFFFFF
+    rank = np.where(ones[0], 2.0, bits.view(np.float32)[0].astype(np.float64))  # numbers are below 1
+    for B, kf, kl in ((L // 2, 0, 0), (max(1, L // 200), 0, 0), (L // 3, 5, 17), (L - 1, 0, 1)):
+        print("NaN of all ones", L, share, B, kf, kl, flush=True)
+        sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=1, h_q=2, h_kv=2, budgets=[B], keep_first=kf, keep_last=kl)
+        got = jq.select_topk(sh, torch.from_numpy(bits.view(np.float32).copy()).cuda())
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy()[0], oracle.select_topk(rank, B, kf, kl))
+
+
 @pytest.mark.parametrize("seq_lens,budgets,pool_k,kf,kl", [
     ([2048], [256], 7, 0, 0), ([2049, 5, 2048], [100, 5, 64], 7, 2, 1), ([4097], [3000], 5, 0, 0), ([4097], [70], 13, 4, 32),
     ([9000, 31], [1000, 1], 1, 0, 0), ([700], [200], 1399, 0, 0), ([16385], [513], 7, 4, 8), ([32768, 100], [2048, 50], 5, 0, 16),
