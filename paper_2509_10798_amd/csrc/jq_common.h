@@ -10,9 +10,7 @@
 
 namespace jq {
 
-constexpr int kRowTile = 32;        // query rows per MFMA tile
 constexpr int kMaxRowTiles = 4;     // query-row tiles one wave keeps in registers (128 rows)
-constexpr int kHeadDim = 128;
 constexpr int kHistBins = 2048;     // level-1 radix bins (top 11 bits of the sortable key)
 constexpr int kHistStride = kHistBins + 16;  // per problem: the bins, then [0] #sure and [1] #candidate counters
 constexpr int kSelectThreads = 1024;

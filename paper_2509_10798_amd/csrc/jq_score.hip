@@ -138,31 +138,19 @@ __device__ __forceinline__ void wait_frags_read() {
     asm volatile("" ::: "memory");
 }
 
-// ---- key tiles: global -> LDS -------------------------------------------------------------------
-// A tile is 32 key rows of 256 B.  Load i (0..7) of a wave moves rows 4i..4i+3: lane l fetches 16 B
-// of row r = 4i + (l >> 4), and the hardware stores them at slot + 1024 i + 16 l, i.e. at row r,
-// physical 16-byte chunk (l & 15).  To realise the swizzle "logical chunk c lives at physical chunk
-// c ^ (r & 15)" the lane therefore fetches logical chunk (l & 15) ^ (r & 15) from global memory.
-// With (r & 15) = 4 (i & 3) + (l >> 4) the lane's byte offset takes four values over the 8 loads, which differ by an
-// exclusive or of 64 (i & 3) (row_bytes is a multiple of 256): one register; the rest of the address is wave-uniform
-// (buffer resource + scalar offset).
-__device__ __forceinline__ uint32_t tile_lane(int lane, uint32_t row_bytes) {  // the offset at i = 0
-    const uint32_t a = (uint32_t)lane >> 4;
-    return a * row_bytes + ((((uint32_t)lane & 15u) ^ a) << 4);
-}
-
+// ---- key tiles: global -> LDS (layout and addresses: jq_sweep.h) ----------------------------------
 __device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, char* dst, uint32_t voff, uint32_t soff) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, (int)voff,
                                              (int)soff, 0, 0);
 }
 
-// `tile_off` = byte offset of the tile's first key row inside the buffer resource (uniform), `tl` = tile_lane().  Rows past the
-// end of a sequence arrive as zeros -- its resource ends there, and the hardware's check covers the scalar offset -- or, in a
-// paged pool, as whatever the rest of the page holds; the first pass masks those keys, the second does not store them, and
-// no other key's values meet them.
-__device__ __forceinline__ void fetch_tile(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off, uint32_t row_bytes, uint32_t tl) {
+// `tile_off` = byte offset of the tile's first key row inside the buffer resource (uniform), `tl` = tile_lane(), `last` =
+// last_request() of the resource.  What arrives for rows past the end of a sequence is zeros or rows of the sequence -- in a
+// paged pool, whatever the rest of the page holds; the first pass masks those keys, the second does not store them, and no
+// other key's values meet them.
+__device__ __forceinline__ void fetch_tile(__amdgpu_buffer_rsrc_t rsrc, char* slot, uint32_t tile_off, uint32_t row_bytes, uint32_t tl, uint32_t last) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl ^ (64u * (i & 3)), tile_off + 4 * i * row_bytes);
+    for (int i = 0; i < 8; ++i) lds_dma16(rsrc, slot + 1024 * i, tl ^ (64u * (i & 3)), request_offset(tile_off, i, row_bytes, last));
 }
 
 // MFMA operand fragments of the tile in `slot`: lane l takes key row (l & 31), logical chunks
@@ -234,9 +222,9 @@ __device__ __forceinline__ void bare_barrier() {
 }
 // The query rows that this wave stages: requested into registers, 16 B per lane, four whole 256-byte rows per instruction.  Every
 // wave requests (those beyond the row tiles the last tile's, and they never store them), so that the requests sit in one basic
-// block with others.  Rows past the end are zeros.  With a power-of-two group of up to 32 heads a tile's rows lie where
-// a key tile's would: a lane part that never changes and a uniform part per request (4 i + a, a < 4, splits without carry),
-// through a resource that ends with the last token, behind which the hardware returns zeros.
+// block with others.  Rows past the end are zeros, or rows of the same head.  With a power-of-two group of up to 32 heads a
+// tile's rows lie where a key tile's would: a lane part that never changes and a uniform part per request (4 i + a, a < 4, splits
+// without carry), through a resource that ends with the last token (query_tile()).
 template <int NQT>
 __device__ __forceinline__ void q_rows_request(KArgs& a, const Share& h, int g, int rg, int lane, u32x4 (&raw)[8]) {
     const int wv = min(__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), NQT - 1);
@@ -248,15 +236,13 @@ __device__ __forceinline__ void q_rows_request(KArgs& a, const Share& h, int g, 
     const int gs = a.group_shift;
     const uint32_t rl = (uint32_t)lane >> 4, piece = ((uint32_t)lane & 15u) ^ rl;
     if (gs >= 0 && gs <= 5 && tok_bytes < (1 << 25)) {  // uniform; a tile's bytes fit a 32-bit offset
-        const int it0 = r0 >> gs, left = min(n_q - it0, kRowTile);  // tokens that the tile reaches, none past the end
-        const uint32_t tok32 = (uint32_t)tok_bytes, group = (uint32_t)a.group;
-        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(qbase + it0 * tok_bytes), 0,
-            left > 0 ? (int)((uint32_t)(left - 1) * tok32 + group * (kHeadDim * 2)) : 0, 0x00020000);
-        const uint32_t tq = (rl >> gs) * tok32 + (rl & (group - 1)) * (kHeadDim * 2) + (piece << 4);
+        const QueryTile qt = query_tile(n_q, r0, gs, (uint32_t)tok_bytes, (uint32_t)a.group);
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(qbase + qt.first * tok_bytes), 0, (int)qt.bytes, 0x00020000);
+        const uint32_t tq = (rl >> gs) * (uint32_t)tok_bytes + (rl & ((uint32_t)a.group - 1)) * (kHeadDim * 2) + (piece << 4);
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             raw[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(tq ^ (64u * (i & 3))),
-                                                           (int)(((uint32_t)(4 * i) >> gs) * tok32 + ((uint32_t)(4 * i) & (group - 1)) * (kHeadDim * 2)), 0);
+                                                           (int)min(query_offset(i, gs, (uint32_t)tok_bytes, (uint32_t)a.group), qt.last), 0);
     } else {
         const int rows = second ? a.rows2 : a.rows;
 #pragma unroll
@@ -299,6 +285,7 @@ constexpr int kLdsBoth = kLdsWord + 16;
 struct KeyStream {
     __amdgpu_buffer_rsrc_t rsrc;  // this head's rows of the whole sequence (PAGED: of the layer's whole pool)
     uint32_t row_bytes;
+    uint32_t last;                // last_request() of the resource; a page has whole tiles, and nothing is clamped there
     const int32_t* pages;         // PAGED: the sequence's row of the block table
     uint32_t page_shift, page_mask, last_page;
 };
@@ -313,6 +300,7 @@ __device__ __forceinline__ KeyStream key_stream(KArgs& a, int layer, int seq, in
     const uint32_t n_rows = PAGED ? (uint32_t)a.n_pages << a.page_shift : (uint32_t)L;
     const char* kseq = (const char*)a.K + (first_row * a.h_kv + g) * kHeadDim * 2;
     const uint32_t bytes = (n_rows - 1) * ks.row_bytes + kHeadDim * 2;
+    ks.last = PAGED ? 0xFFFFFFFFu : last_request(L, ks.row_bytes);
     ks.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kseq, 0, (int)bytes, 0x00020000);
     ks.pages = PAGED ? a.block_table + (int64_t)seq * a.max_pages : nullptr;
     ks.page_shift = (uint32_t)a.page_shift;
@@ -476,10 +464,10 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
             const int t = walk.t, page = page_next;
             walk.step(h);
             if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
-            fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl);
+            fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl, ks.last);
         } else {
             const int t = k - n_tiles;
-            fetch_tile(tail_rsrc, slots + (k & 1) * kSlotBytes, (uint32_t)t * kKeyTile * ks.row_bytes, ks.row_bytes, tl);
+            fetch_tile(tail_rsrc, slots + (k & 1) * kSlotBytes, (uint32_t)t * kKeyTile * ks.row_bytes, ks.row_bytes, tl, last_request(a.n_q, ks.row_bytes));
         }
     };
     // The first key tile goes to slot 0 at once; the second slots first serve as the staging area that turns
@@ -496,14 +484,14 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
     const uint32_t off_first = tile_offset<PAGED>(ks, t_first, page_first);
     bf16x8 qf[NQT][8];
     if (SHARED && q_there) {
-        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl, ks.last);
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
     } else {
         u32x4 qraw[8];
         q_rows_request<NQT>(a, h, g, rg, lane, qraw);
         __builtin_amdgcn_sched_barrier(0);
-        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl, ks.last);
         __builtin_amdgcn_sched_barrier(0);
         q_rows_stage<NQT>(lane, SHARED ? lds + kLdsQ : lds + kSlotBytes, SHARED ? kSlotBytes : 2 * kSlotBytes, qraw, qf);
     }
@@ -793,7 +781,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
         const int t = walk.t, page = page_next;
         walk.step(h);
         if (PAGED && k + 1 < n_tiles) page_next = tile_page<PAGED>(ks, walk.t);
-        fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl);
+        fetch_tile(ks.rsrc, slots + (k & 1) * kSlotBytes, tile_offset<PAGED>(ks, t, page), ks.row_bytes, tl, ks.last);
         return t;
     };
     bf16x8 qf[NQT][8];
@@ -826,7 +814,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     float2 mz[kFirstParts];
     uint2 aug_direct[NQT];  // the terms of the lane's rows where no merging is due
     if (NORMS == kNormsShared && q_there) {
-        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl, ks.last);
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
     } else {
@@ -853,7 +841,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
             else if (NORMS == kNormsMerged) aug_direct[qt] = *(const uint2*)nsrc[qt];
         }
         __builtin_amdgcn_sched_barrier(0);
-        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl);
+        fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl, ks.last);
         __builtin_amdgcn_sched_barrier(0);
         if (NORMS == kNormsLse) {
 #pragma unroll
@@ -1181,7 +1169,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
     {
         const int t = min(tile0 + wv, last_tile);  // tiles past the sequence's end repeat its last one and are not stored
         const uint32_t off = tile_offset<PAGED>(ks, t, tile_page<PAGED>(ks, t));
-        fetch_tile(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, tile_lane(lane, ks.row_bytes));
+        fetch_tile(ks.rsrc, slots + kSlotBytes, off, ks.row_bytes, tile_lane(lane, ks.row_bytes), ks.last);
     }
     fetch_rows(0);
     uint2 aug_next = aug[min(wv, n_rt - 1) * kRowTile];

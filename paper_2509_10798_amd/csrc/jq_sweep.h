@@ -18,6 +18,8 @@
 namespace jq {
 
 constexpr int kKeyTile = 32;        // keys per MFMA tile (one 32x32 block column)
+constexpr int kRowTile = 32;        // query rows per MFMA tile
+constexpr int kHeadDim = 128;
 constexpr int kScoreWaves = 4;      // waves per workgroup in the score kernels
 
 JQ_HD int lesser(int a, int b) { return a < b ? a : b; }
@@ -314,6 +316,46 @@ JQ_HD bool next_share(A& a, const Share& h, bool last, Place& at) {
         if (++at.seq == a.n_seq) { at.seq = 0; ++at.layer; }
     }
     return true;
+}
+
+// ---- where requests lie ---------------------------------------------------------------------------
+// A tile is 32 key rows of 256 B.  Load i (0..7) of a wave moves rows 4i..4i+3: lane l fetches 16 B
+// of row r = 4i + (l >> 4), and the hardware stores them at slot + 1024 i + 16 l, i.e. at row r,
+// physical 16-byte chunk (l & 15).  To realise the swizzle "logical chunk c lives at physical chunk
+// c ^ (r & 15)" the lane therefore fetches logical chunk (l & 15) ^ (r & 15) from global memory.
+// With (r & 15) = 4 (i & 3) + (l >> 4) the lane's byte offset takes four values over the 8 loads, which differ by an
+// exclusive or of 64 (i & 3) (row_bytes is a multiple of 256): one register; the rest of the address is wave-uniform
+// (buffer resource + scalar offset).
+// Of a partial tile -- the last of a sequence -- only the requests whose first row exists lie inside the sequence; the others
+// repeat the last of these (row 0 of it exists, and its rows past the end lie past the end of the resource by the lane part
+// of the address, where the hardware returns zeros).  So no request starts outside what the resource covers: a scalar
+// minimum per request, nothing else.
+JQ_HD uint32_t tile_lane(int lane, uint32_t row_bytes) {  // the offset at i = 0
+    const uint32_t a = (uint32_t)lane >> 4;
+    return a * row_bytes + ((((uint32_t)lane & 15u) ^ a) << 4);
+}
+// offset of the last group of four rows that begins inside `n_rows` rows
+JQ_HD uint32_t last_request(int n_rows, uint32_t row_bytes) { return ((uint32_t)(n_rows - 1) & ~3u) * row_bytes; }
+JQ_HD uint32_t request_offset(uint32_t tile_off, int i, uint32_t row_bytes, uint32_t last) {
+    const uint32_t off = tile_off + 4u * (uint32_t)i * row_bytes;
+    return off < last ? off : last;
+}
+// Query rows r0 .. r0 + 31 of a head with 1 << gs query heads per KV head (gs <= 5, r0 a multiple of 32): the same for rows of
+// `group` consecutive 256-byte pieces per token.  A tile behind the last token reads from the first one instead.
+struct QueryTile {
+    int first;             // token the resource starts with
+    uint32_t bytes, last;  // its length, and the offset of the last request
+};
+JQ_HD uint32_t query_offset(int i, int gs, uint32_t tok_bytes, uint32_t group) {
+    return ((uint32_t)(4 * i) >> gs) * tok_bytes + ((uint32_t)(4 * i) & (group - 1)) * (kHeadDim * 2);
+}
+JQ_HD QueryTile query_tile(int n_q, int r0, int gs, uint32_t tok_bytes, uint32_t group) {
+    QueryTile q;
+    q.first = (r0 >> gs) < n_q ? r0 >> gs : 0;
+    const int left = lesser(n_q - q.first, kRowTile);  // tokens that the tile reaches, none past the end
+    q.bytes = (uint32_t)(left - 1) * tok_bytes + group * (kHeadDim * 2);
+    q.last = query_offset(lesser(((left << gs) - 1) >> 2, 7), gs, tok_bytes, group);
+    return q;
 }
 
 }  // namespace jq

@@ -122,3 +122,27 @@ def test_rest_of_a_page_may_hold_anything(seq_lens, n_q, h_q):
     for x in (two.cpu().numpy(), got.cpu().numpy()):
         for s, L in enumerate(seq_lens):
             assert_scores_close(x[0, :, cu[s]:cu[s + 1]], oracle.score(Q[0, s], K[0, cu[s]:cu[s + 1]]), n_q * (h_q // h_kv) / L, "seq %d" % s)
+
+
+@pytest.mark.parametrize("n_q,h_q,h_kv", [(5, 4, 2), (7, 8, 1), (33, 8, 2), (20, 2, 2), (3, 64, 1), (45, 8, 2), (3, 12, 4)])
+@pytest.mark.parametrize("L", [1, 33, 131, 4099])
+def test_nothing_behind_queries_and_keys_is_read(n_q, h_q, h_kv, L):
+    # row and key tiles that end in the middle: what follows the tensors in memory, NaN here, must not reach any score
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("behind the tensors", n_q, h_q, h_kv, L, flush=True)
+    Q, K = _inputs(1, [L], n_q, h_q, h_kv, seed=23)
+
+    def at_the_start_of_more(x):
+        d = to_dev_bf16(x)
+        more = torch.full((d.numel() + 64 * 64 * 128 * 4,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        more[:d.numel()] = d.view(-1)
+        return more[:d.numel()].view(d.shape)
+    Qd, Kd = at_the_start_of_more(Q), at_the_start_of_more(K)
+    sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=n_q, h_q=h_q, h_kv=h_kv, pool_k=1, budgets=[max(1, L // 4)])
+    two = jq.score(sh, Qd, Kd)
+    one, _ = _evict(sh, Qd, Kd)
+    torch.cuda.synchronize()
+    ref = oracle.score(Q[0, 0], K[0])
+    for x in (two, one):
+        assert_scores_close(x[0].cpu().numpy(), ref, n_q * (h_q // h_kv) / L)

@@ -1,5 +1,6 @@
-"""How a pass over K shares the keys out, walked on the CPU: the header that the kernels find their shares by also compiles for
-the host.  Every quad of 128 keys is taken once, every set of statistics has one writer, both passes visit the same shares."""
+"""How a pass over K shares the keys out and where its requests lie, walked on the CPU: the header that the kernels take both from
+also compiles for the host.  Every quad of 128 keys is taken once, every set of statistics has one writer, both passes visit
+the same shares, and no request starts outside the sequence it reads."""
 import os
 import random
 import subprocess
@@ -10,11 +11,16 @@ import paper_2509_10798_amd as jq
 from conftest import ROOT
 
 
+def _compiled(tmp_path_factory, name):
+    exe = str(tmp_path_factory.mktemp(name) / name)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2509_10798_amd", "csrc"), os.path.join(ROOT, "tests", name + ".cpp"), "-o", exe])
+    return exe
+
+
 @pytest.fixture(scope="module")
 def walk(tmp_path_factory):
-    exe = str(tmp_path_factory.mktemp("split") / "split_walk")
-    subprocess.check_call(["g++", "-O2", "-std=c++17", "-Wall", "-Wno-unknown-pragmas", "-I" + os.path.join(ROOT, "include"),
-                           "-I" + os.path.join(ROOT, "paper_2509_10798_amd", "csrc"), os.path.join(ROOT, "tests", "split_walk.cpp"), "-o", exe])
+    exe = _compiled(tmp_path_factory, "split_walk")
 
     def run(calls):
         """calls: (n_layers, lens, h_kv, rows, rows2, chunk, every quad); returns (workgroups, sets, longest, quads) of each."""
@@ -64,3 +70,8 @@ def test_workspace_of_a_call_that_no_card_holds():
     # 2^32 quads: what a portion is divided by used to come out as zero
     sh = jq.Shape(n_layers=32768, seq_lens=[131072] * 128, n_q=32, h_q=4, h_kv=1)
     assert jq.workspace_bytes(sh) > 32768 * 128 * 131072 * 8
+
+
+def test_no_request_starts_outside_what_it_reads(tmp_path_factory):
+    r = subprocess.run([_compiled(tmp_path_factory, "request_walk")], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout == "ok\n", r.stdout
