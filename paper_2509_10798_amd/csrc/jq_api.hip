@@ -21,7 +21,7 @@ static Knobs read_knobs() {
     k.chunk_keys2 = chunk("JQ_CHUNK_KEYS_2");
     if (!std::getenv("JQ_CHUNK_KEYS_2")) k.chunk_keys2 = k.chunk_keys;
     const char* wait = std::getenv("JQ_WAIT_US");
-    k.wait_us = wait ? (int32_t)std::min(std::max(std::atol(wait), 0l), 1000000l) : 1000;
+    k.wait_us = wait ? (int32_t)std::min(std::max(std::atol(wait), 0l), 1000000l) : 20;
     k.log = std::getenv("JQ_LOG") != nullptr;
     return k;
 }

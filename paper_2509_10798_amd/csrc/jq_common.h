@@ -121,7 +121,7 @@ __device__ inline uint32_t select_key(float x, int j, int L, int keep_first, int
 struct Knobs {
     int32_t chunk_keys;   // JQ_CHUNK_KEYS: keys per wave in the pass that reads K cold, in whole workgroups per sequence (0: planned)
     int32_t chunk_keys2;  // JQ_CHUNK_KEYS_2: the same for the second pass (0: JQ_CHUNK_KEYS if set, else planned)
-    int32_t wait_us;      // JQ_WAIT_US: how long a workgroup waits for others' statistics before it forms them itself (microseconds)
+    int32_t wait_us;      // JQ_WAIT_US: how long a workgroup waits, once, for others' statistics before it forms them itself (microseconds)
     int32_t log;          // JQ_LOG: print the HIP error string when a launch is refused
 };
 const Knobs& knobs();

@@ -867,7 +867,12 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
                 for (;;) {
                     const uint64_t late = __ballot(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.token);
                     if (late == 0u) break;
-                    if (wall_clock64() - t0 >= patience) { missing = 1u + (uint32_t)__builtin_ctzll(late); break; }
+                    if (wall_clock64() - t0 >= patience) {  // the missing one that falls to this workgroup
+                        uint64_t m = n_p < 64 ? late & ((1ull << n_p) - 1) : late;
+                        for (int skip = h.rank % __builtin_popcountll(m); skip > 0; --skip) m &= m - 1;
+                        missing = 1u + (uint32_t)__builtin_ctzll(m);
+                        break;
+                    }
                     __builtin_amdgcn_s_sleep(1);
                 }
                 if (lane == 0) lds_put8(word, make_uint2(missing, 0u));
@@ -1038,9 +1043,14 @@ template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placem
 // sets read and merged 1.2, terms exchanged 0.4.  Whole calls, two launches / one: 2048 tokens and 2 heads 18.7 / 17.0 us, 32768 tokens
 // 48.3 / 44.8, 128K layer 114.7 / 113.0, 32 layers of 8192 246 / 240, 8 x 12345 with window queries 97.3 / 92.8; together with the
 // even shares a paged batch of 8 196 / 187, 16 ragged sequences 821 / 779.
-// No workgroup depends on another one running: a wait ends after `wait_ticks` (or the time the workgroup has run itself, if that
-// is longer), and what is missing then is formed here, from the same keys in the same order -- the same bits, whoever
-// stores them.  The flags need no clearing before the launch: they are compared with a 64-bit token that is the call's
+// No workgroup depends on another one running: it waits for `wait_ticks` (or the time it has run itself, if that is longer), once,
+// and from then on it forms what is missing itself, from the same keys in the same order -- the same bits, whoever
+// stores them.  Several that miss the same sets begin with different ones.  A launch that gets part of the chip only, beside
+// another stream's kernels, so loses a sweep or two over what it has there: 32768 tokens with a quarter of the CUs held by another
+// kernel 99 us (two launches 60; 1000 and more while every missing set cost a wait of its own and all workgroups formed the same
+// one), 128K layer 506 (420; 2200).  Where the device has fewer CUs than the launch has workgroups both passes go one after the other.
+// Two streams with evictions of their own take no longer than one with both.
+// The flags need no clearing before the launch: they are compared with a 64-bit token that is the call's
 // own.  A captured call has the same token in every replay, so a later kernel of the call clears them.
 // One workgroup per CU (99 KB of LDS).
 template <int NQT, bool PAGED>
@@ -1071,6 +1081,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
             q_there = true;
             if (missing >= 0) {
                 help = at.c - h.rank + missing;
+                patience = 0;
             } else {
                 if (!next_share(a, h, true, at)) break;
                 q_there = false;
@@ -1325,6 +1336,20 @@ static hipError_t launch_passes_n(int nqt, const ScoreArgs& a, dim3 grid, hipStr
     }
 }
 
+// Workgroups of jq_passes_kernel that run at the same time on the present device: one per CU.
+static int resident_passes() {
+    constexpr int kDevices = 64;
+    static std::atomic<int> cus[kDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kDevices) return 0;
+    int n = cus[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        cus[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // A value that no flag holds by chance (2^-64): every call's is another one.
 static uint64_t next_token() {
     static std::atomic<uint64_t> count{[] {
@@ -1382,7 +1407,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     const dim3 block(kScoreWaves * 64);
     const unsigned wgs = (unsigned)(p.split.n_wg * p.h_kv);
     hipError_t e;
-    if (!lse && p.one_launch && flags_cleared_later && !marks) {
+    if (!lse && p.one_launch && flags_cleared_later && !marks && wgs <= (unsigned)resident_passes()) {
         a.flags = (uint64_t*)(ws + p.off_flags);
         a.token = next_token();
         a.wait_ticks = (int64_t)knobs().wait_us * 100;

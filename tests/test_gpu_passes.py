@@ -146,3 +146,71 @@ def test_nothing_behind_queries_and_keys_is_read(n_q, h_q, h_kv, L):
     ref = oracle.score(Q[0, 0], K[0])
     for x in (two, one):
         assert_scores_close(x[0].cpu().numpy(), ref, n_q * (h_q // h_kv) / L)
+
+
+def _timed(torch, run):
+    import time
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    run()
+    torch.cuda.synchronize()
+    return time.perf_counter() - t
+
+
+def _eviction(torch, n_layers, L, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    Q = torch.randn((n_layers, 1, 32, 32, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((n_layers, L, 8, 128), generator=gen, device="cuda").bfloat16()
+    sh = jq.Shape(n_layers=n_layers, seq_lens=[L], n_q=32, h_q=32, h_kv=8, budgets=[256])
+    out = dict(zip(("K_out", "V_out", "idx_out", "scores_out"), jq.evict(sh, Q, K, K)))
+    ws = jq.alloc_workspace(sh)
+    torch.cuda.synchronize()
+    return lambda: jq.evict(sh, Q, K, K, ws=ws, **out), out
+
+
+@pytest.mark.parametrize("wait_us", [None, 0])
+@pytest.mark.parametrize("n_layers,L", [(1, 4096), (1, 32768), (3, 40000)])
+def test_evictions_on_two_streams_share_the_chip(knobs, n_layers, L, wait_us):
+    # workgroups of one call may find those that they share a sequence with not yet running: the same bits, and no time lost
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("two streams", n_layers, L, wait_us, flush=True)
+    calls = [_eviction(torch, n_layers, L, seed) for seed in (1, 2)]
+    want = [{k: x.clone() for k, x in out.items()} for _, out in calls]
+    if wait_us is not None:
+        knobs(JQ_WAIT_US=str(wait_us))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+
+    def loop(which, n=50):
+        for _ in range(n):
+            for (call, _), st in zip(calls, which):
+                with torch.cuda.stream(st):
+                    call()
+    loop([streams[0]] * 2, 3)
+    alone = _timed(torch, lambda: loop([streams[0]] * 2))
+    for _, out in calls:
+        for x in out.values():
+            x.zero_()
+    torch.cuda.synchronize()
+    both = min(_timed(torch, lambda: loop(streams)) for _ in range(3))
+    for (_, out), w in zip(calls, want):
+        for k in out:
+            assert torch.equal(out[k].view(torch.int16), w[k].view(torch.int16)), k
+    assert both < 2.0 * alone + 2e-3, (both, alone)
+
+
+def test_more_workgroups_than_the_chip_runs_do_not_wait_for_each_other(knobs):
+    # 512 keys per wave: 512 workgroups of a CU each.  With both passes in one launch the first half would wait for the other,
+    # here a tenth of a second.
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("512 workgroups", flush=True)
+    _, out = _eviction(torch, 1, 131072, 3)
+    want = out["idx_out"].clone()
+    knobs(JQ_CHUNK_KEYS="512", JQ_WAIT_US="100000")
+    call, out = _eviction(torch, 1, 131072, 3)
+    assert _timed(torch, call) < 0.05
+    # (another cut, another order of the sums: 3e-6 of a score, far less than what stands between most kept and dropped sums)
+    for got, ref in zip(out["idx_out"][0].tolist(), want[0].tolist()):
+        assert len(set(got) & set(ref)) >= 250
