@@ -33,6 +33,7 @@
 // fixed channel permutation cancels.  Result: lane l holds column (l & 31), register v holds row
 // 8*(v/4) + 4*(l>>5) + (v&3).
 #include <atomic>
+#include <chrono>
 #include <random>
 #include <type_traits>
 
@@ -1352,9 +1353,13 @@ static int resident_passes() {
 
 // A value that no flag holds by chance (2^-64): every call's is another one.
 static uint64_t next_token() {
-    static std::atomic<uint64_t> count{[] {
-        std::random_device rd;
-        return ((uint64_t)rd() << 32) ^ (uint64_t)rd();
+    static std::atomic<uint64_t> count{[]() -> uint64_t {
+        try {
+            std::random_device rd;
+            return ((uint64_t)rd() << 32) ^ (uint64_t)rd();
+        } catch (...) {  // no source of random numbers: the time, in nanoseconds, which no earlier process had either
+            return (uint64_t)std::chrono::system_clock::now().time_since_epoch().count();
+        }
     }()};
     uint64_t x = count.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);  // splitmix64 (Steele, Lea, Flood 2014): a bijection of the count
     x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
