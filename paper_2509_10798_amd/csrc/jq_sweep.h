@@ -85,7 +85,9 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
     // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
     int64_t n = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per);
     n = std::min(n, n_quads);
-    if (p.by_rows || (n == n_quads && per * n > 64)) n = std::min(n, (n_quads + 1) / 2);
+    // (As many as there are keys for, down to a quad each: 4096 tokens and 8 heads 17.6 us a call, with two quads each 19.0; 2000
+    // tokens 17.2 / 19.0.  With many query rows two quads, which halves the sets of statistics: 1024 rows x 2048 keys 34.7 / 34.8.)
+    if (p.by_rows) n = std::min(n, (n_quads + 1) / 2);
     // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
     // kStartUp of them (5.6 us in the first pass, 7 in the second, 1.25 us a quad).
     constexpr int kStartUp = 5;
