@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "jq.h"
 
@@ -61,8 +62,9 @@ struct Split {
 };
 
 // How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
-// with about that many.  Without it as many workgroups as make one per CU share the quads: whole ones for every (layer, sequence),
-// as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest workgroup.
+// with about that many.  Without it as many workgroups as make one per CU, or two, share the quads: whole ones for every
+// (layer, sequence), as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest
+// workgroup.  Many short sequences get a workgroup each.
 template <class P>
 static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight) {
     Split x{};
@@ -81,64 +83,114 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
     };
     if (chunk) return pieces(chunk);
     const int64_t per = (int64_t)p.h_kv * p.row_groups;
+    // A workgroup's time in quads of either pass (1.25 us each where the whole chip streams); a change of sequence (query rows,
+    // statistics, another merge) costs about as much as kStartUp of them (5.6 us in the first pass, 7 in the second).
+    constexpr double kStartUp = 5.0;
+    struct Deal {
+        int64_t n;      // workgroups per head (and group of query rows)
+        int64_t steps;  // whole workgroups with at most that many quads each; 0: dealt evenly
+        int64_t gap;
+        double cost;    // of the longest workgroup
+    };
+    // The best of n workgroups at `quad` a quad and `start` a share.
+    auto deal = [&](int64_t n, double quad, double start) {
+        Deal d{n, 0, 0, 0.0};
+        auto whole = [&](int64_t steps) {  // workgroups per layer with at most that many quads each
+            int64_t wgs = 0;
+            for (int s = 0; s < p.n_seq; ++s) wgs += (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps;
+            return wgs;
+        };
+        int64_t steps = 0;  // the fewest that n workgroups can do with; 0: more (layer, sequence)s than workgroups
+        if (units <= n) {
+            int64_t lo = (n_quads + n - 1) / n, hi = max_quads;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) / 2;
+                if (p.n_layers * whole(mid) <= n) hi = mid; else lo = mid + 1;
+            }
+            steps = lo;
+        }
+        auto longest = [&](int64_t gap) {
+            const int64_t total = n_quads + (units - 1) * gap;
+            double worst = 0.0;
+            int64_t u0 = 0;
+            int32_t s = 0;
+            for (int64_t c = 0, b0 = 0; c < n; ++c) {
+                const int64_t b1 = (c + 1) * total / n;
+                int64_t quads = 0, shares = 0;
+                for (;;) {
+                    const int64_t nq = p.cu_quad[s + 1] - p.cu_quad[s], lo = std::max(b0, u0), hi = std::min(b1, u0 + nq);
+                    if (hi > lo) { quads += hi - lo; ++shares; }
+                    if (b1 < u0 + nq + gap || (b1 == total && u0 + nq >= total)) break;
+                    u0 += nq + gap;
+                    if (++s == p.n_seq) s = 0;
+                    if (u0 >= b1) break;
+                }
+                worst = std::max(worst, quad * (double)quads + start * (double)shares);
+                b0 = b1;
+            }
+            return worst;
+        };
+        // (A workgroup that comes to more than one sequence may take fewer keys: a gap between sequences in the row that is dealt.)
+        const double one = quad * (double)steps + start;  // whole workgroups
+        d.cost = 1e300;
+        if (units > 1 && units <= 1024 && n > 1) {
+            d.cost = longest(0);
+            const double gapped = n_quads / n > (int64_t)kStartUp ? longest((int64_t)kStartUp) : 1e300;
+            if (gapped < d.cost) { d.cost = gapped; d.gap = (int64_t)kStartUp; }
+        } else if (units > 1) {  // many sequences, a few to every workgroup
+            d.cost = quad * (double)(n_quads / n) + start * (double)(units / n + 1);
+        }
+        if (steps && one <= d.cost) d = Deal{n, steps, 0, one};
+        return d;
+    };
+    // Of n workgroups per head as many as there are keys for, down to a quad each: 4096 tokens and 8 heads 17.6 us a call, with two
+    // quads each 19.0; 2000 tokens 17.2 / 19.0.  With many query rows two, which halves the sets of statistics: 1024 rows x 2048
+    // keys 34.7 / 34.8.
+    auto at_most = [&](int64_t n) {
+        n = std::min(n, n_quads);
+        return p.by_rows ? std::min(n, (n_quads + 1) / 2) : n;
+    };
     // (With many query rows the keys come out of the caches and arithmetic is the bound: two workgroups per CU hide each other's
     // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
-    int64_t n = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per);
-    n = std::min(n, n_quads);
-    // (As many as there are keys for, down to a quad each: 4096 tokens and 8 heads 17.6 us a call, with two quads each 19.0; 2000
-    // tokens 17.2 / 19.0.  With many query rows two quads, which halves the sets of statistics: 1024 rows x 2048 keys 34.7 / 34.8.)
-    if (p.by_rows) n = std::min(n, (n_quads + 1) / 2);
-    // A workgroup's time in quads of either pass; a change of sequence (query rows, statistics, another merge) costs about as much as
-    // kStartUp of them (5.6 us in the first pass, 7 in the second, 1.25 us a quad).
-    constexpr int kStartUp = 5;
-    auto whole = [&](int64_t steps) {  // workgroups per layer with at most that many quads each
-        int64_t wgs = 0;
-        for (int s = 0; s < p.n_seq; ++s) wgs += (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps;
-        return wgs;
-    };
-    int64_t steps = 0;  // the fewest that n workgroups can do with; 0: more (layer, sequence)s than workgroups
-    if (units <= n) {
-        int64_t lo = (n_quads + n - 1) / n, hi = max_quads;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (p.n_layers * whole(mid) <= n) hi = mid; else lo = mid + 1;
+    const int64_t one_per_cu = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per), n1 = at_most(one_per_cu);
+    // 85 % of the CUs take what memory delivers: more make every quad slower, fewer leave it idle.
+    constexpr double kEnough = 0.85;
+    auto busy = [&](int64_t n, int64_t places) { return std::max(kEnough, (double)(n * per) / (double)places); };
+    const bool even = p.by_rows || tight;
+    Deal best = deal(n1, even ? 1.0 : std::min(1.0, busy(one_per_cu, 256)), kStartUp);
+    // Two workgroups per CU, which takes a launch for either pass: they hide part of each other's start-ups, of every share 2.7 us
+    // with one row tile and 4.3 with four, and more of the chip has work where the heads do not divide it; the boundary between the
+    // launches costs 2.5 us, and the sweeps take 4 % longer.  Where sequences are many and alike, one workgroup for each,
+    // which the chip takes up as it has room, beats even portions by a few per cent.  Whole calls in us, one workgroup per CU / two,
+    // even portions / one for each (layer, sequence):
+    //   8 KV heads, 1024 x 512 tokens 769 / 655 / 628, 512 x 3000 1490 / 1463 / 1433, 256 x 300 157 / 129 / 129, 128 x 1024 144 / 137 / 132,
+    //   64 x 4096 223 / 229 / 232, 80 x 3000 230 / 222 / 240, 256 of 100 to 3000 292 / 276 / 292;  96 heads, 32 x 2048 907 / 790 / 771,
+    //   131072 1371 / 1304, 32768 340 / 337, 8192 77 / 85;  72 heads, 131072 945 / 962;  130 heads, 8192 128 / 113, 32768 550 / 438.
+    if (!even && (units > n1 || (double)(per * n1) < kEnough * 256)) {
+        const int64_t two_per_cu = 512 / per, n2 = at_most(two_per_cu);
+        const double start = kStartUp - (0.87 + 0.21 * std::min(4, p.row_tiles)), quad = 1.04;
+        Deal two = best;
+        two.cost = 1e300;
+        if (n2 > n1) two = deal(n2, quad * busy(two_per_cu, 512), start);
+        double each = 1e300;
+        if (units > n1) {
+            // rounds of 512 workgroups, of which the last takes little more than half the time where its workgroups are alone on a CU;
+            // of unequal sequences any may come last
+            const double rounds = (double)(units * per) / 512.0, rest = rounds - std::floor(rounds), longest = quad * max_quads + start;
+            each = rounds < 1.0 ? longest : longest * (std::floor(rounds) + (rest > 0.0 ? 0.55 + 0.9 * std::max(0.0, rest - 0.5) : 0.0));
+            each = std::min(each, longest + (quad * (double)n_quads + start * (double)units) * (double)per / 512.0);
         }
-        steps = lo;
-    }
-    auto longest = [&](int64_t gap) {
-        const int64_t total = n_quads + (units - 1) * gap;
-        int64_t worst = 0, u0 = 0;
-        int32_t s = 0;
-        for (int64_t c = 0, b0 = 0; c < n; ++c) {
-            const int64_t b1 = (c + 1) * total / n;
-            int64_t cost = 0;
-            for (;;) {
-                const int64_t nq = p.cu_quad[s + 1] - p.cu_quad[s], lo = std::max(b0, u0), hi = std::min(b1, u0 + nq);
-                if (hi > lo) cost += hi - lo + kStartUp;
-                if (b1 < u0 + nq + gap || (b1 == total && u0 + nq >= total)) break;
-                u0 += nq + gap;
-                if (++s == p.n_seq) s = 0;
-                if (u0 >= b1) break;
-            }
-            worst = std::max(worst, cost);
-            b0 = b1;
+        if (each <= two.cost) {
+            if (2.0 * each + 2.5 < best.cost) best = Deal{units, max_quads, 0, each};
+        } else if (2.0 * two.cost + 1.0 < best.cost) {
+            best = two;
         }
-        return worst;
-    };
-    // (A workgroup that comes to more than one sequence may take fewer keys: a gap between sequences in the row that is dealt.)
-    int64_t dealt = INT64_MAX;
-    if (units > 1 && units <= 1024 && n > 1) {
-        dealt = longest(0);
-        const int64_t gapped = n_quads / n > kStartUp ? longest(kStartUp) : INT64_MAX;
-        if (gapped < dealt) { dealt = gapped; x.args.gap = kStartUp; }
-    } else if (units > 1) {
-        dealt = n_quads / n + kStartUp;  // many sequences, a few to every workgroup
     }
-    if (steps && steps + kStartUp <= dealt) {
-        x.args = SplitArgs{};
+    const int64_t n = best.n;
+    if (best.steps) {
         x.args.whole = 1;
         for (int s = 0; s < p.n_seq; ++s) {
-            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + steps - 1) / steps);
+            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + best.steps - 1) / best.steps);
             x.cu[s + 1] = x.cu[s] + w;
             x.max_sets = std::max(x.max_sets, w);
         }
@@ -151,11 +203,9 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
     // The arithmetic of even portions is one of 32 bits: n * total has to stay below 2^32.  A call of 2^24 quads or more (2^31 tokens
     // over all layers, which a paged cache reaches where sequences share pages) has whole workgroups of 2048 quads instead, some
     // 2.5 ms of either pass each: thousands of them, at most 64 per sequence, and no start-up that counts.
-    const int64_t total = n_quads + (units - 1) * x.args.gap;
-    if (n * total >= (int64_t)1 << 32) {
-        x.args = SplitArgs{};
-        return pieces(2048 * kKeyTile);
-    }
+    const int64_t total = n_quads + (units - 1) * best.gap;
+    if (n * total >= (int64_t)1 << 32) return pieces(2048 * kKeyTile);
+    x.args.gap = (int32_t)best.gap;
     x.args.n = (int32_t)n;
     x.args.total = (int32_t)total;
     x.args.per_layer = p.cu_quad[p.n_seq] + p.n_seq * x.args.gap;

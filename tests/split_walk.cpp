@@ -13,7 +13,7 @@ using namespace jq;
 
 struct Tab { std::vector<int32_t> cu_seq; };
 struct Call {  // what make_split reads of a plan
-    int32_t n_layers, n_seq, h_kv, row_groups;
+    int32_t n_layers, n_seq, h_kv, row_tiles, row_groups;
     bool by_rows;
     std::vector<int32_t> cu_quad;
     Tab tab;
@@ -95,7 +95,8 @@ int main() {
     while (std::scanf("%d %d %d %d %d %d %d", &n_layers, &n_seq, &h_kv, &rows, &rows2, &chunk, &full) == 7) {
         Call p;
         p.n_layers = n_layers; p.n_seq = n_seq; p.h_kv = h_kv;
-        p.row_groups = ((rows + 31) / 32 + (rows2 + 31) / 32 + 3) / 4;
+        p.row_tiles = (rows + 31) / 32 + (rows2 + 31) / 32;
+        p.row_groups = (p.row_tiles + 3) / 4;
         p.by_rows = p.row_groups > 1 || rows2 > 0;
         p.cu_quad.assign(1, 0); p.tab.cu_seq.assign(1, 0);
         int max_quads = 0;

@@ -33,6 +33,8 @@ SHAPES = [
     (2, [70] * 30, 4, 4, 1),                  # thirty sequences of less than a quad: a workgroup has many shares
     (5, [9999], 32, 12, 4),                   # layers that do not divide the workgroups; a group of three
     (1, [5000, 200, 3000], 7, 9, 3),          # 21 rows; heads that do not divide the chip
+    (9, [300, 1, 129] * 12, 16, 16, 8),       # many short sequences: a workgroup for each, two per CU
+    (2, [6000], 4, 130, 130),                 # more heads than half the CUs: two workgroups per CU, even portions
 ]
 
 

@@ -66,6 +66,19 @@ def test_every_key_is_taken_once_in_the_largest_calls(walk):
         assert n_wg * h_kv * groups >= 250 and longest * 100 <= quads  # and the whole chip takes part
 
 
+def test_the_chip_has_work_whatever_the_number_of_heads(walk):
+    calls = [(1, [131072 if h_kv < 120 else 32768], h_kv, 64, 0, 0, 0) for h_kv in range(1, 257)]
+    for (_, _, h_kv, _, _, _, _), (n_wg, n_sets, longest, quads) in zip(calls, walk(calls)):
+        assert n_wg * h_kv >= 170, (h_kv, n_wg)  # of 256 CUs
+
+
+def test_many_short_sequences_have_a_workgroup_each(walk):
+    # several of them one after the other in one workgroup per CU leave the chip waiting for query rows and statistics
+    calls = [(nl, [L] * n, h_kv, 128, 0, 0, 1) for nl, n, L, h_kv in ((32, 32, 512, 8), (1, 128, 1000, 8), (32, 8, 300, 8), (32, 1, 2048, 96), (100, 1, 700, 8))]
+    for (nl, lens, h_kv, _, _, _, _), (n_wg, n_sets, longest, quads) in zip(calls, walk(calls)):
+        assert n_wg == n_sets == nl * len(lens), (nl, len(lens), h_kv, n_wg)
+
+
 def test_workspace_of_a_call_that_no_card_holds():
     # 2^32 quads: what a portion is divided by used to come out as zero
     sh = jq.Shape(n_layers=32768, seq_lens=[131072] * 128, n_q=32, h_q=4, h_kv=1)
