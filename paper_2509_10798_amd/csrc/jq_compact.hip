@@ -181,20 +181,23 @@ hipError_t launch_mark_dest_pages(const Plan& p, uint32_t* dest_bits, hipStream_
 // list is looked up in the current list by binary search.  Integer work; the quotient is the only rounding.
 // One workgroup per problem is a chain of latencies: searching in memory, nine dependent reads for 512 kept positions.  The
 // current list therefore goes to LDS first, all requests together (lists beyond kHitLds positions, which fill a quarter of a CU's
-// LDS, are searched in memory as before).
+// LDS, are searched in memory).  A workgroup has LDS for the call's longest such list and no more, so that eight of them share a CU where
+// lists are short: 16384 problems of 512 positions 33 us a call (62 searched in memory, 73 with 40 KB each), of 64 positions 17
+// (17, 37), 512 of 10000 62 (137, 63).
 struct HitArgs {
     const int32_t* cur;  // [n_layers][h_kv][TB_cur]
     const int32_t* ref;  // [n_layers][h_kv][TB_ref]
     float* rate;         // [n_layers][n_seq][h_kv]
     int32_t n_layers, n_seq, h_kv;
     int64_t TB_cur, TB_ref;
+    int32_t lds;         // positions that the workgroups' LDS has room for
     int32_t cu_cur[JQ_MAX_SEQ + 1], cu_ref[JQ_MAX_SEQ + 1];
 };
 
 constexpr int kHitLds = 10240;
 __global__ __launch_bounds__(256) void jq_hit_rate_kernel(HitArgs a) {
     __shared__ uint32_t wave_hits[4];
-    __shared__ int32_t list[kHitLds];
+    extern __shared__ int32_t list[];  // [a.lds]
     const int g = blockIdx.x % a.h_kv;
     const int s = (blockIdx.x / a.h_kv) % a.n_seq;
     const int layer = blockIdx.x / (a.h_kv * a.n_seq);
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(256) void jq_hit_rate_kernel(HitArgs a) {
             hits += (lo < nc && sorted[lo] == want);
         }
     };
-    if (nc <= kHitLds) {  // uniform
+    if (nc <= a.lds) {  // uniform
         for (int i = threadIdx.x; i < nc; i += 256) list[i] = cur[i];
         __syncthreads();
         count(list);
@@ -237,7 +240,12 @@ hipError_t launch_hit_rate(const Plan& p, const int32_t* cu_ref_budgets, int64_t
     a.n_layers = p.n_layers; a.n_seq = p.n_seq; a.h_kv = p.h_kv;
     a.TB_cur = p.TB; a.TB_ref = tb_ref;
     for (int s = 0; s <= p.n_seq; ++s) { a.cu_cur[s] = p.tab.cu_bud[s]; a.cu_ref[s] = cu_ref_budgets[s]; }
-    return launch_kernel(jq_hit_rate_kernel, dim3((unsigned)(p.n_layers * p.n_seq * p.h_kv)), dim3(256), 0, st, nullptr, -1, a);
+    a.lds = 0;  // the longest list that goes to LDS
+    for (int s = 0; s < p.n_seq; ++s) {
+        const int32_t n = a.cu_cur[s + 1] - a.cu_cur[s];
+        if (n <= kHitLds && n > a.lds) a.lds = n;
+    }
+    return launch_kernel(jq_hit_rate_kernel, dim3((unsigned)(p.n_layers * p.n_seq * p.h_kv)), dim3(256), (size_t)a.lds * 4, st, nullptr, -1, a);
 }
 
 // Plain streaming copy, 16 bytes per lane: the known-size reference against which hardware traffic

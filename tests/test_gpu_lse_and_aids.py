@@ -270,3 +270,27 @@ def test_map_mse_fused_of_identical_query_sets_is_zero():
     got = jq.map_mse_fused(sh, Q, Q.clone(), K)
     torch.cuda.synchronize()
     assert float(got.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("budgets,ref_budgets", [
+    ([10240, 3, 10241], [700, 3, 5000]),  # the longest list that goes to LDS, the shortest that does not, and a short one
+    ([11000], [12]), ([1, 1, 1], [1, 2, 1]), ([64, 10240], [10240, 1]),
+])
+def test_hit_rate_at_the_edges_of_its_lds(budgets, ref_budgets):
+    torch = torch_()
+    print("hit rate", budgets, ref_budgets, flush=True)
+    rng = np.random.default_rng(8)
+    n_layers, h_kv, L = 2, 3, 12000
+
+    def lists(sizes):
+        return np.concatenate([np.stack([np.stack([np.sort(rng.choice(L, n, replace=False)) for _ in range(h_kv)]) for _ in range(n_layers)])
+                               for n in sizes], axis=2).astype(np.int32)
+    cur, ref = lists(budgets), lists(ref_budgets)
+    sh = jq.Shape(n_layers=n_layers, seq_lens=[L] * len(budgets), n_q=1, h_q=h_kv, h_kv=h_kv, budgets=budgets)
+    got = jq.hit_rate(sh, torch.from_numpy(cur).cuda(), torch.from_numpy(ref).cuda(), ref_budgets=ref_budgets).cpu().numpy()
+    c, r = np.concatenate([[0], np.cumsum(budgets)]), np.concatenate([[0], np.cumsum(ref_budgets)])
+    for layer in range(n_layers):
+        for s in range(len(budgets)):
+            for g in range(h_kv):
+                want = oracle.hit_rate(cur[layer, g, c[s]:c[s + 1]], ref[layer, g, r[s]:r[s + 1]])
+                assert abs(float(got[layer, s, g]) - want) <= 1e-7
