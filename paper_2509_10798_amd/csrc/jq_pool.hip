@@ -77,8 +77,6 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     static_assert(2 * kPoolMaxHalo <= kPoolThreads, "one round of loads for the halo");
     argument_lines<2>();
     const int g = blockIdx.y, layer = blockIdx.z;
-    if (a.flags && blockIdx.x == 0)  // the workgroups of a layer's and head's first segment share it
-        for (int i = (layer * a.h_kv + g) * kPoolThreads + (int)threadIdx.x; i < a.n_flags; i += a.n_layers * a.h_kv * kPoolThreads) a.flags[i] = 0;
     const int s = a.one_L ? 0 : find_seq(a.cu_seg, a.tab.n_seq, blockIdx.x);
     const int64_t lo = a.one_L ? 0 : a.tab.cu_seq[s], hi = a.one_L ? a.one_L : a.tab.cu_seq[s + 1];
     const int Ls = (int)(hi - lo);
@@ -169,6 +167,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
         }
     }
     if (!do_hist) return;  // uniform
+    if (a.flags && blockIdx.x == 0)  // the workgroups of a layer's and head's first segment share it
+        for (int i = (layer * a.h_kv + g) * kPoolThreads + (int)threadIdx.x; i < a.n_flags; i += a.n_layers * a.h_kv * kPoolThreads) a.flags[i] = 0;
 
     uint32_t key[4], bin[4];
     uint32_t top = 0, bottom = 0xFFFFFFFFu;
