@@ -856,7 +856,7 @@ bool evict_tail_small(const Plan& p) {
     const int L = longest_sequence(p);
     if (L > kSmallMax) return false;
     if (p.pool_k != 1 && p.pool_k != 5 && p.pool_k != 7)
-        return L <= 2048 || p.pool_k <= (L <= 4096 ? 29 : L <= 8192 ? 9 : L <= 16384 ? 3 : 0);
+        return L <= 2048 || p.pool_k <= (L <= 4096 ? 31 : L <= 8192 ? 9 : L <= 16384 ? 3 : 0);
     return p.pool_k == 1 || L <= 16384 || (int64_t)p.n_layers * p.n_seq * p.h_kv <= 256;
 }
 
