@@ -169,7 +169,7 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
     p.off_aug = off;    off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * RP * sizeof(uint2));
     // (the flags of a launch that does both passes lie where the merge launch it does without leaves its terms)
     p.off_flags = p.off_aug;
-    p.one_launch = sweeps && !p.by_rows && p.split.max_sets <= 64 && p.split.n_wg * p.h_kv <= 256 &&
+    p.one_launch = sweeps && !p.by_rows && p.split.max_sets <= kMergedSets && p.split.n_wg * p.h_kv <= 256 &&
                    (size_t)p.split.n_sets <= (size_t)p.n_layers * p.n_seq * RP && knobs().chunk_keys == knobs().chunk_keys2;
     p.off_hist = off;   off += align_up((size_t)p.n_layers * p.n_seq * p.h_kv * kHistStride * sizeof(uint32_t));
     p.off_scores = off; off += align_up((size_t)p.n_layers * p.h_kv * p.T * sizeof(float));

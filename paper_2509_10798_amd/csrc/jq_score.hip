@@ -1434,7 +1434,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         // its head's sets itself; a very long sequence has hundreds, and then one small launch merges them
         // once (and clears the selection's words on the way).
         share_out(p.split, a.part, a.cu_part);
-        a.fuse_combine = p.split.max_sets <= 64 && !p.by_rows;
+        a.fuse_combine = p.split.max_sets <= kMergedSets && !p.by_rows;
         if (!a.fuse_combine) {
             const int64_t n_row_tiles = (int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles;
             e = launch_kernel(jq_combine_kernel, dim3((unsigned)min(n_row_tiles, (int64_t)1 << 20)), dim3(kRowTile * kCombineLanes), 0, st, nullptr, -1, a);
@@ -1453,8 +1453,15 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         if (paged) return launch_kernel(jq_score_rows_kernel<true, false>, grid, block, 0, st, marks, kTrScore, a);
         return launch_kernel(jq_score_rows_kernel<false, false>, grid, block, 0, st, marks, kTrScore, a);
     }
-    // the second pass may share the keys out in its own way
-    const Split& own = lse ? p.split : p.split2;
+    // The second pass may share the keys out in its own way; alone, it has no statistics that would have to be merged.
+    const bool wider = lse && p.split.fewer;
+    Split alone;
+    if (wider) {
+        int32_t max_quads = 0;
+        for (int s = 0; s < p.n_seq; ++s) max_quads = std::max(max_quads, p.cu_quad[s + 1] - p.cu_quad[s]);
+        alone = make_split(p, 0, max_quads, false, false);
+    }
+    const Split& own = wider ? alone : lse ? p.split : p.split2;
     share_out(own, a.own, a.cu_wg);
     const dim3 grid((unsigned)(own.n_wg * p.h_kv));
     if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);

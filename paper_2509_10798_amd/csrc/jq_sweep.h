@@ -21,6 +21,7 @@ namespace jq {
 constexpr int kKeyTile = 32;        // keys per MFMA tile (one 32x32 block column)
 constexpr int kRowTile = 32;        // query rows per MFMA tile
 constexpr int kHeadDim = 128;
+constexpr int kMergedSets = 64;     // sets of statistics of a (layer, sequence) that the second pass merges itself
 constexpr int kScoreWaves = 4;      // waves per workgroup in the score kernels
 
 JQ_HD int lesser(int a, int b) { return a < b ? a : b; }
@@ -58,15 +59,17 @@ struct Split {
     int32_t n_wg;       // workgroups per KV head (and group of query rows)
     int32_t n_sets;     // sets of statistics per KV head that a first pass shared out like this leaves
     int32_t max_sets;   // ... of one (layer, sequence) at most
+    bool fewer;         // there are fewer workgroups than the chip has room for, for no more than kMergedSets sets
     int32_t cu[JQ_MAX_SEQ + 1];  // first position, or workgroup, of every sequence in a layer
 };
 
 // How the passes over K share the keys out.  `chunk` (keys per wave, a knob) gives every sequence whole workgroups of four waves
 // with about that many.  Without it as many workgroups as make one per CU, or two, share the quads: whole ones for every
 // (layer, sequence), as many as keep the longest of them shortest, or all quads dealt evenly, whichever has the shorter longest
-// workgroup.  Many short sequences get a workgroup each.
+// workgroup.  Many short sequences get a workgroup each.  `first`: the split is a first pass's (the second pass alone has no
+// statistics to merge).
 template <class P>
-static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight) {
+static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight, bool first = true) {
     Split x{};
     const int64_t n_quads = (int64_t)p.n_layers * p.cu_quad[p.n_seq], units = (int64_t)p.n_layers * p.n_seq;
     auto pieces = [&](int32_t keys) {
@@ -84,8 +87,9 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
     if (chunk) return pieces(chunk);
     const int64_t per = (int64_t)p.h_kv * p.row_groups;
     // A workgroup's time in quads of either pass (1.25 us each where the whole chip streams); a change of sequence (query rows,
-    // statistics, another merge) costs about as much as kStartUp of them (5.6 us in the first pass, 7 in the second).
-    constexpr double kStartUp = 5.0;
+    // statistics, another merge) costs about as much as kStartUp of them (5.6 us in the first pass, 7 in the second).  More than
+    // kMergedSets sets of a (layer, sequence) take a launch that merges them and two for the passes.
+    constexpr double kStartUp = 5.0, kMerge = 2.7;
     struct Deal {
         int64_t n;      // workgroups per head (and group of query rows)
         int64_t steps;  // whole workgroups with at most that many quads each; 0: dealt evenly
@@ -141,56 +145,74 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
             d.cost = quad * (double)(n_quads / n) + start * (double)(units / n + 1);
         }
         if (steps && one <= d.cost) d = Deal{n, steps, 0, one};
+        const int64_t each = d.steps ? d.steps : n_quads / n;  // quads of a (layer, sequence) that one workgroup takes, at least
+        if (first && !p.by_rows && (d.steps ? (max_quads - 1) / each + 1 : (max_quads - 2) / each + 2) > kMergedSets) d.cost += kMerge;
         return d;
     };
     // Of n workgroups per head as many as there are keys for, down to a quad each: 4096 tokens and 8 heads 17.6 us a call, with two
-    // quads each 19.0; 2000 tokens 17.2 / 19.0.  With many query rows two, which halves the sets of statistics: 1024 rows x 2048
-    // keys 34.7 / 34.8.
+    // quads each 19.0; 2000 tokens 17.2 / 19.0.  With many query rows two, which halves the sets of statistics (1024 rows x 2048
+    // keys 34.7 / 34.8), but a workgroup for every (layer, sequence): 256 rows, 8 layers of 37 keys 22.1 us, two to a workgroup 27.4.
     auto at_most = [&](int64_t n) {
         n = std::min(n, n_quads);
-        return p.by_rows ? std::min(n, (n_quads + 1) / 2) : n;
+        return p.by_rows ? std::min(n, std::max(units, (n_quads + 1) / 2)) : n;
     };
     // (With many query rows the keys come out of the caches and arithmetic is the bound: two workgroups per CU hide each other's
-    // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, training forward 88.6 -> 86.3; three and four lose that again.)
-    const int64_t one_per_cu = tight ? 1 : std::max<int64_t>(1, (p.by_rows ? 512 : 256) / per), n1 = at_most(one_per_cu);
-    // 85 % of the CUs take what memory delivers: more make every quad slower, fewer leave it idle.
-    constexpr double kEnough = 0.85;
+    // start-ups, 1024 rows x 16384 keys 94.4 -> 93.3 us per evaluation step, x 131072 keys 531 -> 511, training forward 88.6 -> 86.3;
+    // three and four lose that again.  With more than about twelve workgroups per head merging takes it back unless they have
+    // long to run: 256 rows x 65536 keys of 8 heads 91.6 against 89.6, x 131072 167.9 / 168.8, 1024 rows x 131072 of one head 84.7 / 83.2.)
+    const bool pairs = p.by_rows && (per >= 40 || n_quads * per >= 24 * 512);
+    const int64_t one_per_cu = tight ? 1 : std::max<int64_t>(1, (pairs ? 512 : 256) / per), n1 = at_most(one_per_cu);
+    // 84 % of the CUs take what memory delivers: more make every quad slower, fewer leave it idle.
+    constexpr double kEnough = 0.84;
     auto busy = [&](int64_t n, int64_t places) { return std::max(kEnough, (double)(n * per) / (double)places); };
-    const bool even = p.by_rows || tight;
-    Deal best = deal(n1, even ? 1.0 : std::min(1.0, busy(one_per_cu, 256)), kStartUp);
-    // Two workgroups per CU, which takes a launch for either pass: they hide part of each other's start-ups, of every share 2.7 us
-    // with one row tile and 4.3 with four, and more of the chip has work where the heads do not divide it; the boundary between the
-    // launches costs 2.5 us, and the sweeps take 4 % longer.  Where sequences are many and alike, one workgroup for each,
-    // which the chip takes up as it has room, beats even portions by a few per cent.  Whole calls in us, one workgroup per CU / two,
-    // even portions / one for each (layer, sequence):
+    // Two workgroups per CU hide part of each other's start-ups, and their sweeps take 6 % longer; one for each sequence, 4 %.
+    constexpr double kPairStart = 3.55, kPairQuad = 1.065, kEachQuad = 1.04;
+    auto one = [&](int64_t n, int64_t per_cu) { return deal(n, p.by_rows || tight ? 1.0 : std::min(1.0, busy(per_cu, 256)), kStartUp); };
+    auto two = [&](int64_t n, int64_t per_cu) {
+        Deal d = deal(n, kPairQuad * busy(per_cu, 512), kPairStart);
+        d.cost *= 2.0;
+        return d;
+    };
+    Deal best = pairs && !tight ? two(n1, one_per_cu) : one(n1, one_per_cu);
+    // One or two KV heads: fewer workgroups than CUs, but no sets that a launch of its own would have to merge.  In us, all / at most 64
+    // a sequence: 16384 tokens of one head 29.3 / 26.1, 32768 31.7 / 31.5, 50000 147.1 / 149.0; of two heads 24000 35.9 / 32.6, 65536 173.6 /
+    // 175.1; of three 131072 46.1 / 42.6 (scores alone).
+    if (n1 > kMergedSets && max_quads > kMergedSets && !p.by_rows && first) {
+        const int64_t fewer = units == 1 ? kMergedSets : std::max<int64_t>(1, n_quads / ((max_quads + kMergedSets - 3) / (kMergedSets - 2)));
+        if (fewer < n1) {
+            const Deal d = one(fewer, fewer);
+            if (d.cost < best.cost) { best = d; x.fewer = true; }
+        }
+    }
+    // Two workgroups per CU, which takes a launch for either pass (unless there are many query rows), where sequences are short or the
+    // heads do not divide the chip.  Where sequences are many and alike, one workgroup for each, which the chip takes up as it
+    // has room, beats even portions.  The constants are fitted to 580 calls of 1 to 200 KV heads, 1 to 128 sequences and 1 to
+    // 128 layers, each timed all three ways (0.4 % slower than the best of them on average).  Whole calls in us, one workgroup per CU /
+    // two, even portions / one for each (layer, sequence):
     //   8 KV heads, 1024 x 512 tokens 769 / 655 / 628, 512 x 3000 1490 / 1463 / 1433, 256 x 300 157 / 129 / 129, 128 x 1024 144 / 137 / 132,
     //   64 x 4096 223 / 229 / 232, 80 x 3000 230 / 222 / 240, 256 of 100 to 3000 292 / 276 / 292;  96 heads, 32 x 2048 907 / 790 / 771,
     //   131072 1371 / 1304, 32768 340 / 337, 8192 77 / 85;  72 heads, 131072 945 / 962;  130 heads, 8192 128 / 113, 32768 550 / 438.
-    if (!even && (units > n1 || (double)(per * n1) < kEnough * 256)) {
-        const int64_t two_per_cu = 512 / per, n2 = at_most(two_per_cu);
-        const double start = kStartUp - (0.87 + 0.21 * std::min(4, p.row_tiles)), quad = 1.04;
-        Deal two = best;
-        two.cost = 1e300;
-        if (n2 > n1) two = deal(n2, quad * busy(two_per_cu, 512), start);
-        double each = 1e300;
-        if (units > n1) {
-            // rounds of 512 workgroups, of which the last takes little more than half the time where its workgroups are alone on a CU;
-            // of unequal sequences any may come last
-            const double rounds = (double)(units * per) / 512.0, rest = rounds - std::floor(rounds), longest = quad * max_quads + start;
-            each = rounds < 1.0 ? longest : longest * (std::floor(rounds) + (rest > 0.0 ? 0.55 + 0.9 * std::max(0.0, rest - 0.5) : 0.0));
-            each = std::min(each, longest + (quad * (double)n_quads + start * (double)units) * (double)per / 512.0);
+    if (!tight && (2 * units > n1 || (double)(per * n1) < kEnough * 256)) {
+        const int64_t n2 = at_most(512 / per);
+        if (n2 > n1) {
+            const Deal d = two(n2, 512 / per);
+            if (d.cost < best.cost) { best = d; x.fewer = false; }
         }
-        if (each <= two.cost) {
-            if (2.0 * each + 2.5 < best.cost) best = Deal{units, max_quads, 0, each};
-        } else if (2.0 * two.cost + 1.0 < best.cost) {
-            best = two;
+        if (units > n1) {
+            // rounds of 512 workgroups, of which the last takes two thirds of the time where its workgroups are alone on a CU; of
+            // unequal sequences a long one may come last
+            const double rounds = (double)(units * per) / 512.0, rest = rounds - std::floor(rounds);
+            const double mean = kEachQuad * (double)n_quads / (double)units + kPairStart, longest = kEachQuad * max_quads + kPairStart;
+            const double r = rounds < 1.0 ? 1.0 : std::floor(rounds) + (rest > 0.0 ? 0.67 + 0.66 * std::max(0.0, rest - 0.5) : 0.0);
+            const double cost = std::max(2.0 * mean * r, 2.0 * mean * (r - 1.0) + 1.1 * longest + 0.75 * mean) + 0.65;
+            if (cost <= best.cost) { best = Deal{units, max_quads, 0, cost}; x.fewer = false; }
         }
     }
     const int64_t n = best.n;
     if (best.steps) {
         x.args.whole = 1;
         for (int s = 0; s < p.n_seq; ++s) {
-            const int32_t w = (int32_t)(p.n_seq == 1 ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + best.steps - 1) / best.steps);
+            const int32_t w = (int32_t)(p.n_seq == 1 && !x.fewer ? n / units : (p.cu_quad[s + 1] - p.cu_quad[s] + best.steps - 1) / best.steps);
             x.cu[s + 1] = x.cu[s] + w;
             x.max_sets = std::max(x.max_sets, w);
         }

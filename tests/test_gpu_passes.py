@@ -35,6 +35,8 @@ SHAPES = [
     (1, [5000, 200, 3000], 7, 9, 3),          # 21 rows; heads that do not divide the chip
     (9, [300, 1, 129] * 12, 16, 16, 8),       # many short sequences: a workgroup for each, two per CU
     (2, [6000], 4, 130, 130),                 # more heads than half the CUs: two workgroups per CU, even portions
+    (12, [100, 1, 300] * 8, 64, 8, 2),        # 256 query rows: a workgroup for every sequence and group of rows
+    (1, [9135], 8, 4, 1),                     # one head: 36 sets of statistics, not one for each of 72 quads
 ]
 
 

@@ -41,3 +41,24 @@ def test_scores_do_not_depend_on_the_cut(knobs, n_layers, seq_lens, h_q, h_kv):
     for L in seq_lens:
         np.testing.assert_allclose(planned[:, :, at:at + L].double().sum(-1).cpu().numpy(), n_q * h_q / h_kv, rtol=1e-5)
         at += L
+
+
+@pytest.mark.parametrize("n_layers,seq_lens,h_q,h_kv", [(1, [16384], 4, 1), (2, [9999, 300], 4, 2)])
+def test_scores_from_supplied_normalisers_do_not_depend_on_the_cut(knobs, n_layers, seq_lens, h_q, h_kv):
+    # the second pass alone has no sets to merge and shares the keys out more finely than a call of both
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("work split with normalisers", n_layers, seq_lens, h_q, h_kv, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    T, n_q = sum(seq_lens), 32
+    Q = torch.randn((n_layers, len(seq_lens), n_q, h_q, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((n_layers, T, h_kv, 128), generator=gen, device="cuda").bfloat16()
+    lse = 9.0 + torch.rand((n_layers, len(seq_lens), n_q, h_q), generator=gen, device="cuda")
+    sh = jq.Shape(n_layers=n_layers, seq_lens=seq_lens, n_q=n_q, h_q=h_q, h_kv=h_kv)
+    planned = jq.score(sh, Q, K, lse=lse)
+    torch.cuda.synchronize()
+    knobs(JQ_CHUNK_KEYS="64")
+    small = jq.score(sh, Q, K, lse=lse)
+    torch.cuda.synchronize()
+    assert torch.equal(planned, small)  # a key's sum is formed by one wave, in the same order whatever the cut

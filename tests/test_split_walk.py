@@ -72,11 +72,17 @@ def test_the_chip_has_work_whatever_the_number_of_heads(walk):
         assert n_wg * h_kv >= 170, (h_kv, n_wg)  # of 256 CUs
 
 
-def test_many_short_sequences_have_a_workgroup_each(walk):
+def test_many_short_sequences_do_not_queue_in_one_workgroup_per_cu(walk):
     # several of them one after the other in one workgroup per CU leave the chip waiting for query rows and statistics
     calls = [(nl, [L] * n, h_kv, 128, 0, 0, 1) for nl, n, L, h_kv in ((32, 32, 512, 8), (1, 128, 1000, 8), (32, 8, 300, 8), (32, 1, 2048, 96), (100, 1, 700, 8))]
     for (nl, lens, h_kv, _, _, _, _), (n_wg, n_sets, longest, quads) in zip(calls, walk(calls)):
-        assert n_wg == n_sets == nl * len(lens), (nl, len(lens), h_kv, n_wg)
+        assert n_wg * h_kv > 256, (nl, len(lens), h_kv, n_wg)
+
+
+def test_long_sequences_of_few_heads_leave_sets_that_need_no_merge_launch(walk):
+    calls = [(1, [L], h_kv, 128, 0, 0, 1) for L, h_kv in ((16384, 1), (24000, 2), (40000, 3))]
+    for _, n_sets, _, _ in walk(calls):
+        assert n_sets <= 64
 
 
 def test_workspace_of_a_call_that_no_card_holds():
