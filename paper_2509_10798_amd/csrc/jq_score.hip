@@ -687,6 +687,7 @@ constexpr float kPadTerm = -1.0e30f;  // for padded rows: 2^(c * x) = 0
 
 constexpr int kCombineLanes = 32;  // partial-lanes per query row
 __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(ScoreArgs) {
+    argument_lines<5>();
     KArgs& a = kernel_args();
     // one workgroup per (layer, sequence, head, tile of 32 rows); thread = (row r, partial-lane kl)
     __shared__ float2 part[kCombineLanes][kRowTile];
