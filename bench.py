@@ -16,7 +16,8 @@ protocol is reported beside it (``from_idle``).
 
 The ``roofline`` object is measured live right after the timed loop, in the same state:
 ``jq_evict_traced`` gives every kernel HIP start/stop events on the launch stream; the dominant
-kernel is the slower of the two passes over K.  ``cpu_baseline`` times the fp64 oracle on the
+kernel is the slower of the two passes over K.  Traced, either pass is a launch of its own; the timed steps run
+both in one (``jq_passes_kernel``), whose duration ``profiles/`` has.  ``cpu_baseline`` times the fp64 oracle on the
 host cores for the same workload.
 """
 import argparse
@@ -270,7 +271,8 @@ def main():
                 "bytes_per_launch": pass_bytes[dom], "us_per_launch": kernels_us[dom],
                 "us_per_launch_median": kernels_us_median[dom],
                 "frac_at_median": round(pass_bytes[dom] / (kernels_us_median[dom] * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
-                "launches_measured": int(per_step.shape[0])}
+                "launches_measured": int(per_step.shape[0]),
+                "note": "the passes over K timed apart (jq_evict_traced); the timed steps run both in one launch, jq_passes_kernel"}
     if traffic_note:
         roofline["traffic_note"] = traffic_note
     k_passes = kernels_us["jq_stats_kernel"] + kernels_us["jq_score_kernel"]

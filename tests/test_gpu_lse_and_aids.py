@@ -113,8 +113,9 @@ def test_traced_evict_equals_evict_and_times_every_kernel():
 
 
 @pytest.mark.parametrize("L,pool_k", [(4096, 7), (20000, 7), (20000, 31), (40000, 7)])
-def test_traced_evict_times_the_kernels_that_evict_runs(L, pool_k):
-    # short sequences in one kernel, at a width that is not compiled in and above 32768 tokens in two
+def test_traced_evict_times_the_tail_that_evict_runs_and_its_passes_apart(L, pool_k):
+    # short sequences in one kernel, at a width that is not compiled in and above 32768 tokens in two; both passes over K in one
+    # launch, traced in two
     torch = torch_()
     gen = torch.Generator(device="cuda")
     gen.manual_seed(4)
@@ -126,15 +127,21 @@ def test_traced_evict_times_the_kernels_that_evict_runs(L, pool_k):
         ev.record()
     plain = jq.evict(sh, Q, K, K)
     from torch.profiler import ProfilerActivity, profile
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        out = jq.evict(sh, Q, K, K, marks=marks)
-        torch.cuda.synchronize()
-    ran = [e.name for e in prof.events() if "jq_" in e.name]  # (the profiler may miss one)
+
+    def kernels(run):
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            out = run()
+            torch.cuda.synchronize()
+        return out, [e.name for e in prof.events() if "jq_" in e.name]  # (the profiler may miss one)
+    _, ran_plain = kernels(lambda: [jq.evict(sh, Q, K, K) for _ in range(3)])
+    out, ran = kernels(lambda: jq.evict(sh, Q, K, K, marks=marks))
     for x, y in zip(out, plain):
         assert torch.equal(x.view(torch.int16), y.view(torch.int16))
-    assert ran
+    assert ran and ran_plain
     other = ("jq_pool_kernel", "jq_select_finalize_kernel") if L <= 32768 and pool_k == 7 else ("jq_pool_select_kernel",)
-    assert not [n for n in ran if any(o in n for o in other)]
+    assert not [n for n in ran + ran_plain if any(o in n for o in other)]
+    assert not [n for n in ran if "jq_passes_kernel" in n]
+    assert not [n for n in ran_plain if "jq_stats_kernel" in n or "jq_score_kernel" in n]
     assert all(0.0 < marks[2 * j].elapsed_time(marks[2 * j + 1]) < 50.0 for j in range(len(jq.TRACE_KERNELS)))
 
 
