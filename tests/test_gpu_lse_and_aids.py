@@ -119,9 +119,9 @@ def test_traced_evict_times_the_tail_that_evict_runs_and_its_passes_apart(L, poo
     torch = torch_()
     gen = torch.Generator(device="cuda")
     gen.manual_seed(4)
-    Q = torch.randn((1, 1, 8, 8, 128), generator=gen, device="cuda").bfloat16()
+    Q = torch.randn((1, 1, 32, 8, 128), generator=gen, device="cuda").bfloat16()
     K = torch.randn((1, L, 2, 128), generator=gen, device="cuda").bfloat16()
-    sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=8, h_q=8, h_kv=2, pool_k=pool_k, budgets=[256])
+    sh = jq.Shape(n_layers=1, seq_lens=[L], n_q=32, h_q=8, h_kv=2, pool_k=pool_k, budgets=[256])
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(jq.TRACE_MARKS)]
     for ev in marks:
         ev.record()
