@@ -43,7 +43,7 @@ struct Plan {
     int32_t row_groups;   // ceil(row_tiles / 4): 1, or the groups of rows that the first pass handles side by side
     bool by_rows;         // the second pass streams query rows past keys held in registers (jq_score_rows_kernel)
     Split split, split2;  // the first pass over K (or the only one), and a second launch's
-    bool one_launch;      // both passes may go in one launch (jq_passes_kernel)
+    bool one_launch;      // both passes may go in one launch (jq_passes_kernel): a workgroup per CU at most, room for the flags
     int32_t cu_quad[JQ_MAX_SEQ + 1];  // groups of 128 keys per sequence
     double scale;         // logit scale actually used
     // paged cache (block_table null: dense K, V): page = 1 << page_shift tokens, n_pages per layer's pool

@@ -6,8 +6,8 @@
 //   merge:           beta_r = m_r + log2 Z_r over a sequence's partials, as -beta_r / c split into three
 //                    bf16 terms -- done by every pass-2 workgroup for its own head in its start-up (a
 //                    separate small kernel only when a sequence leaves more than 64 partials).
-// An eviction runs both passes in one launch, jq_passes_kernel: a workgroup scores the keys it has swept as soon as the others
-// that share their sequence have published their statistics.
+// An eviction whose workgroups all run at once does both passes in one launch, jq_passes_kernel: a workgroup scores the keys it has
+// swept as soon as the others that share their sequence have published their statistics.
 //   pass 2 (score):  score_j = sum_r 2^(c * (q_r.k_j - beta_r / c)).  The -beta_r/c term enters
 //                    through one extra MFMA step whose key-side operand is 1.0, so the epilogue is one
 //                    multiply, one exp2 and one add per logit.
