@@ -251,6 +251,7 @@ static Split make_split(const P& p, int32_t chunk, int32_t max_quads, bool tight
 // 128K layer).  Dealt evenly, a (layer, sequence) has at most one workgroup that comes to it late (the first), workgroups that
 // work on nothing else, and one that leaves early (the last), so the number of quads taken before a workgroup's step i has a
 // closed form.
+constexpr int kWhole = 0x7FFFFFFF;  // Share::q of a whole workgroup
 struct Share {
     int layer, seq, L, seq_tiles;  // seq_tiles: 32-key tiles of the sequence
     int64_t tok0;                  // first token of the sequence in the flattened T axis
@@ -309,7 +310,7 @@ JQ_HD Share share_of(A& a, int c, int layer, int seq) {
         h.x = 0;
         const uint32_t steps = (uint32_t)(nq - h.rank + h.n_sets - 1);  // >= n_sets: no more workgroups than quads
         h.len = (int)(sp.inv_n ? udiv(steps, (uint32_t)h.n_sets, sp.inv_n) : steps / (uint32_t)h.n_sets);
-        h.full = h.n_sets; h.at = h.rank; h.q = 0x7FFFFFFF;
+        h.full = h.n_sets; h.at = h.rank; h.q = kWhole;
         return h;
     }
     const int ca = h.set0 - (layer * a.n_seq + seq), cb = ca + h.n_sets - 1;
@@ -340,6 +341,11 @@ template <bool BACK>
 struct Walk {
     int i, t, stride, left;  // step, its tile, distance to the next step's and for how many more steps it holds
     JQ_HD void turn(const Share& h) {
+        if (h.q == kWhole) {  // whole workgroups: one distance throughout (2048 tokens 15.3 -> 15.0 us a call, 32768 41.3 -> 40.8)
+            stride = kScoreWaves * (BACK ? -h.full : h.full);
+            left = 0x7FFFFFFF;
+            return;
+        }
         const int at[5] = {h.q - 1, h.q, h.late_from, h.late_from + h.late_n, h.early};
         int next = BACK ? -1 : 0x7FFFFFFF;
 #pragma unroll
