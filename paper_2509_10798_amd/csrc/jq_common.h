@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "jq_sweep.h"
 
 namespace jq {
@@ -226,6 +228,20 @@ inline hipError_t launch_kernel(Kernel kernel, dim3 grid, dim3 block, size_t lds
         return hipExtLaunchKernel((const void*)kernel, grid, block, ptrs, lds_bytes, st, (hipEvent_t)marks[2 * tr],
                                   (hipEvent_t)marks[2 * tr + 1], 0);
     return hipLaunchKernel((const void*)kernel, grid, block, ptrs, lds_bytes, st);
+}
+
+// Launches with more than 64 KiB of dynamic LDS need the function's limit raised.  That
+// is done once per device, to the fixed maximum any call can ask for (never to a call's own size: the attribute is
+// process-wide, and two host threads with different sequence lengths must not undo each other's setting).
+inline hipError_t allow_dynamic_lds(const void* kernel, int most, std::atomic<uint64_t>& done) {  // done, bit d: device d has the limit raised
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+    if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
+    return e;
 }
 
 // Stage launchers (enqueue only).  Each returns a hipError_t from the launch.

@@ -73,6 +73,7 @@ struct ScoreArgs {
     uint64_t token;
     int64_t wait_ticks;
     int32_t n_sets;
+    int32_t held;         // second pass: tiles whose scores a wave holds back before it writes them (0: none), see score_share
     float* scores;        // [n_layers][h_kv][T]
     const float* lse;     // [n_layers][n_seq][n_q][h_q] caller-supplied natural-log normalisers, or null
     uint2* aug;           // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
@@ -192,6 +193,7 @@ __device__ __forceinline__ void lds_put8(uint32_t addr, uint2 v) {
     const uint64_t x = (uint64_t)v.x | ((uint64_t)v.y << 32);
     asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(x) : "memory");
 }
+__device__ __forceinline__ void lds_put4(uint32_t addr, uint32_t v) { asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory"); }
 __device__ __forceinline__ uint2 lds_get8_waited(uint32_t addr) {
     uint64_t x;
     asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x) : "v"(addr) : "memory");
@@ -282,6 +284,11 @@ constexpr int kLdsSet = kLdsQ + kMaxRowTiles * kSlotBytes;          // the set o
 constexpr int kLdsAug = kLdsSet + kMaxRowTiles * kRowTile * 8;     // the rows' normalisers
 constexpr int kLdsWord = kLdsAug + kMaxRowTiles * kRowTile * 8;
 constexpr int kLdsBoth = kLdsWord + 16;
+// Behind that, where a second pass holds scores back: per wave the scores of `held` tiles, then the tiles' numbers.
+constexpr int kHeldTile = kKeyTile * 4 + 4;
+constexpr int kMaxHeld = 119;  // what one workgroup of jq_passes_kernel has room for in the 160 KB of a CU
+constexpr int kFewHeld = 31;   // ... two workgroups of jq_score_kernel
+static_assert(kLdsBoth + kScoreWaves * kMaxHeld * kHeldTile <= 160 * 1024 && 2 * (kSlotsBytes + kScoreWaves * kFewHeld * kHeldTile) <= 160 * 1024, "LDS of a CU");
 
 struct KeyStream {
     __amdgpu_buffer_rsrc_t rsrc;  // this head's rows of the whole sequence (PAGED: of the layer's whole pool)
@@ -331,6 +338,12 @@ __device__ __forceinline__ uint32_t tile_offset(const KeyStream& ks, int t, int 
 template <bool PAGED>
 __device__ __forceinline__ int tile_page(const KeyStream& ks, int t) {
     return PAGED ? ((const_i32_ptr)ks.pages)[((uint32_t)t * kKeyTile) >> ks.page_shift] : 0;
+}
+
+// x of the lane and of the one 32 further on (or back)
+__device__ __forceinline__ float add_halves(float x) {
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(y[0]) + __uint_as_float(y[1]);
 }
 
 // One stage of the sweeps' software pipeline: `step(i)`, i = 0 .. NM - 1, issues the i-th matrix instruction of the NEXT
@@ -765,8 +778,8 @@ enum Norms {
 // A workgroup's share of one (layer, sequence): its waves score their tiles, from the share's last to its first (the first pass went
 // the other way, and the caches still hold what it read last: front to back it takes 1.7 us longer on the 128K layer).
 // Returns -1, or (kNormsShared) the number of a set that others have not published within `patience` ticks; nothing is scored then.
-template <int NQT, Norms NORMS, bool PAGED>
-__device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char* lds, int64_t patience, bool q_there = false) {
+template <int NQT, Norms NORMS, bool PAGED, bool HOLD>
+__device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char* lds, char* held_lds, int64_t patience, bool q_there = false) {
     const int lane = lane_again(), half = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     char* slots = lds + wv * 2 * kSlotBytes;
@@ -956,7 +969,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc((void*)(a.scores + ((int64_t)h.layer * a.h_kv + g) * a.T + h.tok0), 0,
                                                                           h.L * 4, 0x00020000);
     const float c = a.c;
-    float pending = 0.f;  // previous tile's result, stored one iteration late
+    float pending = 0.f;  // previous tile's result, handed out one iteration late
     const int n_scored = a.window ? h.L - a.n_q : h.L;  // the window's own positions report 0
     // Always one store instruction: the upper lane half (which holds the same sums), rows past the end of the sequence's last
     // tile and whatever goes to kNowhere fall behind the end of the resource, where the hardware drops them.
@@ -965,6 +978,46 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     auto store_tile = [&](int t, float v) {
         if (t * kKeyTile + kKeyTile > n_scored && t * kKeyTile + (lane & 31) >= n_scored) v = 0.f;
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, (int)(out_lane + 4u * (uint32_t)(t * kKeyTile)), 0, 0);
+    };
+    // HOLD: the scores wait in LDS and leave together, a.held tiles of every wave at a time -- the whole share's, if they fit.
+    const int hold = HOLD ? a.held : 0;
+    const uint32_t held = lds_addr(held_lds) + (uint32_t)(wv * hold * kHeldTile);
+    const uint32_t held_lane = held + 4u * ((uint32_t)lane & 31u), held_t = held + (uint32_t)hold * (kKeyTile * 4);
+    int n_held = 0;
+    auto write_out = [&]() __attribute__((always_inline)) {
+        lds_wait_all();
+        for (int i = 0; i < n_held; i += 8) {  // two tiles per store, one for either lane half (where they are too few, the last one again)
+            uint32_t v[4], t[4], at_v[4], at_t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = (uint32_t)min(i + 2 * u + half, n_held - 1);
+                at_v[u] = held_lane + j * (kKeyTile * 4);
+                at_t[u] = held_t + j * 4u;
+            }
+            // (explicit, as everything that touches LDS while key tiles are in flight)
+            asm volatile("ds_read_b32 %0, %8\n\tds_read_b32 %1, %9\n\tds_read_b32 %2, %10\n\tds_read_b32 %3, %11\n\t"
+                         "ds_read_b32 %4, %12\n\tds_read_b32 %5, %13\n\tds_read_b32 %6, %14\n\tds_read_b32 %7, %15\n\t"
+                         "s_waitcnt lgkmcnt(0)"
+                         : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+                         : "v"(at_v[0]), "v"(at_v[1]), "v"(at_v[2]), "v"(at_v[3]), "v"(at_t[0]), "v"(at_t[1]), "v"(at_t[2]), "v"(at_t[3])
+                         : "memory");
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int key = (int)t[u] * kKeyTile + (lane & 31);  // behind the sequence's end: dropped as above
+                __builtin_amdgcn_raw_buffer_store_b32(key < n_scored ? v[u] : 0u, out, 4 * key, 0, 0);
+            }
+        }
+        n_held = 0;
+    };
+    auto hand_out = [&](int t, float v) __attribute__((always_inline)) {
+        if (!HOLD) {
+            store_tile(t, v);
+        } else if (t != kNowhere) {
+            if (n_held == hold) write_out();
+            lds_put4(held_lane + (uint32_t)n_held * (kKeyTile * 4), __float_as_uint(v));
+            lds_put4(held_t + (uint32_t)n_held * 4u, (uint32_t)t);
+            ++n_held;
+        }
     };
 
     // Software pipeline over the query-row tiles and across key tiles, as in the first pass: while one tile's logits are
@@ -975,7 +1028,7 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     lds_get_frags(slots, kf, lane);
     wait_frags_read();
     int t_done = kNowhere, t_here = t_first, t_next = n_tiles > 1 ? fetch(1) : 0;  // the tiles k - 1, k, k + 1
-    store_tile(kNowhere, 0.f);  // for the sweep's first wait
+    hand_out(kNowhere, 0.f);  // for the sweep's first wait
     f32x16 acc = score_chain(qf[0], qaug[0], kf, ones);
     for (int k = 0; k < n_tiles; ++k) {
         float sum = 0.f;
@@ -983,7 +1036,10 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
         for (int qt = 0; qt < NQT; ++qt) {
             const bool reads = qt == (NQT > 1 ? NQT - 2 : 0);
             const char* next_slot = slots + ((k + 1) & 1) * kSlotBytes;
-            if (reads) wait_tile_landed_before_store();  // tile k + 1, behind which tile k - 2's scores were stored
+            if (reads) {  // tile k + 1, behind which tile k - 2's scores were stored
+                if (!HOLD) wait_tile_landed_before_store();
+                else wait_tile_landed();
+            }
             const uint32_t next_at = frag_addr(next_slot, lane);
             if (NQT == 1) lds_get_frags(next_slot, kf, lane);
             f32x16 nxt = zero_acc();
@@ -999,14 +1055,14 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
                 const int t_stored = t_done;
                 t_done = t_here; t_here = t_next;
                 if (k + 2 < n_tiles) t_next = fetch(k + 2);
-                store_tile(t_stored, pending);
+                hand_out(t_stored, pending);
             }
             acc = nxt;
         }
-        sum += __shfl_xor(sum, 32);  // the two lane halves hold complementary query rows of the same key
-        pending = sum;
+        pending = add_halves(sum);  // complementary query rows of the same key
     }
-    store_tile(t_done, pending);
+    hand_out(t_done, pending);
+    if (HOLD) write_out();
     return -1;
 }
 
@@ -1017,21 +1073,22 @@ __device__ __forceinline__ void clear_words(KArgs& a) {  // what the selection n
     for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
 }
 
-template <int NQT, bool FROM_LSE, bool PAGED>
+template <int NQT, bool FROM_LSE, bool PAGED, bool HOLD>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
+    extern __shared__ char held_lds[];
     argument_lines<5>();
     Place at = place_of(kernel_args(), gridDim.x - 1 - blockIdx.x, true);  // from the end: the keys pass 1 read last are fetched first
     clear_words(kernel_args());
     for (;;) {
         KArgs& a = kernel_args();
         const Share h = share_of(a, at.c, at.layer, at.seq);
-        score_share<NQT, FROM_LSE ? kNormsLse : kNormsMerged, PAGED>(a, h, at.g, lds, 0);
+        score_share<NQT, FROM_LSE ? kNormsLse : kNormsMerged, PAGED, HOLD>(a, h, at.g, lds, held_lds, 0);
         if (!next_share(a, h, true, at)) break;
     }
 }
 
-template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placement: see jq_lib.hip
+template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  // placement: see jq_lib.hip
 
 // ------------------------------------------------------------------------------------------------
 // both passes in one launch
@@ -1055,9 +1112,10 @@ template __global__ void jq_score_kernel<4, false, false>(ScoreArgs);  // placem
 // The flags need no clearing before the launch: they are compared with a 64-bit token that is the call's
 // own.  A captured call has the same token in every replay, so a later kernel of the call clears them.
 // One workgroup per CU (99 KB of LDS).
-template <int NQT, bool PAGED>
+template <int NQT, bool PAGED, bool HOLD>
 __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
+    extern __shared__ char held_lds[];
     argument_lines<5>();
     const int64_t t_entry = wall_clock64();
     Place at = place_of(kernel_args(), blockIdx.x, false);
@@ -1079,7 +1137,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
             q_there = scoring;
         } else {
             const Share h = share_of(a, at.c, at.layer, at.seq);
-            const int missing = score_share<NQT, kNormsShared, PAGED>(a, h, at.g, lds, patience, q_there);
+            const int missing = score_share<NQT, kNormsShared, PAGED, HOLD>(a, h, at.g, lds, held_lds, patience, q_there);
             q_there = true;
             if (missing >= 0) {
                 help = at.c - h.rank + missing;
@@ -1092,7 +1150,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
     }
 }
 
-template __global__ void jq_passes_kernel<4, false>(ScoreArgs);
+template __global__ void jq_passes_kernel<4, false, false>(ScoreArgs);
 
 // ------------------------------------------------------------------------------------------------
 // many query rows (more than kMaxRowTiles tiles per KV head): keys stationary, query rows streamed
@@ -1316,25 +1374,43 @@ static hipError_t launch_stats_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
     }
 }
 
+// The kernel that holds scores back where the call wants it (a.held) and the device grants the LDS they take, else the other one.
+template <class Kernel>
+static hipError_t launch_second(Kernel direct, Kernel holding, std::atomic<uint64_t>& allowed, const ScoreArgs& a, dim3 grid, hipStream_t st,
+                                void* const* marks) {
+    const dim3 block(kScoreWaves * 64);
+    if (a.held && allow_dynamic_lds((const void*)holding, kScoreWaves * kMaxHeld * kHeldTile, allowed) == hipSuccess)
+        return launch_kernel(holding, grid, block, (size_t)(kScoreWaves * a.held * kHeldTile), st, marks, kTrScore, a);
+    return launch_kernel(direct, grid, block, 0, st, marks, kTrScore, a);
+}
+
+template <int NQT, bool FROM_LSE, bool PAGED>
+static hipError_t launch_score_k(const ScoreArgs& a, dim3 grid, hipStream_t st, void* const* marks) {
+    static std::atomic<uint64_t> allowed;
+    return launch_second(jq_score_kernel<NQT, FROM_LSE, PAGED, false>, jq_score_kernel<NQT, FROM_LSE, PAGED, true>, allowed, a, grid, st, marks);
+}
 template <bool FROM_LSE, bool PAGED>
 static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st, void* const* marks) {
-    dim3 block(kScoreWaves * 64);
     switch (nqt) {
-        case 1: return launch_kernel(jq_score_kernel<1, FROM_LSE, PAGED>, grid, block, 0, st, marks, kTrScore, a);
-        case 2: return launch_kernel(jq_score_kernel<2, FROM_LSE, PAGED>, grid, block, 0, st, marks, kTrScore, a);
-        case 3: return launch_kernel(jq_score_kernel<3, FROM_LSE, PAGED>, grid, block, 0, st, marks, kTrScore, a);
-        default: return launch_kernel(jq_score_kernel<4, FROM_LSE, PAGED>, grid, block, 0, st, marks, kTrScore, a);
+        case 1: return launch_score_k<1, FROM_LSE, PAGED>(a, grid, st, marks);
+        case 2: return launch_score_k<2, FROM_LSE, PAGED>(a, grid, st, marks);
+        case 3: return launch_score_k<3, FROM_LSE, PAGED>(a, grid, st, marks);
+        default: return launch_score_k<4, FROM_LSE, PAGED>(a, grid, st, marks);
     }
 }
 
+template <int NQT, bool PAGED>
+static hipError_t launch_passes_k(const ScoreArgs& a, dim3 grid, hipStream_t st) {
+    static std::atomic<uint64_t> allowed;
+    return launch_second(jq_passes_kernel<NQT, PAGED, false>, jq_passes_kernel<NQT, PAGED, true>, allowed, a, grid, st, nullptr);
+}
 template <bool PAGED>
 static hipError_t launch_passes_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st) {
-    dim3 block(kScoreWaves * 64);
     switch (nqt) {
-        case 1: return launch_kernel(jq_passes_kernel<1, PAGED>, grid, block, 0, st, nullptr, -1, a);
-        case 2: return launch_kernel(jq_passes_kernel<2, PAGED>, grid, block, 0, st, nullptr, -1, a);
-        case 3: return launch_kernel(jq_passes_kernel<3, PAGED>, grid, block, 0, st, nullptr, -1, a);
-        default: return launch_kernel(jq_passes_kernel<4, PAGED>, grid, block, 0, st, nullptr, -1, a);
+        case 1: return launch_passes_k<1, PAGED>(a, grid, st);
+        case 2: return launch_passes_k<2, PAGED>(a, grid, st);
+        case 3: return launch_passes_k<3, PAGED>(a, grid, st);
+        default: return launch_passes_k<4, PAGED>(a, grid, st);
     }
 }
 
@@ -1409,7 +1485,17 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.lse = lse;
     a.part = a.own; a.fuse_combine = 0;
     a.flags = nullptr; a.token = 0; a.wait_ticks = 0; a.n_sets = p.split.n_sets;
-
+    a.held = 0;
+    // Scores are held back where the pass that makes them reads much of K from memory: 1.6 % of its bytes, they cost a tenth of its
+    // time when they are written between the reads (a build that stored none took 44.2 us for the pass of 4 x 32768, 51.2 with stores after
+    // every tile, 45.4 held back), and next to nothing while the Infinity Cache (256 MB) delivers K.  Written at the end they take
+    // 0.5 us of a short call.  Whole calls, stored at once / held back, 8 KV heads, us:
+    //   one pass (normalisers supplied): 30000 tokens 27.7 / 28.0, 40000 33.6 / 33.9, 60000 43.3 / 42.2, 80000 51.6 / 49.6, 2 x 32768 42.6 / 41.1,
+    //     4 x 32768 72.5 / 67.6, 8 x 65536 245 / 223;
+    //   two: 131072 110.2 / 110.9, 28 x 8192 219.6 / 221.1, 4 x 50000 164.7 / 165.4, 250000 205.2 / 203.3, 4 x 60000 paged 209 / 206, 32 x 8192
+    //     236.7 / 233.6, 8 x 65536 416 / 402, 16 ragged sequences of 981293 together 780 / 753.
+    const int64_t k_bytes = (int64_t)p.n_layers * p.T * p.h_kv * kHeadDim * 2;
+    const bool holds = k_bytes >= (lse ? (int64_t)110000000 : (int64_t)480000000);
     const dim3 block(kScoreWaves * 64);
     const unsigned wgs = (unsigned)(p.split.n_wg * p.h_kv);
     hipError_t e;
@@ -1417,6 +1503,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         a.flags = (uint64_t*)(ws + p.off_flags);
         a.token = next_token();
         a.wait_ticks = (int64_t)knobs().wait_us * 100;
+        a.held = holds ? kMaxHeld : 0;
         const int nqt = p.row_tiles;
         return paged ? launch_passes_n<true>(nqt, a, dim3(wgs), st) : launch_passes_n<false>(nqt, a, dim3(wgs), st);
     }
@@ -1465,6 +1552,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     const Split& own = wider ? alone : lse ? p.split : p.split2;
     share_out(own, a.own, a.cu_wg);
     const dim3 grid((unsigned)(own.n_wg * p.h_kv));
+    a.held = !holds ? 0 : grid.x <= (unsigned)resident_passes() ? kMaxHeld : kFewHeld;
     if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);
     return lse ? launch_score_n<true, false>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, false>(p.row_tiles, a, grid, st, marks);
 }

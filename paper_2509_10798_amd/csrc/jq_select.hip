@@ -788,20 +788,6 @@ bool select_fast_path(const Plan& p) {
     return qual_cap >= kQualCapMin;  // otherwise the bitmaps (nearly) fill LDS: stream instead
 }
 
-// Launches with more than 64 KiB of dynamic LDS need the function's limit raised.  That
-// is done once per device, to the fixed maximum any call can ask for (never to a call's own size: the attribute is
-// process-wide, and two host threads with different sequence lengths must not undo each other's setting).
-static hipError_t allow_large_lds(const void* kernel, std::atomic<uint64_t>& done) {  // done, bit d: device d has the limit raised
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
-    if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
-    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kMaxLds - 1024));
-    if (e == hipSuccess && bit) done.fetch_or(bit, std::memory_order_release);
-    return e;
-}
-
 static SelectArgs select_args(const Plan& p, const float* pooled, uint32_t* hist, char* ws, int32_t* idx, const void* K, const void* V,
                               void* K_out, void* V_out, void* stage, const int32_t* pos_in, int32_t* pos_out, const uint32_t* dest_bits) {
     SelectArgs a;
@@ -866,7 +852,7 @@ static hipError_t launch_small_k(const Plan& p, const PoolSelectArgs& a, hipStre
     const int words = kSmallFixedWords + small_pad(THREADS * VPT + 8) + 4;
     const size_t lds_bytes = (size_t)words * sizeof(uint32_t);
     if (lds_bytes > 64 * 1024) {
-        const hipError_t e = allow_large_lds((const void*)jq_pool_select_kernel<THREADS, VPT, K>, done);
+        const hipError_t e = allow_dynamic_lds((const void*)jq_pool_select_kernel<THREADS, VPT, K>, (int)(kMaxLds - 1024), done);
         if (e != hipSuccess) return e;
     }
     const unsigned n_prob = (unsigned)((int64_t)p.n_layers * p.n_seq * p.h_kv);
@@ -917,7 +903,7 @@ hipError_t launch_select(const Plan& p, const float* pooled, uint32_t* hist, cha
     const size_t lds_bytes = finalize_lds(p, &words_cap, &qual_cap);
     if (lds_bytes > 64 * 1024) {
         static std::atomic<uint64_t> done{0};
-        const hipError_t e = allow_large_lds((const void*)jq_select_finalize_kernel, done);
+        const hipError_t e = allow_dynamic_lds((const void*)jq_select_finalize_kernel, (int)(kMaxLds - 1024), done);
         if (e != hipSuccess) return e;
     }
     const unsigned slices = slices_of(p, false);

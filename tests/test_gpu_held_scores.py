@@ -1,0 +1,57 @@
+"""Scores held back in LDS and written together (second passes that read much of K from memory): the same bits as the scores that
+smaller calls, which store every tile's at once, make of the same keys -- with the normalisers supplied a score depends on its
+own key alone."""
+import pytest
+
+import paper_2509_10798_amd as jq
+
+pytestmark = pytest.mark.gpu
+
+HELD = 110_000_000  # bytes of K from which on one pass holds its scores back
+
+
+@pytest.mark.parametrize("h_q,h_kv,n_q,window,page,chunk,n_layers,seq_lens", [
+    (32, 8, 32, False, 0, None, 1, [30001, 20011, 77, 1, 4128, 12345]),   # a workgroup per CU, odd ends
+    (8, 8, 8, False, 0, None, 2, [29999, 127]),                            # one tile of query rows
+    (6, 2, 20, True, 0, None, 4, [50001, 4100]),                           # the window's own positions are 0; 60 rows
+    (32, 8, 32, False, 64, None, 1, [30001, 20011, 77, 1, 4128, 12345]),   # paged
+    (8, 1, 16, False, 0, 8192, 8, [53000, 1, 2000]),                       # 256 tiles a wave: more than are held at once
+    (16, 8, 16, False, 0, 1312, 3, [40000, 20000]),                        # two workgroups per CU, 41 tiles a wave
+])
+def test_held_back_scores_equal_those_stored_at_once(knobs, h_q, h_kv, n_q, window, page, chunk, n_layers, seq_lens):
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("held back", h_q, h_kv, n_q, window, page, chunk, n_layers, seq_lens, flush=True)
+    T = sum(seq_lens)
+    assert n_layers * T * h_kv * 256 >= HELD
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(6)
+    Q = torch.randn((n_layers, len(seq_lens), n_q, h_q, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((n_layers, T, h_kv, 128), generator=gen, device="cuda").bfloat16()
+    lse = 9.0 + torch.rand((n_layers, len(seq_lens), n_q, h_q), generator=gen, device="cuda")
+    if chunk:
+        knobs(JQ_CHUNK_KEYS=chunk, JQ_CHUNK_KEYS_2=chunk)
+    common = dict(n_q=n_q, h_q=h_q, h_kv=h_kv, window=window)
+    sh = jq.Shape(n_layers=n_layers, seq_lens=seq_lens, **common)
+    out = torch.full((n_layers, h_kv, T), float("nan"), device="cuda")
+    if page:
+        per = [-(-L // page) for L in seq_lens]
+        table = torch.full((len(seq_lens), max(per)), -1, dtype=torch.int32)
+        pool = torch.zeros((n_layers, sum(per), page, h_kv, 128), dtype=torch.bfloat16, device="cuda")
+        flat, at, nxt = pool.view(n_layers, -1, h_kv, 128), 0, 0
+        for s, L in enumerate(seq_lens):
+            table[s, :per[s]] = torch.arange(nxt, nxt + per[s])
+            flat[:, nxt * page:nxt * page + L] = K[:, at:at + L]
+            at, nxt = at + L, nxt + per[s]
+        got = jq.score_paged(sh, jq.Pages(page, sum(per), table.cuda()), Q, pool, lse=lse, scores=out)
+    else:
+        got = jq.score(sh, Q, K, lse=lse, scores=out)
+    at = 0
+    for s, L in enumerate(seq_lens):
+        for layer in range(n_layers):
+            assert L * h_kv * 256 < HELD
+            one = jq.score(jq.Shape(n_layers=1, seq_lens=[L], **common), Q[layer:layer + 1, s:s + 1].contiguous(),
+                           K[layer:layer + 1, at:at + L].contiguous(), lse=lse[layer:layer + 1, s:s + 1].contiguous())
+            torch.cuda.synchronize()
+            assert torch.equal(got[layer, :, at:at + L], one[0]), (layer, s)
+        at += L
