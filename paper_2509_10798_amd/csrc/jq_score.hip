@@ -67,8 +67,8 @@ struct ScoreArgs {
     float2* stats;    // [sets][h_kv][RP]: (m, Z) of every share of a (layer, sequence), see Share
     float c;             // scale * log2(e)
     int32_t window;       // 1: the queries are the sequence's own last n_q tokens; query i sees keys 0 .. L - n_q + i
-    // both passes in one launch: flags[h_kv][n_sets], set to `token` when a set of statistics is complete, and how long (ticks of
-    // 10 ns) a workgroup waits for others' before it forms them itself
+    // flags[h_kv][n_sets], set to `token` when a set of statistics is complete (first pass alone: [h_kv][n_rg][n_sets], with many
+    // query rows only); both passes in one launch: how long (ticks of 10 ns) a workgroup waits for others' before it forms them itself
     uint64_t* flags;
     uint64_t token;
     int64_t wait_ticks;
@@ -646,9 +646,9 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
             M = mm;
         }
         float2* to = &a.stats[((int64_t)set * a.h_kv + g) * a.RP + row];
-        if (SHARED) {
+        if (SHARED || a.flags) {
             __hip_atomic_store((uint64_t*)to, (uint64_t)__float_as_uint(M) | (uint64_t)__float_as_uint(Z) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            ((float2*)(lds + kLdsSet))[threadIdx.x] = make_float2(M, Z);
+            if (SHARED) ((float2*)(lds + kLdsSet))[threadIdx.x] = make_float2(M, Z);
         } else {
             *to = make_float2(M, Z);
         }
@@ -659,24 +659,6 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
         if (threadIdx.x == 0 && h.n_sets > 1) __hip_atomic_store(&a.flags[(int64_t)g * a.n_sets + set], a.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
-
-template <int NQT, bool PAGED>
-__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
-    __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
-    argument_lines<5>();
-    Place at = place_of(kernel_args(), blockIdx.x, false);
-    for (;;) {
-        KArgs& a = kernel_args();
-        const Share h = share_of(a, at.c, at.layer, at.seq);
-        stats_share<NQT, PAGED, false>(a, h, at.g, at.rg, lds);
-        if (!next_share(a, h, false, at)) break;
-        bare_barrier();  // the statistics have left the slots
-    }
-}
-
-// The instance of the headline shape (128 query rows per KV head, dense cache), emitted here so that it lies next
-// to the other kernels of a step in the library's code (see jq_lib.hip).
-template __global__ void jq_stats_kernel<4, false>(ScoreArgs);
 
 // -beta/c as the three bf16 terms (all 24 bits of an fp32 number) that enter the second pass through its extra MFMA step.
 // (A fourth term, bits 25..32, is truncated away inside the MFMA's addition: a common factor 1 + 3e-7.)
@@ -697,6 +679,90 @@ __device__ __forceinline__ uint2 neg_beta_terms(float m, float z, double inv_c) 
     return split_bf16x3((float)(-beta * inv_c));
 }
 constexpr float kPadTerm = -1.0e30f;  // for padded rows: 2^(c * x) = 0
+
+// (m, Z) of a row merged over sets from, from + 2, ... of the n there are; `u` of them in `t`
+template <int N>
+__device__ __forceinline__ void merge_sets(const float2 (&t)[N], int from, int n, float& M, float& Z) {
+    float mm = M;
+#pragma unroll
+    for (int u = 0; u < N; ++u) mm = fmaxf(mm, from + 2 * u < n ? t[u].x : -1.0e30f);
+    Z *= __builtin_amdgcn_exp2f(M - mm);
+#pragma unroll
+    for (int u = 0; u < N; ++u) Z = fmaf(t[u].y, from + 2 * u < n ? __builtin_amdgcn_exp2f(t[u].x - mm) : 0.f, Z);
+    M = mm;
+}
+// a set's pair for one row, formed and stored by another workgroup of this launch: read past the caches that are not shared
+__device__ __forceinline__ float2 load_pair(const float2* p) {
+    const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
+// Many query rows: the workgroup whose set completes those of a (layer, sequence), head and group of rows merges them, so that no
+// launch has to.  Each stores its set where every XCD sees it, then its flag, and then looks at all flags: whoever stored the
+// last one finds them all (two may, and write the same bits).  Nobody waits for another workgroup.  The three round trips and the
+// merge lengthen the first pass by 2.8 us, the launch took 4.3-6.8 and the gap in front of it 2.2: 16384 keys under 1024 rows 92.0 -> 90.8
+// us an evaluation step, training forward of 4 x 6007 keys 84.7 -> 81.7, 2000 keys under 256 rows 41.8 -> 37.4, 1500 keys trained 23.7 -> 20.4.
+// (Adding up the training objective's partial sums the same way costs every workgroup of the second pass a round trip with its
+// LDS held, several rounds of them: 1 x 16384 keys, 64 response tokens 44.0 -> 47.3 us, 4 x 16384 135.5 -> 141; that stays a launch.)
+template <int NQT>
+__device__ __forceinline__ void merge_if_last(KArgs& a, const Share& h, int g, int rg, char* lds) {
+    static_assert(kScoreWaves * 64 >= 2 * NQT * kRowTile, "two threads a row");
+    const int lane = lane_again();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the set
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        uint64_t* flag = a.flags + ((int64_t)g * a.n_rg + rg) * a.n_sets + h.set0;
+        if (lane == 0) __hip_atomic_store(flag + h.rank, a.token, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        const bool all = __all(__hip_atomic_load(flag + min(lane, h.n_sets - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.token);
+        if (lane == 0) *(int*)lds = all;
+    }
+    __syncthreads();
+    if (!*(const int*)lds) return;
+    const int p0 = (int)(threadIdx.x & 1), in_group = (int)(threadIdx.x >> 1), row = rg * NQT * kRowTile + in_group;
+    if (in_group >= NQT * kRowTile || row >= a.RP) return;  // both threads of a row
+    const float2* from = a.stats + ((int64_t)h.set0 * a.h_kv + g) * a.RP + row;
+    const int64_t step = (int64_t)a.h_kv * a.RP;
+    float M = -1.0e30f, Z = 0.f;
+    for (int k = p0; k < h.n_sets; k += 16) {
+        float2 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = load_pair(from + min(k + 2 * u, h.n_sets - 1) * step);
+        merge_sets(t, k, h.n_sets, M, Z);
+    }
+    const float oM = __shfl_xor(M, 1), oZ = __shfl_xor(Z, 1);
+    const float mm = fmaxf(M, oM), zz = Z * __builtin_amdgcn_exp2f(M - mm) + oZ * __builtin_amdgcn_exp2f(oM - mm);
+    if (p0) return;
+    const bool real = row < a.tiles1 * (int64_t)kRowTile ? row < a.rows : row - a.tiles1 * kRowTile < a.rows2;
+    a.aug[((int64_t)(h.layer * a.n_seq + h.seq) * a.h_kv + g) * a.RP + row] = real ? neg_beta_terms(mm, zz, a.inv_c) : split_bf16x3(kPadTerm);
+}
+
+__device__ __forceinline__ void clear_words(KArgs& a) {  // every workgroup its part
+    if (!a.zero) return;
+    const uint64_t per = (a.zero_words + gridDim.x - 1) / gridDim.x;
+    const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
+    for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
+}
+
+template <int NQT, bool PAGED>
+__global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_stats_kernel(ScoreArgs) {
+    __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
+    argument_lines<5>();
+    Place at = place_of(kernel_args(), blockIdx.x, false);
+    const bool many_rows = kernel_args().flags != nullptr;  // uniform
+    for (;;) {
+        KArgs& a = kernel_args();
+        const Share h = share_of(a, at.c, at.layer, at.seq);
+        stats_share<NQT, PAGED, false>(a, h, at.g, at.rg, lds);
+        if (many_rows) merge_if_last<NQT>(a, h, at.g, at.rg, lds);
+        if (!next_share(a, h, false, at)) break;
+        bare_barrier();  // the statistics have left the slots
+    }
+}
+
+// The instance of the headline shape (128 query rows per KV head, dense cache), emitted here so that it lies next
+// to the other kernels of a step in the library's code (see jq_lib.hip).
+template __global__ void jq_stats_kernel<4, false>(ScoreArgs);
 
 constexpr int kCombineLanes = 32;  // partial-lanes per query row
 __global__ __launch_bounds__(kRowTile * kCombineLanes) void jq_combine_kernel(ScoreArgs) {
@@ -902,39 +968,22 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
             }
         }
 #pragma unroll
-        for (int u = 0; u < kFirstParts; ++u) {  // formed and stored by other workgroups of this launch: read past the caches that are not shared
-            const uint64_t v = __hip_atomic_load((const uint64_t*)(pp + min(p0 + 2 * u, n_p - 1) * pstep), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            mz[u] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
-        }
+        for (int u = 0; u < kFirstParts; ++u) mz[u] = load_pair(pp + min(p0 + 2 * u, n_p - 1) * pstep);
     }
     float cM = -1.0e30f, cZ = 0.f;
     if (own_set) {
         const uint2 v = lds_get8_waited(lds_addr(lds + kLdsSet) + 8u * (uint32_t)mrow);
         if (p0 == 0) { cM = __uint_as_float(v.x); cZ = __uint_as_float(v.y); }
     } else if (merging && (threadIdx.x >> 1) < NQT * kRowTile) {  // the same order of additions whatever the number of sets
-        auto merge_in = [&](const float2* t, int n, int from) __attribute__((always_inline)) {  // sets from, from + 2, ...
-            float mm = cM;
-#pragma unroll
-            for (int u = 0; u < n; ++u) mm = fmaxf(mm, from + 2 * u < n_p ? t[u].x : -1.0e30f);
-            cZ *= __builtin_amdgcn_exp2f(cM - mm);
-#pragma unroll
-            for (int u = 0; u < n; ++u) cZ = fmaf(t[u].y, from + 2 * u < n_p ? __builtin_amdgcn_exp2f(t[u].x - mm) : 0.f, cZ);
-            cM = mm;
-        };
-        merge_in(mz, kFirstParts, p0);
+        merge_sets(mz, p0, n_p, cM, cZ);
         for (int k0 = p0 + 2 * kFirstParts; k0 < n_p; k0 += 16) {  // more than 32 sets
             float2 more[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const float2* src = pp + min(k0 + 2 * u, n_p - 1) * pstep;
-                if (NORMS == kNormsShared) {
-                    const uint64_t v = __hip_atomic_load((const uint64_t*)src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    more[u] = make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
-                } else {
-                    more[u] = *src;
-                }
+                more[u] = NORMS == kNormsShared ? load_pair(src) : *src;
             }
-            merge_in(more, 8, k0);
+            merge_sets(more, k0, n_p, cM, cZ);
         }
     }
     bf16x8 qaug[NQT];
@@ -1066,13 +1115,6 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     return -1;
 }
 
-__device__ __forceinline__ void clear_words(KArgs& a) {  // what the selection needs cleared: every workgroup its part
-    if (!a.zero) return;
-    const uint64_t per = (a.zero_words + gridDim.x - 1) / gridDim.x;
-    const uint64_t z0 = per * blockIdx.x, z1 = z0 + per < a.zero_words ? z0 + per : a.zero_words;
-    for (uint64_t i = z0 + threadIdx.x; i < z1; i += blockDim.x) a.zero[i] = 0u;
-}
-
 template <int NQT, bool FROM_LSE, bool PAGED, bool HOLD>
 __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kSlotsBytes];
@@ -1167,7 +1209,7 @@ template __global__ void jq_passes_kernel<4, false, false>(ScoreArgs);
 // the combine launch now (1.05 PFLOP/s; a plain library product of 8192^3 reaches 1.2 on this card, which lowers its
 // clock under matrix work).  Two waves per key group instead of four: 42.9 against 41.5 us there, 5 % better only with
 // thousands of workgroups: not kept.
-// -beta/c comes from `aug`, which a combine launch (or jq_lse_aug_kernel) has filled.
+// -beta/c comes from `aug`, which the first pass's last workgroups (or jq_combine_kernel, jq_lse_aug_kernel) have filled.
 // DIFF: two query sets, whose row tiles follow each other (tiles1).  A key's two sums form in the same sweep, and instead of
 // storing either map the workgroup leaves its sum of (sum1 / rows1 - sum2 / rows2)^2 (Eq. 5 of the paper on the maps of Eq. 3
 // and Eq. 4), in fp64 per key, then in a fixed order over lanes and waves.  The first set has four tiles where the second has
@@ -1306,6 +1348,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 2) void jq_score_rows_kernel(Scor
         }
     }
     if (DIFF && n_first == n_mine) next_set();  // a wave with tiles of the first set alone
+    clear_words(a);
     constexpr int kKeys = kMaxRowTiles * kKeyTile;
 #pragma unroll
     for (int kt = 0; kt < kMaxRowTiles; ++kt) {
@@ -1511,6 +1554,15 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         const int nqt = min(p.row_tiles, kMaxRowTiles);
         // all row groups in one launch (in several where the grid would get too large for one)
         const int per_launch = (int)max((int64_t)1, min((int64_t)p.row_groups, ((int64_t)1 << 23) / wgs));
+        // Many query rows: the sets are merged by the workgroup that completes them.  Its flags lie in the selection's histograms, which
+        // the next launch clears.
+        const size_t n_flags = (size_t)p.split.n_sets * p.h_kv * p.row_groups;
+        const bool last_merges = p.by_rows && per_launch >= p.row_groups && p.split.max_sets <= kMergedSets &&
+                                 n_flags * sizeof(uint64_t) <= p.off_scores - p.off_hist && (!zero || (char*)zero == ws + p.off_hist);
+        if (last_merges) {
+            a.flags = (uint64_t*)(ws + p.off_hist);
+            a.token = next_token();
+        }
         for (a.rg0 = 0; a.rg0 < p.row_groups; a.rg0 += per_launch) {
             a.n_rg = min(per_launch, p.row_groups - a.rg0);
             const dim3 g1(wgs * a.n_rg);
@@ -1523,7 +1575,11 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         // once (and clears the selection's words on the way).
         share_out(p.split, a.part, a.cu_part);
         a.fuse_combine = p.split.max_sets <= kMergedSets && !p.by_rows;
-        if (!a.fuse_combine) {
+        if (last_merges) {
+            a.flags = nullptr;
+            a.zero = (uint32_t*)(ws + p.off_hist);
+            a.zero_words = std::max<uint64_t>(zero ? zero_words : 0, 2 * n_flags);
+        } else if (!a.fuse_combine) {
             const int64_t n_row_tiles = (int64_t)p.n_layers * p.n_seq * p.h_kv * p.row_tiles;
             e = launch_kernel(jq_combine_kernel, dim3((unsigned)min(n_row_tiles, (int64_t)1 << 20)), dim3(kRowTile * kCombineLanes), 0, st, nullptr, -1, a);
             if (e != hipSuccess) return e;
@@ -1535,6 +1591,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
             const int64_t n = (int64_t)p.n_layers * p.n_seq * p.h_kv * a.RP;
             e = launch_kernel(jq_lse_aug_kernel, dim3((unsigned)min((n + 255) / 256, (int64_t)2048)), dim3(256), 0, st, nullptr, -1, a, n);
             if (e != hipSuccess) return e;
+            a.zero = nullptr;  // done by that launch
         }
         const dim3 grid((unsigned)((int64_t)p.n_layers * a.layer_quads * p.h_kv));
         if (diff_part) return launch_kernel(jq_score_rows_kernel<false, true>, grid, block, 0, st, nullptr, -1, a);

@@ -54,3 +54,47 @@ def test_many_query_rows_match_the_oracle(n_layers, seq_lens, n_q, h_q, h_kv, fo
                 assert not seg[:, L - n_q:].any()
                 seg, ref = seg[:, :L - n_q], ref[:, :L - n_q]
             assert_scores_close(seg, ref, n_q * G / L, "layer %d seq %d" % (layer, s))
+
+
+@pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv", [
+    (1, [16384], 64, 32, 8),                 # two groups of rows, eight sets each
+    (3, [1000, 127, 1, 2049], 40, 8, 2),     # 160 rows: the last group is partial; workgroups with several sequences
+    (40, [130], 33, 4, 1),                   # a set per sequence and group: every workgroup is the last
+])
+def test_replays_of_captured_scores_merge_their_own_statistics(n_layers, seq_lens, n_q, h_q, h_kv):
+    # The workgroup that completes the sets of statistics merges them, by flags that have the same value in every replay: left over
+    # from the one before, they would have it merge sets of the keys that the buffers held before.
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("captured scores", n_layers, seq_lens, n_q, h_q, h_kv, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+
+    def new(*size):
+        return torch.randn(size, generator=gen, device="cuda").bfloat16()
+    T, n = sum(seq_lens), len(seq_lens)
+    common = dict(n_layers=n_layers, seq_lens=seq_lens, h_q=h_q, h_kv=h_kv, pool_k=1)
+    sh, few = jq.Shape(n_q=n_q, budgets=[max(1, L // 4) for L in seq_lens], **common), jq.Shape(n_q=8, **common)
+    Q, Qf, K = new(n_layers, n, n_q, h_q, 128), new(n_layers, n, 8, h_q, 128), new(n_layers, T, h_kv, 128)
+
+    def run():
+        return (jq.score(sh, Q, K), jq.evict(sh, Q, K, K)[3], jq.map_mse_fused(few, Qf, Q, K))
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = run()
+    for i in range(4):
+        Q.copy_(new(n_layers, n, n_q, h_q, 128) * (1.0 + i))
+        K.copy_(new(n_layers, T, h_kv, 128))
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(got, run()):
+            assert torch.equal(a, b), i
+        assert torch.equal(got[0], got[1])
+        torch.cuda.synchronize()
+        at = 0
+        for L in seq_lens:  # every row's probabilities add up to one
+            total = got[0][:, :, at:at + L].double().sum(-1)
+            assert torch.allclose(total, torch.full_like(total, n_q * h_q / h_kv), rtol=1e-5)
+            at += L
