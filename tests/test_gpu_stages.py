@@ -587,3 +587,26 @@ def test_evict_inplace_on_a_long_sequence_takes_the_streaming_selection():
     assert torch.equal(idx, idx2)
     assert torch.equal(Ki[:, :B].view(torch.int16), Ko.view(torch.int16)) and torch.equal(Vi[:, :B].view(torch.int16), Vo.view(torch.int16))
     assert torch.equal(Ki[:, B:].view(torch.int16), Kd[:, B:].view(torch.int16))
+
+
+@pytest.mark.parametrize("kind", ["distinct", "whole_bin", "low_bits", "ties", "low_bits_and_ties"])
+def test_long_selection_at_every_depth_of_its_descent(kind):
+    # 11 + 11 + 10 bits: the last level runs only where the bin of 22 bits that holds the last place is not kept whole
+    L, B = 40000, 1500
+    rng = np.random.default_rng(31)
+    x = rng.random(L).astype(np.float32) * 0.5 + 0.001
+    top = rng.permutation(L)[:B + 700]
+    bits = np.float32(0.75).view(np.uint32)
+    if kind == "whole_bin":      # the last place's bin has 200 values that differ in their low bits, all of them kept
+        x[top[:B - 200]] = 0.9 + 0.05 * rng.random(B - 200).astype(np.float32)
+        x[top[B - 200:B]] = (bits + rng.permutation(1024)[:200].astype(np.uint32)).view(np.float32)
+    elif kind == "low_bits":     # 1024 values of one such bin, 400 of them kept
+        x[top[:B - 400]] = 0.9 + 0.05 * rng.random(B - 400).astype(np.float32)
+        x[top[B - 400:B - 400 + 1024]] = (bits + rng.permutation(1024).astype(np.uint32)).view(np.float32)
+    elif kind == "ties":         # 900 equal values, 300 of them kept: those at the lowest positions
+        x[top[:B - 300]] = 0.9 + 0.05 * rng.random(B - 300).astype(np.float32)
+        x[top[B - 300:B + 600]] = 0.75
+    elif kind == "low_bits_and_ties":
+        x[top[:B - 300]] = 0.9 + 0.05 * rng.random(B - 300).astype(np.float32)
+        x[top[B - 300:B + 600]] = (bits + rng.integers(0, 6, 900).astype(np.uint32)).view(np.float32)
+    run_select_case(np.stack([x, x[::-1]])[None].copy(), [L], [B])
