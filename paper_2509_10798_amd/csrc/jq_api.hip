@@ -137,20 +137,8 @@ int make_plan(const jq_shape* sh, bool need_budgets, Plan* out, bool sweeps = tr
         p.cu_seg[s + 1] = p.cu_seg[s] + (int32_t)((L + kSegLen - 1) / kSegLen);
     }
     p.n_seg = p.cu_seg[sh->n_seq];
-    // Entries a segment keeps: eight times what a block of kSegLen scores contributes to the kept set on average
-    // (densest sequence of the call), as a power of two in 128..kSegLen; blocks that hold more are re-read from
-    // the scores by the selection.
-    {
-        double dens = 0.0;  // kept positions per score
-        for (int s = 0; s < sh->n_seq; ++s) {
-            const double L = sh->cu_seqlens[s + 1] - sh->cu_seqlens[s];
-            const double B = p.tab.cu_bud[s + 1] - p.tab.cu_bud[s];
-            if (B / L > dens) dens = B / L;
-        }
-        int head = 128;
-        while (head < kSegLen && head < 8.0 * dens * kSegLen) head *= 2;
-        p.seg_head = head;
-    }
+    p.seg_head = 0;
+    for (int s = 0; s < sh->n_seq; ++s) p.seg_head = std::max(p.seg_head, seg_head_of(p.tab.cu_bud[s + 1] - p.tab.cu_bud[s], sh->cu_seqlens[s + 1] - sh->cu_seqlens[s]));
 
     const size_t RP = (size_t)p.row_tiles * kRowTile;
     size_t off = 0;

@@ -56,13 +56,21 @@ struct Plan {
     // pooling workgroups ("segments") per layer and head: ceil(L_s / kSegLen) per sequence, never across sequences
     int32_t n_seg;
     int32_t cu_seg[JQ_MAX_SEQ + 1];
-    int32_t seg_head;  // entries kept per segment: several times the average kept positions per kSegLen scores
+    int32_t seg_head;  // room per segment in the selection's lists: the most entries that a sequence's segments keep (seg_head_of)
     PageMap page_map() const { return PageMap{block_table, page_shift, n_pages, max_pages}; }
     PageMap out_map;      // where the pruned cache goes (block_table null: dense [n_layers][TB] rows)
     void* const* marks;   // host only: nullptr, or 2 * kTraceKernels events (start, stop) for jq_evict_traced
     // workspace layout (byte offsets, 256-aligned)
     size_t off_stats, off_flags, off_aug, off_hist, off_scores, off_pooled, off_idx, off_seg, off_seghdr, ws_bytes;
 };
+
+// Entries that a segment of the selection's lists keeps: eight times what a block of kSegLen scores contributes to its sequence's
+// kept set on average, as a power of two in 128..kSegLen; blocks that hold more are re-read from the scores by the selection.
+__host__ __device__ inline int32_t seg_head_of(int32_t B, int32_t L) {
+    int32_t head = 128;
+    while (head < kSegLen && (int64_t)head * L < (int64_t)8 * kSegLen * B) head *= 2;
+    return head;
+}
 
 // Order-preserving map from fp32 to uint32 (larger float <=> larger key); -0 is folded onto +0.
 __device__ inline uint32_t sortable_key(float x) {

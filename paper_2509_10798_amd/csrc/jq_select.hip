@@ -529,8 +529,8 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n_seg = a.one_L ? a.n_seg : a.cu_seg[p.s + 1] - a.cu_seg[p.s];
     const int64_t seg0 = ((int64_t)p.layer * a.h_kv + p.g) * a.n_seg + (a.one_L ? 0 : a.cu_seg[p.s]);
-    const int head = a.head;
-    const uint2* segs = a.seg + seg0 * head;
+    const int head = a.one_L ? a.head : seg_head_of(a.tab.cu_bud[p.s + 1] - a.tab.cu_bud[p.s], p.L);  // as the pooling kernel has it
+    const uint2* segs = a.seg + seg0 * a.head;
     const uint4* seg_hdr = a.seg_hdr + seg0;
 
     // Requested first: this thread's four level-1 bins, the header of "its" segment (thread t looks after segment
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     uint4 ent[kSegBatch];  // entries 2 * lane and 2 * lane + 1 of the wave's i-th segment: (key, position) twice
 #pragma unroll
     for (int i = 0; i < kSegBatch; ++i) {
-        const uint2* sp = segs + (int64_t)min(wave + i * kFinWaves, n_seg - 1) * head;
+        const uint2* sp = segs + (int64_t)min(wave + i * kFinWaves, n_seg - 1) * a.head;
         ent[i] = ((const uint4*)sp)[lane];  // one 16-byte load per lane covers the segment's first 128 entries
     }
     for (int w = 4 * threadIdx.x; w < 2 * words_cap; w += 4 * kFinThreads) *(uint4*)&keep[w] = make_uint4(0u, 0u, 0u, 0u);  // keep, ties
@@ -617,7 +617,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
         // chunks of 64 entries while the previous chunk's last entry still qualified
         bool last_in = true;
         for (; off < n && last_in; off += 64) {
-            const uint2 e = segs[(int64_t)sg * head + min(off + lane, head - 1)];
+            const uint2 e = segs[(int64_t)sg * a.head + min(off + lane, head - 1)];
             const bool ge = off + lane < n && (e.x >> 21) >= b1;
             if (ge) put(e.x, e.y);
             last_in = (__ballot(ge) >> 63) != 0;

@@ -610,3 +610,13 @@ def test_long_selection_at_every_depth_of_its_descent(kind):
         x[top[:B - 300]] = 0.9 + 0.05 * rng.random(B - 300).astype(np.float32)
         x[top[B - 300:B + 600]] = (bits + rng.integers(0, 6, 900).astype(np.uint32)).view(np.float32)
     run_select_case(np.stack([x, x[::-1]])[None].copy(), [L], [B])
+
+
+def test_lists_of_sequences_of_very_different_density():
+    # the lists of the long selection keep as many of a block's largest values as each sequence's own density asks for: an eighth of
+    # the short sequence kept (1024 of a block), a hundredth of the long one (128), and a dense one whose blocks overflow their lists
+    rng = np.random.default_rng(33)
+    seq_lens, budgets = [40000, 2050, 1, 9000], [400, 256, 1, 60]
+    x = rng.random((2, 2, sum(seq_lens))).astype(np.float32)
+    x[:, :, 40000 + 2051:40000 + 2051 + 1024] += 1.0   # all kept positions of the last sequence in one of its blocks
+    run_select_case(x, seq_lens, budgets)
