@@ -508,7 +508,7 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
 // ------------------------------------------------------------------------------------------------
 constexpr int kFinThreads = 512;
 constexpr int kFinWaves = kFinThreads / 64;
-constexpr int kSegBatch = 16;  // segments whose first 64 entries a wave requests before it knows the threshold bin
+constexpr int kSegBatch = 16;  // segments whose first entries a wave requests before it knows the threshold bin
 
 __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectArgs a, int words_cap, int qual_cap) {
     argument_lines<5>();
@@ -535,19 +535,26 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
 
     // Requested first: this thread's four level-1 bins, the header of "its" segment (thread t looks after segment
     // t), and the first entries of the wave's first segments; all of that arrives while the
-    // threshold bin is being picked (128 entries of each, two per lane in one 16-byte load: the CU's load path is
-    // what bounds this phase, and it counts instructions).  The entry loads are unconditional, from clamped and therefore always valid
+    // threshold bin is being picked (the CU's load path is what bounds this phase, and it counts instructions and bytes: a load covers
+    // 64 entries of two segments, two per lane; where a block keeps more than 16 positions on average -- `dense` -- the next 64
+    // are requested as well.  128 entries of one segment per load, whatever the density: list complete 11.3 us after entry on the 128K
+    // layer, 6.3 so, the call 110.5 -> 106.4; 65536 tokens 65.3 -> 62.7, 100000 with 3072 kept 93.9 -> 92.9).  The entry loads are unconditional, from clamped and therefore always valid
     // addresses -- a segment's storage holds `head` entries whatever its element count -- so that all of them are in
     // flight together; what lies outside is masked afterwards.
     uint32_t c1[kHistBins / kFinThreads];
 #pragma unroll
     for (int e = 0; e < kHistBins / kFinThreads; ++e) c1[e] = p.hist[kHistBins - 1 - ((kHistBins / kFinThreads) * (int)threadIdx.x + e)];
     const uint4 my_hdr = seg_hdr[min((int)threadIdx.x, n_seg - 1)];
-    uint4 ent[kSegBatch];  // entries 2 * lane and 2 * lane + 1 of the wave's i-th segment: (key, position) twice
+    constexpr int kPairs = kSegBatch / 2;
+    const bool dense = head > 128;  // uniform
+    const int half = lane >> 5, l32 = lane & 31;
+    auto seg_of = [&](int i) __attribute__((always_inline)) { return wave + (2 * i + half) * kFinWaves; };  // the lane's segment of the i-th pair
+    uint4 ent[kPairs], ent2[kPairs];  // its entries 2 * l32 and 2 * l32 + 1, and 64 further on: (key, position) twice
 #pragma unroll
-    for (int i = 0; i < kSegBatch; ++i) {
-        const uint2* sp = segs + (int64_t)min(wave + i * kFinWaves, n_seg - 1) * a.head;
-        ent[i] = ((const uint4*)sp)[lane];  // one 16-byte load per lane covers the segment's first 128 entries
+    for (int i = 0; i < kPairs; ++i) ent[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[l32];
+    if (dense) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) ent2[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[32 + l32];
     }
     for (int w = 4 * threadIdx.x; w < 2 * words_cap; w += 4 * kFinThreads) *(uint4*)&keep[w] = make_uint4(0u, 0u, 0u, 0u);  // keep, ties
     for (int b = 4 * threadIdx.x; b < 3072 + 96; b += 4 * kFinThreads) *(uint4*)&bins2[b] = make_uint4(0u, 0u, 0u, 0u);  // histograms, tmp, res, cnt
@@ -581,33 +588,38 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
             if ((key >> 21) >= b1) f(key, (uint32_t)j);
         }
     };
-    const int my_n = seg_n[min(wave + (lane & (kSegBatch - 1)) * kFinWaves, n_seg - 1)];  // lane i < 16: the wave's i-th segment
-    uint64_t ge_even[kSegBatch], ge_odd[kSegBatch];  // wave-uniform: lanes whose even / odd entry of the i-th segment qualifies
-    uint32_t n_mine = 0, again = 0;                  // again, bit i: the 128th entry of the i-th segment still qualified
+    const int my_seg = wave + (lane & (kSegBatch - 1)) * kFinWaves, my_n = my_seg < n_seg ? seg_n[my_seg] : 0;  // lane i < 16: the wave's i-th segment
+    uint32_t again = 0;  // bit i: the last entry looked at of the i-th segment still qualified
+    auto list_entries = [&](const uint4 (&e)[kPairs], int first, bool last) __attribute__((always_inline)) {
+        uint64_t ge_even[kPairs], ge_odd[kPairs];  // wave-uniform: lanes whose even / odd entry qualifies
+        uint32_t n_mine = 0;
 #pragma unroll
-    for (int i = 0; i < kSegBatch; ++i) {
-        const int n = wave + i * kFinWaves < n_seg ? __builtin_amdgcn_readlane(my_n, i) : 0;  // -1: not from its entries
-        ge_even[i] = __ballot(2 * lane < n && (ent[i].x >> 21) >= b1);
-        ge_odd[i] = __ballot(2 * lane + 1 < n && (ent[i].z >> 21) >= b1);
-        n_mine += (uint32_t)(__popcll(ge_even[i]) + __popcll(ge_odd[i]));
-        again |= (uint32_t)(ge_odd[i] >> 63) << i;
-    }
-    if (n_mine) {  // wave-uniform
-        uint32_t to = 0;
-        if (lane == 0) to = atomicAdd(&cnt[0], n_mine);
-        to = __builtin_amdgcn_readfirstlane(to);
-#pragma unroll
-        for (int i = 0; i < kSegBatch; ++i) {
-            const uint64_t me = ge_even[i], mo = ge_odd[i];
-            const uint32_t se = to + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
-            if (((me >> lane) & 1) && se < (uint32_t)qual_cap) qual[se] = make_uint2(ent[i].x, ent[i].y);
-            to += (uint32_t)__popcll(me);
-            const uint32_t so = to + __builtin_amdgcn_mbcnt_hi((uint32_t)(mo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mo, 0u));
-            if (((mo >> lane) & 1) && so < (uint32_t)qual_cap) qual[so] = make_uint2(ent[i].z, ent[i].w);
-            to += (uint32_t)__popcll(mo);
+        for (int i = 0; i < kPairs; ++i) {
+            const int na = __builtin_amdgcn_readlane(my_n, 2 * i), nb = __builtin_amdgcn_readlane(my_n, 2 * i + 1), n = half ? nb : na;  // -1: not from its entries
+            ge_even[i] = __ballot(first + 2 * l32 < n && (e[i].x >> 21) >= b1);
+            ge_odd[i] = __ballot(first + 2 * l32 + 1 < n && (e[i].z >> 21) >= b1);
+            n_mine += (uint32_t)(__popcll(ge_even[i]) + __popcll(ge_odd[i]));
+            if (last) again |= (uint32_t)((ge_odd[i] >> 31) & 1) << (2 * i) | (uint32_t)(ge_odd[i] >> 63) << (2 * i + 1);
         }
-    }
-    // Second visits (a segment whose 128th entry still qualified, a block that is classified from its scores), and
+        if (n_mine) {  // wave-uniform
+            uint32_t to = 0;
+            if (lane == 0) to = atomicAdd(&cnt[0], n_mine);
+            to = __builtin_amdgcn_readfirstlane(to);
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) {
+                const uint64_t me = ge_even[i], mo = ge_odd[i];
+                const uint32_t se = to + __builtin_amdgcn_mbcnt_hi((uint32_t)(me >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)me, 0u));
+                if (((me >> lane) & 1) && se < (uint32_t)qual_cap) qual[se] = make_uint2(e[i].x, e[i].y);
+                to += (uint32_t)__popcll(me);
+                const uint32_t so = to + __builtin_amdgcn_mbcnt_hi((uint32_t)(mo >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mo, 0u));
+                if (((mo >> lane) & 1) && so < (uint32_t)qual_cap) qual[so] = make_uint2(e[i].z, e[i].w);
+                to += (uint32_t)__popcll(mo);
+            }
+        }
+    };
+    list_entries(ent, 0, !dense);
+    if (dense) list_entries(ent2, 64, true);
+    // Second visits (a segment whose last entry looked at still qualified, a block that is classified from its scores), and
     // the segments beyond the first batch: rare, so the common case only tests one mask.
     auto visit = [&](int sg, int n, int off) __attribute__((always_inline)) {
         if (n < 0) {
@@ -628,7 +640,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
         const int i = __builtin_ctz(again);
         again &= again - 1;
         const int sg = wave + i * kFinWaves;
-        visit(sg, seg_n[sg], 128);
+        visit(sg, seg_n[sg], dense ? 128 : 64);
     }
     for (int sg = wave + kSegBatch * kFinWaves; sg < n_seg; sg += kFinWaves) visit(sg, seg_n[sg], 0);
     lds_barrier();

@@ -620,3 +620,17 @@ def test_lists_of_sequences_of_very_different_density():
     x = rng.random((2, 2, sum(seq_lens))).astype(np.float32)
     x[:, :, 40000 + 2051:40000 + 2051 + 1024] += 1.0   # all kept positions of the last sequence in one of its blocks
     run_select_case(x, seq_lens, budgets)
+
+
+@pytest.mark.parametrize("B", [600, 1500])  # lists of 128 and of 512 entries per block: the first 64 and the first 128 are read at once
+@pytest.mark.parametrize("in_one", [63, 64, 65, 127, 128, 129, 192, 512])
+def test_blocks_with_more_kept_positions_than_are_read_at_once(B, in_one):
+    rng = np.random.default_rng(35)
+    L = 131073 if in_one in (64, 128) else 40000  # 129 blocks: the last one is beyond a wave's first batch
+    x = (rng.random((1, 2, L)) * 0.5 + 0.01).astype(np.float32)
+    for g in range(2):
+        blocks = rng.permutation(L // 1024)[:3]
+        for b, n in zip(blocks, (in_one, in_one - 1, 5)):
+            x[0, g, b * 1024 + rng.permutation(1024)[:min(n, B // 3)]] += 0.5 + rng.random(min(n, B // 3)).astype(np.float32)
+        x[0, g, L - 1] = 3.0
+    run_select_case(x, [L], [B if L == 40000 else B * 3])
