@@ -896,8 +896,6 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     uint2 aug_direct[NQT];  // the terms of the lane's rows where no merging is due
     if (NORMS == kNormsShared && q_there) {
         fetch_tile(ks.rsrc, slots, off_first, ks.row_bytes, tl, ks.last);
-#pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
     } else {
         const float* nsrc[NQT];  // kNormsLse: the lane's rows' normalisers; kNormsMerged: the terms of a combine launch
 #pragma unroll
@@ -969,6 +967,14 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
         }
 #pragma unroll
         for (int u = 0; u < kFirstParts; ++u) mz[u] = load_pair(pp + min(p0 + 2 * u, n_p - 1) * pstep);
+    }
+    // The query rows out of LDS, half a microsecond of the CU's LDS, while the sets are on their way (in front of the flags: 2048 tokens
+    // 14.81 us a call, 14.58 here; 8192 21.2 / 20.8, 16384 27.1 / 26.7, 32768 39.2 / 39.0).
+    if (NORMS == kNormsShared && q_there) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int qt = 0; qt < NQT; ++qt) lds_get_frags_waited(lds_addr(lds + kLdsQ + qt * kSlotBytes), qf[qt], lane);
+        __builtin_amdgcn_sched_barrier(0);
     }
     float cM = -1.0e30f, cZ = 0.f;
     if (own_set) {
