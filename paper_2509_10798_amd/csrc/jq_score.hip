@@ -199,6 +199,26 @@ __device__ __forceinline__ uint2 lds_get8_waited(uint32_t addr) {
     asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x) : "v"(addr) : "memory");
     return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
 }
+// N of them, `step` bytes apart
+template <int N>
+__device__ __forceinline__ void lds_get8s_waited(uint32_t addr, uint32_t step, uint2 (&v)[N]) {
+    static_assert(N >= 1 && N <= 4, "written out");
+    uint64_t x0, x1, x2, x3;
+    if constexpr (N == 4)
+        asm volatile("ds_read_b64 %0, %4\n\tds_read_b64 %1, %5\n\tds_read_b64 %2, %6\n\tds_read_b64 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(addr), "v"(addr + step), "v"(addr + 2 * step), "v"(addr + 3 * step) : "memory");
+    else if constexpr (N == 3)
+        asm volatile("ds_read_b64 %0, %3\n\tds_read_b64 %1, %4\n\tds_read_b64 %2, %5\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x0), "=&v"(x1), "=&v"(x2) : "v"(addr), "v"(addr + step), "v"(addr + 2 * step) : "memory");
+    else if constexpr (N == 2)
+        asm volatile("ds_read_b64 %0, %2\n\tds_read_b64 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x0), "=&v"(x1) : "v"(addr), "v"(addr + step) : "memory");
+    else
+        asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(x0) : "v"(addr) : "memory");
+    v[0] = make_uint2((uint32_t)x0, (uint32_t)(x0 >> 32));
+    if constexpr (N > 1) v[1] = make_uint2((uint32_t)x1, (uint32_t)(x1 >> 32));
+    if constexpr (N > 2) v[2] = make_uint2((uint32_t)x2, (uint32_t)(x2 >> 32));
+    if constexpr (N > 3) v[3] = make_uint2((uint32_t)x3, (uint32_t)(x3 >> 32));
+}
 // lds_get_frags with explicit instructions; returns when the fragments are in registers
 __device__ __forceinline__ void lds_get_frags_waited(uint32_t slot, bf16x8 (&kf)[8], int lane) {
     const uint32_t r = (uint32_t)lane & 31u, hi = (uint32_t)lane >> 5;
@@ -340,10 +360,14 @@ __device__ __forceinline__ int tile_page(const KeyStream& ks, int t) {
     return PAGED ? ((const_i32_ptr)ks.pages)[((uint32_t)t * kKeyTile) >> ks.page_shift] : 0;
 }
 
-// x of the lane and of the one 32 further on (or back)
-__device__ __forceinline__ float add_halves(float x) {
+// x of the lane and of the one 32 further on (or back): of the lower one first
+__device__ __forceinline__ float2 both_halves(float x) {
     const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(y[0]) + __uint_as_float(y[1]);
+    return make_float2(__uint_as_float(y[0]), __uint_as_float(y[1]));
+}
+__device__ __forceinline__ float add_halves(float x) {
+    const float2 y = both_halves(x);
+    return y.x + y.y;
 }
 
 // One stage of the sweeps' software pipeline: `step(i)`, i = 0 .. NM - 1, issues the i-th matrix instruction of the NEXT
@@ -628,23 +652,23 @@ __device__ __forceinline__ void stats_share(KArgs& a, const Share& h, int g, int
     float2* mine = (float2*)slots;  // [NQT * 32] of this wave
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
-        const float mo = __shfl_xor(m[qt], 32), zo = __shfl_xor(z[qt], 32);
-        const float mm = fmaxf(m[qt], mo);
-        const float zz = z[qt] * __builtin_amdgcn_exp2f(m[qt] - mm) + zo * __builtin_amdgcn_exp2f(mo - mm);
+        const float2 mh = both_halves(m[qt]), zh = both_halves(z[qt]);
+        const float mm = fmaxf(mh.x, mh.y);
+        const float zz = zh.x * __builtin_amdgcn_exp2f(mh.x - mm) + zh.y * __builtin_amdgcn_exp2f(mh.y - mm);
         if (half == 0) mine[qt * kRowTile + lane] = make_float2(mm, zz);
     }
     __syncthreads();
     const int row = rg * NQT * kRowTile + (int)threadIdx.x;  // the last group may reach past the head's row tiles
     const int set = h.set0 + h.rank;
     if (threadIdx.x < NQT * kRowTile && row < a.RP) {
+        float2 mz[kScoreWaves];
         float M = -1.0e30f, Z = 0.f;
 #pragma unroll
-        for (int w = 0; w < kScoreWaves; ++w) {
-            const float2 mz = ((const float2*)(lds + w * 2 * kSlotBytes))[threadIdx.x];
-            const float mm = fmaxf(M, mz.x);
-            Z = Z * __builtin_amdgcn_exp2f(M - mm) + mz.y * __builtin_amdgcn_exp2f(mz.x - mm);
-            M = mm;
-        }
+        for (int w = 0; w < kScoreWaves; ++w) mz[w] = ((const float2*)(lds + w * 2 * kSlotBytes))[threadIdx.x];
+#pragma unroll
+        for (int w = 0; w < kScoreWaves; ++w) M = fmaxf(M, mz[w].x);
+#pragma unroll
+        for (int w = 0; w < kScoreWaves; ++w) Z = fmaf(mz[w].y, __builtin_amdgcn_exp2f(mz[w].x - M), Z);
         float2* to = &a.stats[((int64_t)set * a.h_kv + g) * a.RP + row];
         if (SHARED || a.flags) {
             __hip_atomic_store((uint64_t*)to, (uint64_t)__float_as_uint(M) | (uint64_t)__float_as_uint(Z) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1008,8 +1032,10 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
             lds_wait_all();
         }
         bare_barrier();
+        uint2 terms[NQT];
+        lds_get8s_waited(aug_s + 8u * ((uint32_t)lane & 31u), 8u * kRowTile, terms);
 #pragma unroll
-        for (int qt = 0; qt < NQT; ++qt) set_aug(qt, lds_get8_waited(aug_s + 8u * (qt * kRowTile + (lane & 31))));
+        for (int qt = 0; qt < NQT; ++qt) set_aug(qt, terms[qt]);
         if (NORMS != kNormsShared) bare_barrier();  // the slot is refilled with a key tile next
     } else {
 #pragma unroll
