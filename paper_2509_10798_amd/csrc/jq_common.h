@@ -153,6 +153,15 @@ __device__ __forceinline__ void store_stream16(void* p, uint4 v) {
     const jq_u32x4 x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, (jq_u32x4*)p);
 }
+// Sixteen bytes at an address that is a multiple of four only: rows of odd lengths.  One store all the same; four of four bytes each
+// touched every line of the wave's kilobyte four times (see the callers for what that cost).
+typedef float any_f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+template <bool STREAM>
+__device__ __forceinline__ void store16_any(float* p, const float* v) {
+    const any_f32x4 x = {v[0], v[1], v[2], v[3]};
+    if (STREAM) __builtin_nontemporal_store(x, (any_f32x4*)p);
+    else *(any_f32x4*)p = x;
+}
 
 typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr;
 // The first lines of a kernel's arguments, which lie in memory, requested together: read where they are used, they arrive one

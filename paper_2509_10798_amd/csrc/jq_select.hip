@@ -358,14 +358,24 @@ __global__ __launch_bounds__(THREADS) void jq_pool_select_kernel(PoolSelectArgs 
     }
     // This slice's share of the pooled scores, stored non-temporally like the pooling kernel's (see store_stream): as plain
     // stores they were 4 MB of dirty lines at the end of a call over 4 x 32768 tokens, 79.3 us against 78.4, 32 x 8192 251.8
-    // against 246.4, 7 x 28000 + 28000 190.6 against 187.6.  Runs that are not 16-byte aligned go through the caches, which
-    // merge them (8 x 12345: 102.8 us non-temporally, 97.4 so).
+    // against 246.4, 7 x 28000 + 28000 190.6 against 187.6.  Rows that are not 16-byte aligned (odd lengths) get 16-byte stores too,
+    // where four of 4 bytes each had cost 8 x 12345 tokens 89.4 us a call (87.7 through the caches, 86.9 streamed), 12 ragged sequences of
+    // 3001 to 15001 105.2 (103.2, 101.5), 16 x 3001 53.0 (52.7, 51.9); with 32 positions per thread, whose stores lie 128 bytes apart,
+    // the caches are better (8 x 30001 189.2 / 188.3 / 190.3), and so they are for a few problems (5001 tokens 21.8 / 21.7 / 22.0).
     if (pa.out && (uint32_t)tid * gridDim.y / THREADS == blockIdx.y && j0 < L) {  // this slice's share of the pooled scores
         float* o = pa.out + row + j0;
+        const bool streams = VPT <= 16 && gridDim.x > 32;  // uniform
         if (j0 + VPT <= L && (((uintptr_t)o) & 15u) == 0) {
 #pragma unroll
             for (int q = 0; q < VPT; q += 4)  // streamed, as the pooling kernel's
                 store_stream16(o + q, make_uint4(__float_as_uint(v[q]), __float_as_uint(v[q + 1]), __float_as_uint(v[q + 2]), __float_as_uint(v[q + 3])));
+        } else if (j0 + VPT <= L && streams) {
+#pragma unroll
+            for (int q = 0; q < VPT; q += 4) store16_any<true>(o + q, v + q);
+            asm volatile("" ::: "memory");  // or the compiler makes one loop of both, with plain stores
+        } else if (j0 + VPT <= L) {
+#pragma unroll
+            for (int q = 0; q < VPT; q += 4) store16_any<false>(o + q, v + q);
         } else {
 #pragma unroll
             for (int u = 0; u < VPT; ++u)
