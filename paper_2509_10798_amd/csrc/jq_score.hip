@@ -11,8 +11,8 @@
 //   pass 2 (score):  score_j = sum_r 2^(c * (q_r.k_j - beta_r / c)).  The -beta_r/c term enters
 //                    through one extra MFMA step whose key-side operand is 1.0, so the epilogue is one
 //                    multiply, one exp2 and one add per logit.
-// With more than 128 query rows per KV head pass 1 takes a grid slice per 128 rows, the merge is a kernel of its own, and
-// pass 2 turns around: jq_score_rows_kernel keeps 128 keys in registers and streams the query rows past them, so that a
+// With more than 128 query rows per KV head pass 1 takes a grid slice per 128 rows, the merge is done by the workgroup that completes
+// a (layer, sequence), head and group of rows, and pass 2 turns around: jq_score_rows_kernel keeps 128 keys in registers and streams the query rows past them, so that a
 // key's score is complete in one launch whatever the number of rows.
 // Variants of the same kernels: supplied normalisers (pass 2 alone), the soft tokens' own keys or the prompt's
 // own last tokens as causally masked tiles of pass 1, keys read out of a paged pool.
@@ -1172,8 +1172,8 @@ template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  //
 // launch per pass that saves the boundary between two dependent kernels (2.2 us), the second request for the query rows
 // (they wait in LDS) and, where one workgroup has a whole (layer, sequence), the way of the statistics through memory; and no
 // workgroup waits for any other sequence's.  Device timestamps, 32768 tokens, 8 heads, from a workgroup's last tile of the
-// first pass to its first of the second: set stored 0.8 us, flag 0.4, share and query rows 1.5, all flags seen 0.5,
-// sets read and merged 1.2, terms exchanged 0.4.  Whole calls, two launches / one: 2048 tokens and 2 heads 18.7 / 17.0 us, 32768 tokens
+// first pass to its first of the second: waves' statistics merged 0.45 us, set and flag out 0.3, share 0.8, all flags seen 0.4-0.6,
+// query rows and sets read and merged 1.25, terms exchanged 0.3.  Whole calls, two launches / one: 2048 tokens and 2 heads 18.7 / 17.0 us, 32768 tokens
 // 48.3 / 44.8, 128K layer 114.7 / 113.0, 32 layers of 8192 246 / 240, 8 x 12345 with window queries 97.3 / 92.8; together with the
 // even shares a paged batch of 8 196 / 187, 16 ragged sequences 821 / 779.
 // No workgroup depends on another one running: it waits for `wait_ticks` (or the time it has run itself, if that is longer), once,
@@ -1237,8 +1237,8 @@ template __global__ void jq_passes_kernel<4, false, false>(ScoreArgs);
 // order and stored once.  Before, every 128 rows took a launch of each pass that read K and added to the scores in
 // memory: launches of 64..256 keys per wave that were mostly start-up.  The work is a contraction that K does not
 // bound (every key is used by all rows): 9 MFMA per 32 x 32 logits against 16 exp2/mul/add per lane.  Measured at 16384
-// keys x 8 heads x 1024 rows: eight launches of 12.4 us and eight first passes of 10.9 us before, 37 + 37 us + 5 us for
-// the combine launch now (1.05 PFLOP/s; a plain library product of 8192^3 reaches 1.2 on this card, which lowers its
+// keys x 8 heads x 1024 rows: eight launches of 12.4 us and eight first passes of 10.9 us before, 39 + 38 us
+// now (1.05 PFLOP/s; a plain library product of 8192^3 reaches 1.2 on this card, which lowers its
 // clock under matrix work).  Two waves per key group instead of four: 42.9 against 41.5 us there, 5 % better only with
 // thousands of workgroups: not kept.
 // -beta/c comes from `aug`, which the first pass's last workgroups (or jq_combine_kernel, jq_lse_aug_kernel) have filled.
