@@ -545,8 +545,8 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     // Requested first: this thread's four level-1 bins, the header of "its" segment (thread t looks after segment
     // t), and the first entries of the wave's first segments; all of that arrives while the
     // threshold bin is being picked (the CU's load path is what bounds this phase, and it counts instructions and bytes: a load covers
-    // 64 entries of two segments, two per lane; where a block keeps more than 16 positions on average -- `dense` -- the next 64
-    // are requested as well.  128 entries of one segment per load, whatever the density: list complete 11.3 us after entry on the 128K
+    // 64 entries of two segments, two per lane; where a block keeps more than 32 positions on average -- `dense` -- the next 64
+    // are requested as well (from 16 on: 65536 tokens with 2048 kept 68.3 us a call, 67.3 so, 50000 with 1536 56.7 / 55.7).  128 entries of one segment per load, whatever the density: list complete 11.3 us after entry on the 128K
     // layer, 6.3 so, the call 110.5 -> 106.4; 65536 tokens 65.3 -> 62.7, 100000 with 3072 kept 93.9 -> 92.9).  The entry loads are unconditional, from clamped and therefore always valid
     // addresses -- a segment's storage holds `head` entries whatever its element count -- so that all of them are in
     // flight together; what lies outside is masked afterwards.
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     counts_down<kHistBins / kFinThreads>(p.hist, kHistBins, c1);
     const uint4 my_hdr = seg_hdr[min((int)threadIdx.x, n_seg - 1)];
     constexpr int kPairs = kSegBatch / 2;
-    const bool dense = head > 128;  // uniform
+    const bool dense = head > 256;  // uniform
     const int half = lane >> 5, l32 = lane & 31;
     auto seg_of = [&](int i) __attribute__((always_inline)) { return wave + (2 * i + half) * kFinWaves; };  // the lane's segment of the i-th pair
     uint4 ent[kPairs], ent2[kPairs];  // its entries 2 * l32 and 2 * l32 + 1, and 64 further on: (key, position) twice

@@ -622,7 +622,7 @@ def test_lists_of_sequences_of_very_different_density():
     run_select_case(x, seq_lens, budgets)
 
 
-@pytest.mark.parametrize("B", [600, 1500])  # lists of 128 and of 512 entries per block: the first 64 and the first 128 are read at once
+@pytest.mark.parametrize("B", [600, 1000, 1500])  # lists of 128, 256 and 512 entries per block: the first 64, 64 and 128 are read at once
 @pytest.mark.parametrize("in_one", [63, 64, 65, 127, 128, 129, 192, 512])
 def test_blocks_with_more_kept_positions_than_are_read_at_once(B, in_one):
     rng = np.random.default_rng(35)
