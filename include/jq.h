@@ -374,7 +374,8 @@ int jq_copy_probe(const void* src, void* dst, size_t bytes, void* stream);
  * call (never on the path of a later call): JQ_CHUNK_KEYS / JQ_CHUNK_KEYS_2 (keys per wave in the first / second
  * pass over K, multiples of 32 up to 8192), JQ_WAIT_US (how long a workgroup that does both passes waits for the statistics
  * of others before it forms those that are missing itself: once, 0..1000000 microseconds, 20 by default, and at least as long as
- * its own first pass took unless it is 0), JQ_LOG (print the HIP error string when a launch is refused).  Results do
+ * its own first pass took unless it is 0), JQ_HOLD_BYTES (bytes of K, 0 or more, from which on the second pass keeps its scores in LDS and
+ * writes them together), JQ_LOG (print the HIP error string when a launch is refused).  Results do
  * not depend on them beyond rounding order.  jq_reload_knobs reads the environment again; it must not run
  * concurrently with other calls (tests use it to force rarely taken code paths at small sizes).  Always returns JQ_OK. */
 int jq_reload_knobs(void);

@@ -459,7 +459,7 @@ def map_mse_fused(shape: Shape, Q_a, Q_b, K, mse=None, ws=None, stream=None):
 
 
 def reload_knobs() -> None:
-    """Make the library read its ablation knobs (JQ_CHUNK_KEYS, JQ_CHUNK_KEYS_2, JQ_LOG) from the environment again."""
+    """Make the library read its ablation knobs (JQ_CHUNK_KEYS, JQ_CHUNK_KEYS_2, JQ_WAIT_US, JQ_HOLD_BYTES, JQ_LOG) from the environment again."""
     _check(lib().jq_reload_knobs(), "jq_reload_knobs")
 
 

@@ -22,6 +22,8 @@ static Knobs read_knobs() {
     if (!std::getenv("JQ_CHUNK_KEYS_2")) k.chunk_keys2 = k.chunk_keys;
     const char* wait = std::getenv("JQ_WAIT_US");
     k.wait_us = wait ? (int32_t)std::min(std::max(std::atol(wait), 0l), 1000000l) : 20;
+    const char* hold = std::getenv("JQ_HOLD_BYTES");
+    k.hold_bytes = hold ? (int64_t)std::max(std::atoll(hold), -1ll) : -1;
     k.log = std::getenv("JQ_LOG") != nullptr;
     return k;
 }

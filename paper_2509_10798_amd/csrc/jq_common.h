@@ -132,6 +132,7 @@ struct Knobs {
     int32_t chunk_keys;   // JQ_CHUNK_KEYS: keys per wave in the pass that reads K cold, in whole workgroups per sequence (0: planned)
     int32_t chunk_keys2;  // JQ_CHUNK_KEYS_2: the same for the second pass (0: JQ_CHUNK_KEYS if set, else planned)
     int32_t wait_us;      // JQ_WAIT_US: how long a workgroup waits, once, for others' statistics before it forms them itself (microseconds)
+    int64_t hold_bytes;   // JQ_HOLD_BYTES: bytes of K from which on the second pass holds its scores back (-1: as measured, see launch_score)
     int32_t log;          // JQ_LOG: print the HIP error string when a launch is refused
 };
 const Knobs& knobs();

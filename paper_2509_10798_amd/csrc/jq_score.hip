@@ -1570,7 +1570,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     //   two: 131072 110.2 / 110.9, 28 x 8192 219.6 / 221.1, 4 x 50000 164.7 / 165.4, 250000 205.2 / 203.3, 4 x 60000 paged 209 / 206, 32 x 8192
     //     236.7 / 233.6, 8 x 65536 416 / 402, 16 ragged sequences of 981293 together 780 / 753.
     const int64_t k_bytes = (int64_t)p.n_layers * p.T * p.h_kv * kHeadDim * 2;
-    const bool holds = k_bytes >= (lse ? (int64_t)110000000 : (int64_t)480000000);
+    const bool holds = k_bytes >= (knobs().hold_bytes >= 0 ? knobs().hold_bytes : lse ? (int64_t)110000000 : (int64_t)480000000);
     const dim3 block(kScoreWaves * 64);
     const unsigned wgs = (unsigned)(p.split.n_wg * p.h_kv);
     hipError_t e;

@@ -55,3 +55,64 @@ def test_held_back_scores_equal_those_stored_at_once(knobs, h_q, h_kv, n_q, wind
             torch.cuda.synchronize()
             assert torch.equal(got[layer, :, at:at + L], one[0]), (layer, s)
         at += L
+
+
+def _paged(torch, K, seq_lens, page):
+    """The same keys in a pool whose pages lie in reverse order, and its block table."""
+    n_layers, _, h_kv, d = K.shape
+    per = [-(-L // page) for L in seq_lens]
+    n = sum(per)
+    table = torch.full((len(seq_lens), max(per)), -1, dtype=torch.int32)
+    pool = torch.zeros((n_layers, n, page, h_kv, d), dtype=K.dtype, device=K.device)
+    at, left = 0, n
+    for s, L in enumerate(seq_lens):
+        for j in range(per[s]):
+            left -= 1
+            table[s, j] = left
+            rows = min(page, L - j * page)
+            pool[:, left, :rows] = K[:, at + j * page:at + j * page + rows]
+        at += L
+    return jq.Pages(page, n, table.cuda()), pool
+
+
+@pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv", [
+    (1, [129], 8, 8, 8),                       # a tile of query rows; a wave has one tile of keys or none
+    (1, [4099], 16, 8, 2),                     # two
+    (3, [1000, 127, 45, 128, 2049], 24, 8, 2),  # three; portions that end inside sequences
+    (5, [9999], 32, 12, 4),                    # three; layers that do not divide the workgroups
+    (40, [300], 32, 8, 2),                     # four; more layers than workgroups per head: several shares a workgroup
+    (9, [300, 33, 129] * 12, 32, 32, 8),       # four; many short sequences, two workgroups per CU in two launches
+    (1, [40000], 32, 32, 8),                   # a workgroup per CU
+])
+@pytest.mark.parametrize("form", ["dense", "paged", "window"])
+@pytest.mark.parametrize("wait_us", [None, 0])
+def test_passes_that_form_their_statistics_hold_the_same_scores_back(knobs, n_layers, seq_lens, n_q, h_q, h_kv, form, wait_us):
+    # both passes in one launch (evict) and one after the other (score), every number of row tiles; without patience a workgroup
+    # finds sets missing, forms them itself and starts the second pass of its share again
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("held back, two passes", n_layers, seq_lens[:4], n_q, h_q, h_kv, form, wait_us, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    Q = torch.randn((n_layers, len(seq_lens), n_q, h_q, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((n_layers, sum(seq_lens), h_kv, 128), generator=gen, device="cuda").bfloat16()
+    sh = jq.Shape(n_layers=n_layers, seq_lens=seq_lens, n_q=n_q, h_q=h_q, h_kv=h_kv, pool_k=1, window=form == "window",
+                  budgets=[max(n_q, L // 8) if form == "window" else max(1, L // 8) for L in seq_lens])
+    if form == "paged":
+        pages, pool = _paged(torch, K, seq_lens, 64)
+
+    def run(hold):
+        knobs(JQ_HOLD_BYTES=str(hold), **({} if wait_us is None else {"JQ_WAIT_US": str(wait_us)}))
+        if form == "paged":
+            two, one = jq.score_paged(sh, pages, Q, pool), jq.evict_paged(sh, pages, Q, pool, pool)
+        else:
+            two, one = jq.score(sh, Q, K), jq.evict(sh, Q, K, K)
+        torch.cuda.synchronize()
+        return two, one[3], one[2]
+    at_once = run(1 << 60)
+    held = run(0)
+    for name, a, b in zip(("two launches", "one launch", "positions"), held, at_once):
+        assert torch.equal(a, b), name
+    assert torch.equal(held[0], held[1])
+    total = held[0].double().cpu()
+    assert torch.isfinite(total).all() and float(total.sum()) > 0
