@@ -560,10 +560,11 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     uint4 ent[kPairs], ent2[kPairs];  // its entries 2 * l32 and 2 * l32 + 1, and 64 further on: (key, position) twice
 #pragma unroll
     for (int i = 0; i < kPairs; ++i) ent[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[l32];
-    if (dense) {
+    auto next_entries = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) ent2[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[32 + l32];
-    }
+    };
+    if (dense) next_entries();
     for (int w = 4 * threadIdx.x; w < 2 * words_cap; w += 4 * kFinThreads) *(uint4*)&keep[w] = make_uint4(0u, 0u, 0u, 0u);  // keep, ties
     for (int b = 4 * threadIdx.x; b < 3072 + 96; b += 4 * kFinThreads) *(uint4*)&bins2[b] = make_uint4(0u, 0u, 0u, 0u);  // histograms, tmp, res, cnt
     lds_barrier();
@@ -598,7 +599,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     };
     const int my_seg = wave + (lane & (kSegBatch - 1)) * kFinWaves, my_n = my_seg < n_seg ? seg_n[my_seg] : 0;  // lane i < 16: the wave's i-th segment
     uint32_t again = 0;  // bit i: the last entry looked at of the i-th segment still qualified
-    auto list_entries = [&](const uint4 (&e)[kPairs], int first, bool last) __attribute__((always_inline)) {
+    auto list_entries = [&](const uint4 (&e)[kPairs], int first) __attribute__((always_inline)) {
         uint64_t ge_even[kPairs], ge_odd[kPairs];  // wave-uniform: lanes whose even / odd entry qualifies
         uint32_t n_mine = 0;
 #pragma unroll
@@ -607,7 +608,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
             ge_even[i] = __ballot(first + 2 * l32 < n && (e[i].x >> 21) >= b1);
             ge_odd[i] = __ballot(first + 2 * l32 + 1 < n && (e[i].z >> 21) >= b1);
             n_mine += (uint32_t)(__popcll(ge_even[i]) + __popcll(ge_odd[i]));
-            if (last) again |= (uint32_t)((ge_odd[i] >> 31) & 1) << (2 * i) | (uint32_t)(ge_odd[i] >> 63) << (2 * i + 1);
+            again |= (uint32_t)((ge_odd[i] >> 31) & 1) << (2 * i) | (uint32_t)(ge_odd[i] >> 63) << (2 * i + 1);
         }
         if (n_mine) {  // wave-uniform
             uint32_t to = 0;
@@ -625,14 +626,47 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
             }
         }
     };
-    list_entries(ent, 0, !dense);
-    if (dense) list_entries(ent2, 64, true);
+    // Where the last of the 64 still qualified in any of the wave's segments, the next 64 of all of them are read together: one round
+    // trip, where one after the other 2048 kept of 131072 flat scores (threshold bins that reach far down) lost the call 2.5 us against
+    // 128 entries read at once (107.1 / 109.8; 106.7 so), blocks with 64 to 100 kept each 0.5 to 2.
+    list_entries(ent, 0);
+    if (dense || again) {  // wave-uniform
+        if (!dense) next_entries();
+        again = 0;
+        list_entries(ent2, 64);
+    }
     // Second visits (a segment whose last entry looked at still qualified, a block that is classified from its scores), and
     // the segments beyond the first batch: rare, so the common case only tests one mask.
-    auto visit = [&](int sg, int n, int off) __attribute__((always_inline)) {
-        if (n < 0) {
-            scan_block(sg, put);
-            return;
+    again |= (uint32_t)__ballot(lane < kSegBatch && wave + lane * kFinWaves < n_seg && my_n < 0);
+    for (int beyond = wave + kSegBatch * kFinWaves;;) {  // wave-uniform
+        int sg, off;
+        if (again) {
+            sg = wave + __builtin_ctz(again) * kFinWaves;
+            off = 128;
+            again &= again - 1;
+        } else {
+            if (beyond >= n_seg) break;
+            sg = beyond;
+            off = 0;
+            beyond += kFinWaves;
+        }
+        const int n = seg_n[sg];
+        if (n < 0) {  // four requests at a time: one after the other they were 16 memory latencies a block (16 blocks with 128 kept each
+                      // out of 131072: 150.4 us a call, 118.0 so; written out at every call of scan_block it is 3 KB more code than
+                      // the instruction cache has room for, and calls that never come here lose 1 us)
+            const int j0 = sg * kSegLen + lane, j1 = min(p.L, (sg + 1) * kSegLen);
+            for (int j = j0; j < j1; j += 4 * 64) {
+                float x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = p.x[min(j + 64 * u, j1 - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int at = j + 64 * u;
+                    const uint32_t key = select_key(x[u], at, p.L, a.keep_first, a.keep_last);
+                    if (at < j1 && (key >> 21) >= b1) put(key, (uint32_t)at);
+                }
+            }
+            continue;
         }
         // chunks of 64 entries while the previous chunk's last entry still qualified
         bool last_in = true;
@@ -642,15 +676,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
             if (ge) put(e.x, e.y);
             last_in = (__ballot(ge) >> 63) != 0;
         }
-    };
-    again |= (uint32_t)__ballot(lane < kSegBatch && wave + lane * kFinWaves < n_seg && my_n < 0);
-    while (again) {  // wave-uniform
-        const int i = __builtin_ctz(again);
-        again &= again - 1;
-        const int sg = wave + i * kFinWaves;
-        visit(sg, seg_n[sg], dense ? 128 : 64);
     }
-    for (int sg = wave + kSegBatch * kFinWaves; sg < n_seg; sg += kFinWaves) visit(sg, seg_n[sg], 0);
     lds_barrier();
     const uint32_t n_qual = cnt[0];
     const bool listed = n_qual <= (uint32_t)qual_cap;  // uniform; otherwise every pass re-reads the scores

@@ -634,3 +634,21 @@ def test_blocks_with_more_kept_positions_than_are_read_at_once(B, in_one):
             x[0, g, b * 1024 + rng.permutation(1024)[:min(n, B // 3)]] += 0.5 + rng.random(min(n, B // 3)).astype(np.float32)
         x[0, g, L - 1] = 3.0
     run_select_case(x, [L], [B if L == 40000 else B * 3])
+
+
+@pytest.mark.parametrize("L", [40000, 131073])  # 40 blocks, the last with 64 positions; 129: some are beyond a wave's first batch
+@pytest.mark.parametrize("lo,hi", [(60, 70), (64, 64), (100, 140), (300, 1024)])
+def test_most_blocks_have_more_candidates_than_are_read_at_once(L, lo, hi):
+    # All candidates in the threshold's bin (a quarter octave), so that every one is listed before any is dropped: blocks whose
+    # next entries are read together, blocks that their lists cannot answer for, and both in one wave.
+    rng = np.random.default_rng(lo + L)
+    x = (rng.random((1, 2, L)) * 0.4 + 0.01).astype(np.float32)
+    n = 0
+    for g in range(2):
+        for j in range(0, L, 1024):
+            size = min(1024, L - j)
+            at = j + rng.permutation(size)[:min(size, int(rng.integers(lo, hi + 1)))]
+            x[0, g, at] = 0.76 + 0.1 * rng.random(at.size).astype(np.float32)
+            n += at.size
+    B = min(n // 4, L // 64)  # 16 of a block on average: lists of 128
+    run_select_case(x, [L], [B])
