@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
     lds_barrier();
     // Thread t owns the run of four consecutive positions 4t ..: with the taps unrolled a run reads its 4 + 2r
     // inputs as a few 16-byte LDS loads (lanes 16 B apart: no bank conflict) instead of 2r + 1 loads per output,
-    // and stores one 16-byte vector when the row allows it.
+    // and stores one 16-byte vector where it is complete.
     const int j0 = threadIdx.x * 4;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     if (j0 < cnt) {
@@ -157,10 +157,8 @@ __global__ __launch_bounds__(kPoolThreads) void jq_pool_kernel(PoolArgs a) {
             }
         }
         if (POOL) {
-            if (((row + p0) & 3) == 0 && j0 + 3 < cnt) {
-                store_stream16(&a.out[row + p0 + j0], make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-            } else if (j0 + 3 < cnt) {  // (as four stores: 16 ragged sequences 741.6 us a call, 733.9 so; a paged batch of 8 180.9, 176.4; 60001 tokens 60.6, 60.0)
-                store16_any<true>(&a.out[row + p0 + j0], v);
+            if (j0 + 3 < cnt) {  // at any alignment: a sequence's rows begin where the one before ends, the caller's buffer at a multiple of four bytes
+                store16_any<true>(&a.out[row + p0 + j0], v);  // (as four stores: 16 ragged sequences 741.6 us a call, 733.9 so; a paged batch of 8 180.9, 176.4; 60001 tokens 60.6, 60.0)
             } else {
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
