@@ -304,11 +304,18 @@ constexpr int kLdsSet = kLdsQ + kMaxRowTiles * kSlotBytes;          // the set o
 constexpr int kLdsAug = kLdsSet + kMaxRowTiles * kRowTile * 8;     // the rows' normalisers
 constexpr int kLdsWord = kLdsAug + kMaxRowTiles * kRowTile * 8;
 constexpr int kLdsBoth = kLdsWord + 16;
-// Behind that, where a second pass holds scores back: per wave the scores of `held` tiles, then the tiles' numbers.
+// Where a second pass holds scores back: per wave the scores of kMaxHeld tiles, then the tiles' numbers.  In the kernel of both
+// passes they take the place of the query rows, which are in registers by then, a wave's in the slot that it fills itself: it needs no
+// more LDS than the one that stores at once.  (With room for 119 tiles a wave it filled a CU's 160 KB, nothing of another stream that uses
+// LDS could share a CU with it, and workgroups that so started late had their statistics formed by others: 8 x 65536 tokens beside 64
+// workgroups of 32 KB 534 us a call, 404 stored at once, 422 so; 16 ragged sequences 989, 770, 750.  Alone 119 take up to 1.1 % less.)
+// jq_score_kernel keeps them behind its slots and leaves 64 KB, the tiles of many a matrix product, to others.
 constexpr int kHeldTile = kKeyTile * 4 + 4;
-constexpr int kMaxHeld = 119;  // what one workgroup of jq_passes_kernel has room for in the 160 KB of a CU
-constexpr int kFewHeld = 31;   // ... two workgroups of jq_score_kernel
-static_assert(kLdsBoth + kScoreWaves * kMaxHeld * kHeldTile <= 160 * 1024 && 2 * (kSlotsBytes + kScoreWaves * kFewHeld * kHeldTile) <= 160 * 1024, "LDS of a CU");
+constexpr int kMaxHeld = 60;
+constexpr int kFewHeld = 31;  // two workgroups of jq_score_kernel per CU
+static_assert(kMaxHeld * kHeldTile <= kSlotBytes && kLdsBoth <= 100 * 1024, "as much LDS as without");
+static_assert((kSlotsBytes + kScoreWaves * kMaxHeld * kHeldTile + 1279) / 1280 * 1280 + 64 * 1024 <= 160 * 1024, "64 KB for others");
+static_assert(2 * (kSlotsBytes + kScoreWaves * kFewHeld * kHeldTile) <= 160 * 1024, "LDS of a CU");
 
 struct KeyStream {
     __amdgpu_buffer_rsrc_t rsrc;  // this head's rows of the whole sequence (PAGED: of the layer's whole pool)
@@ -1060,9 +1067,10 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
         if (t * kKeyTile + kKeyTile > n_scored && t * kKeyTile + (lane & 31) >= n_scored) v = 0.f;
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, (int)(out_lane + 4u * (uint32_t)(t * kKeyTile)), 0, 0);
     };
-    // HOLD: the scores wait in LDS and leave together, a.held tiles of every wave at a time -- the whole share's, if they fit.
-    const int hold = HOLD ? a.held : 0;
-    const uint32_t held = lds_addr(held_lds) + (uint32_t)(wv * hold * kHeldTile);
+    // HOLD: the scores wait in LDS and leave together, `hold` tiles of every wave at a time -- the whole share's, if they fit.
+    // (kNormsShared: where the query rows were; the barrier above is behind every wave's last read of them.)
+    const int hold = !HOLD ? 0 : NORMS == kNormsShared ? kMaxHeld : a.held;
+    const uint32_t held = NORMS == kNormsShared ? lds_addr(lds + kLdsQ + wv * kSlotBytes) : lds_addr(held_lds) + (uint32_t)(wv * hold * kHeldTile);
     const uint32_t held_lane = held + 4u * ((uint32_t)lane & 31u), held_t = held + (uint32_t)hold * (kKeyTile * 4);
     int n_held = 0;
     auto write_out = [&]() __attribute__((always_inline)) {
@@ -1189,7 +1197,6 @@ template __global__ void jq_score_kernel<4, false, false, false>(ScoreArgs);  //
 template <int NQT, bool PAGED, bool HOLD>
 __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArgs) {
     __shared__ __attribute__((aligned(1024))) char lds[kLdsBoth];
-    extern __shared__ char held_lds[];
     argument_lines<5>();
     const int64_t t_entry = wall_clock64();
     Place at = place_of(kernel_args(), blockIdx.x, false);
@@ -1211,7 +1218,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, 1) void jq_passes_kernel(ScoreArg
             q_there = scoring;
         } else {
             const Share h = share_of(a, at.c, at.layer, at.seq);
-            const int missing = score_share<NQT, kNormsShared, PAGED, HOLD>(a, h, at.g, lds, held_lds, patience, q_there);
+            const int missing = score_share<NQT, kNormsShared, PAGED, HOLD>(a, h, at.g, lds, nullptr, patience, q_there);
             q_there = true;
             if (missing >= 0) {
                 help = at.c - h.rank + missing;
@@ -1450,19 +1457,14 @@ static hipError_t launch_stats_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
 }
 
 // The kernel that holds scores back where the call wants it (a.held) and the device grants the LDS they take, else the other one.
-template <class Kernel>
-static hipError_t launch_second(Kernel direct, Kernel holding, std::atomic<uint64_t>& allowed, const ScoreArgs& a, dim3 grid, hipStream_t st,
-                                void* const* marks) {
-    const dim3 block(kScoreWaves * 64);
-    if (a.held && allow_dynamic_lds((const void*)holding, kScoreWaves * kMaxHeld * kHeldTile, allowed) == hipSuccess)
-        return launch_kernel(holding, grid, block, (size_t)(kScoreWaves * a.held * kHeldTile), st, marks, kTrScore, a);
-    return launch_kernel(direct, grid, block, 0, st, marks, kTrScore, a);
-}
-
 template <int NQT, bool FROM_LSE, bool PAGED>
 static hipError_t launch_score_k(const ScoreArgs& a, dim3 grid, hipStream_t st, void* const* marks) {
     static std::atomic<uint64_t> allowed;
-    return launch_second(jq_score_kernel<NQT, FROM_LSE, PAGED, false>, jq_score_kernel<NQT, FROM_LSE, PAGED, true>, allowed, a, grid, st, marks);
+    const dim3 block(kScoreWaves * 64);
+    const auto holding = jq_score_kernel<NQT, FROM_LSE, PAGED, true>;
+    if (a.held && allow_dynamic_lds((const void*)holding, kScoreWaves * kMaxHeld * kHeldTile, allowed) == hipSuccess)
+        return launch_kernel(holding, grid, block, (size_t)(kScoreWaves * a.held * kHeldTile), st, marks, kTrScore, a);
+    return launch_kernel(jq_score_kernel<NQT, FROM_LSE, PAGED, false>, grid, block, 0, st, marks, kTrScore, a);
 }
 template <bool FROM_LSE, bool PAGED>
 static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st, void* const* marks) {
@@ -1476,8 +1478,9 @@ static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
 
 template <int NQT, bool PAGED>
 static hipError_t launch_passes_k(const ScoreArgs& a, dim3 grid, hipStream_t st) {
-    static std::atomic<uint64_t> allowed;
-    return launch_second(jq_passes_kernel<NQT, PAGED, false>, jq_passes_kernel<NQT, PAGED, true>, allowed, a, grid, st, nullptr);
+    const dim3 block(kScoreWaves * 64);
+    if (a.held) return launch_kernel(jq_passes_kernel<NQT, PAGED, true>, grid, block, 0, st, nullptr, -1, a);
+    return launch_kernel(jq_passes_kernel<NQT, PAGED, false>, grid, block, 0, st, nullptr, -1, a);
 }
 template <bool PAGED>
 static hipError_t launch_passes_n(int nqt, const ScoreArgs& a, dim3 grid, hipStream_t st) {

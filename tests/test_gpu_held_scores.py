@@ -75,23 +75,26 @@ def _paged(torch, K, seq_lens, page):
     return jq.Pages(page, n, table.cuda()), pool
 
 
-@pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv", [
-    (1, [129], 8, 8, 8),                       # a tile of query rows; a wave has one tile of keys or none
-    (1, [4099], 16, 8, 2),                     # two
-    (3, [1000, 127, 45, 128, 2049], 24, 8, 2),  # three; portions that end inside sequences
-    (5, [9999], 32, 12, 4),                    # three; layers that do not divide the workgroups
-    (40, [300], 32, 8, 2),                     # four; more layers than workgroups per head: several shares a workgroup
-    (9, [300, 33, 129] * 12, 32, 32, 8),       # four; many short sequences, two workgroups per CU in two launches
-    (1, [40000], 32, 32, 8),                   # a workgroup per CU
+@pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv,chunk", [
+    (2, [40000, 129, 9000], 32, 32, 8, 4096),  # 128 tiles a wave: more than are held at once
+    (5, [12000], 8, 64, 64, None),             # the same, over several layers a workgroup, whose query rows come where scores were
+    (1, [7681], 16, 16, 4, 1920),              # as many as are held, 60, and one
+    (1, [129], 8, 8, 8, None),                 # a tile of query rows; a wave has one tile of keys or none
+    (1, [4099], 16, 8, 2, None),               # two
+    (3, [1000, 127, 45, 128, 2049], 24, 8, 2, None),  # three; portions that end inside sequences
+    (5, [9999], 32, 12, 4, None),              # three; layers that do not divide the workgroups
+    (40, [300], 32, 8, 2, None),               # four; more layers than workgroups per head: several shares a workgroup
+    (9, [300, 33, 129] * 12, 32, 32, 8, None),  # four; many short sequences, two workgroups per CU in two launches
+    (1, [40000], 32, 32, 8, None),             # a workgroup per CU
 ])
 @pytest.mark.parametrize("form", ["dense", "paged", "window"])
 @pytest.mark.parametrize("wait_us", [None, 0])
-def test_passes_that_form_their_statistics_hold_the_same_scores_back(knobs, n_layers, seq_lens, n_q, h_q, h_kv, form, wait_us):
+def test_passes_that_form_their_statistics_hold_the_same_scores_back(knobs, n_layers, seq_lens, n_q, h_q, h_kv, chunk, form, wait_us):
     # both passes in one launch (evict) and one after the other (score), every number of row tiles; without patience a workgroup
     # finds sets missing, forms them itself and starts the second pass of its share again
     import torch
     assert torch.cuda.is_available(), "these tests need the GPU"
-    print("held back, two passes", n_layers, seq_lens[:4], n_q, h_q, h_kv, form, wait_us, flush=True)
+    print("held back, two passes", n_layers, seq_lens[:4], n_q, h_q, h_kv, chunk, form, wait_us, flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(8)
     Q = torch.randn((n_layers, len(seq_lens), n_q, h_q, 128), generator=gen, device="cuda").bfloat16()
@@ -102,7 +105,7 @@ def test_passes_that_form_their_statistics_hold_the_same_scores_back(knobs, n_la
         pages, pool = _paged(torch, K, seq_lens, 64)
 
     def run(hold):
-        knobs(JQ_HOLD_BYTES=str(hold), **({} if wait_us is None else {"JQ_WAIT_US": str(wait_us)}))
+        knobs(JQ_HOLD_BYTES=str(hold), **({} if wait_us is None else {"JQ_WAIT_US": str(wait_us)}), **({"JQ_CHUNK_KEYS": str(chunk)} if chunk else {}))
         if form == "paged":
             two, one = jq.score_paged(sh, pages, Q, pool), jq.evict_paged(sh, pages, Q, pool, pool)
         else:
