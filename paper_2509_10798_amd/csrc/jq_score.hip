@@ -73,7 +73,7 @@ struct ScoreArgs {
     uint64_t token;
     int64_t wait_ticks;
     int32_t n_sets;
-    int32_t held;         // second pass: tiles whose scores a wave holds back before it writes them (0: none), see score_share
+    int32_t holds;        // second pass: scores are held back, see score_share
     float* scores;        // [n_layers][h_kv][T]
     const float* lse;     // [n_layers][n_seq][n_q][h_q] caller-supplied natural-log normalisers, or null
     uint2* aug;           // [n_layers][n_seq][h_kv][RP]: bf16 terms of -beta/c
@@ -304,18 +304,18 @@ constexpr int kLdsSet = kLdsQ + kMaxRowTiles * kSlotBytes;          // the set o
 constexpr int kLdsAug = kLdsSet + kMaxRowTiles * kRowTile * 8;     // the rows' normalisers
 constexpr int kLdsWord = kLdsAug + kMaxRowTiles * kRowTile * 8;
 constexpr int kLdsBoth = kLdsWord + 16;
-// Where a second pass holds scores back: per wave the scores of kMaxHeld tiles, then the tiles' numbers.  In the kernel of both
+// Where a second pass holds scores back: per wave the scores of a number of tiles, then the tiles' numbers.  In the kernel of both
 // passes they take the place of the query rows, which are in registers by then, a wave's in the slot that it fills itself: it needs no
 // more LDS than the one that stores at once.  (With room for 119 tiles a wave it filled a CU's 160 KB, nothing of another stream that uses
 // LDS could share a CU with it, and workgroups that so started late had their statistics formed by others: 8 x 65536 tokens beside 64
 // workgroups of 32 KB 534 us a call, 404 stored at once, 422 so; 16 ragged sequences 989, 770, 750.  Alone 119 take up to 1.1 % less.)
-// jq_score_kernel keeps them behind its slots and leaves 64 KB, the tiles of many a matrix product, to others.
+// jq_score_kernel keeps them behind its slots: as many as two workgroups per CU have room for, also where there is one, so that kernels of
+// other streams with up to 80 KB share the CU.  (60 and 119 tiles take 0.5 to 2.5 % less alone, but beside 4096^3 matrix products a call of
+// 8 x 65536 530 to 542 us instead of 361, 359 to 390 stored at once, 400000 tokens 373, 305 and 306.)
 constexpr int kHeldTile = kKeyTile * 4 + 4;
-constexpr int kMaxHeld = 60;
-constexpr int kFewHeld = 31;  // two workgroups of jq_score_kernel per CU
-static_assert(kMaxHeld * kHeldTile <= kSlotBytes && kLdsBoth <= 100 * 1024, "as much LDS as without");
-static_assert((kSlotsBytes + kScoreWaves * kMaxHeld * kHeldTile + 1279) / 1280 * 1280 + 64 * 1024 <= 160 * 1024, "64 KB for others");
-static_assert(2 * (kSlotsBytes + kScoreWaves * kFewHeld * kHeldTile) <= 160 * 1024, "LDS of a CU");
+constexpr int kHeldPasses = 62, kHeldScore = 31;
+static_assert(kHeldPasses * kHeldTile <= kSlotBytes, "in place of a wave's query rows");
+static_assert(2 * (kSlotsBytes + kScoreWaves * kHeldScore * kHeldTile) <= 160 * 1024, "LDS of a CU");
 
 struct KeyStream {
     __amdgpu_buffer_rsrc_t rsrc;  // this head's rows of the whole sequence (PAGED: of the layer's whole pool)
@@ -1069,7 +1069,8 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     };
     // HOLD: the scores wait in LDS and leave together, `hold` tiles of every wave at a time -- the whole share's, if they fit.
     // (kNormsShared: where the query rows were; the barrier above is behind every wave's last read of them.)
-    const int hold = !HOLD ? 0 : NORMS == kNormsShared ? kMaxHeld : a.held;
+    int hold = NORMS == kNormsShared ? kHeldPasses : kHeldScore;
+    asm("" : "+s"(hold));  // (known to the compiler, it costs 8 to 34 spilled registers)
     const uint32_t held = NORMS == kNormsShared ? lds_addr(lds + kLdsQ + wv * kSlotBytes) : lds_addr(held_lds) + (uint32_t)(wv * hold * kHeldTile);
     const uint32_t held_lane = held + 4u * ((uint32_t)lane & 31u), held_t = held + (uint32_t)hold * (kKeyTile * 4);
     int n_held = 0;
@@ -1456,14 +1457,15 @@ static hipError_t launch_stats_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
     }
 }
 
-// The kernel that holds scores back where the call wants it (a.held) and the device grants the LDS they take, else the other one.
+// The kernel that holds scores back where the call wants it and the device grants the LDS they take, else the other one.
 template <int NQT, bool FROM_LSE, bool PAGED>
 static hipError_t launch_score_k(const ScoreArgs& a, dim3 grid, hipStream_t st, void* const* marks) {
     static std::atomic<uint64_t> allowed;
     const dim3 block(kScoreWaves * 64);
     const auto holding = jq_score_kernel<NQT, FROM_LSE, PAGED, true>;
-    if (a.held && allow_dynamic_lds((const void*)holding, kScoreWaves * kMaxHeld * kHeldTile, allowed) == hipSuccess)
-        return launch_kernel(holding, grid, block, (size_t)(kScoreWaves * a.held * kHeldTile), st, marks, kTrScore, a);
+    constexpr int lds_bytes = kScoreWaves * kHeldScore * kHeldTile;
+    if (a.holds && allow_dynamic_lds((const void*)holding, lds_bytes, allowed) == hipSuccess)
+        return launch_kernel(holding, grid, block, (size_t)lds_bytes, st, marks, kTrScore, a);
     return launch_kernel(jq_score_kernel<NQT, FROM_LSE, PAGED, false>, grid, block, 0, st, marks, kTrScore, a);
 }
 template <bool FROM_LSE, bool PAGED>
@@ -1479,7 +1481,7 @@ static hipError_t launch_score_n(int nqt, const ScoreArgs& a, dim3 grid, hipStre
 template <int NQT, bool PAGED>
 static hipError_t launch_passes_k(const ScoreArgs& a, dim3 grid, hipStream_t st) {
     const dim3 block(kScoreWaves * 64);
-    if (a.held) return launch_kernel(jq_passes_kernel<NQT, PAGED, true>, grid, block, 0, st, nullptr, -1, a);
+    if (a.holds) return launch_kernel(jq_passes_kernel<NQT, PAGED, true>, grid, block, 0, st, nullptr, -1, a);
     return launch_kernel(jq_passes_kernel<NQT, PAGED, false>, grid, block, 0, st, nullptr, -1, a);
 }
 template <bool PAGED>
@@ -1563,7 +1565,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     a.lse = lse;
     a.part = a.own; a.fuse_combine = 0;
     a.flags = nullptr; a.token = 0; a.wait_ticks = 0; a.n_sets = p.split.n_sets;
-    a.held = 0;
+    a.holds = 0;
     // Scores are held back where the pass that makes them reads much of K from memory: 1.6 % of its bytes, they cost a tenth of its
     // time when they are written between the reads (a build that stored none took 44.2 us for the pass of 4 x 32768, 51.2 with stores after
     // every tile, 45.4 held back), and next to nothing while the Infinity Cache (256 MB) delivers K.  Written at the end they take
@@ -1581,7 +1583,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
         a.flags = (uint64_t*)(ws + p.off_flags);
         a.token = next_token();
         a.wait_ticks = (int64_t)knobs().wait_us * 100;
-        a.held = holds ? kMaxHeld : 0;
+        a.holds = holds;
         const int nqt = p.row_tiles;
         return paged ? launch_passes_n<true>(nqt, a, dim3(wgs), st) : launch_passes_n<false>(nqt, a, dim3(wgs), st);
     }
@@ -1644,7 +1646,7 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     const Split& own = wider ? alone : lse ? p.split : p.split2;
     share_out(own, a.own, a.cu_wg);
     const dim3 grid((unsigned)(own.n_wg * p.h_kv));
-    a.held = !holds ? 0 : grid.x <= (unsigned)resident_passes() ? kMaxHeld : kFewHeld;
+    a.holds = holds;
     if (paged) return lse ? launch_score_n<true, true>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, true>(p.row_tiles, a, grid, st, marks);
     return lse ? launch_score_n<true, false>(p.row_tiles, a, grid, st, marks) : launch_score_n<false, false>(p.row_tiles, a, grid, st, marks);
 }

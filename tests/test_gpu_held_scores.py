@@ -78,7 +78,7 @@ def _paged(torch, K, seq_lens, page):
 @pytest.mark.parametrize("n_layers,seq_lens,n_q,h_q,h_kv,chunk", [
     (2, [40000, 129, 9000], 32, 32, 8, 4096),  # 128 tiles a wave: more than are held at once
     (5, [12000], 8, 64, 64, None),             # the same, over several layers a workgroup, whose query rows come where scores were
-    (1, [7681], 16, 16, 4, 1920),              # as many as are held, 60, and one
+    (1, [7937], 16, 16, 4, 1984),              # as many as are held, 62, and one
     (1, [129], 8, 8, 8, None),                 # a tile of query rows; a wave has one tile of keys or none
     (1, [4099], 16, 8, 2, None),               # two
     (3, [1000, 127, 45, 128, 2049], 24, 8, 2, None),  # three; portions that end inside sequences
