@@ -1570,12 +1570,18 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     // time when they are written between the reads (a build that stored none took 44.2 us for the pass of 4 x 32768, 51.2 with stores after
     // every tile, 45.4 held back), and next to nothing while the Infinity Cache (256 MB) delivers K.  Written at the end they take
     // 0.5 us of a short call.  Whole calls, stored at once / held back, 8 KV heads, us:
-    //   one pass (normalisers supplied): 30000 tokens 27.7 / 28.0, 40000 33.6 / 33.9, 60000 43.3 / 42.2, 80000 51.6 / 49.6, 2 x 32768 42.6 / 41.1,
-    //     4 x 32768 72.5 / 67.6, 8 x 65536 245 / 223;
-    //   two: 131072 110.2 / 110.9, 28 x 8192 219.6 / 221.1, 4 x 50000 164.7 / 165.4, 250000 205.2 / 203.3, 4 x 60000 paged 209 / 206, 32 x 8192
-    //     236.7 / 233.6, 8 x 65536 416 / 402, 16 ragged sequences of 981293 together 780 / 753.
+    //   one pass (normalisers supplied) alone or with the one-kernel tail: 30000 tokens 27.7 / 28.0, 2 x 32768 42.6 / 41.1, 4 x 25000 59.9 / 57.2,
+    //     4 x 32768 71.5 / 66.9, 16 x 16384 137.4 / 128.0, 8 x 32768 131.2 / 119.5;
+    //   one pass and a tail of two kernels (`zero`: the second one's histograms): 80000 tokens 48.4 / 45.9, 120000 64.4 / 62.0, 131072 69.0 / 64.5,
+    //     250000 124.8 / 116.9, 400000 201.4 / 184.6, 8 x 65536 244 / 223 -- but up to some 400 MB that depends on the card: on 4 of 21 cards calls
+    //     one after the other lose instead, on the worst 80000 53.9 / 56.8, 120000 68.4 / 78.6, 131072 73.5 / 78.4, 2 x 60000 70.0 / 78.9,
+    //     200000 109.3 / 114.4, 250000 131.3 / 131.5, 400000 210.5 / 206.8, 8 x 65536 244 / 227; on 4 more nothing is gained up to 131072.
+    //     The pass alone takes less on those too (2 x 60000 51.2 / 48.1), and with the one-kernel tail behind it they lose nothing (4 x 32768
+    //     76.0 / 75.1); the number of tiles held, the kind of stores and the shader clock make no difference.  No such call holds back below;
+    //   two passes: 131072 110.2 / 110.9, 28 x 8192 219.6 / 221.1, 4 x 50000 164.7 / 165.4, 250000 203.2 / 197.7, 4 x 60000 paged 209 / 206, 32 x 8192
+    //     233.8 / 230.4, 8 x 65536 402 / 387, 16 ragged sequences of 981293 together 751 / 735.
     const int64_t k_bytes = (int64_t)p.n_layers * p.T * p.h_kv * kHeadDim * 2;
-    const bool holds = k_bytes >= (knobs().hold_bytes >= 0 ? knobs().hold_bytes : lse ? (int64_t)110000000 : (int64_t)480000000);
+    const bool holds = k_bytes >= (knobs().hold_bytes >= 0 ? knobs().hold_bytes : lse && !zero ? (int64_t)110000000 : (int64_t)480000000);
     const dim3 block(kScoreWaves * 64);
     const unsigned wgs = (unsigned)(p.split.n_wg * p.h_kv);
     hipError_t e;

@@ -119,3 +119,32 @@ def test_passes_that_form_their_statistics_hold_the_same_scores_back(knobs, n_la
     assert torch.equal(held[0], held[1])
     total = held[0].double().cpu()
     assert torch.isfinite(total).all() and float(total.sum()) > 0
+
+
+@pytest.mark.parametrize("n_layers,L,lse,evicts,held", [
+    (1, 120000, True, True, False),   # a tail of two kernels behind one pass over 246 MB: slower on some cards if held back
+    (1, 120000, True, False, True),   # the scores alone
+    (2, 32768, True, True, True),     # the one-kernel tail
+    (1, 250000, True, True, True),
+    (1, 120000, False, True, False),
+    (1, 250000, False, True, True),
+])
+def test_which_calls_hold_their_scores_back(n_layers, L, lse, evicts, held):
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    print("which kernel", n_layers, L, lse, evicts, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    Q = torch.randn((n_layers, 1, 32, 32, 128), generator=gen, device="cuda").bfloat16()
+    K = torch.randn((n_layers, L, 8, 128), generator=gen, device="cuda").bfloat16()
+    norms = torch.full((n_layers, 1, 32, 32), 12.0, device="cuda") if lse else None
+    sh = jq.Shape(n_layers=n_layers, seq_lens=[L], n_q=32, h_q=32, h_kv=8, budgets=[256])
+    jq.score(sh, Q, K, lse=norms)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        for _ in range(3):  # (the profiler may miss one)
+            jq.evict(sh, Q, K, K, lse=norms) if evicts else jq.score(sh, Q, K, lse=norms)
+        torch.cuda.synchronize()
+    ran = {e.name.split("(")[0] for e in prof.events() if "jq_score_kernel" in e.name or "jq_passes_kernel" in e.name}
+    assert ran and all(("passes" in n) == (not lse) for n in ran), ran
+    assert all(n.endswith("true>") == held for n in ran), ran
