@@ -293,26 +293,28 @@ bool select_fast_path(const Plan& p);
 // A selection alone always takes it (32768 values, 512 kept: 14.9 us against 35.6 for the three launches of the other way).
 // An eviction weighs it against the pooling kernel followed by the selection's (evict_tail_small): every slice of a problem
 // repeats pooling and selection in its one workgroup, which costs more the longer the sequence, while the lists of the other
-// way cost more the more is kept.  Whole calls of one layer with 8 KV heads, one kernel / two, in us:
+// way cost more the more is kept.  Whole calls of one layer with 8 KV heads, keys drawn so that the kept ones stand out, one kernel / two, in us:
 //   kept:          256          512          1024         2048         3072
-//    2048     18.4 / 28.1
-//   12000     26.2 / 31.5               26.3 / 32.8
-//   16384     28.6 / 34.6               28.4 / 35.4
-//   20000     34.4 / 36.9                            35.3 / 39.2
-//   28000     39.1 / 41.7                                         40.1 / 47.0
-//   32768     41.9 / 43.8  40.3 / 44.1  40.4 / 44.7               42.1 / 48.8
-// 4 layers: 20000, 256 kept 70.7 / 73.7; 32768 105.6 / 109.7, 3072 kept 123.9 / 133.3.  Above 16384 positions one workgroup fills a
-// CU's LDS, and more than 256 problems take turns: 32768 + 63 x 300 (512 problems) 88.7 / 88.1, 36 x 18000 557.5 / 551.6,
-// 20000 + 35 x 500 68.6 / 67.4 -- two kernels then, except without pooling (earlier builds: 36 x 18000 591 / 621).  Up to
-// 16384 it wins there too (earlier builds: 48 x 9000 435 / 447, 40 x 16000 569 / 579).
-// Widths 1, 5 and 7 are compiled in; any other is summed tap by tap out of LDS, for 4 to 32 positions per thread:
+//    2048     15.4 / 24.6
+//   12000     25.2 / 28.0               25.4 / 30.7
+//   16384     27.5 / 30.4               27.1 / 32.7  27.0 / 35.3
+//   20000     33.6 / 32.6               33.3 / 34.5  34.3 / 36.6
+//   24576     35.5 / 35.1               35.4 / 37.1  36.9 / 39.2
+//   28000     38.5 / 37.2  37.8 / 37.5               39.4 / 42.6  39.9 / 45.2
+//   32768     40.8 / 40.1  39.7 / 40.2  39.7 / 41.1  42.7 / 45.5  42.8 / 47.4
+// and on flat scores, of which the lists of the two kernels hold many more than are kept: 16384, 512 kept 28.5 / 45.1, 32768 42.4 / 92.3, 4 layers of
+// 32768 with 1024 113.5 / 160.5 -- far more than the 1 us by which two kernels are ahead where few are kept and stand out.
+// 4 layers: 20000, 256 kept 73.9 / 74.3; 32768 105.0 / 106.4, 3072 kept 120.2 / 126.8; 30 layers of 32768 790 / 778.  Above 16384 positions one workgroup
+// fills a CU's LDS, and more than 256 problems take turns: 32768 + 63 x 300 (512 problems) 95.8 / 91.5, 36 x 18000 586 / 575, 32 x 32768 856 / 831,
+// 20000 + 35 x 500 71.3 / 67.1 -- two kernels then, except without pooling.  Up to 16384 it wins there too (48 x 9000 417 / 428, 40 x 16000 570 / 572).
+// Widths 1, 5 and 7 are compiled in; any other is summed tap by tap out of LDS, for 4 to 32 positions per thread (256 kept):
 //   width:        3            9            13           31           63
-//    2048                               20.6 / 29.5  24.0 / 30.2  31.2 / 33.7
-//    4096                               23.9 / 28.9  30.7 / 29.9  44.1 / 32.8
-//    8192                  29.1 / 30.4  32.2 / 30.9  45.6 / 31.8
-//   16384     30.9 / 34.9  35.9 / 35.1  39.1 / 35.7
-// (Keys drawn so that the kept ones stand out.  Where scores are flat, the lists of the two kernels hold many more: width 31, 4096 tokens,
-// 256 kept 30.5 / 37.6, 2100 tokens 30.3 / 38.0, 8 layers of 4096 45.9 / 53.9 -- one kernel up to width 31 there.)
+//    2048                               18.0 / 26.1  21.4 / 27.0  28.7 / 30.9
+//    4096                               21.7 / 25.6  28.6 / 27.1  41.7 / 30.7
+//    8192                  27.8 / 26.9  31.1 / 27.8  44.5 / 28.5
+//   16384     29.6 / 31.0  34.5 / 31.2  37.8 / 31.6
+// (Flat scores: width 31, 4096 tokens 29.6 / 32.9, 2100 tokens 29.5 / 36.4, 8 layers of 4096 46.8 / 51.2 -- one kernel up to width 31 there, and up to 9
+// at 8192.)
 constexpr int kSmallMax = 32768;
 bool select_small(const Plan& p);
 bool evict_tail_small(const Plan& p);

@@ -711,7 +711,7 @@ __device__ __forceinline__ uint2 neg_beta_terms(float m, float z, double inv_c) 
 }
 constexpr float kPadTerm = -1.0e30f;  // for padded rows: 2^(c * x) = 0
 
-// (m, Z) of a row merged over sets from, from + 2, ... of the n there are; `u` of them in `t`
+// (m, Z) of a row merged with those of up to N more sets, number from, from + 2, ... of the n there are, which `t` holds
 template <int N>
 __device__ __forceinline__ void merge_sets(const float2 (&t)[N], int from, int n, float& M, float& Z) {
     float mm = M;
@@ -1059,8 +1059,8 @@ __device__ __forceinline__ int score_share(KArgs& a, const Share& h, int g, char
     const float c = a.c;
     float pending = 0.f;  // previous tile's result, handed out one iteration late
     const int n_scored = a.window ? h.L - a.n_q : h.L;  // the window's own positions report 0
-    // Always one store instruction: the upper lane half (which holds the same sums), rows past the end of the sequence's last
-    // tile and whatever goes to kNowhere fall behind the end of the resource, where the hardware drops them.
+    // Stored at once, a tile is always one store instruction: the upper lane half (which holds the same sums), rows past the end of the
+    // sequence's last tile and whatever goes to kNowhere fall behind the end of the resource, where the hardware drops them.
     constexpr int kNowhere = 0x40000000 / (4 * kKeyTile);  // (the resource has at most 2^26 bytes)
     const uint32_t out_lane = half == 0 ? 4u * (uint32_t)lane : 0x40000000u;
     auto store_tile = [&](int t, float v) {

@@ -57,10 +57,6 @@ struct SelectArgs {
     SeqTab tab;
 };
 
-// bins[0..n_bins): find the bin b with (#elements in bins > b) < need <= (#elements in bins >= b).
-// Thread t owns PER consecutive bins, highest bins first.  result[0] = b, result[1] = #elements above,
-// result[2] = #elements inside b.
-// pick_bin_counts takes the thread's PER counts already loaded (c[e] = count of bin n_bins - 1 - (PER * thread + e)).
 // The thread's PER counts (c[e] = count of bin n_bins - 1 - (PER * thread + e)) in one load; `bins` is aligned to it, n_bins = PER * THREADS.
 // (Word by word they were 2- to 4-way bank conflicts each: 2048 tokens 14.94 -> 14.76 us a call, 32768 41.35 -> 40.7, 8192 21.6 -> 21.3.)
 template <int PER, typename BinPtr>
@@ -78,6 +74,9 @@ __device__ __forceinline__ void counts_down(BinPtr bins, int n_bins, uint32_t (&
     }
 }
 
+// bins[0..n_bins): find the bin b with (#elements in bins > b) < need <= (#elements in bins >= b).
+// Thread t owns PER consecutive bins, highest bins first.  result[0] = b, result[1] = #elements above,
+// result[2] = #elements inside b.  pick_bin_counts takes the thread's counts as counts_down has loaded them.
 template <int THREADS, int PER>
 __device__ __forceinline__ void pick_bin_counts(const uint32_t (&c)[PER], int n_bins, uint32_t need, uint32_t* tmp,
                                                 uint32_t* result) {
@@ -546,10 +545,11 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     // t), and the first entries of the wave's first segments; all of that arrives while the
     // threshold bin is being picked (the CU's load path is what bounds this phase, and it counts instructions and bytes: a load covers
     // 64 entries of two segments, two per lane; where a block keeps more than 32 positions on average -- `dense` -- the next 64
-    // are requested as well (from 16 on: 65536 tokens with 2048 kept 68.3 us a call, 67.3 so, 50000 with 1536 56.7 / 55.7).  128 entries of one segment per load, whatever the density: list complete 11.3 us after entry on the 128K
-    // layer, 6.3 so, the call 110.5 -> 106.4; 65536 tokens 65.3 -> 62.7, 100000 with 3072 kept 93.9 -> 92.9).  The entry loads are unconditional, from clamped and therefore always valid
-    // addresses -- a segment's storage holds `head` entries whatever its element count -- so that all of them are in
-    // flight together; what lies outside is masked afterwards.
+    // are requested as well (from 16 on: 65536 tokens with 2048 kept 68.3 us a call, 67.3 so, 50000 with 1536 56.7 / 55.7).  With 128
+    // entries of one segment per load, whatever the density, the list was complete 10.0 us after entry on the 128K layer, 6.2 so, the
+    // call 110.5 -> 106.4; 65536 tokens 65.3 -> 62.7, 100000 with 3072 kept 93.9 -> 92.9).  The entry loads are unconditional, from clamped
+    // and therefore always valid addresses -- a segment's storage holds `head` entries whatever its element count -- so that all of
+    // them are in flight together; what lies outside is masked afterwards.
     uint32_t c1[kHistBins / kFinThreads];
     counts_down<kHistBins / kFinThreads>(p.hist, kHistBins, c1);
     const uint4 my_hdr = seg_hdr[min((int)threadIdx.x, n_seg - 1)];
