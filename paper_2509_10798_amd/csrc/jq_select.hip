@@ -553,6 +553,9 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     uint32_t c1[kHistBins / kFinThreads];
     counts_down<kHistBins / kFinThreads>(p.hist, kHistBins, c1);
     const uint4 my_hdr = seg_hdr[min((int)threadIdx.x, n_seg - 1)];
+    // (Or the compiler requests the bins behind the entries, and the scan of the bins waits for all of them: 131072 tokens 107.5 us a call,
+    // 106.9 so, a paged batch of 8 175.2 / 174.7, 4 x 38189 with 1433 kept 127.4 / 127.0; where every block is scanned it costs 1 %.)
+    __builtin_amdgcn_sched_barrier(0);
     constexpr int kPairs = kSegBatch / 2;
     const bool dense = head > 256;  // uniform
     const int half = lane >> 5, l32 = lane & 31;
@@ -629,11 +632,16 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     // Where the last of the 64 still qualified in any of the wave's segments, the next 64 of all of them are read together: one round
     // trip, where one after the other 2048 kept of 131072 flat scores (threshold bins that reach far down) lost the call 2.5 us against
     // 128 entries read at once (107.1 / 109.8; 106.7 so), blocks with 64 to 100 kept each 0.5 to 2.
-    list_entries(ent, 0);
-    if (dense || again) {  // wave-uniform
-        if (!dense) next_entries();
+    // One copy of the code, gone through twice: two are 2.5 KB more, which every wave fetches from cold (4 x 38189 tokens with 1433 kept
+    // 127.8 us a call, 127.0 so; 5 ragged sequences of 145197 together with 1634 kept each 130.7 / 130.3).
+#pragma nounroll
+    for (int first = 0;; first = 64) {
+        list_entries(ent, first);
+        if (first || !(dense || again)) break;  // wave-uniform
         again = 0;
-        list_entries(ent2, 64);
+        if (!dense) next_entries();
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) ent[i] = ent2[i];
     }
     // Second visits (a segment whose last entry looked at still qualified, a block that is classified from its scores), and
     // the segments beyond the first batch: rare, so the common case only tests one mask.
@@ -652,8 +660,8 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
         }
         const int n = seg_n[sg];
         if (n < 0) {  // four requests at a time: one after the other they were 16 memory latencies a block (16 blocks with 128 kept each
-                      // out of 131072: 150.4 us a call, 118.0 so; written out at every call of scan_block it is 3 KB more code than
-                      // the instruction cache has room for, and calls that never come here lose 1 us)
+                      // out of 131072: 150.4 us a call, 118.0 so; written out at every call of scan_block it is 3 KB more code, for
+                      // which calls that never come here lost 1 us)
             const int j0 = sg * kSegLen + lane, j1 = min(p.L, (sg + 1) * kSegLen);
             for (int j = j0; j < j1; j += 4 * 64) {
                 float x[4];
