@@ -2,7 +2,7 @@
 //
 // Why: the kernels of an eviction step over more than 32768 tokens (both passes over K in one, pooling, selection +
 // gather) run back to back, thousands of times, and the instruction cache of a compute-unit pair (64 KB) keeps its
-// contents across kernel launches.  Their code is 60.7 KB together (37.9 + 4.1 + 18.7; 61.8 with
+// contents across kernel launches.  Their code is 60.5 KB together (37.9 + 4.1 + 18.5; 61.5 with
 // the passes that hold scores back, of 65.5 in these units; a shorter call runs two kernels of at most 59.0 KB: both passes and
 // jq_pool_select_kernel).  Compiled as separate translation units every file becomes a code
 // object of its own and the loader decides where each one goes; in one code object the kernels lie where the

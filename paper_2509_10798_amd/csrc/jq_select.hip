@@ -559,15 +559,18 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
     constexpr int kPairs = kSegBatch / 2;
     const bool dense = head > 256;  // uniform
     const int half = lane >> 5, l32 = lane & 31;
-    auto seg_of = [&](int i) __attribute__((always_inline)) { return wave + (2 * i + half) * kFinWaves; };  // the lane's segment of the i-th pair
+    const char* entries = (const char*)segs;
+    uint32_t ent_at[kPairs];  // bytes from there to the lane's part of its segment of the i-th pair (at most 2^14 segments of 2^13 bytes)
     uint4 ent[kPairs], ent2[kPairs];  // its entries 2 * l32 and 2 * l32 + 1, and 64 further on: (key, position) twice
 #pragma unroll
-    for (int i = 0; i < kPairs; ++i) ent[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[l32];
-    auto next_entries = [&]() __attribute__((always_inline)) {
+    for (int i = 0; i < kPairs; ++i) {
+        ent_at[i] = (uint32_t)min(wave + (2 * i + half) * kFinWaves, n_seg - 1) * (uint32_t)(a.head * 8) + 16u * (uint32_t)l32;
+        ent[i] = *(const uint4*)(entries + ent_at[i]);
+    }
+    if (dense) {
 #pragma unroll
-        for (int i = 0; i < kPairs; ++i) ent2[i] = ((const uint4*)(segs + (int64_t)min(seg_of(i), n_seg - 1) * a.head))[32 + l32];
-    };
-    if (dense) next_entries();
+        for (int i = 0; i < kPairs; ++i) ent2[i] = *(const uint4*)(entries + ent_at[i] + 512);
+    }
     for (int w = 4 * threadIdx.x; w < 2 * words_cap; w += 4 * kFinThreads) *(uint4*)&keep[w] = make_uint4(0u, 0u, 0u, 0u);  // keep, ties
     for (int b = 4 * threadIdx.x; b < 3072 + 96; b += 4 * kFinThreads) *(uint4*)&bins2[b] = make_uint4(0u, 0u, 0u, 0u);  // histograms, tmp, res, cnt
     lds_barrier();
@@ -629,19 +632,27 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
             }
         }
     };
-    // Where the last of the 64 still qualified in any of the wave's segments, the next 64 of all of them are read together: one round
-    // trip, where one after the other 2048 kept of 131072 flat scores (threshold bins that reach far down) lost the call 2.5 us against
-    // 128 entries read at once (107.1 / 109.8; 106.7 so), blocks with 64 to 100 kept each 0.5 to 2.
+    // Where the last of the 64 still qualified in more than two of the wave's segments, the next 64 of all of them are read together: one
+    // round trip, where one after the other 2048 kept of 131072 flat scores (threshold bins that reach far down) lost the call 2.5 us
+    // against 128 entries read at once (107.1 / 109.8; 106.7 so).  One or two are visited below, which costs a wave less than
+    // this turn: pooling left out, 131072 scores, together from one / two / three segments on and never: 4 blocks with 100 kept
+    // each 19.2 / 18.7 / 18.5 / 18.6 us, 8 with 90 19.7 / 19.5 / 19.3 / 19.5, 26 with 80 20.7 / 20.5 / 20.4 / 22.1.
     // One copy of the code, gone through twice: two are 2.5 KB more, which every wave fetches from cold (4 x 38189 tokens with 1433 kept
-    // 127.8 us a call, 127.0 so; 5 ragged sequences of 145197 together with 1634 kept each 130.7 / 130.3).
+    // 127.7 us a call, 126.7 so; 5 ragged sequences of 145197 together with 1634 kept each 130.9 / 130.3).
+    int listed_to = 64;
 #pragma nounroll
     for (int first = 0;; first = 64) {
         list_entries(ent, first);
-        if (first || !(dense || again)) break;  // wave-uniform
+        if (first || !(dense || __popc(again) > 2)) break;  // wave-uniform
+        listed_to = 128;
         again = 0;
-        if (!dense) next_entries();
+        if (dense) {
 #pragma unroll
-        for (int i = 0; i < kPairs; ++i) ent[i] = ent2[i];
+            for (int i = 0; i < kPairs; ++i) ent[i] = ent2[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) ent[i] = *(const uint4*)(entries + ent_at[i] + 512);
+        }
     }
     // Second visits (a segment whose last entry looked at still qualified, a block that is classified from its scores), and
     // the segments beyond the first batch: rare, so the common case only tests one mask.
@@ -650,7 +661,7 @@ __global__ __launch_bounds__(kFinThreads) void jq_select_finalize_kernel(SelectA
         int sg, off;
         if (again) {
             sg = wave + __builtin_ctz(again) * kFinWaves;
-            off = 128;
+            off = listed_to;
             again &= again - 1;
         } else {
             if (beyond >= n_seg) break;

@@ -652,3 +652,18 @@ def test_most_blocks_have_more_candidates_than_are_read_at_once(L, lo, hi):
             n += at.size
     B = min(n // 4, L // 64)  # 16 of a block on average: lists of 128
     run_select_case(x, [L], [B])
+
+
+@pytest.mark.parametrize("n", [64, 65, 128, 129, 400])
+@pytest.mark.parametrize("hot", [1, 2, 3, 4])
+def test_some_blocks_of_one_wave_have_more_candidates_than_are_read_at_once(hot, n):
+    # up to two such blocks are continued one after the other, from the third on their next entries are read together
+    rng = np.random.default_rng(8 * n + hot)
+    L, B = 131072, 2000  # lists of 128
+    x = (rng.random((1, 2, L)) * 0.4 + 0.01).astype(np.float32)
+    for g in range(2):
+        for b in range(L // 1024):
+            size = n + 3 * (b // 8) if b % 8 == 3 and b < 8 * hot else 20
+            at = b * 1024 + rng.permutation(1024)[:size]
+            x[0, g, at] = 0.76 + 0.1 * rng.random(size).astype(np.float32)  # the threshold's bin
+    run_select_case(x, [L], [B])
