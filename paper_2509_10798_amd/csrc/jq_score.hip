@@ -1576,8 +1576,11 @@ hipError_t launch_score(const Plan& p, const void* Q, const void* K, float* scor
     //     250000 124.8 / 116.9, 400000 201.4 / 184.6, 8 x 65536 244 / 223 -- but up to some 400 MB that depends on the card: on 4 of 21 cards calls
     //     one after the other lose instead, on the worst 80000 53.9 / 56.8, 120000 68.4 / 78.6, 131072 73.5 / 78.4, 2 x 60000 70.0 / 78.9,
     //     200000 109.3 / 114.4, 250000 131.3 / 131.5, 400000 210.5 / 206.8, 8 x 65536 244 / 227; on 4 more nothing is gained up to 131072.
-    //     The pass alone takes less on those too (2 x 60000 51.2 / 48.1), and with the one-kernel tail behind it they lose nothing (4 x 32768
-    //     76.0 / 75.1); the number of tiles held, the kind of stores and the shader clock make no difference.  No such call holds back below;
+    //     The number of tiles held, the kind of stores and the shader clock make no difference.  No such call holds back below;
+    //   the first group on such a card, two runs: alone 2 x 32768 34.4 / 34.8 and 34.7 / 35.3, 4 x 25000 43.1 / 41.1 and 42.9 / 40.8, 4 x 32768 54.4 / 51.2
+    //     and 54.1 / 51.5; with the one-kernel tail 2 x 32768 44.7 / 43.4 and 46.2 / 45.4, 4 x 25000 59.3 / 59.8 and 60.5 / 61.6, 4 x 32768 73.8 / 70.5 and
+    //     75.1 / 74.9, 8 x 16384 74.1 / 73.5 and 75.1 / 78.8, 16 x 16384 137.4 / 131.5 and 137.7 / 131.6, 8 x 32768 131.6 / 120.1 and 132.3 / 125.3: 3 %
+    //     less on average there too, 5 % more at worst;
     //   two passes: 131072 110.2 / 110.9, 28 x 8192 219.6 / 221.1, 4 x 50000 164.7 / 165.4, 250000 203.2 / 197.7, 4 x 60000 paged 209 / 206, 32 x 8192
     //     233.8 / 230.4, 8 x 65536 402 / 387, 16 ragged sequences of 981293 together 751 / 735.
     const int64_t k_bytes = (int64_t)p.n_layers * p.T * p.h_kv * kHeadDim * 2;
